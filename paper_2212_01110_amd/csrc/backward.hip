@@ -5,6 +5,8 @@
 // data: u = K x, x^c = Abar^c x), and the cost-weight gradients.
 #include "device_common.h"
 
+#include <algorithm>
+
 namespace spk {
 
 // J_G d on a translated SOC block by one wavefront: vector part of len <=
@@ -121,61 +123,110 @@ __global__ void __launch_bounds__(256) k_jg(DevProb<S> P, const S* __restrict__ 
   }
 }
 
-// Transpose of the root-state map Phi of the S1 projection, one stage per
-// launch (stage N-1 .. 0): mu^j = c_x^j at leaves, mu^i = c_x^i + K^i' c_u^i +
-// sum_c Abar^c' mu^c; mu^0 is the gradient with respect to x0.
+// Inputs of the adjoint of every instance in one launch: v* (and the root
+// state) gathered from the callers' buffers, the cotangent g = gV on s^0 and
+// gu0 on u^0 (element u0off on), and w = g. Instance b sits `is` elements
+// apart; tab holds the pointers of the instances (v*, x0, gu0 or null). A
+// launch bound, not a bandwidth bound: 64 instances of the 95-node tree took
+// 4 copies each (and a synchronisation for gu0).
 template <typename S>
-__global__ void k_phiT(DevProb<S> P, const S* __restrict__ cz, S* __restrict__ mu, int first, int count) {
-  const int f = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ void __launch_bounds__(256) k_adj_load(long long nv, int nx, int nu, long long u0off, double gV,
+                                                  const AdjPtrs<S>* __restrict__ tab, long long is,
+                                                  S* __restrict__ v, double* __restrict__ x0s, S* __restrict__ g,
+                                                  S* __restrict__ w) {
+  const AdjPtrs<S> t = tab[blockIdx.y];
+  const size_t o = (size_t)blockIdx.y * is;
+  for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < nv; e += (long long)gridDim.x * blockDim.x) {
+    if (v) v[o + e] = t.vstar[e];
+    S c = S(0);
+    if (e == 0) c = (S)gV;
+    else if (t.gu0 && e >= u0off && e < u0off + nu) c = (S)t.gu0[e - u0off];
+    g[o + e] = c;
+    w[o + e] = c;
+    if (x0s && e < nx) x0s[(size_t)blockIdx.y * nx + e] = t.x0[e];
+  }
+}
+
+// Transpose of the root-state map Phi of the S1 projection, one stage per
+// launch (stage N-1 .. 0) for every instance: mu^j = c_x^j at leaves, mu^i =
+// c_x^i + K^i' c_u^i + sum_c Abar^c' mu^c; mu^0 is the gradient with respect
+// to x0, written to gx0. One wavefront per (node, instance), lane o on
+// component o (nx <= 64): the rows of K and Abar are read coalesced and the
+// sums run in the order of the formula. Bound by the latency of a stage's
+// chain; one thread per node walked nx (nu + n nx) dependent loads (85 us per
+// stage on the 95-node tree in FP64, once per instance: 43 of the 60 ms of a
+// 64-instance adjoint of 32 applications, now 10.5 ms in all).
+template <typename S>
+__global__ void __launch_bounds__(256) k_phiT(DevProb<S> P, const S* __restrict__ cz, long long is,
+                                              S* __restrict__ mu, long long ms, int first, int count,
+                                              const AdjPtrs<S>* __restrict__ tab) {
+  const int lane = threadIdx.x & 63;
+  const int f = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (f >= count) return;
   const int i = first + f;
+  cz += (size_t)blockIdx.y * is;
+  mu += (size_t)blockIdx.y * ms;
   const Off<S> O(P);
   const int nx = P.nx, nu = P.nu, fc = P.fc[i], n = P.nch[i];
-  for (int k = 0; k < nx; ++k) {
-    double acc = (double)cz[O.x(i) + k];
-    for (int j = 0; j < nu; ++j) acc += (double)P.KR[(size_t)i * nu * nx + (size_t)j * nx + k] * (double)cz[O.u(i) + j];
-    for (int cc = 0; cc < n; ++cc) {
-      const int c = fc + cc;
-      const S* Ab = P.AbR + (size_t)c * nx * nx;  // row-major Abar: (Abar' mu)_k = sum_r Abar[r][k] mu_r
-      const bool leaf = c >= P.nl;
-      for (int r = 0; r < nx; ++r) {
-        const double m = leaf ? (double)cz[O.x(c) + r] : (double)mu[(size_t)c * nx + r];
-        acc += (double)Ab[(size_t)r * nx + k] * m;
-      }
-    }
-    mu[(size_t)i * nx + k] = (S)acc;
+  const int o = lane < nx ? lane : 0;
+  double acc = (double)cz[O.x(i) + o];
+  const S* K = P.KR + (size_t)i * nu * nx + o;
+  const S* cu = cz + O.u(i);
+#pragma unroll 8
+  for (int j = 0; j < nu; ++j) acc += (double)K[(size_t)j * nx] * (double)cu[j];
+  for (int c = fc; c < fc + n; ++c) {
+    const S* Ab = P.AbR + (size_t)c * nx * nx + o;  // row-major Abar: (Abar' mu)_o = sum_r Abar[r][o] mu_r
+    const S* m = c >= P.nl ? cz + O.x(c) : mu + (size_t)c * nx;
+#pragma unroll 8
+    for (int r = 0; r < nx; ++r) acc += (double)Ab[(size_t)r * nx] * (double)m[r];
+  }
+  if (lane < nx) {
+    mu[(size_t)i * nx + lane] = (S)acc;
+    if (i == 0) tab[blockIdx.y].gx0[lane] = (double)(S)acc;
   }
 }
 
 // Cost-weight gradients from the adjoint quantities: for a non-root c with
 // ancestor i, d/dq^c_k = alpha (x*_{i,k} lb_{c,k} - la_{x^i,k} eta*_{c,k}) / (2 sqrt(q^c_k))
-// on the group-2 x rows; for a leaf j, the same with group 3 and Q_N.
+// on the group-2 x rows; for a leaf j, the same with group 3 and Q_N. Every
+// entry of both outputs is written (row 0 and the other rows of gqN are
+// zero), one thread per entry and instance.
 template <typename S>
-__global__ void k_grad_q(DevProb<S> P, const S* __restrict__ vstar, const S* __restrict__ la,
-                         const S* __restrict__ lb, double* __restrict__ gq, double* __restrict__ gqN) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= P.nn || c == 0) return;
-  const Off<S> O(P);
+__global__ void __launch_bounds__(256) k_grad_q(DevProb<S> P, const S* __restrict__ vstar, const S* __restrict__ la,
+                                                const S* __restrict__ lb, long long is,
+                                                const AdjPtrs<S>* __restrict__ tab) {
+  const long long e = blockIdx.x * 256LL + threadIdx.x;
   const int nx = P.nx;
-  const int i = P.anc[c];
-  const S* z = vstar;
-  const S* eta = vstar + P.nz;
+  if (e >= (long long)P.nn * nx) return;
+  const AdjPtrs<S> t = tab[blockIdx.y];
+  const size_t b = (size_t)blockIdx.y * is;
+  const int c = (int)(e / nx), k = (int)(e - (long long)c * nx);
+  const Off<S> O(P);
+  const S* z = vstar ? vstar + b : t.vstar;
+  const S* eta = z + P.nz;
+  la += b;
+  lb += b;
   const double al = (double)P.alpha;
-  if (gq) {
-    const long long e2 = O.e2(c);
-    for (int k = 0; k < nx; ++k) {
+  if (t.gq) {
+    double out = 0.0;
+    if (c > 0) {
+      const int i = P.anc[c];
+      const long long e2 = O.e2(c);
       const double sq = (double)P.sq[(size_t)c * nx + k];
       const double d = al * ((double)z[O.x(i) + k] * (double)lb[e2 + k] - (double)la[O.x(i) + k] * (double)eta[e2 + k]);
-      gq[(size_t)c * nx + k] = d / (2.0 * sq);
+      out = d / (2.0 * sq);
     }
+    t.gq[e] = out;
   }
-  if (gqN && c >= P.nl) {
-    const long long e3q = O.e3(c) + nx;
-    for (int k = 0; k < nx; ++k) {
+  if (t.gqN) {
+    double out = 0.0;
+    if (c >= P.nl) {
+      const long long e3q = O.e3(c) + nx;
       const double sq = (double)P.sqN[(size_t)c * nx + k];
       const double d = al * ((double)z[O.x(c) + k] * (double)lb[e3q + k] - (double)la[O.x(c) + k] * (double)eta[e3q + k]);
-      gqN[(size_t)c * nx + k] = sq > 0.0 ? d / (2.0 * sq) : 0.0;
+      out = sq > 0.0 ? d / (2.0 * sq) : 0.0;
     }
+    t.gqN[e] = out;
   }
 }
 
@@ -229,22 +280,33 @@ hipError_t launch_jg_batch(const Problem& P, const S* b, const S* w, S* out, lon
   return hipGetLastError();
 }
 template <typename S>
-hipError_t launch_phiT(const Problem& P, const S* cz, S* mu, hipStream_t st) {
+hipError_t launch_adj_load(const Problem& P, double gV, const AdjPtrs<S>* tab, long long is, int B, S* v, double* x0s,
+                           S* g, S* w, hipStream_t st) {
+  const long long nv = P.nz + P.neta;
+  const int nb = (int)std::min<long long>((nv + 255) / 256, 64);
+  hipLaunchKernelGGL(k_adj_load<S>, dim3(nb, B), dim3(256), 0, st, nv, P.nx, P.nu,
+                     1 + (long long)P.tree->nn * P.nx, gV, tab, is, v, x0s, g, w);
+  return hipGetLastError();
+}
+template <typename S>
+hipError_t launch_phiT(const Problem& P, const S* cz, long long is, S* mu, long long ms, int B,
+                       const AdjPtrs<S>* tab, hipStream_t st) {
   const DevProb<S>& D = (sizeof(S) == 8) ? *reinterpret_cast<const DevProb<S>*>(&P.dp64)
                                          : *reinterpret_cast<const DevProb<S>*>(&P.dp32);
   const Tree& T = *P.tree;
   for (int t = T.N - 1; t >= 0; --t) {
     const int first = T.stage_off[t], count = T.stage_off[t + 1] - first;
-    hipLaunchKernelGGL(k_phiT<S>, dim3((count + 127) / 128), dim3(128), 0, st, D, cz, mu, first, count);
+    hipLaunchKernelGGL(k_phiT<S>, dim3((count + 3) / 4, B), dim3(256), 0, st, D, cz, is, mu, ms, first, count, tab);
   }
   return hipGetLastError();
 }
 template <typename S>
-hipError_t launch_grad_q(const Problem& P, const S* vstar, const S* la, const S* lb, double* gq, double* gqN,
-                         hipStream_t st) {
+hipError_t launch_grad_q(const Problem& P, const S* vstar, const S* la, const S* lb, long long is, int B,
+                         const AdjPtrs<S>* tab, hipStream_t st) {
   const DevProb<S>& D = (sizeof(S) == 8) ? *reinterpret_cast<const DevProb<S>*>(&P.dp64)
                                          : *reinterpret_cast<const DevProb<S>*>(&P.dp32);
-  hipLaunchKernelGGL(k_grad_q<S>, dim3((P.tree->nn + 127) / 128), dim3(128), 0, st, D, vstar, la, lb, gq, gqN);
+  const long long ne = (long long)P.tree->nn * P.nx;
+  hipLaunchKernelGGL(k_grad_q<S>, dim3((unsigned)((ne + 255) / 256), B), dim3(256), 0, st, D, vstar, la, lb, is, tab);
   return hipGetLastError();
 }
 template <typename S>
@@ -259,9 +321,12 @@ hipError_t launch_maxdiff(long long n, const S* a, const S* b, double* partials,
   template hipError_t launch_copy_elem<S>(S*, const S*, hipStream_t);                                 \
   template hipError_t launch_jg<S>(const Problem&, const S*, const S*, S*, hipStream_t);              \
   template hipError_t launch_jg_batch<S>(const Problem&, const S*, const S*, S*, long long, int, hipStream_t); \
-  template hipError_t launch_phiT<S>(const Problem&, const S*, S*, hipStream_t);                      \
-  template hipError_t launch_grad_q<S>(const Problem&, const S*, const S*, const S*, double*, double*, \
-                                       hipStream_t);                                                  \
+  template hipError_t launch_adj_load<S>(const Problem&, double, const AdjPtrs<S>*, long long, int, S*, double*, S*, \
+                                         S*, hipStream_t);                                            \
+  template hipError_t launch_phiT<S>(const Problem&, const S*, long long, S*, long long, int,         \
+                                     const AdjPtrs<S>*, hipStream_t);                                 \
+  template hipError_t launch_grad_q<S>(const Problem&, const S*, const S*, const S*, long long, int,  \
+                                       const AdjPtrs<S>*, hipStream_t);                               \
   template hipError_t launch_maxdiff<S>(long long, const S*, const S*, double*, double*, hipStream_t);
 SPK_BINST(double)
 SPK_BINST(float)

@@ -2055,22 +2055,12 @@ int backward_once(Problem& P, const S* vstar, const double* x0, double gV, const
   HIP_TRY(launch_lincomb<S>(nz, dz, 2.0, Tv, -1.0, vstar, st));
   HIP_TRY(launch_L<S>(P, dz, Ldz, st));
   HIP_TRY(launch_lincomb<S>(ne, b, 1.0, vstar + nz, al, Ldz, st));
-  // cotangent of v*: gV on s^0, gu0 on u^0
-  HIP_TRY(launch_fill<S>(nv, g, 0.0, st));
-  {
-    std::vector<S> head(1 + (size_t)T.nn * P.nx + P.nu, S(0));
-    HIP_TRY(hipMemcpyAsync(head.data(), g, head.size() * sizeof(S), hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
-    head[0] = (S)gV;
-    if (gu0) {
-      std::vector<double> hu(P.nu);
-      HIP_TRY(hipMemcpy(hu.data(), gu0, P.nu * sizeof(double), hipMemcpyDeviceToHost));
-      const size_t u0 = 1 + (size_t)T.nn * P.nx;  // u^0 follows every x^i
-      for (int k = 0; k < P.nu; ++k) head[u0 + k] = (S)hu[k];
-    }
-    HIP_TRY(hipMemcpyAsync(g, head.data(), head.size() * sizeof(S), hipMemcpyHostToDevice, st));
-  }
-  HIP_TRY(launch_lincomb<S>(nv, w, 1.0, g, 0.0, nullptr, st));
+  // the buffers' table, the cotangent of v* (gV on s^0, gu0 on u^0) and w = g
+  const AdjPtrs<S> tab{vstar, x0, gu0, gx0, gq, gqN};
+  AdjPtrs<S>* tab_d = reinterpret_cast<AdjPtrs<S>*>(W.dots);
+  static_assert(sizeof(tab) <= sizeof(double) * 8, "the table shares the dot products' block");
+  HIP_TRY(hipMemcpyAsync(tab_d + 1, &tab, sizeof(tab), hipMemcpyHostToDevice, st));
+  HIP_TRY(launch_adj_load<S>(P, gV, tab_d + 1, 0, 1, nullptr, nullptr, g, w, st));
   S* zeros = W.pool[12];
   HIP_TRY(launch_fill<S>(nv, zeros, 0.0, st));
   HIP_TRY(hipMemsetAsync(W.x0_zero, 0, sizeof(double) * kMaxDim, st));
@@ -2294,19 +2284,8 @@ int backward_once(Problem& P, const S* vstar, const double* x0, double gV, const
     if (rc) return rc;
     if (gave_up) return kFlowGaveUp;
   }
-  S* mu = W.q;
-  HIP_TRY(launch_phiT<S>(P, cz, mu, st));
-  {
-    std::vector<S> hm(P.nx);
-    HIP_TRY(hipMemcpyAsync(hm.data(), mu, P.nx * sizeof(S), hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
-    std::vector<double> out(P.nx);
-    for (int j = 0; j < P.nx; ++j) out[j] = hm[j];
-    HIP_TRY(hipMemcpy(gx0, out.data(), P.nx * sizeof(double), hipMemcpyHostToDevice));
-  }
-  if (gq) HIP_TRY(hipMemsetAsync(gq, 0, sizeof(double) * (size_t)T.nn * P.nx, st));
-  if (gqN) HIP_TRY(hipMemsetAsync(gqN, 0, sizeof(double) * (size_t)T.nn * P.nx, st));
-  if (gq || gqN) HIP_TRY(launch_grad_q<S>(P, vstar, la, lb, gq, gqN, st));
+  HIP_TRY(launch_phiT<S>(P, cz, 0, W.q, 0, 1, tab_d + 1, st));
+  if (gq || gqN) HIP_TRY(launch_grad_q<S>(P, vstar, la, lb, 0, 1, tab_d + 1, st));
   HIP_TRY(hipStreamSynchronize(st));
   return SPOCK_OK;
 }

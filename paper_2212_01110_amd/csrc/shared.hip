@@ -1247,7 +1247,8 @@ int shared_backward(Problem& P, int B, const void* const* vstar, const double* c
   const size_t o_c = reserve(sizeof(double) * (size_t)Bp * ldc * 3);
   const size_t o_part = reserve(sizeof(double) * (size_t)Bp * (kMax + 2) * cb);
   const size_t o_md = reserve(sizeof(double) * (size_t)Bp * 2);
-  const size_t o_mu = reserve(sizeof(S) * (size_t)Tr.nn * nx);
+  const size_t o_mu = reserve(sizeof(S) * (size_t)B * Tr.nn * nx);
+  const size_t o_tab = reserve(sizeof(AdjPtrs<S>) * (size_t)B);
   void* mem = nullptr;
   if (hipMalloc(&mem, off) != hipSuccess) return SPOCK_ENOMEM;
   struct Guard {
@@ -1255,7 +1256,10 @@ int shared_backward(Problem& P, int B, const void* const* vstar, const double* c
     ~Guard() { (void)hipFree(m); }
   } guard{mem};
   char* base = static_cast<char*>(mem);
-  SH_TRY(hipMemsetAsync(base, 0, off, st));  // padding instances stay at zero
+  // padding instances stay at zero; a basis vector is written (by every
+  // instance) before anything reads it
+  SH_TRY(hipMemsetAsync(base, 0, o_bas, st));
+  SH_TRY(hipMemsetAsync(base + o_qx, 0, off - o_qx, st));
   S* vec[kNVec];
   for (int r = 0; r < kNVec; ++r) vec[r] = reinterpret_cast<S*>(base + o_vec) + (size_t)r * nvec;
   S* basis = reinterpret_cast<S*>(base + o_bas);
@@ -1272,6 +1276,7 @@ int shared_backward(Problem& P, int B, const void* const* vstar, const double* c
   double* part = reinterpret_cast<double*>(base + o_part);
   double* md = reinterpret_cast<double*>(base + o_md);
   S* mu = reinterpret_cast<S*>(base + o_mu);
+  AdjPtrs<S>* tab_d = reinterpret_cast<AdjPtrs<S>*>(base + o_tab);
   const int vb = (int)std::min<long long>((nv + 255) / 256, 64);
   auto op = [&](int r, long long o = 0) { return BOp<S>{vec[r], vs, o}; };
   auto lin3 = [&](long long len, BOp<S> o, double a, BOp<S> x, double c = 0, BOp<S> y = BOp<S>{nullptr, 0, 0},
@@ -1280,27 +1285,13 @@ int shared_backward(Problem& P, int B, const void* const* vstar, const double* c
     SH_TRY(hipGetLastError());
     return SPOCK_OK;
   };
-  // ---- inputs: v* and x0 of every instance, the cotangents
-  for (int b = 0; b < B; ++b) {
-    SH_TRY(hipMemcpyAsync(vec[kV] + (size_t)b * vs, vstar[b], sizeof(S) * nv, hipMemcpyDeviceToDevice, st));
-    SH_TRY(hipMemcpyAsync(x0s + (size_t)b * nx, x0[b], sizeof(double) * nx, hipMemcpyDeviceToDevice, st));
-  }
-  {
-    const size_t head = 1 + (size_t)Tr.nn * nx + nu;
-    std::vector<S> hg((size_t)B * head, S(0));
-    std::vector<double> hu(nu);
-    for (int b = 0; b < B; ++b) {
-      hg[(size_t)b * head] = (S)gV;
-      if (gu0 && gu0[b]) {
-        SH_TRY(hipMemcpy(hu.data(), gu0[b], sizeof(double) * nu, hipMemcpyDeviceToHost));
-        for (int k = 0; k < nu; ++k) hg[(size_t)b * head + 1 + (size_t)Tr.nn * nx + k] = (S)hu[k];
-      }
-    }
-    for (int b = 0; b < B; ++b)
-      SH_TRY(hipMemcpyAsync(vec[kG] + (size_t)b * vs, hg.data() + (size_t)b * head, sizeof(S) * head,
-                            hipMemcpyHostToDevice, st));
-    SH_TRY(hipStreamSynchronize(st));  // hg is a local buffer
-  }
+  // ---- inputs: v* and x0 of every instance, the cotangents and w = g
+  std::vector<AdjPtrs<S>> tab(B);
+  for (int b = 0; b < B; ++b)
+    tab[b] = AdjPtrs<S>{static_cast<const S*>(vstar[b]), x0[b], gu0 ? gu0[b] : nullptr,
+                        gx0[b], gq ? gq[b] : nullptr, gqN ? gqN[b] : nullptr};
+  SH_TRY(hipMemcpyAsync(tab_d, tab.data(), sizeof(AdjPtrs<S>) * B, hipMemcpyHostToDevice, st));
+  SH_TRY(launch_adj_load<S>(P, gV, tab_d, vs, B, vec[kV], x0s, vec[kG], vec[kW], st));
   // T of the instances without (with) the dual part: pre-pass, then the
   // sweeps in the phases of the shared-tree form
   int maxch = 1;
@@ -1376,7 +1367,6 @@ int shared_backward(Problem& P, int B, const void* const* vstar, const double* c
   };
   auto V = [&](int j) { return basis + (size_t)j * vs; };  // vector j of instance 0 (instances bs apart)
   // ---- restarted GMRES per instance, Arnoldi steps in lockstep
-  SH_TRY(hipMemcpyAsync(vec[kW], vec[kG], sizeof(S) * nvec, hipMemcpyDeviceToDevice, st));
   const double tol = std::max(s.eps_abs, 1e-15);
   std::vector<int> kk(B, 0), state(B, 0);  // state: 0 running, 1 converged, 2 numerical, 3 max_iters
   std::vector<double> diff(B, 0.0);
@@ -1495,21 +1485,9 @@ int shared_backward(Problem& P, int B, const void* const* vstar, const double* c
   // gradients from the converged adjoints
   SH_TRY(hipMemcpyAsync(vec[kIn], vec[kW], sizeof(S) * nvec, hipMemcpyDeviceToDevice, st));
   if (int r = partial(kIn)) return r;
+  SH_TRY(launch_phiT<S>(P, vec[kCz], vs, mu, (long long)Tr.nn * nx, B, tab_d, st));
+  if (gq || gqN) SH_TRY(launch_grad_q<S>(P, vec[kV], vec[kLa], vec[kLb], vs, B, tab_d, st));
   for (int b = 0; b < B; ++b) {
-    SH_TRY(launch_phiT<S>(P, vec[kCz] + (size_t)b * vs, mu, st));
-    std::vector<S> hm(nx);
-    SH_TRY(hipMemcpyAsync(hm.data(), mu, nx * sizeof(S), hipMemcpyDeviceToHost, st));
-    SH_TRY(hipStreamSynchronize(st));
-    std::vector<double> outv(nx);
-    for (int k = 0; k < nx; ++k) outv[k] = hm[k];
-    SH_TRY(hipMemcpy(gx0[b], outv.data(), nx * sizeof(double), hipMemcpyHostToDevice));
-    double* gqb = gq ? gq[b] : nullptr;
-    double* gqNb = gqN ? gqN[b] : nullptr;
-    if (gqb) SH_TRY(hipMemsetAsync(gqb, 0, sizeof(double) * (size_t)Tr.nn * nx, st));
-    if (gqNb) SH_TRY(hipMemsetAsync(gqNb, 0, sizeof(double) * (size_t)Tr.nn * nx, st));
-    if (gqb || gqNb)
-      SH_TRY(launch_grad_q<S>(P, vec[kV] + (size_t)b * vs, vec[kLa] + (size_t)b * vs, vec[kLb] + (size_t)b * vs, gqb,
-                              gqNb, st));
     spock_info loc{};
     loc.V_nested = std::numeric_limits<double>::quiet_NaN();
     loc.status = state[b] == 1 ? SPOCK_CONVERGED : (state[b] == 2 ? SPOCK_NUMERICAL : SPOCK_MAXITER);

@@ -396,11 +396,29 @@ template <typename S>
 hipError_t launch_jg(const Problem& P, const S* b, const S* w, S* out, hipStream_t st);
 template <typename S>
 hipError_t launch_jg_batch(const Problem& P, const S* b, const S* w, S* out, long long is, int B, hipStream_t st);
+// Buffers of one instance of an adjoint (device table, one entry per
+// instance): inputs v*, x0 and gu0 (or null), outputs gx0 and gq, gqN (or null).
 template <typename S>
-hipError_t launch_phiT(const Problem& P, const S* cz, S* mu, hipStream_t st);
+struct AdjPtrs {
+  const S* vstar;
+  const double* x0;
+  const double* gu0;
+  double* gx0;
+  double* gq;
+  double* gqN;
+};
+// Instances `is` elements apart. v and x0s may be null (not gathered).
 template <typename S>
-hipError_t launch_grad_q(const Problem& P, const S* vstar, const S* la, const S* lb, double* gq,
-                         double* gqN, hipStream_t st);
+hipError_t launch_adj_load(const Problem& P, double gV, const AdjPtrs<S>* tab, long long is, int B, S* v, double* x0s,
+                           S* g, S* w, hipStream_t st);
+// mu: [nn][nx] per instance, ms apart; gx0 written from mu^0
+template <typename S>
+hipError_t launch_phiT(const Problem& P, const S* cz, long long is, S* mu, long long ms, int B,
+                       const AdjPtrs<S>* tab, hipStream_t st);
+// every entry of gq and gqN (where given); vstar null: the table's
+template <typename S>
+hipError_t launch_grad_q(const Problem& P, const S* vstar, const S* la, const S* lb, long long is, int B,
+                         const AdjPtrs<S>* tab, hipStream_t st);
 template <typename S>
 hipError_t launch_maxdiff(long long n, const S* a, const S* b, double* partials, double* out,
                           hipStream_t st);
