@@ -4,22 +4,27 @@
 // the parts of T that touch y, the constraint rows and the leaves' rows
 // change; the Alg. 2 sweeps are shared with every other problem.
 //
-// One thread per family (nonleaf node i with its children). Every row of L
-// and every column of L* belongs to exactly one family:
-//   rows:    group 1 of i (y^i, s^i - b'y^i, the nc constraint rows), group
-//            2 of each child (the SOC block), group 3 of each leaf child
-//            (ncN constraint rows, then its SOC block);
-//   columns: y^i, s^i, x^i, u^i, tau of each child, and x^j, s^j of each
-//            leaf child.
+// One wavefront per unit. The units are the families (nonleaf node i: group 1
+// of i, group 2 of each child; columns y^i, s^i, x^i, u^i, tau of each child)
+// and the leaves (group 3; columns x^j, s^j): every row of L and every column
+// of L* belongs to exactly one unit, so no unit waits on another. Lane o owns
+// component o of every state and input (n_x, n_u <= 64); constraint rows go 64
+// at a time, one lane a row, with the row values left in LDS for the columns.
+// The kernels are bound by the latency of a unit's load chains (a unit's data
+// is a few KiB): one thread per family walked every row and column alone, 372
+// and 115 us for the post- and pre-pass of a 364-node tree (n_x 13, n_u 6, 9
+// and 7 rows, FP64) that move 0.5 MB.
 #include "device_common.h"
 
 #include <math.h>
+#include <algorithm>
 
 namespace spk {
 
 namespace {
 
 constexpr int kGenThreads = 256;
+constexpr int kGenWaves = kGenThreads / 64;
 
 // Offsets in the general layout.
 template <typename S>
@@ -48,112 +53,90 @@ struct GOff {
   __device__ const S* Gx(int i) const { return G.Gx + (size_t)i * G.nc * P.nx; }
   __device__ const S* Gu(int i) const { return G.Gu + (size_t)i * G.nc * P.nu; }
   __device__ const S* GN(int j) const { return G.GN + (size_t)(j - P.nl) * G.ncN * P.nx; }
-  // Row o of a cost root applied to the vector f(base + k), k < n: kind 0
-  // Q^c (on x), 1 R^c (on u), 2 Q_N^c (on x). Dense symmetric roots when the
-  // problem has dense costs, else the roots of the diagonals. The roots are
-  // symmetric, so the same rows give the L* columns.
-  template <typename F>
-  __device__ S croot(int kind, int c, int o, long long base, F&& f) const {
+  __device__ const S* root(int kind) const { return kind == 0 ? G.Qh : (kind == 1 ? G.Rh : G.QNh); }
+  // Component o of a cost root of node c applied to a vector: kind 0 Q^c (on
+  // x), 1 R^c (on u), 2 Q_N^c (on x). Diagonal roots scale the lane's own
+  // component; dense ones (symmetric, so the columns are read: lane o at
+  // k n + o, coalesced) need the whole vector at vec (LDS or global). The
+  // same columns give the L* columns.
+  __device__ S croot(int kind, int c, int o, S own, const S* vec) const {
     const int n = kind == 1 ? P.nu : P.nx;
-    const S* M = kind == 0 ? G.Qh : (kind == 1 ? G.Rh : G.QNh);
+    const S* M = root(kind);
     if (M) {
-      const S* row = M + ((size_t)c * n + o) * n;
+      const S* col = M + (size_t)c * n * n + o;
       S acc = 0;
-      for (int k = 0; k < n; ++k) acc += row[k] * f(base + k);
+#pragma unroll 4
+      for (int k = 0; k < n; ++k) acc += col[(size_t)k * n] * vec[k];
       return acc;
     }
     const S* dg = kind == 0 ? P.sq : (kind == 1 ? P.sr : P.sqN);
-    return dg[(size_t)c * n + o] * f(base + o);
+    return dg[(size_t)c * n + o] * own;
   }
 };
 
-// (L* eta) on column x^i of nonleaf i, component o: Gamma_x' eta_c plus the
-// children's Q^{1/2} rows.
+// sum_r M[r][o] v[r], r < rows (M row-major with ld columns): lane o's column
 template <typename S>
-__device__ S lt_x(const GOff<S>& O, const S* eta, int i, int o) {
+__device__ __forceinline__ S col_dot(const S* __restrict__ M, int rows, int ld, int o, const S* v, S acc) {
+#pragma unroll 8
+  for (int r = 0; r < rows; ++r) acc += M[(size_t)r * ld + o] * v[r];
+  return acc;
+}
+// sum_o row[o] v[o], o < n: one lane per row
+template <typename S>
+__device__ __forceinline__ S row_dot(const S* __restrict__ row, int n, const S* v, S acc) {
+#pragma unroll 8
+  for (int o = 0; o < n; ++o) acc += row[o] * v[o];
+  return acc;
+}
+
+// (L* eta) on columns x^i (or u^i) of nonleaf i, component o: Gamma' eta_c
+// plus the children's cost-root rows.
+template <typename S>
+__device__ __forceinline__ S lt_x(const GOff<S>& O, const S* eta, int i, int o) {
   const DevProb<S>& P = O.P;
-  const int nx = P.nx, nc = O.G.nc;
-  const S* gx = O.Gx(i);
-  const long long ec = O.e1c(i);
-  S acc = 0;
-  for (int r = 0; r < nc; ++r) acc += gx[(size_t)r * nx + o] * eta[ec + r];
-  auto ev = [&](long long e) { return eta[e]; };
-  for (int c = P.fc[i]; c < P.fc[i] + P.nch[i]; ++c) acc += O.croot(0, c, o, O.e2(c), ev);
+  S acc = col_dot(O.Gx(i), O.G.nc, P.nx, o, eta + O.e1c(i), S(0));
+  for (int c = P.fc[i]; c < P.fc[i] + P.nch[i]; ++c) acc += O.croot(0, c, o, eta[O.e2(c) + o], eta + O.e2(c));
   return acc;
 }
 template <typename S>
-__device__ S lt_u(const GOff<S>& O, const S* eta, int i, int o) {
+__device__ __forceinline__ S lt_u(const GOff<S>& O, const S* eta, int i, int o) {
   const DevProb<S>& P = O.P;
-  const int nx = P.nx, nu = P.nu, nc = O.G.nc;
-  const S* gu = O.Gu(i);
-  const long long ec = O.e1c(i);
-  S acc = 0;
-  for (int r = 0; r < nc; ++r) acc += gu[(size_t)r * nu + o] * eta[ec + r];
-  auto ev = [&](long long e) { return eta[e]; };
-  for (int c = P.fc[i]; c < P.fc[i] + P.nch[i]; ++c) acc += O.croot(1, c, o, O.e2(c) + nx, ev);
+  S acc = col_dot(O.Gu(i), O.G.nc, P.nu, o, eta + O.e1c(i), S(0));
+  for (int c = P.fc[i]; c < P.fc[i] + P.nch[i]; ++c) {
+    const long long e = O.e2(c) + P.nx;
+    acc += O.croot(1, c, o, eta[e + o], eta + e);
+  }
   return acc;
 }
 // column x^j of leaf j: Gamma_N' eta_cN + Q_N^{1/2} eta_q
 template <typename S>
-__device__ S lt_xleaf(const GOff<S>& O, const S* eta, int j, int o) {
-  const DevProb<S>& P = O.P;
-  const int nx = P.nx, ncN = O.G.ncN;
-  const S* gn = O.GN(j);
-  const long long e3 = O.e3(j);
-  S acc = O.croot(2, j, o, O.e3q(j), [&](long long e) { return eta[e]; });
-  for (int r = 0; r < ncN; ++r) acc += gn[(size_t)r * nx + o] * eta[e3 + r];
-  return acc;
+__device__ __forceinline__ S lt_xleaf(const GOff<S>& O, const S* eta, int j, int o) {
+  const long long e3q = O.e3q(j);
+  return col_dot(O.GN(j), O.G.ncN, O.P.nx, o, eta + O.e3(j), O.croot(2, j, o, eta[e3q + o], eta + e3q));
 }
 // column s^c: the s-row of c when c is nonleaf, else half the sum of its
 // group-3 pair
 template <typename S>
-__device__ S lt_s(const GOff<S>& O, const S* eta, int c) {
+__device__ __forceinline__ S lt_s(const GOff<S>& O, const S* eta, int c) {
   if (c < O.P.nl) return eta[O.e1s(c)];
   const long long e = O.e3q(c) + O.P.nx;
   return S(0.5) * (eta[e] + eta[e + 1]);
 }
-// row r of Gamma_x x^i + Gamma_u u^i for the vector z
-template <typename S>
-__device__ S l_c(const GOff<S>& O, const S* z, int i, int r) {
-  const DevProb<S>& P = O.P;
-  const S* gx = O.Gx(i) + (size_t)r * P.nx;
-  const S* gu = O.Gu(i) + (size_t)r * P.nu;
-  S acc = 0;
-  for (int o = 0; o < P.nx; ++o) acc += gx[o] * z[O.x(i) + o];
-  for (int o = 0; o < P.nu; ++o) acc += gu[o] * z[O.u(i) + o];
-  return acc;
-}
-template <typename S>
-__device__ S l_cN(const GOff<S>& O, const S* z, int j, int r) {
-  const DevProb<S>& P = O.P;
-  const S* gn = O.GN(j) + (size_t)r * P.nx;
-  S acc = 0;
-  for (int o = 0; o < P.nx; ++o) acc += gn[o] * z[O.x(j) + o];
-  return acc;
-}
-// s^i - b'y^i
-template <typename S>
-__device__ S l_s(const GOff<S>& O, const S* z, int i) {
-  const S* b = O.G.b + O.G.yoff[i];
-  S acc = z[O.s(i)];
-  for (int k = 0; k < O.G.ny[i]; ++k) acc -= b[k] * z[O.y(i) + k];
-  return acc;
-}
 
-// prox of g* on the translated SOC block (eq. S3-def, shift (0,..,0,1/2,-1/2))
-// of len entries at w (then the two trailing scalars): out = w - alpha
-// (shift + proj_SOC(w / alpha - shift)); one thread.
+// prox of g* on a translated SOC block (eq. S3-def, shift (0,..,0,1/2,-1/2))
+// by one wavefront: the vector part in two components per lane (w0 counts if
+// on0, w1 if on1), the two trailing scalars in every lane; out = w - alpha
+// (shift + proj_SOC(w / alpha - shift)).
 template <typename S>
-__device__ void soc_prox_one(const S* w, S* out, int len, S al) {
+__device__ __forceinline__ void soc_prox_wave(S& w0, bool on0, S& w1, bool on1, S& wa, S& wb, S al) {
   const S ia = S(1) / al;
-  double n2 = 0;
-  for (int o = 0; o < len; ++o) {
-    const double t = (double)(w[o] * ia);
-    n2 += t * t;
-  }
-  const S va = w[len] * ia - S(0.5);
-  const S t = w[len + 1] * ia + S(0.5);
-  const S nrm = (S)sqrt(n2 + (double)va * (double)va);
+  const S t0 = w0 * ia, t1 = w1 * ia;
+  double part = 0;
+  if (on0) part += (double)t0 * (double)t0;
+  if (on1) part += (double)t1 * (double)t1;
+  const S va = wa * ia - S(0.5);
+  const S t = wb * ia + S(0.5);
+  const S nrm = (S)sqrt(team_sum<64>(part) + (double)va * (double)va);
   S scale, pt;
   if (nrm <= t) {
     scale = S(1);
@@ -166,309 +149,383 @@ __device__ void soc_prox_one(const S* w, S* out, int len, S al) {
     scale = cc / nrm;
     pt = cc;
   }
-  for (int o = 0; o < len; ++o) out[o] = w[o] - al * (scale * (w[o] * ia));
-  out[len] = w[len] - al * (S(0.5) + scale * va);
-  out[len + 1] = w[len + 1] - al * (S(-0.5) + pt);
+  w0 = w0 - al * (scale * t0);
+  w1 = w1 - al * (scale * t1);
+  wa = wa - al * (S(0.5) + scale * va);
+  wb = wb - al * (S(-0.5) + pt);
 }
 
-// prox of g* on the rows of family i for the dual argument at w (rows as in
-// eta), written to out: group 1 (K* on y, R_+ on the s-row, C^i on the
-// constraint rows), group 2 of every child, group 3 of leaf children.
-// The SOC blocks go through out itself (the argument is read first).
+// prox of g* of one unit for the dual argument at w (rows as in eta), written
+// to out (which may be w): group 1 (K* on y, R_+ on the s-row, C^i on the
+// constraint rows) and group 2 of every child of a family, or group 3 of a
+// leaf.
 template <typename S>
-__device__ void fam_gen_prox(const GOff<S>& O, const S* w, S* out, int i) {
+__device__ void unit_gen_prox(const GOff<S>& O, const S* w, S* out, int i, int lane) {
   const DevProb<S>& P = O.P;
   const GenDev<S>& G = O.G;
+  const int nx = P.nx, nu = P.nu;
   const S al = P.alpha, ia = S(1) / al;
-  const long long e1 = O.e1(i);
-  const int ny = G.ny[i], kp = G.kpos[i];
-  for (int k = 0; k < ny; ++k) {
-    const S v = w[e1 + k];
-    out[e1 + k] = k < kp ? (v < S(0) ? v : S(0)) : S(0);
-  }
-  {
-    const S v = w[O.e1s(i)];
-    out[O.e1s(i)] = v < S(0) ? v : S(0);
-  }
-  const long long ec = O.e1c(i);
-  for (int r = 0; r < G.nc; ++r) {
-    const S v = w[ec + r];
-    out[ec + r] = v - al * clampv(v * ia, G.cmin[(size_t)i * G.nc + r], G.cmax[(size_t)i * G.nc + r]);
-  }
-  for (int c = P.fc[i]; c < P.fc[i] + P.nch[i]; ++c) {
-    soc_prox_one<S>(w + O.e2(c), out + O.e2(c), P.nx + P.nu, al);
-    if (c >= P.nl) {
-      const long long e3 = O.e3(c);
-      const size_t lj = (size_t)(c - P.nl) * G.ncN;
-      for (int r = 0; r < G.ncN; ++r) {
-        const S v = w[e3 + r];
-        out[e3 + r] = v - al * clampv(v * ia, G.cNmin[lj + r], G.cNmax[lj + r]);
+  const bool onx = lane < nx, onu = lane < nu;
+  if (i < P.nl) {
+    const long long e1 = O.e1(i), ec = O.e1c(i);
+    const int ny = G.ny[i], kp = G.kpos[i];
+    for (int k = lane; k <= ny; k += 64) {  // y, then the s-row
+      const S v = w[e1 + k];
+      out[e1 + k] = (k < kp || k == ny) ? (v < S(0) ? v : S(0)) : S(0);
+    }
+    for (int r = lane; r < G.nc; r += 64) {
+      const S v = w[ec + r];
+      out[ec + r] = v - al * clampv(v * ia, G.cmin[(size_t)i * G.nc + r], G.cmax[(size_t)i * G.nc + r]);
+    }
+    for (int c = P.fc[i]; c < P.fc[i] + P.nch[i]; ++c) {
+      const long long e2 = O.e2(c);
+      S wx = onx ? w[e2 + lane] : S(0), wu = onu ? w[e2 + nx + lane] : S(0);
+      S wa = w[e2 + nx + nu], wb = w[e2 + nx + nu + 1];
+      soc_prox_wave(wx, onx, wu, onu, wa, wb, al);
+      if (onx) out[e2 + lane] = wx;
+      if (onu) out[e2 + nx + lane] = wu;
+      if (lane == 0) {
+        out[e2 + nx + nu] = wa;
+        out[e2 + nx + nu + 1] = wb;
       }
-      soc_prox_one<S>(w + O.e3q(c), out + O.e3q(c), P.nx, al);
     }
+    return;
+  }
+  const long long e3 = O.e3(i), e3q = O.e3q(i);
+  const size_t lj = (size_t)(i - P.nl) * G.ncN;
+  for (int r = lane; r < G.ncN; r += 64) {
+    const S v = w[e3 + r];
+    out[e3 + r] = v - al * clampv(v * ia, G.cNmin[lj + r], G.cNmax[lj + r]);
+  }
+  S wx = onx ? w[e3q + lane] : S(0), none = S(0);
+  S wa = w[e3q + nx], wb = w[e3q + nx + 1];
+  soc_prox_wave(wx, onx, none, false, wa, wb, al);
+  if (onx) out[e3q + lane] = wx;
+  if (lane == 0) {
+    out[e3q + nx] = wa;
+    out[e3q + nx + 1] = wb;
   }
 }
 
-// rows of L z owned by family i, written into eta (or, with scale and base,
-// eta = base + scale L z)
+// rows of L z of one unit, written into eta (or, with base, eta = base + scale L z)
 template <typename S>
-__device__ void fam_gen_L(const GOff<S>& O, const S* z, S* eta, int i, const S* base, S scale) {
+__device__ void unit_gen_L(const GOff<S>& O, const S* z, S* eta, int i, const S* base, S scale, int lane) {
   const DevProb<S>& P = O.P;
   const GenDev<S>& G = O.G;
   const int nx = P.nx, nu = P.nu;
+  const bool onx = lane < nx, onu = lane < nu;
   auto put = [&](long long e, S v) { eta[e] = base ? base[e] + scale * v : v; };
-  const long long e1 = O.e1(i);
-  for (int k = 0; k < G.ny[i]; ++k) put(e1 + k, z[O.y(i) + k]);
-  put(O.e1s(i), l_s<S>(O, z, i));
-  for (int r = 0; r < G.nc; ++r) put(O.e1c(i) + r, l_c<S>(O, z, i, r));
-  for (int c = P.fc[i]; c < P.fc[i] + P.nch[i]; ++c) {
-    const long long e2 = O.e2(c);
-    auto zv = [&](long long e) { return z[e]; };
-    for (int o = 0; o < nx; ++o) put(e2 + o, O.croot(0, c, o, O.x(i), zv));
-    for (int o = 0; o < nu; ++o) put(e2 + nx + o, O.croot(1, c, o, O.u(i), zv));
-    const S th = S(0.5) * z[O.tau(c)];
-    put(e2 + nx + nu, th);
-    put(e2 + nx + nu + 1, th);
-    if (c >= P.nl) {
-      const long long e3 = O.e3(c);
-      for (int r = 0; r < G.ncN; ++r) put(e3 + r, l_cN<S>(O, z, c, r));
-      const long long e3q = O.e3q(c);
-      for (int o = 0; o < nx; ++o) put(e3q + o, O.croot(2, c, o, O.x(c), zv));
-      const S sh = S(0.5) * z[O.s(c)];
-      put(e3q + nx, sh);
-      put(e3q + nx + 1, sh);
+  const S* xi = z + O.x(i);
+  if (i < P.nl) {
+    const long long e1 = O.e1(i), zy = O.y(i);
+    const int ny = G.ny[i];
+    const S* b = G.b + G.yoff[i];
+    double by = 0;
+    for (int k = lane; k < ny; k += 64) {
+      const S y = z[zy + k];
+      put(e1 + k, y);
+      by += (double)(b[k] * y);
     }
+    by = team_sum<64>(by);
+    if (lane == 0) put(O.e1s(i), (S)((double)z[O.s(i)] - by));
+    const S* ui = z + O.u(i);
+    for (int r = lane; r < G.nc; r += 64)
+      put(O.e1c(i) + r,
+          row_dot(O.Gu(i) + (size_t)r * nu, nu, ui, row_dot(O.Gx(i) + (size_t)r * nx, nx, xi, S(0))));
+    for (int c = P.fc[i]; c < P.fc[i] + P.nch[i]; ++c) {
+      const long long e2 = O.e2(c);
+      if (onx) put(e2 + lane, O.croot(0, c, lane, xi[lane], xi));
+      if (onu) put(e2 + nx + lane, O.croot(1, c, lane, ui[lane], ui));
+      if (lane < 2) put(e2 + nx + nu + lane, S(0.5) * z[O.tau(c)]);
+    }
+    return;
   }
+  const long long e3 = O.e3(i), e3q = O.e3q(i);
+  for (int r = lane; r < G.ncN; r += 64) put(e3 + r, row_dot(O.GN(i) + (size_t)r * nx, nx, xi, S(0)));
+  if (onx) put(e3q + lane, O.croot(2, i, lane, xi[lane], xi));
+  if (lane < 2) put(e3q + nx + lane, S(0.5) * z[O.s(i)]);
 }
 
-// columns of L* eta owned by family i, written into z (or z = base + scale L* eta)
+// columns of L* eta of one unit, written into z (or, with base, z = base + scale L* eta)
 template <typename S>
-__device__ void fam_gen_Lt(const GOff<S>& O, const S* eta, S* z, int i, const S* base, S scale) {
+__device__ void unit_gen_Lt(const GOff<S>& O, const S* eta, S* z, int i, const S* base, S scale, int lane) {
   const DevProb<S>& P = O.P;
   const GenDev<S>& G = O.G;
   const int nx = P.nx, nu = P.nu;
+  const bool onx = lane < nx, onu = lane < nu;
   auto put = [&](long long e, S v) { z[e] = base ? base[e] + scale * v : v; };
-  const S es = eta[O.e1s(i)];
-  const S* b = G.b + G.yoff[i];
-  for (int k = 0; k < G.ny[i]; ++k) put(O.y(i) + k, eta[O.e1(i) + k] - b[k] * es);
-  put(O.s(i), es);
-  for (int o = 0; o < nx; ++o) put(O.x(i) + o, lt_x<S>(O, eta, i, o));
-  for (int o = 0; o < nu; ++o) put(O.u(i) + o, lt_u<S>(O, eta, i, o));
-  for (int c = P.fc[i]; c < P.fc[i] + P.nch[i]; ++c) {
-    const long long e2 = O.e2(c) + nx + nu;
-    put(O.tau(c), S(0.5) * (eta[e2] + eta[e2 + 1]));
-    if (c >= P.nl) {
-      for (int o = 0; o < nx; ++o) put(O.x(c) + o, lt_xleaf<S>(O, eta, c, o));
-      put(O.s(c), lt_s<S>(O, eta, c));
+  if (i < P.nl) {
+    const S es = eta[O.e1s(i)];
+    const S* b = G.b + G.yoff[i];
+    for (int k = lane; k < G.ny[i]; k += 64) put(O.y(i) + k, eta[O.e1(i) + k] - b[k] * es);
+    if (lane == 0) put(O.s(i), es);
+    if (onx) put(O.x(i) + lane, lt_x<S>(O, eta, i, lane));
+    if (onu) put(O.u(i) + lane, lt_u<S>(O, eta, i, lane));
+    for (int k = lane; k < P.nch[i]; k += 64) {
+      const int c = P.fc[i] + k;
+      const long long e2 = O.e2(c) + nx + nu;
+      put(O.tau(c), S(0.5) * (eta[e2] + eta[e2 + 1]));
     }
+    return;
   }
+  if (onx) put(O.x(i) + lane, lt_xleaf<S>(O, eta, i, lane));
+  if (lane == 0) put(O.s(i), lt_s<S>(O, eta, i));
 }
 
 // ---------------------------------------------------------------- kernels
-// pre-pass of T: xbar, ubar = (x, u) - alpha L* eta; leaf children seed the
-// backward sweep with q = -xbar; the (y, tau, s) block of the step
-// z - alpha L* eta is projected on S2 (kernel of [E' -I -I; F' 0 0], the
-// projector formed offline); s^0 - alpha at the root.
+// pre-pass of T: xbar, ubar = (x, u) - alpha L* eta; leaves seed the backward
+// sweep with q = -xbar; the (y, tau, s) block of the step z - alpha L* eta is
+// projected on S2 (kernel of [E' -I -I; F' 0 0], the projector formed
+// offline; symmetric, so lane r reads column r); s^0 - alpha at the root.
 template <typename S>
 __global__ void __launch_bounds__(kGenThreads) k_gen_pre(DevProb<S> P, GenDev<S> G, const S* __restrict__ z,
                                                        const S* __restrict__ eta, S* __restrict__ zout,
                                                        S* __restrict__ xbar, S* __restrict__ ubar,
                                                        S* __restrict__ qbuf) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= P.nl) return;
+  __shared__ S wsh[kGenWaves][kGenMaxBlock];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int i = blockIdx.x * kGenWaves + wave;
+  if (i >= P.nn) return;  // whole wavefronts only; no block barrier below
   const GOff<S> O(P, G);
-  const int nx = P.nx, nu = P.nu, fc = P.fc[i], n = P.nch[i], ny = G.ny[i];
+  const int nx = P.nx, nu = P.nu;
   const S al = P.alpha;
-  for (int o = 0; o < nx; ++o) xbar[(size_t)i * nx + o] = z[O.x(i) + o] - al * lt_x<S>(O, eta, i, o);
-  for (int o = 0; o < nu; ++o) ubar[(size_t)i * nu + o] = z[O.u(i) + o] - al * lt_u<S>(O, eta, i, o);
-  if (fc >= P.nl)  // children are leaves
-    for (int c = fc; c < fc + n; ++c)
-      for (int o = 0; o < nx; ++o)
-        qbuf[(size_t)c * nx + o] = -(z[O.x(c) + o] - al * lt_xleaf<S>(O, eta, c, o));
-  // the (y, tau, s) block after the step, then its projection on S2
-  S w[kGenMaxBlock];
+  if (i >= P.nl) {
+    if (lane < nx) qbuf[(size_t)i * nx + lane] = -(z[O.x(i) + lane] - al * lt_xleaf<S>(O, eta, i, lane));
+    return;
+  }
+  const int fc = P.fc[i], n = P.nch[i], ny = G.ny[i];
+  // the (y, tau, s) block after the step
+  S* w = wsh[wave];
   const S es = eta[O.e1s(i)];
   const S* b = G.b + G.yoff[i];
-  for (int k = 0; k < ny; ++k) w[k] = z[O.y(i) + k] - al * (eta[O.e1(i) + k] - b[k] * es);
-  for (int k = 0; k < n; ++k) {
+  const long long zb = O.y(i);
+  for (int k = lane; k < ny; k += 64) w[k] = z[zb + k] - al * (eta[O.e1(i) + k] - b[k] * es);
+  for (int k = lane; k < n; k += 64) {
     const int c = fc + k;
     const long long e2 = O.e2(c) + nx + nu;
-    w[ny + k] = z[O.tau(c)] - al * S(0.5) * (eta[e2] + eta[e2 + 1]);
-    w[ny + n + k] = z[O.s(c)] - al * lt_s<S>(O, eta, c);
+    w[ny + k] = z[zb + ny + k] - al * S(0.5) * (eta[e2] + eta[e2 + 1]);
+    w[ny + n + k] = z[zb + ny + n + k] - al * lt_s<S>(O, eta, c);
   }
+  if (lane < nx) xbar[(size_t)i * nx + lane] = z[O.x(i) + lane] - al * lt_x<S>(O, eta, i, lane);
+  if (lane < nu) ubar[(size_t)i * nu + lane] = z[O.u(i) + lane] - al * lt_u<S>(O, eta, i, lane);
+  if (i == 0 && lane == 0) zout[0] = z[0] - al * es - al;
+  wave_lds_sync();
   const int m = ny + 2 * n;
   const S* Pm = G.PS2 + G.Poff[i];
-  const long long zb = O.y(i);
-  for (int r = 0; r < m; ++r) {
-    S acc = 0;
-    for (int k = 0; k < m; ++k) acc += Pm[(size_t)r * m + k] * w[k];
-    zout[zb + r] = acc;
-  }
-  if (i == 0) zout[0] = z[0] - al * es - al;
+  for (int r = lane; r < m; r += 64) zout[zb + r] = col_dot(Pm, m, m, r, w, S(0));
 }
 
 // post-pass of T: eta+ = prox_{alpha g*}(eta + alpha L (2 z+ - z)) on the
-// family's rows, and the residual statistics of r = v - T(v) on its rows
+// unit's rows, and the residual statistics of r = v - T(v) on its rows
 // (||r_eta||^2, <r_eta, L r_z>, |r_eta / alpha - L r_z|) and columns
-// (||r_z||^2, |r_z / alpha - L* r_eta|).
+// (||r_z||^2, |r_z / alpha - L* r_eta|). Grid-stride over units, one record
+// per block. LDS per wavefront: 2 z+ - z and r_z of (x, u), and the r_eta of
+// 64 constraint rows or of a cone block (dense roots read it whole).
 template <typename S>
 __global__ void __launch_bounds__(kGenThreads) k_gen_post(DevProb<S> P, GenDev<S> G, const S* __restrict__ z,
                                                         const S* __restrict__ eta, const S* __restrict__ zout,
                                                         S* __restrict__ eout, double* __restrict__ partials) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  __shared__ S lds[kGenWaves][6][64];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  S* X2 = lds[wave][0];
+  S* U2 = lds[wave][1];
+  S* RX = lds[wave][2];
+  S* RU = lds[wave][3];
+  S* E0 = lds[wave][4];
+  S* E1 = lds[wave][5];
+  const GOff<S> O(P, G);
+  const int nx = P.nx, nu = P.nu;
+  const bool onx = lane < nx, onu = lane < nu;
+  const int ox = onx ? lane : 0, ou = onu ? lane : 0;
+  const S al = P.alpha, sia = S(1) / al;
+  const double ia = 1.0 / (double)al;
   StatAcc st;
-  if (i < P.nl) {
-    const GOff<S> O(P, G);
-    const int nx = P.nx, nu = P.nu, fc = P.fc[i], n = P.nch[i], ny = G.ny[i];
-    const S al = P.alpha;
-    const double ia = 1.0 / (double)al;
-    // z2 = 2 z+ - z on the entries the family's rows read, via a lambda
-    auto zz = [&](long long e) { return S(2) * zout[e] - z[e]; };
-    auto rz = [&](long long e) { return z[e] - zout[e]; };
-    // ---- rows: the prox argument w = eta + alpha L(2 z+ - z) into eout,
-    // then the prox in place (fam_gen_prox reads w first)
-    const long long e1 = O.e1(i);
-    for (int k = 0; k < ny; ++k) eout[e1 + k] = eta[e1 + k] + al * zz(O.y(i) + k);
-    {
-      const S* b = G.b + G.yoff[i];
-      S ls = zz(O.s(i));
-      for (int k = 0; k < ny; ++k) ls -= b[k] * zz(O.y(i) + k);
-      eout[O.e1s(i)] = eta[O.e1s(i)] + al * ls;
-    }
-    for (int r = 0; r < G.nc; ++r) {
-      const S* gx = O.Gx(i) + (size_t)r * nx;
-      const S* gu = O.Gu(i) + (size_t)r * nu;
-      S acc = 0;
-      for (int o = 0; o < nx; ++o) acc += gx[o] * zz(O.x(i) + o);
-      for (int o = 0; o < nu; ++o) acc += gu[o] * zz(O.u(i) + o);
-      eout[O.e1c(i) + r] = eta[O.e1c(i) + r] + al * acc;
-    }
-    for (int c = fc; c < fc + n; ++c) {
-      const long long e2 = O.e2(c);
-      for (int o = 0; o < nx; ++o) eout[e2 + o] = eta[e2 + o] + al * O.croot(0, c, o, O.x(i), zz);
-      for (int o = 0; o < nu; ++o) eout[e2 + nx + o] = eta[e2 + nx + o] + al * O.croot(1, c, o, O.u(i), zz);
-      const S th = S(0.5) * zz(O.tau(c));
-      eout[e2 + nx + nu] = eta[e2 + nx + nu] + al * th;
-      eout[e2 + nx + nu + 1] = eta[e2 + nx + nu + 1] + al * th;
-      if (c >= P.nl) {
-        const long long e3 = O.e3(c), e3q = O.e3q(c);
-        for (int r = 0; r < G.ncN; ++r) {
-          const S* gn = O.GN(c) + (size_t)r * nx;
-          S acc = 0;
-          for (int o = 0; o < nx; ++o) acc += gn[o] * zz(O.x(c) + o);
-          eout[e3 + r] = eta[e3 + r] + al * acc;
-        }
-        for (int o = 0; o < nx; ++o) eout[e3q + o] = eta[e3q + o] + al * O.croot(2, c, o, O.x(c), zz);
-        const S sh = S(0.5) * zz(O.s(c));
-        eout[e3q + nx] = eta[e3q + nx] + al * sh;
-        eout[e3q + nx + 1] = eta[e3q + nx + 1] + al * sh;
-      }
-    }
-    fam_gen_prox<S>(O, eout, eout, i);
-    // ---- row statistics: r_eta = eta - eta+ against (L r_z) on the row
-    auto row = [&](long long e, S Lrz) { st.row((double)(eta[e] - eout[e]), (double)Lrz, ia); };
-    for (int k = 0; k < ny; ++k) row(e1 + k, rz(O.y(i) + k));
-    {
-      const S* b = G.b + G.yoff[i];
-      S ls = rz(O.s(i));
-      for (int k = 0; k < ny; ++k) ls -= b[k] * rz(O.y(i) + k);
-      row(O.e1s(i), ls);
-    }
-    for (int r = 0; r < G.nc; ++r) {
-      const S* gx = O.Gx(i) + (size_t)r * nx;
-      const S* gu = O.Gu(i) + (size_t)r * nu;
-      S acc = 0;
-      for (int o = 0; o < nx; ++o) acc += gx[o] * rz(O.x(i) + o);
-      for (int o = 0; o < nu; ++o) acc += gu[o] * rz(O.u(i) + o);
-      row(O.e1c(i) + r, acc);
-    }
-    for (int c = fc; c < fc + n; ++c) {
-      const long long e2 = O.e2(c);
-      for (int o = 0; o < nx; ++o) row(e2 + o, O.croot(0, c, o, O.x(i), rz));
-      for (int o = 0; o < nu; ++o) row(e2 + nx + o, O.croot(1, c, o, O.u(i), rz));
-      row(e2 + nx + nu, S(0.5) * rz(O.tau(c)));
-      row(e2 + nx + nu + 1, S(0.5) * rz(O.tau(c)));
-      if (c >= P.nl) {
-        const long long e3 = O.e3(c), e3q = O.e3q(c);
-        for (int r = 0; r < G.ncN; ++r) {
-          const S* gn = O.GN(c) + (size_t)r * nx;
-          S acc = 0;
-          for (int o = 0; o < nx; ++o) acc += gn[o] * rz(O.x(c) + o);
-          row(e3 + r, acc);
-        }
-        for (int o = 0; o < nx; ++o) row(e3q + o, O.croot(2, c, o, O.x(c), rz));
-        row(e3q + nx, S(0.5) * rz(O.s(c)));
-        row(e3q + nx + 1, S(0.5) * rz(O.s(c)));
-      }
-    }
-    // ---- column statistics: r_z against (L* r_eta) on the column, with
-    // r_eta = eta - eta+ (rows the same thread has just written)
-    auto col = [&](long long e, S Ltre) { st.col((double)rz(e), (double)Ltre, ia); };
-    auto re = [&](long long e) { return eta[e] - eout[e]; };
-    {
-      const S* b = G.b + G.yoff[i];
-      const S res = re(O.e1s(i));
-      for (int k = 0; k < ny; ++k) col(O.y(i) + k, re(e1 + k) - b[k] * res);
-      col(O.s(i), res);
-    }
-    for (int o = 0; o < nx; ++o) {
-      const S* gx = O.Gx(i);
-      S acc = 0;
-      for (int r = 0; r < G.nc; ++r) acc += gx[(size_t)r * nx + o] * re(O.e1c(i) + r);
-      for (int c = fc; c < fc + n; ++c) acc += O.croot(0, c, o, O.e2(c), re);
-      col(O.x(i) + o, acc);
-    }
-    for (int o = 0; o < nu; ++o) {
-      const S* gu = O.Gu(i);
-      S acc = 0;
-      for (int r = 0; r < G.nc; ++r) acc += gu[(size_t)r * nu + o] * re(O.e1c(i) + r);
-      for (int c = fc; c < fc + n; ++c) acc += O.croot(1, c, o, O.e2(c) + nx, re);
-      col(O.u(i) + o, acc);
-    }
-    for (int c = fc; c < fc + n; ++c) {
-      const long long e2 = O.e2(c) + nx + nu;
-      col(O.tau(c), S(0.5) * (re(e2) + re(e2 + 1)));
-      if (c >= P.nl) {
-        const long long e3 = O.e3(c), e3q = O.e3q(c);
+  // one row: the argument's prox ep given, its r_eta against (L r_z)
+  auto row = [&](long long e, S old, S ep, S Lrz) {
+    eout[e] = ep;
+    const S re = old - ep;
+    st.row((double)re, (double)Lrz, ia);
+    return re;
+  };
+  // rows of a constraint block (Gamma z in [lo, hi]), 64 at a time; their
+  // part of the columns added to cx, cu (lane o: component o)
+  auto cons = [&](int rows, long long ec, const S* gx, const S* gu, const S* lo, const S* hi, S& cx, S& cu) {
+    for (int r0 = 0; r0 < rows; r0 += 64) {
+      const int r = r0 + lane;
+      wave_lds_sync();
+      if (r < rows) {
+        const S* rx = gx + (size_t)r * nx;
+        S a2 = 0, ar = 0;
+#pragma unroll 8
         for (int o = 0; o < nx; ++o) {
-          const S* gn = O.GN(c);
-          S acc = O.croot(2, c, o, e3q, re);
-          for (int r = 0; r < G.ncN; ++r) acc += gn[(size_t)r * nx + o] * re(e3 + r);
-          col(O.x(c) + o, acc);
+          a2 += rx[o] * X2[o];
+          ar += rx[o] * RX[o];
         }
-        col(O.s(c), S(0.5) * (re(e3q + nx) + re(e3q + nx + 1)));
+        if (gu) {
+          const S* ru = gu + (size_t)r * nu;
+#pragma unroll 8
+          for (int o = 0; o < nu; ++o) {
+            a2 += ru[o] * U2[o];
+            ar += ru[o] * RU[o];
+          }
+        }
+        const S old = eta[ec + r];
+        const S w = old + al * a2;
+        E0[lane] = row(ec + r, old, w - al * clampv(w * sia, lo[r], hi[r]), ar);
       }
+      wave_lds_sync();
+      const int m = rows - r0 < 64 ? rows - r0 : 64;
+      if (onx) cx = col_dot(gx + (size_t)r0 * nx, m, nx, lane, E0, cx);
+      if (gu && onu) cu = col_dot(gu + (size_t)r0 * nu, m, nu, lane, E0, cu);
     }
+    wave_lds_sync();
+  };
+  for (int i = blockIdx.x * kGenWaves + wave; i < P.nn; i += gridDim.x * kGenWaves) {
+    const long long xi = O.x(i);
+    const S zx = z[xi + ox], zxp = zout[xi + ox];
+    const S x2 = S(2) * zxp - zx, rx = zx - zxp;
+    wave_lds_sync();  // the previous unit's readers are done
+    if (onx) {
+      X2[lane] = x2;
+      RX[lane] = rx;
+    }
+    S cx = 0, cu = 0;  // (L* r_eta) on columns x^i, u^i
+    if (i >= P.nl) {   // ---- a leaf: group 3, columns x^i, s^i
+      wave_lds_sync();
+      const long long e3 = O.e3(i), e3q = O.e3q(i), sp = O.s(i);
+      const S s2 = S(2) * zout[sp] - z[sp], rs = z[sp] - zout[sp];
+      const S oq = eta[e3q + ox], oa = eta[e3q + nx], ob = eta[e3q + nx + 1];
+      S w = oq + al * O.croot(2, i, ox, x2, X2), none = S(0);
+      const S lr = O.croot(2, i, ox, rx, RX);
+      S wa = oa + al * S(0.5) * s2, wb = ob + al * S(0.5) * s2;
+      soc_prox_wave(w, onx, none, false, wa, wb, al);
+      S req = 0;
+      if (onx) req = row(e3q + lane, oq, w, lr);
+      if (lane == 0) {
+        const S ra = row(e3q + nx, oa, wa, S(0.5) * rs), rb = row(e3q + nx + 1, ob, wb, S(0.5) * rs);
+        st.col((double)rs, (double)(S(0.5) * (ra + rb)), ia);
+      }
+      if (onx) E1[lane] = req;
+      wave_lds_sync();
+      if (onx) cx = O.croot(2, i, lane, req, E1);
+      const size_t lj = (size_t)(i - P.nl) * G.ncN;
+      cons(G.ncN, e3, O.GN(i), nullptr, G.cNmin + lj, G.cNmax + lj, cx, cu);
+      if (onx) st.col((double)rx, (double)cx, ia);
+      continue;
+    }
+    const long long ui = O.u(i);
+    const S zu = z[ui + ou], zup = zout[ui + ou];
+    const S u2 = S(2) * zup - zu, ru = zu - zup;
+    if (onu) {
+      U2[lane] = u2;
+      RU[lane] = ru;
+    }
+    wave_lds_sync();
+    const int fc = P.fc[i], n = P.nch[i], ny = G.ny[i], kp = G.kpos[i];
+    // ---- group 1: y in K*, s - b'y in R_+, the constraint rows; columns y^i, s^i
+    const long long e1 = O.e1(i), zy = O.y(i), sp = O.s(i);
+    const S* b = G.b + G.yoff[i];
+    double by2 = 0, byr = 0;
+    for (int k = lane; k < ny; k += 64) {
+      const S y = z[zy + k], yp = zout[zy + k];
+      by2 += (double)(b[k] * (S(2) * yp - y));
+      byr += (double)(b[k] * (y - yp));
+    }
+    by2 = team_sum<64>(by2);
+    byr = team_sum<64>(byr);
+    const S s0 = z[sp], sp0 = zout[sp], es = eta[e1 + ny];
+    const S ws = es + al * (S)((double)(S(2) * sp0 - s0) - by2);
+    const S esn = ws < S(0) ? ws : S(0);
+    const S res = es - esn;
+    for (int k = lane; k < ny; k += 64) {
+      const S y = z[zy + k], yp = zout[zy + k], old = eta[e1 + k];
+      const S w = old + al * (S(2) * yp - y);
+      const S re = row(e1 + k, old, k < kp ? (w < S(0) ? w : S(0)) : S(0), y - yp);
+      st.col((double)(y - yp), (double)(re - b[k] * res), ia);
+    }
+    if (lane == 0) {
+      row(e1 + ny, es, esn, (S)((double)(s0 - sp0) - byr));
+      st.col((double)(s0 - sp0), (double)res, ia);
+    }
+    cons(G.nc, O.e1c(i), O.Gx(i), O.Gu(i), G.cmin + (size_t)i * G.nc, G.cmax + (size_t)i * G.nc, cx, cu);
+    // ---- group 2 of every child: (Q^{1/2} x^i, R^{1/2} u^i, tau/2, tau/2); column tau
+    for (int c = fc; c < fc + n; ++c) {
+      const long long e2 = O.e2(c), tp = zy + ny + (c - fc);
+      const S t2 = S(2) * zout[tp] - z[tp], rt = z[tp] - zout[tp];
+      const S ex = eta[e2 + ox], eu = eta[e2 + nx + ou], ea = eta[e2 + nx + nu], eb = eta[e2 + nx + nu + 1];
+      S wx = ex + al * O.croot(0, c, ox, x2, X2), wu = eu + al * O.croot(1, c, ou, u2, U2);
+      const S lx = O.croot(0, c, ox, rx, RX), lu = O.croot(1, c, ou, ru, RU);
+      S wa = ea + al * S(0.5) * t2, wb = eb + al * S(0.5) * t2;
+      soc_prox_wave(wx, onx, wu, onu, wa, wb, al);
+      S rex = 0, reu = 0;
+      if (onx) rex = row(e2 + lane, ex, wx, lx);
+      if (onu) reu = row(e2 + nx + lane, eu, wu, lu);
+      if (lane == 0) {
+        const S ra = row(e2 + nx + nu, ea, wa, S(0.5) * rt), rb = row(e2 + nx + nu + 1, eb, wb, S(0.5) * rt);
+        st.col((double)rt, (double)(S(0.5) * (ra + rb)), ia);
+      }
+      if (onx) E0[lane] = rex;
+      if (onu) E1[lane] = reu;
+      wave_lds_sync();
+      if (onx) cx += O.croot(0, c, lane, rex, E0);
+      if (onu) cu += O.croot(1, c, lane, reu, E1);
+      wave_lds_sync();
+    }
+    if (onx) st.col((double)rx, (double)cx, ia);
+    if (onu) st.col((double)ru, (double)cu, ia);
   }
-  block_stats(st, partials);
+  // wavefront, then the block's wavefronts in order
+  double v[kStats] = {st.rz2, st.re2, st.cross, st.xip, st.xid};
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) {
+    v[0] += __shfl_xor(v[0], m, 64);
+    v[1] += __shfl_xor(v[1], m, 64);
+    v[2] += __shfl_xor(v[2], m, 64);
+    v[3] = fmax(v[3], __shfl_xor(v[3], m, 64));
+    v[4] = fmax(v[4], __shfl_xor(v[4], m, 64));
+  }
+  __shared__ double red[kGenWaves][kStats];
+  if (lane == 0) {
+#pragma unroll
+    for (int k = 0; k < kStats; ++k) red[wave][k] = v[k];
+  }
+  __syncthreads();
+  if (threadIdx.x < kStats) {
+    const int k = threadIdx.x;
+    double a = red[0][k];
+    for (int w = 1; w < kGenWaves; ++w) a = (k < 3) ? a + red[w][k] : fmax(a, red[w][k]);
+    partials[(size_t)blockIdx.x * kStats + k] = a;
+  }
 }
 
 template <typename S>
-__global__ void k_gen_L(DevProb<S> P, GenDev<S> G, const S* __restrict__ z, S* __restrict__ eta) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= P.nl) return;
-  fam_gen_L<S>(GOff<S>(P, G), z, eta, i, nullptr, S(1));
+__global__ void __launch_bounds__(kGenThreads) k_gen_L(DevProb<S> P, GenDev<S> G, const S* __restrict__ z,
+                                                     S* __restrict__ eta) {
+  const int i = blockIdx.x * kGenWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (i < P.nn) unit_gen_L<S>(GOff<S>(P, G), z, eta, i, nullptr, S(1), threadIdx.x & 63);
 }
 template <typename S>
-__global__ void k_gen_Lt(DevProb<S> P, GenDev<S> G, const S* __restrict__ eta, S* __restrict__ z) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= P.nl) return;
-  fam_gen_Lt<S>(GOff<S>(P, G), eta, z, i, nullptr, S(1));
+__global__ void __launch_bounds__(kGenThreads) k_gen_Lt(DevProb<S> P, GenDev<S> G, const S* __restrict__ eta,
+                                                      S* __restrict__ z) {
+  const int i = blockIdx.x * kGenWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (i < P.nn) unit_gen_Lt<S>(GOff<S>(P, G), eta, z, i, nullptr, S(1), threadIdx.x & 63);
 }
 template <typename S>
-__global__ void k_gen_prox_gstar(DevProb<S> P, GenDev<S> G, const S* __restrict__ w, S* __restrict__ out) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= P.nl) return;
-  fam_gen_prox<S>(GOff<S>(P, G), w, out, i);
+__global__ void __launch_bounds__(kGenThreads) k_gen_prox_gstar(DevProb<S> P, GenDev<S> G, const S* w, S* out) {
+  const int i = blockIdx.x * kGenWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (i < P.nn) unit_gen_prox<S>(GOff<S>(P, G), w, out, i, threadIdx.x & 63);
 }
 // M d = (d_z - alpha L* d_eta, d_eta - alpha L d_z)
 template <typename S>
-__global__ void k_gen_M(DevProb<S> P, GenDev<S> G, const S* __restrict__ d, S* __restrict__ Md) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= P.nl) return;
+__global__ void __launch_bounds__(kGenThreads) k_gen_M(DevProb<S> P, GenDev<S> G, const S* __restrict__ d,
+                                                     S* __restrict__ Md) {
+  const int i = blockIdx.x * kGenWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (i >= P.nn) return;
   const GOff<S> O(P, G);
-  fam_gen_Lt<S>(O, d + P.nz, Md, i, d, -P.alpha);
-  fam_gen_L<S>(O, d, Md + P.nz, i, d + P.nz, -P.alpha);
+  unit_gen_Lt<S>(O, d + P.nz, Md, i, d, -P.alpha, threadIdx.x & 63);
+  unit_gen_L<S>(O, d, Md + P.nz, i, d + P.nz, -P.alpha, threadIdx.x & 63);
 }
 
 template <typename S>
@@ -484,11 +541,13 @@ const DevProb<double>& dev_of_g<double>(const Problem& P) { return P.dp64; }
 template <>
 const DevProb<float>& dev_of_g<float>(const Problem& P) { return P.dp32; }
 
-int gen_blocks(const Problem& P) { return (P.tree->nl + kGenThreads - 1) / kGenThreads; }
+int gen_blocks(const Problem& P) { return (P.tree->nn + kGenWaves - 1) / kGenWaves; }
 
 }  // namespace
 
-int gen_post_blocks(const Problem& P) { return gen_blocks(P); }
+// one statistics record per block; the partials hold one per nonleaf node
+// plus one, so wide families make the wavefronts loop
+int gen_post_blocks(const Problem& P) { return std::max(1, std::min(gen_blocks(P), P.tree->nl + 1)); }
 
 template <typename S>
 hipError_t launch_gen_pre(const Problem& P, const S* z, const S* eta, S* zout, S* xbar, S* ubar, S* qbuf,
@@ -500,7 +559,7 @@ hipError_t launch_gen_pre(const Problem& P, const S* z, const S* eta, S* zout, S
 template <typename S>
 hipError_t launch_gen_post(const Problem& P, const S* z, const S* eta, const S* zout, S* eout, double* partials,
                            hipStream_t st) {
-  hipLaunchKernelGGL(k_gen_post<S>, dim3(gen_blocks(P)), dim3(kGenThreads), 0, st, dev_of_g<S>(P), gen_of<S>(P),
+  hipLaunchKernelGGL(k_gen_post<S>, dim3(gen_post_blocks(P)), dim3(kGenThreads), 0, st, dev_of_g<S>(P), gen_of<S>(P),
                      z, eta, zout, eout, partials);
   return hipGetLastError();
 }

@@ -225,7 +225,7 @@ int family_wave_blocks(int nl);
 template <typename S>
 int flat_post_occupancy();
 // General problems (general.hip): pre-pass, post-pass with statistics
-// (post_blocks records), L, L*, prox of g* and M, one thread per family.
+// (post_blocks records), L, L*, prox of g* and M, one wavefront per unit.
 // kGenMaxBlock bounds ny + 2 n_i of a family (its (y, tau, s) block).
 constexpr int kGenMaxBlock = 96;
 int gen_post_blocks(const Problem& P);

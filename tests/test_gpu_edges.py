@@ -43,3 +43,44 @@ def test_adjoint_gradients_at_dimension_edges(nx, nu, br):
               1e-6)
         assert np.all(host(gq)[0] == 0.0)
         assert np.all(np.delete(host(gqN), lv, axis=0) == 0.0)
+
+
+# more rows than a wavefront has lanes, single rows, wide and narrow families,
+# the largest dimensions; dense costs read the whole vector of a cone block
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("nx,nu,br,nc,ncN,dense", [(64, 64, [2, 1], 70, 130, False), (1, 1, [3, 2], 1, 1, False),
+                                                   (5, 2, [11, 1], 64, 65, False), (33, 17, [1, 3], 3, 2, True),
+                                                   (64, 2, [2], None, None, True)])
+def test_general_operators_at_dimension_edges(nx, nu, br, nc, ncN, dense, prec):
+    inst = G.make_random_small(500 + nx + nu, br, nx, nu, a=0.5)
+    rng = np.random.default_rng([nx, nu, 5])
+    if nc is not None:
+        inst.cons = G.random_constraints(rng, inst, nc, ncN, 1.0)
+    inst.risk = G.mixture_risk(inst, 0.4)
+    if dense:
+        inst = G.dense_costs(inst, 3)
+    op = O.Problem(inst)
+    gp = SP.Problem.from_instance(inst, precision=SP.FP64 if prec == "fp64" else SP.FP32, alpha=op.alpha)
+    # rounding of sums of up to n_x + n_u or n_c products: a few hundred units
+    # in FP64, and the per-operator FP32 bound of the other parity tests
+    tol = 1e-12 if prec == "fp64" else 5e-6
+    v = dev(rng.standard_normal(gp.n_v), gp.torch_dtype)
+    x0 = dev(inst.x0, torch.float64)
+    hv = host(v)
+    z, eta = hv[:gp.n_z], hv[gp.n_z:]
+    dz, de = v[:gp.n_z].clone(), v[gp.n_z:].clone()
+    Lz, Lte, pg, Tv = (torch.zeros(m, dtype=gp.torch_dtype, device="cuda") for m in (gp.n_eta, gp.n_z, gp.n_eta, gp.n_v))
+    gp.apply_L(dz, Lz)
+    gp.apply_Lt(de, Lte)
+    gp.prox_gstar(de, pg)
+    stats = gp.T(v, x0, Tv)
+    ref_T = O.T_apply(op, hv, inst.x0)
+    for tag, got, ref in (("L", Lz, O.L_apply(op.lay, inst, z)), ("Lt", Lte, O.Lt_apply(op.lay, inst, eta)),
+                          ("prox", pg, O.prox_gstar(op.lay, inst, eta, op.alpha)), ("T", Tv, ref_T)):
+        check(f"edge_gen_{tag}:{nx}:{nu}:{nc}:{prec}", np.max(np.abs(host(got) - ref)) / max(1.0, np.max(np.abs(ref))),
+              tol)
+    rs = O.residual_stats(op, hv - host(Tv))
+    for k in ("xi_p", "xi_d"):
+        ref = float(np.max(np.abs(rs[k])))
+        check(f"edge_gen_{k}:{nx}:{nu}:{nc}:{prec}", abs(stats[k] - ref) / max(1.0, ref),
+              1e-11 if prec == "fp64" else 2e-5)
