@@ -223,11 +223,11 @@ int spock_solve(spock_problem* prob, const double* x0_dev, const spock_settings*
                 void* v_io_dev, spock_info* info_host, void* stream);
 
 /* Solves B independent instances (trees may differ) in one persistent launch
- * captured in a HIP graph: one 256-thread workgroup per instance runs Alg. 3
- * (or CP) to its own termination with no host round trip; the lanes of the
- * workgroup are split into teams, one tree family per team, the team size
- * picked by timing short runs the first time a batch shape is seen (or fixed
- * by the environment variable SPOCK_BATCH_TEAM). probs[b], x0_dev[b] and
+ * captured in a HIP graph: one 1024-thread workgroup per instance runs Alg. 3
+ * (or CP) to its own termination with no host round trip, the largest trees
+ * first; the lanes of the workgroup are split into teams, one tree family per
+ * team, of the fewest lanes that hold a state and an input (more when the
+ * environment variable SPOCK_BATCH_TEAM asks). probs[b], x0_dev[b] and
  * v_io_dev[b] are as in spock_solve; every problem must have the same
  * precision, nx and nu. infos_host[B] receives the per-instance results
  * (seconds is the wall time of the whole call). The library keeps one device

@@ -18,11 +18,46 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
 }
 
+// The value of the partner lane of a butterfly step, without the LDS pipe:
+// steps 1 and 2 by quad permutes, 4 and 8 by the mirrors of 8 and 16 lanes
+// (a partner's value, since the smaller steps have made each group uniform),
+// 16 and 32 by the row and half swaps of the value with itself. A shuffle
+// through LDS costs about 120 cycles a step; these cost a few.
+template <int M>
+__device__ __forceinline__ double lane_partner(double v) {
+  unsigned w[2];
+  __builtin_memcpy(w, &v, 8);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    if constexpr (M <= 8) {
+      constexpr int ctrl = M == 1 ? 0xB1 : (M == 2 ? 0x4E : (M == 4 ? 0x141 : 0x140));
+      w[k] = (unsigned)__builtin_amdgcn_update_dpp((int)w[k], (int)w[k], ctrl, 0xF, 0xF, false);
+    } else {
+      w[k] = (unsigned)__shfl_xor((int)w[k], M, 64);
+    }
+  }
+  double o;
+  __builtin_memcpy(&o, w, 8);
+  return o;
+}
+// Sum (maximum) over the team of T lanes, the same bits in every lane.
 template <int T>
 __device__ __forceinline__ double team_sum(double v) {
-#pragma unroll
-  for (int m = T / 2; m >= 1; m >>= 1) v += __shfl_xor(v, m, T);
+  if constexpr (T >= 2) v += lane_partner<1>(v);
+  if constexpr (T >= 4) v += lane_partner<2>(v);
+  if constexpr (T >= 8) v += lane_partner<4>(v);
+  if constexpr (T >= 16) v += lane_partner<8>(v);
+  if constexpr (T >= 32) v += lane_partner<16>(v);
+  if constexpr (T >= 64) v += lane_partner<32>(v);
   return v;
+}
+__device__ __forceinline__ double wave_max(double v) {
+  v = fmax(v, lane_partner<1>(v));
+  v = fmax(v, lane_partner<2>(v));
+  v = fmax(v, lane_partner<4>(v));
+  v = fmax(v, lane_partner<8>(v));
+  v = fmax(v, lane_partner<16>(v));
+  return fmax(v, lane_partner<32>(v));
 }
 
 template <typename S>
@@ -75,38 +110,65 @@ __device__ __forceinline__ void mv_acc(S (&acc)[(D + T - 1) / T], const S* __res
   }
 }
 
+// Element i of an array. IX = unsigned: the byte offset fits 32 bits (the
+// caller's rule), so that a divergent index costs one multiply-add on a uniform
+// base; IX = long long: any size.
+template <typename S, typename IX>
+__device__ __forceinline__ const S& at(const S* p, IX i) {
+  if constexpr (sizeof(IX) == 4) return *reinterpret_cast<const S*>(reinterpret_cast<const char*>(p) + (unsigned)(i * (IX)sizeof(S)));
+  else return p[i];
+}
+template <typename S, typename IX>
+__device__ __forceinline__ S& at(S* p, IX i) {
+  if constexpr (sizeof(IX) == 4) return *reinterpret_cast<S*>(reinterpret_cast<char*>(p) + (unsigned)(i * (IX)sizeof(S)));
+  else return p[i];
+}
+
+// The array (a for states, b for inputs) that a lane reads at i: with 32-bit
+// offsets both through the base a, i moved by the arrays' distance (they sit
+// in one allocation, b above a), so that the base stays uniform.
+template <typename S, typename IX>
+__device__ __forceinline__ const S* pair_base(const S* a, const S* b, bool first, IX& i) {
+  if constexpr (sizeof(IX) == 4) {
+    i += first ? IX(0) : (IX)(b - a);
+    return a;
+  } else {
+    return first ? a : b;
+  }
+}
+
 // Offsets in the canonical layout (closed forms of the breadth-first sizes).
-template <typename S>
+template <typename S, typename IX = long long>
 struct Off {
   const DevProb<S>& P;
   __device__ Off(const DevProb<S>& p) : P(p) {}
-  __device__ long long x(int i) const { return 1 + (long long)i * P.nx; }
-  __device__ long long u(int i) const { return P.zU + (long long)i * P.nu; }
+  __device__ IX x(int i) const { return 1 + (IX)i * P.nx; }
+  __device__ IX u(int i) const { return (IX)P.zU + (IX)i * P.nu; }
   // z2 block of nonleaf i: y (2n+1), tau (n), s (n)
-  __device__ long long z2(int i) const { return P.zZ2 + 4LL * (P.fc[i] - 1) + i; }
+  __device__ IX z2(int i) const { return (IX)P.zZ2 + (IX)4 * (P.fc[i] - 1) + i; }
   // slot of s^c in its ancestor's block (s^0 at 0)
-  __device__ long long s(int c) const {
+  __device__ IX s(int c) const {
     if (c == 0) return 0;
     const int a = P.anc[c];
     const int n = P.nch[a];
-    return z2(a) + 3LL * n + 1 + (c - P.fc[a]);
+    return z2(a) + 3 * n + 1 + (c - P.fc[a]);
   }
-  __device__ long long tau(int c) const {
+  __device__ IX tau(int c) const {
     const int a = P.anc[c];
     const int n = P.nch[a];
-    return z2(a) + 2LL * n + 1 + (c - P.fc[a]);
+    return z2(a) + 2 * n + 1 + (c - P.fc[a]);
   }
   // eta group 1 of nonleaf i: y (2n+1), s-row, x (nx), u (nu)
-  __device__ long long e1(int i) const {
-    return 2LL * (P.fc[i] - 1) + (long long)i * (2 + P.nx + P.nu);
+  __device__ IX e1(int i) const {
+    return (IX)2 * (P.fc[i] - 1) + (IX)i * (2 + P.nx + P.nu);
   }
-  __device__ long long e1s(int i) const { return e1(i) + 2LL * P.nch[i] + 1; }
-  __device__ long long e1x(int i) const { return e1s(i) + 1; }
-  __device__ long long e1u(int i) const { return e1x(i) + P.nx; }
+  __device__ IX e1s(int i) const { return e1(i) + (IX)2 * P.nch[i] + 1; }
+  __device__ IX e1x(int i) const { return e1s(i) + 1; }
+  __device__ IX e1u(int i) const { return e1x(i) + P.nx; }
   // eta group 2 of non-root c: x (nx), u (nu), a, b
-  __device__ long long e2(int c) const { return P.eE2 + (long long)(c - 1) * (P.nx + P.nu + 2); }
+  __device__ IX e2(int c) const { return (IX)P.eE2 + (IX)(c - 1) * (P.nx + P.nu + 2); }
   // eta group 3 of leaf j: x (nx), Q_N^{1/2} x (nx), a, b
-  __device__ long long e3(int j) const { return P.eE3 + (long long)(j - P.nl) * (2 * P.nx + 2); }
+  __device__ IX e3(int j) const { return (IX)P.eE3 + (IX)(j - P.nl) * (2 * P.nx + 2); }
 };
 
 // Running residual statistics of one lane (FP64).
@@ -691,6 +753,360 @@ __device__ __forceinline__ void fam_post_team(const DevProb<S>& P, const S* __re
   wave_lds_sync();
 }
 
+// Pre-pass of a family by a team: b[s] = component lane + T s of (xbar, ubar)
+// = (x, u) - alpha L* eta; the (y, tau, s) block's step and its projection on
+// S2 (closed form, as fam_s2), held in registers between its two sums while
+// n <= T; s^0 - alpha at the root.
+template <typename S, int T, int SL, typename IX>
+__device__ __forceinline__ void flat_pre_family(const DevProb<S>& P, const Off<S, IX>& O, const S* __restrict__ z,
+                                                const S* __restrict__ eta, S* __restrict__ zout, int i, int fc, int n,
+                                                int lane, S (&b)[SL]) {
+  const int nx = P.nx, nu = P.nu, K = nx + nu;
+  const S al = P.alpha;
+  const IX e1 = (IX)2 * (fc - 1) + (IX)i * (2 + K), e1s = e1 + 2 * n + 1;
+  const IX zb = (IX)P.zZ2 + (IX)4 * (fc - 1) + i, e2 = O.e2(fc);
+  // One batch of loads, without branches around them (clamped indices): the
+  // y block's operands (child `lane`) and the columns x^i, u^i with the first
+  // child; the next child's are in flight while one is added.
+  const S es = at<S, IX>(eta, e1s), a = at<S, IX>(P.a, i), y3 = at<S, IX>(z, zb + 2 * n), ey3 = at<S, IX>(eta, e1 + 2 * n);
+  const bool leaf = fc >= P.nl;
+  struct Slack {
+    S z1, z2, zt, zs, e1, e2, p, ta, tb, sa, sb;
+  };
+  auto load = [&](int k, Slack& w) {
+    const IX e = e2 + (IX)k * (K + 2) + K;
+    const IX sa = leaf ? O.e3(fc + k) + 2 * nx : O.e1s(leaf ? 0 : fc + k);
+    w.sa = at<S, IX>(eta, sa);
+    w.sb = at<S, IX>(eta, leaf ? sa + 1 : sa);
+    w.ta = at<S, IX>(eta, e);
+    w.tb = at<S, IX>(eta, e + 1);
+    w.z1 = at<S, IX>(z, zb + k);
+    w.z2 = at<S, IX>(z, zb + n + k);
+    w.zt = at<S, IX>(z, zb + 2 * n + 1 + k);
+    w.zs = at<S, IX>(z, zb + 3 * n + 1 + k);
+    w.e1 = at<S, IX>(eta, e1 + k);
+    w.e2 = at<S, IX>(eta, e1 + n + k);
+    w.p = at<S, IX>(P.p, fc + k);
+  };
+  auto step = [&](const Slack& w, S& y1h, S& y2h, S& th, S& sh) {
+    y1h = w.z1 - al * (w.e1 - w.p * es);
+    y2h = w.z2 - al * w.e2;
+    th = w.zt - al * S(0.5) * (w.ta + w.tb);
+    sh = w.zs - al * (leaf ? S(0.5) * (w.sa + w.sb) : w.sa);
+  };
+  Slack mine;
+  load(lane < n ? lane : n - 1, mine);
+  S zv[SL], acc[SL], cs[SL], ce[SL];
+  const S* sc[SL];
+  IX so[SL];
+  int kk[SL];
+#pragma unroll
+  for (int s = 0; s < SL; ++s) {
+    const int k = lane + T * s;
+    kk[s] = k < K ? k : 0;
+    const bool isx = kk[s] < nx;
+    so[s] = (IX)fc * (isx ? nx : nu) + (isx ? kk[s] : kk[s] - nx);
+    sc[s] = pair_base<S, IX>(P.sq, P.sr, isx, so[s]);
+    zv[s] = at<S, IX>(z, isx ? O.x(i) + kk[s] : O.u(i) + (kk[s] - nx));
+    acc[s] = at<S, IX>(eta, e1s + 1 + kk[s]);
+    cs[s] = at<S, IX>(sc[s], so[s]);
+    ce[s] = at<S, IX>(eta, e2 + kk[s]);
+  }
+  for (int c = 0; c < n; ++c) {
+#pragma unroll
+    for (int s = 0; s < SL; ++s) {
+      const S f = cs[s], g = ce[s];
+      if (c + 1 < n) {
+        so[s] += kk[s] < nx ? nx : nu;
+        cs[s] = at<S, IX>(sc[s], so[s]);
+        ce[s] = at<S, IX>(eta, e2 + (IX)(c + 1) * (K + 2) + kk[s]);
+      }
+      acc[s] += f * g;
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < SL; ++s) b[s] = zv[s] - al * acc[s];
+  S y1h, y2h, th, sh;
+  step(mine, y1h, y2h, th, sh);
+  // ---- S2
+  const S y3h = y3 - al * (ey3 - es);
+  const S cc = a * a + S(3);
+  auto g_of = [&](S y1, S y2, S t, S s) { return a * y1 - y2 + y3h - t - s; };
+  double gsum = lane < n ? (double)g_of(y1h, y2h, th, sh) : 0.0;
+  for (int k = lane + T; k < n; k += T) {
+    S p, q, t, s;
+    Slack w;
+    load(k, w);
+    step(w, p, q, t, s);
+    gsum += (double)g_of(p, q, t, s);
+  }
+  const S corr = (S)team_sum<T>(gsum) / (cc + S(n));
+  double wsum = 0;
+  auto store = [&](int k, S y1, S y2, S t, S s) {
+    const S w = (g_of(y1, y2, t, s) - corr) / cc;
+    wsum += (double)w;
+    at<S, IX>(zout, zb + k) = y1 - a * w;
+    at<S, IX>(zout, zb + n + k) = y2 + w;
+    at<S, IX>(zout, zb + 2 * n + 1 + k) = t + w;
+    at<S, IX>(zout, zb + 3 * n + 1 + k) = s + w;
+  };
+  for (int k = lane + T; k < n; k += T) {  // more than T children
+    S p, q, t, s;
+    Slack w;
+    load(k, w);
+    step(w, p, q, t, s);
+    store(k, p, q, t, s);
+  }
+  if (lane < n) store(lane, y1h, y2h, th, sh);
+  const S Ws = (S)team_sum<T>(wsum);
+  if (lane == 0) {
+    at<S, IX>(zout, zb + 2 * n) = y3h - Ws;
+    if (i == 0) at<S, IX>(zout, 0) = at<S, IX>(z, 0) - al * es - al;
+  }
+}
+
+// Flat forms of the passes: a team of T lanes (T <= 64, inside one wavefront)
+// owns a unit, a nonleaf family (group 1 of i and group 2 of each child c) or
+// a leaf (group 3). The rows and columns a unit touches are exactly those of
+// the family-serial form, so no unit waits on another. A family's columns
+// x^i and u^i share one index k < nx + nu <= T SL with the first rows of each
+// child's group 2, so every lane holds the same SL components of all of them.
+// Offsets are arithmetic in i once fc = fc[i], n = nch[i] and the slot sp of
+// s^i in its ancestor's block are known: one level of index loads, then every
+// data load of the unit at once. zp_at(kk): component kk of (x+, u+).
+template <typename S, int T, int SL, typename IX, typename F>
+__device__ __forceinline__ void flat_family(const DevProb<S>& P, const Off<S, IX>& O, IX sp,
+                                            const S* __restrict__ z, const S* __restrict__ eta,
+                                            const S* __restrict__ zout, S* __restrict__ eout, int i, int fc, int n,
+                                            int lane, F&& zp_at, StatAcc& st) {
+  const int nx = P.nx, nu = P.nu, K = nx + nu;
+  const S al = P.alpha;
+  const S ia = S(1) / al;
+  const IX e1 = (IX)2 * (fc - 1) + (IX)i * (2 + K), e1x = e1 + 2 * n + 2, zb = (IX)P.zZ2 + (IX)4 * (fc - 1) + i;
+  const IX xi = O.x(i), ui = O.u(i);
+  // One batch of loads, with clamped indices and no branches, so that
+  // every load of the unit is in flight at once: columns x^i, u^i (slot s:
+  // k = lane + 64 s), the y block (one entry per lane when 2n + 1 <= T)
+  // and the scalars.
+  // FP64 loads the box rows' and the y block's operands after the cone
+  // blocks at two components a lane (fewer live registers across them)
+  constexpr bool kLateBox = sizeof(S) == 8 && SL > 1;
+  bool on[SL];
+  S zp[SL], zo[SL], lo[SL], hi[SL], eb[SL], gc[SL];
+  auto load_box = [&](int s) {
+    const int k = lane + T * s;
+    const int kk = on[s] ? k : 0;
+    const bool isx = kk < nx;
+    const IX bi = isx ? (IX)i * nx + kk : (IX)i * nu + (kk - nx);
+    IX bl = bi, bh = bi;
+    const S* plo = pair_base<S, IX>(P.xlo, P.ulo, isx, bl);
+    const S* phi = pair_base<S, IX>(P.xhi, P.uhi, isx, bh);
+    lo[s] = at<S, IX>(plo, bl);
+    hi[s] = at<S, IX>(phi, bh);
+    eb[s] = at<S, IX>(eta, e1x + kk);
+  };
+#pragma unroll
+  for (int s = 0; s < SL; ++s) {
+    const int k = lane + T * s;
+    on[s] = k < K;
+    const int kk = on[s] ? k : 0;
+    const bool isx = kk < nx;
+    const IX zi = isx ? xi + kk : ui + (kk - nx);
+    zp[s] = zp_at(kk);
+    zo[s] = at<S, IX>(z, zi);
+    if (!kLateBox) load_box(s);
+    gc[s] = 0;
+  }
+  const int ny = 2 * n + 1;
+  const int ky = lane < ny ? lane : 0;
+  S yv, ypv, eyv, pk, si, sip, y3, y3p, es;
+  auto load_y = [&]() {
+    yv = at<S, IX>(z, zb + ky);
+    ypv = at<S, IX>(zout, zb + ky);
+    eyv = at<S, IX>(eta, e1 + ky);
+    pk = at<S, IX>(P.p, fc + (lane < n ? lane : 0));
+    si = at<S, IX>(z, sp);
+    sip = at<S, IX>(zout, sp);
+    y3 = at<S, IX>(z, zb + 2 * n);
+    y3p = at<S, IX>(zout, zb + 2 * n);
+    es = at<S, IX>(eta, e1 + 2 * n + 1);
+  };
+  if (!kLateBox) load_y();
+  // group 2 of every child: (Q^{1/2} x^i, R^{1/2} u^i, tau/2, tau/2); at one
+  // component a lane the next child's operands are in flight meanwhile
+  struct Child {
+    S sc[SL], ev[SL], tau, taup, ea, ebb;
+  };
+  auto load_child = [&](int c, Child& C) {
+    const IX e2 = O.e2(c);
+    const IX tp = zb + 2 * n + 1 + (c - fc);
+#pragma unroll
+    for (int s = 0; s < SL; ++s) {
+      const int kk = on[s] ? lane + T * s : 0;
+      IX so = kk < nx ? (IX)c * nx + kk : (IX)c * nu + (kk - nx);
+      const S* ps = pair_base<S, IX>(P.sq, P.sr, kk < nx, so);
+      C.sc[s] = at<S, IX>(ps, so);
+      C.ev[s] = at<S, IX>(eta, e2 + kk);
+    }
+    C.tau = at<S, IX>(z, tp);
+    C.taup = at<S, IX>(zout, tp);
+    C.ea = at<S, IX>(eta, e2 + K);
+    C.ebb = at<S, IX>(eta, e2 + K + 1);
+  };
+  Child nxt;
+  if (SL == 1) load_child(fc, nxt);
+  for (int c = fc; c < fc + n; ++c) {
+    const IX e2 = O.e2(c);
+    if (SL > 1) load_child(c, nxt);
+    const Child C = nxt;
+    if (SL == 1 && c + 1 < fc + n) load_child(c + 1, nxt);
+    const S(&sc)[SL] = C.sc;
+    const S(&ev)[SL] = C.ev;
+    const S tau = C.tau, taup = C.taup, ea = C.ea, ebb = C.ebb;
+    S wv[SL], ov[SL], lz[SL];
+#pragma unroll
+    for (int s = 0; s < SL; ++s) {
+      wv[s] = on[s] ? ev[s] + al * sc[s] * (S(2) * zp[s] - zo[s]) : S(0);
+      lz[s] = sc[s] * (zo[s] - zp[s]);
+      ov[s] = 0;
+    }
+    const S wa = ea + al * S(0.5) * (S(2) * taup - tau);
+    const S wb = ebb + al * S(0.5) * (S(2) * taup - tau);
+    S oa, ob;
+    soc_prox<S, T, T * SL / 2>(wv, ov, K, wa, wb, oa, ob, al, lane);
+#pragma unroll
+    for (int s = 0; s < SL; ++s) {
+      if (on[s]) {
+        at<S, IX>(eout, e2 + lane + T * s) = ov[s];
+        const S re = ev[s] - ov[s];
+        st.row((double)re, (double)lz[s], (double)ia);
+        gc[s] += sc[s] * re;
+      }
+    }
+    if (lane == 0) {
+      const S rtau = tau - taup;
+      const S rea = ea - oa, reb = ebb - ob;
+      at<S, IX>(eout, e2 + K) = oa;
+      at<S, IX>(eout, e2 + K + 1) = ob;
+      st.row((double)rea, 0.5 * (double)rtau, (double)ia);
+      st.row((double)reb, 0.5 * (double)rtau, (double)ia);
+      st.col((double)rtau, 0.5 * ((double)rea + (double)reb), (double)ia);
+    }
+  }
+  // group 1: the boxes on (x^i, u^i) and the columns x^i, u^i
+  if (kLateBox) {
+#pragma unroll
+    for (int s = 0; s < SL; ++s) load_box(s);
+    load_y();
+  }
+#pragma unroll
+  for (int s = 0; s < SL; ++s) {
+    if (on[s]) {
+      const S w = eb[s] + al * (S(2) * zp[s] - zo[s]);
+      const S ep = w - al * clampv(w * ia, lo[s], hi[s]);
+      at<S, IX>(eout, e1x + lane + T * s) = ep;
+      const S re = eb[s] - ep;
+      const S rz = zo[s] - zp[s];
+      st.row((double)re, (double)rz, (double)ia);
+      st.col((double)rz, (double)(re + gc[s]), (double)ia);
+    }
+  }
+  // group 1: y in K* = R^{2n}_+ x R and the row s^i - b'y
+  double bw = lane < n ? (double)(pk * (S(2) * ypv - yv)) : 0.0;
+  double bry = lane < n ? (double)(pk * (yv - ypv)) : 0.0;
+  for (int k = lane + T; k < n; k += T) {  // more than T children
+    const S pq = at<S, IX>(P.p, fc + k);
+    const S y1 = at<S, IX>(z, zb + k), y1p = at<S, IX>(zout, zb + k);
+    bw += (double)(pq * (S(2) * y1p - y1));
+    bry += (double)(pq * (y1 - y1p));
+  }
+  const S bW = (S)team_sum<T>(bw) + (S(2) * y3p - y3);
+  const S bR = (S)team_sum<T>(bry) + (y3 - y3p);
+  const S ws = es + al * ((S(2) * sip - si) - bW);
+  const S es_new = ws < S(0) ? ws : S(0);
+  const S res_ = es - es_new;
+  auto yrow = [&](int k, S y, S yp, S e, S pq) {
+    const S w = e + al * (S(2) * yp - y);
+    const S ep = (k < 2 * n) ? (w < S(0) ? w : S(0)) : S(0);
+    at<S, IX>(eout, e1 + k) = ep;
+    const S re = e - ep;
+    const S ry = y - yp;
+    st.row((double)re, (double)ry, (double)ia);
+    const S bk = (k < n) ? pq : ((k == 2 * n) ? S(1) : S(0));
+    st.col((double)ry, (double)(re - bk * res_), (double)ia);
+  };
+  if (lane < ny) yrow(lane, yv, ypv, eyv, pk);
+  for (int k = lane + T; k < ny; k += T) yrow(k, at<S, IX>(z, zb + k), at<S, IX>(zout, zb + k), at<S, IX>(eta, e1 + k), k < n ? at<S, IX>(P.p, fc + k) : S(0));
+  if (lane == 0) {
+    at<S, IX>(eout, e1 + 2 * n + 1) = es_new;
+    const S rsi = si - sip;
+    st.row((double)res_, (double)(rsi - bR), (double)ia);
+    st.col((double)rsi, (double)res_, (double)ia);
+  }
+}
+
+// Leaf j: group 3 (box on x^j, (Q_N^{1/2} x^j, s/2, s/2) in the SOC) and
+// the columns x^j, s^j; one batch of loads as in flat_family.
+// n_x <= T SL; xp_at(o): component o of x+^j.
+template <typename S, int T, int SL, typename IX, typename F>
+__device__ __forceinline__ void flat_leaf(const DevProb<S>& P, const Off<S, IX>& O, IX sp,
+                                          const S* __restrict__ z, const S* __restrict__ eta,
+                                          const S* __restrict__ zout, S* __restrict__ eout, int j, int lane,
+                                          F&& xp_at, StatAcc& st) {
+  const int nx = P.nx;
+  const S al = P.alpha;
+  const S ia = S(1) / al;
+  const IX e3 = O.e3(j), xj = O.x(j);
+  S xc[SL], xin[SL], ebx[SL], eq[SL], lo[SL], hi[SL], sqn[SL];
+  bool on[SL];
+#pragma unroll
+  for (int s = 0; s < SL; ++s) {
+    on[s] = lane + T * s < nx;
+    const int kk = on[s] ? lane + T * s : 0;
+    xc[s] = xp_at(kk);
+    xin[s] = at<S, IX>(z, xj + kk);
+    ebx[s] = at<S, IX>(eta, e3 + kk);
+    eq[s] = at<S, IX>(eta, e3 + nx + kk);
+    lo[s] = at<S, IX>(P.xlo, (IX)j * nx + kk);
+    hi[s] = at<S, IX>(P.xhi, (IX)j * nx + kk);
+    sqn[s] = at<S, IX>(P.sqN, (IX)j * nx + kk);
+  }
+  const S sv = at<S, IX>(z, sp), svp = at<S, IX>(zout, sp);
+  const S ea = at<S, IX>(eta, e3 + 2 * nx), ebb = at<S, IX>(eta, e3 + 2 * nx + 1);
+  S wq[SL], oq[SL];
+#pragma unroll
+  for (int s = 0; s < SL; ++s) {
+    wq[s] = on[s] ? eq[s] + al * sqn[s] * (S(2) * xc[s] - xin[s]) : S(0);
+    oq[s] = 0;
+  }
+  const S wsa = ea + al * S(0.5) * (S(2) * svp - sv);
+  const S wsb = ebb + al * S(0.5) * (S(2) * svp - sv);
+  S osa, osb;
+  soc_prox<S, T, T * SL / 2>(wq, oq, nx, wsa, wsb, osa, osb, al, lane);
+#pragma unroll
+  for (int s = 0; s < SL; ++s) {
+    if (!on[s]) continue;
+    const S w = ebx[s] + al * (S(2) * xc[s] - xin[s]);
+    const S pb = w - al * clampv(w * ia, lo[s], hi[s]);
+    const S rex = ebx[s] - pb, rx = xin[s] - xc[s];
+    at<S, IX>(eout, e3 + lane + T * s) = pb;
+    st.row((double)rex, (double)rx, (double)ia);
+    at<S, IX>(eout, e3 + nx + lane + T * s) = oq[s];
+    const S req = eq[s] - oq[s];
+    st.row((double)req, (double)(sqn[s] * rx), (double)ia);
+    st.col((double)rx, (double)(rex + sqn[s] * req), (double)ia);
+  }
+  if (lane == 0) {
+    const S rs = sv - svp;
+    at<S, IX>(eout, e3 + 2 * nx) = osa;
+    at<S, IX>(eout, e3 + 2 * nx + 1) = osb;
+    const S rea = ea - osa, reb = ebb - osb;
+    st.row((double)rea, 0.5 * (double)rs, (double)ia);
+    st.row((double)reb, 0.5 * (double)rs, (double)ia);
+    st.col((double)rs, 0.5 * ((double)rea + (double)reb), (double)ia);
+  }
+}
+
 // M d = (d_z - alpha L* d_eta, d_eta - alpha L d_z), the metric of the
 // SuperMann line search (Alg. 3): one team of T lanes per family writes the
 // family's columns of L* (y^i, s^i, x^i, u^i, tau^c, and x^c, s^c of leaf
@@ -777,6 +1193,204 @@ __device__ __forceinline__ void fam_apply_M(const DevProb<S>& P, const S* __rest
       me[e3 + 2 * nx + 1] = de[e3 + 2 * nx + 1] - al * S(0.5) * sc;
     }
   }
+}
+
+// Anderson step on the device (section 6.2, type-II; one thread, k <= 4):
+// the Gram row of the newest difference and the right-hand side <dR_j, r>
+// come from the push dot products; the oldest columns are dropped until the
+// Gram matrix of the kept ones has lambda_min / lambda_max >= 1e-12 (the
+// singular-value ratio 1e-6 of the residual differences; cyclic Jacobi until
+// the test is decided) and a Cholesky factor; gamma solves G gamma = rhs. gamma
+// is written for every column of the order (0 for dropped ones), and the
+// device ring takes the new order (the kept columns) and the direction's
+// columns.
+// Fixed-size (N <= 4) helpers, fully unrolled so that the matrices stay in
+// registers.
+template <int N>
+__device__ __forceinline__ bool dev_chol(double (&A)[16]) {
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    double d = A[j * 4 + j];
+#pragma unroll
+    for (int k = 0; k < j; ++k) d -= A[j * 4 + k] * A[j * 4 + k];
+    if (!(d > 0.0) || !isfinite(d)) return false;
+    d = sqrt(d);
+    A[j * 4 + j] = d;
+#pragma unroll
+    for (int i = j + 1; i < N; ++i) {
+      double s = A[i * 4 + j];
+#pragma unroll
+      for (int k = 0; k < j; ++k) s -= A[i * 4 + k] * A[j * 4 + k];
+      A[i * 4 + j] = s / d;
+    }
+  }
+  return true;
+}
+
+// Rank test of a symmetric N x N matrix: lambda_min / lambda_max >= 1e-12
+// with lambda_max > 0. Cyclic Jacobi sweeps until the test is decided: with
+// off the sum of squares of the upper off-diagonal entries, every eigenvalue
+// lies within e = sqrt(2 off) of a diagonal entry (Weyl), so the extreme
+// eigenvalues are within e of the smallest and largest diagonal entries.
+template <int N>
+__device__ __forceinline__ bool dev_rank_ok(double (&A)[16]) {
+  constexpr double kTol = 1e-12;
+  for (int sweep = 0;; ++sweep) {
+    double off = 0, dmin = A[0], dmax = A[0];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      dmin = fmin(dmin, A[i * 4 + i]);
+      dmax = fmax(dmax, A[i * 4 + i]);
+#pragma unroll
+      for (int j = i + 1; j < N; ++j) off += A[i * 4 + j] * A[i * 4 + j];
+    }
+    const double e = sqrt(2.0 * off);
+    if (dmax - e > 0.0 && dmin - e >= kTol * (dmax + e)) return true;           // certainly passes
+    if (dmax + e <= 0.0 || (dmax - e > 0.0 && dmin + e < kTol * (dmax - e))) return false;  // certainly fails
+    if (sweep == 60 || off < 1e-300) return dmax > 0.0 && dmin >= kTol * dmax;  // the diagonal is the spectrum
+#pragma unroll
+    for (int p = 0; p < N; ++p)
+#pragma unroll
+      for (int q = p + 1; q < N; ++q) {
+        const double apq = A[p * 4 + q];
+        if (apq != 0.0) {
+          const double th = 0.5 * (A[q * 4 + q] - A[p * 4 + p]) / apq;
+          const double t = (th >= 0 ? 1.0 : -1.0) / (fabs(th) + sqrt(th * th + 1.0));
+          const double c = 1.0 / sqrt(t * t + 1.0), s = t * c;
+#pragma unroll
+          for (int k = 0; k < N; ++k) {
+            const double akp = A[k * 4 + p], akq = A[k * 4 + q];
+            A[k * 4 + p] = c * akp - s * akq;
+            A[k * 4 + q] = s * akp + c * akq;
+          }
+#pragma unroll
+          for (int k = 0; k < N; ++k) {
+            const double apk = A[p * 4 + k], aqk = A[q * 4 + k];
+            A[p * 4 + k] = c * apk - s * aqk;
+            A[q * 4 + k] = s * apk + c * aqk;
+          }
+        }
+      }
+  }
+}
+
+// Rank test and solve for the last N of the k active columns (rows/cols
+// `off..off+N` of Gk, right-hand side rk); true when kept.
+template <int N, int off>
+__device__ __forceinline__ bool dev_aa_try(const double (&Gk)[16], const double (&rk)[4], double (&g)[4]) {
+  double E[16], L[16];
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+#pragma unroll
+    for (int j = 0; j < N; ++j) E[i * 4 + j] = L[i * 4 + j] = Gk[(off + i) * 4 + off + j];
+  if (!dev_rank_ok<N>(E) || !dev_chol<N>(L)) return false;
+  double y[4];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    double s = rk[off + i];
+#pragma unroll
+    for (int j = 0; j < i; ++j) s -= L[i * 4 + j] * y[j];
+    y[i] = s / L[i * 4 + i];
+  }
+#pragma unroll
+  for (int i = N - 1; i >= 0; --i) {
+    double s = y[i];
+#pragma unroll
+    for (int j = i + 1; j < N; ++j) s -= L[j * 4 + i] * g[off + j];
+    g[off + i] = s / L[i * 4 + i];
+  }
+  return true;
+}
+
+// Tries the last K - DROP columns, then fewer; the number kept (0: none).
+template <int K, int DROP>
+__device__ __forceinline__ int aa_try_from(const double (&Gk)[16], const double (&rk)[4], double (&g)[4]) {
+  if constexpr (DROP >= K) {
+    return 0;
+  } else {
+    if (dev_aa_try<K - DROP, DROP>(Gk, rk, g)) return K - DROP;
+    return aa_try_from<K, DROP + 1>(Gk, rk, g);
+  }
+}
+
+// MO columns before the push (all indices fixed at compile time). Gold:
+// the Gram entries of the old columns (oldest first), read before the sums
+// were done; the new column's entries and the right-hand side <dR_j, r>
+// come from the dots. The new row is stored in G (by slot) for later pushes.
+template <int MO>
+__device__ __forceinline__ void aa_solve_dev(double* __restrict__ G, const double (&dots)[8],
+                                             const double (&Gold)[16], const AAPush& a,
+                                             double* __restrict__ gamma, AARingDev* __restrict__ ring) {
+  const int m = a.m, slot = a.slot;
+#pragma unroll
+  for (int j = 0; j < MO; ++j) {
+    G[a.order_old[j] * m + slot] = dots[j];
+    G[slot * m + a.order_old[j]] = dots[j];
+  }
+  G[slot * m + slot] = dots[MO];
+  constexpr int k = MO + 1;  // order_new = order_old + [slot]
+  // Gram matrix and right-hand side of the active columns, in registers
+  double Gk[16], rk[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    rk[i] = i < MO ? dots[MO + 1 + i] : (i == MO ? dots[2 * MO + 1] : 0.0);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      Gk[i * 4 + j] = (i < MO && j < MO) ? Gold[i * 4 + j]
+                    : (i == MO && j < MO) ? dots[j]
+                    : (j == MO && i < MO) ? dots[i]
+                    : (i == MO && j == MO) ? dots[MO] : 0.0;
+  }
+  double g[4] = {0, 0, 0, 0};
+  // drop the oldest columns until the rest pass the rank test
+  const int kept = aa_try_from<k, 0>(Gk, rk, g);
+  if (kept == 0) g[0] = g[1] = g[2] = g[3] = 0.0;
+#pragma unroll
+  for (int j = 0; j < k; ++j) gamma[j] = g[j];
+  // the ring: the direction uses the k columns (dropped ones with gamma 0);
+  // the next push keeps the newest `kept`
+  int ord[4] = {0, 0, 0, 0};
+#pragma unroll
+  for (int j = 0; j < MO; ++j) ord[j] = a.order_old[j];
+  ord[MO] = slot;
+  ring->dk = k;
+#pragma unroll
+  for (int j = 0; j < k; ++j) ring->dslot[j] = ord[j];
+  ring->cnt = kept;
+#pragma unroll
+  for (int j = 0; j < k; ++j) {
+    int sel = 0;
+#pragma unroll
+    for (int q = 0; q < k; ++q) sel = (q == k - kept + j) ? ord[q] : sel;
+    if (j < kept) ring->order[j] = sel;
+  }
+}
+
+// The push that follows the ring as the last solve left it: the new column
+// takes the oldest slot when the ring is full, else the lowest free one; the
+// dots run against the other columns of the order.
+__device__ __forceinline__ AAPush aa_next_push(const AARingDev* ring) {
+  // (fixed indices and selects only, so that nothing lands in scratch)
+  AAPush a{};
+  a.m = ring->m;
+  const int cnt = ring->cnt;
+  int o[kAAMax];
+#pragma unroll
+  for (int j = 0; j < kAAMax; ++j) o[j] = ring->order[j];
+  const bool full = cnt == a.m;
+  a.mo = full ? cnt - 1 : cnt;
+#pragma unroll
+  for (int j = 0; j < kAAMax; ++j) a.order_old[j] = full ? (j + 1 < kAAMax ? o[j + 1] : 0) : o[j];
+  int fr = kAAMax;  // lowest slot not in the order
+#pragma unroll
+  for (int s = kAAMax - 1; s >= 0; --s) {
+    bool used = false;
+#pragma unroll
+    for (int j = 0; j < kAAMax; ++j) used = used || (j < cnt && o[j] == s);
+    if (!used && s < a.m) fr = s;
+  }
+  a.slot = full ? o[0] : fr;
+  return a;
 }
 
 // Tagged words: element e of a vector occupies kTW<S> 64-bit words, each

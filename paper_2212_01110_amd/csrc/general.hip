@@ -477,15 +477,8 @@ __global__ void __launch_bounds__(kGenThreads) k_gen_post(DevProb<S> P, GenDev<S
     if (onu) st.col((double)ru, (double)cu, ia);
   }
   // wavefront, then the block's wavefronts in order
-  double v[kStats] = {st.rz2, st.re2, st.cross, st.xip, st.xid};
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) {
-    v[0] += __shfl_xor(v[0], m, 64);
-    v[1] += __shfl_xor(v[1], m, 64);
-    v[2] += __shfl_xor(v[2], m, 64);
-    v[3] = fmax(v[3], __shfl_xor(v[3], m, 64));
-    v[4] = fmax(v[4], __shfl_xor(v[4], m, 64));
-  }
+  const double v[kStats] = {team_sum<64>(st.rz2), team_sum<64>(st.re2), team_sum<64>(st.cross), wave_max(st.xip),
+                            wave_max(st.xid)};
   __shared__ double red[kGenWaves][kStats];
   if (lane == 0) {
 #pragma unroll

@@ -1807,7 +1807,6 @@ struct BatchCache {
   size_t desc_bytes = 0;
   double* infos = nullptr;
   size_t infos_n = 0;
-  std::vector<std::pair<std::vector<long long>, int>> tuned;  // key -> team
   // the instantiated graph of the last launch, reused while its arguments
   // (descriptor and info buffers, settings, team, grid) stay the same
   hipGraphExec_t exec = nullptr;
@@ -1825,14 +1824,12 @@ int batched_impl(int B, spock_problem* const* probs, const double* const* x0, co
   BatchCache& C = batch_cache();
   const Problem& P0 = probs[0]->p;
   const int nx = P0.nx, nu = P0.nu;
-  const size_t pool = batched_pool_vectors();
-  // workspace: pool vectors + sweep buffers per instance
   std::vector<size_t> off(B);
   size_t total = 0;
   for (int b = 0; b < B; ++b) {
     const Problem& P = probs[b]->p;
     off[b] = total;
-    const size_t elems = pool * (size_t)(P.nz + P.neta) + (size_t)P.tree->nn * (2 * nx + 2 * nu);
+    const size_t elems = batched_work_elems(P.tree->nn, P.tree->nl, nx, nu, P.nz + P.neta);
     total += (elems * sizeof(S) + 255) & ~size_t(255);
   }
   if (C.bytes < total) {
@@ -1842,16 +1839,24 @@ int batched_impl(int B, spock_problem* const* probs, const double* const* x0, co
     if (hipMalloc(&C.work, total) != hipSuccess) return SPOCK_ENOMEM;
     C.bytes = total;
   }
+  // Descriptors, the largest trees first: a workgroup starts as another ends,
+  // and the largest tree alone takes as long as two mean ones.
+  std::vector<int> order(B);
+  for (int b = 0; b < B; ++b) order[b] = b;
+  std::stable_sort(order.begin(), order.end(),
+                   [&](int a, int b) { return probs[a]->p.tree->nn > probs[b]->p.tree->nn; });
   std::vector<BatchInst<S>> h(B);
-  for (int b = 0; b < B; ++b) {
+  for (int k = 0; k < B; ++k) {
+    const int b = order[k];
     const Problem& P = probs[b]->p;
-    h[b].P = (sizeof(S) == 8) ? *reinterpret_cast<const DevProb<S>*>(&P.dp64)
+    h[k].P = (sizeof(S) == 8) ? *reinterpret_cast<const DevProb<S>*>(&P.dp64)
                               : *reinterpret_cast<const DevProb<S>*>(&P.dp32);
-    h[b].stage_off = P.d_stage_off;
-    h[b].x0 = x0[b];
-    h[b].vio = static_cast<S*>(vio[b]);
-    h[b].work = reinterpret_cast<S*>(static_cast<char*>(C.work) + off[b]);
-    h[b].nv = P.nz + P.neta;
+    h[k].stage_off = P.d_stage_off;
+    h[k].id = b;
+    h[k].x0 = x0[b];
+    h[k].vio = static_cast<S*>(vio[b]);
+    h[k].work = reinterpret_cast<S*>(static_cast<char*>(C.work) + off[b]);
+    h[k].nv = P.nz + P.neta;
   }
   const size_t dbytes = sizeof(BatchInst<S>) * B;
   if (C.desc_bytes < dbytes) {
@@ -1871,54 +1876,31 @@ int batched_impl(int B, spock_problem* const* probs, const double* const* x0, co
   HIP_TRY(hipMemcpyAsync(C.desc, h.data(), dbytes, hipMemcpyHostToDevice, stream));
   BatchSettings bs{st.eps_abs, st.eps_rel, st.max_iters, st.method, st.m, st.max_ls, st.c0, st.c1,
                    st.c2, st.beta, st.sigma, st.lambda, 1};
-  const int VM = (std::max(nx, nu) + 3) & ~3;
-  const int grid = B;
   const auto* dev_desc = static_cast<const BatchInst<S>*>(C.desc);
-  // ---- team size: autotuned once per batch shape (short runs, no output)
-  std::vector<long long> key = {nx, nu, (long long)sizeof(S), B};
-  for (int b = 0; b < B; ++b) key.push_back(probs[b]->p.tree->nn);
-  // the block engine needs T >= max(nx, nu) lanes per family
-  const int tmin = next_pow2_team(std::max(nx, nu));
-  int team = -1;
+  // Lanes per family: the fewest that hold a state and an input (two
+  // components a lane above 64), so that the most families share a stage, or
+  // more when SPOCK_BATCH_TEAM asks for them (512 trees of n_x 10, n_u 5 in
+  // FP32, six iterations of the earlier 256-thread form: 10.1 ms at 16 lanes,
+  // 16.0 at 32, 26.3 at 64).
+  const int tmin = next_pow2_team(nx + nu);
+  int team = tmin;
   if (const char* env = std::getenv("SPOCK_BATCH_TEAM")) {
     const int v = std::atoi(env);
     if (v == 8 || v == 16 || v == 32 || v == 64) team = std::max(v, tmin);
   }
-  for (auto& kv : C.tuned)
-    if (team < 0 && kv.first == key) team = kv.second;
-  if (team < 0) {
-    BatchSettings tb = bs;
-    tb.write_out = 0;
-    tb.max_iters = std::min(st.max_iters, 20);
-    hipEvent_t e0, e1;
-    HIP_TRY(hipEventCreate(&e0));
-    HIP_TRY(hipEventCreate(&e1));
-    float best = 1e30f;
-    for (int cand : {8, 16, 32, 64}) {
-      if (cand < tmin) continue;
-      if ((size_t)(256 / cand) * 3 * VM * sizeof(S) > 48 * 1024) continue;
-      HIP_TRY(hipEventRecord(e0, stream));
-      HIP_TRY(launch_solve_batched<S>(dev_desc, B, tb, cand, VM, C.infos, grid, stream));
-      HIP_TRY(hipEventRecord(e1, stream));
-      HIP_TRY(hipEventSynchronize(e1));
-      float ms = 0;
-      HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
-      if (ms < best) {
-        best = ms;
-        team = cand;
-      }
-    }
-    (void)hipEventDestroy(e0);
-    (void)hipEventDestroy(e1);
-    if (team < 0) team = 64;
-    C.tuned.push_back({key, team});
+  BatchShape shape{0, 0, nx, nu, 0};
+  for (int b = 0; b < B; ++b) {
+    const Tree& T = *probs[b]->p.tree;
+    shape.nn = std::max(shape.nn, T.nn);
+    shape.nl = std::max(shape.nl, T.nl);
+    shape.N = std::max(shape.N, T.N);
   }
   // ---- the persistent launch, captured in a graph (instantiated once per
   // set of launch arguments and kept)
   {
-    std::vector<unsigned char> key2(sizeof(BatchSettings) + 6 * sizeof(long long));
-    const long long parts[6] = {(long long)(uintptr_t)dev_desc, (long long)(uintptr_t)C.infos, B, team, VM,
-                                (long long)sizeof(S)};
+    std::vector<unsigned char> key2(sizeof(BatchSettings) + 8 * sizeof(long long));
+    const long long parts[8] = {(long long)(uintptr_t)dev_desc, (long long)(uintptr_t)C.infos, B, team,
+                                (long long)sizeof(S), shape.nn, shape.nl, ((long long)nx << 40) | ((long long)nu << 32) | shape.N};
     std::memcpy(key2.data(), &bs, sizeof(BatchSettings));
     std::memcpy(key2.data() + sizeof(BatchSettings), parts, sizeof(parts));
     if (!C.exec || C.exec_key != key2) {
@@ -1928,7 +1910,7 @@ int batched_impl(int B, spock_problem* const* probs, const double* const* x0, co
       if (!C.cap) HIP_TRY(hipStreamCreateWithFlags(&C.cap, hipStreamNonBlocking));
       hipGraph_t graph = nullptr;
       HIP_TRY(hipStreamBeginCapture(C.cap, hipStreamCaptureModeThreadLocal));
-      const hipError_t le = launch_solve_batched<S>(dev_desc, B, bs, team, VM, C.infos, grid, C.cap);
+      const hipError_t le = launch_solve_batched<S>(dev_desc, B, bs, team, shape, C.infos, C.cap);
       const hipError_t ee = hipStreamEndCapture(C.cap, &graph);
       if (le != hipSuccess || ee != hipSuccess) {
         if (graph) (void)hipGraphDestroy(graph);

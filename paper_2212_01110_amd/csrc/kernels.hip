@@ -151,215 +151,9 @@ __global__ void __launch_bounds__(256) k_post_nodes(DevProb<S> P, const int* __r
   block_stats(st, partials);
 }
 
-// Flat post-pass: one wavefront per unit, a unit being a nonleaf family
-// (group 1 of i and group 2 of each child c) or a leaf (group 3). The rows
-// and columns a unit touches are exactly those of the family-serial form,
-// so no unit waits on another. A family's columns x^i and u^i share one
-// index k < nx + nu with the first rows of each child's group 2, so every
-// lane holds the same two components of all of them. Offsets are
-// arithmetic in i once fc[i] and nch[i] are read, and the slot of s^i in
-// its ancestor's block comes from spos[i]: one level of scalar loads, then
-// every data load of the unit at once. Statistics: wavefront shuffles,
-// then the block's four wavefronts in order, one record per block.
-template <typename S>
-__device__ __forceinline__ void flat_family(const DevProb<S>& P, const Off<S>& O, const long long* __restrict__ spos,
-                                            const S* __restrict__ z, const S* __restrict__ eta,
-                                            const S* __restrict__ zout, S* __restrict__ eout, int i, int lane,
-                                            StatAcc& st) {
-  const int nx = P.nx, nu = P.nu, K = nx + nu;
-  const int fc = P.fc[i], n = P.nch[i];
-  const S al = P.alpha;
-  const S ia = S(1) / al;
-  const long long e1 = O.e1(i), e1x = e1 + 2LL * n + 2, zb = O.z2(i);
-  const long long xi = O.x(i), ui = O.u(i);
-  const long long sp = spos[i];
-  // One batch of loads, with clamped indices and no branches, so that
-  // every load of the unit is in flight at once: columns x^i, u^i (slot s:
-  // k = lane + 64 s), the y block (one entry per lane when 2n + 1 <= 64)
-  // and the scalars.
-  // FP64 loads the box rows' and the y block's operands after the cone
-  // blocks (fewer live registers across them)
-  constexpr bool kLateBox = sizeof(S) == 8;
-  bool on[2];
-  S zp[2], zo[2], lo[2], hi[2], eb[2], gc[2];
-  auto load_box = [&](int s) {
-    const int k = lane + 64 * s;
-    const int kk = on[s] ? k : 0;
-    const bool isx = kk < nx;
-    const size_t bi = isx ? (size_t)i * nx + kk : (size_t)i * nu + (kk - nx);
-    lo[s] = (isx ? P.xlo : P.ulo)[bi];
-    hi[s] = (isx ? P.xhi : P.uhi)[bi];
-    eb[s] = eta[e1x + kk];
-  };
-#pragma unroll
-  for (int s = 0; s < 2; ++s) {
-    const int k = lane + 64 * s;
-    on[s] = k < K;
-    const int kk = on[s] ? k : 0;
-    const bool isx = kk < nx;
-    const long long zi = isx ? xi + kk : ui + (kk - nx);
-    zp[s] = zout[zi];
-    zo[s] = z[zi];
-    if (!kLateBox) load_box(s);
-    gc[s] = 0;
-  }
-  const int ny = 2 * n + 1;
-  const int ky = lane < ny ? lane : 0;
-  S yv, ypv, eyv, pk, si, sip, y3, y3p, es;
-  auto load_y = [&]() {
-    yv = z[zb + ky];
-    ypv = zout[zb + ky];
-    eyv = eta[e1 + ky];
-    pk = P.p[fc + (lane < n ? lane : 0)];
-    si = z[sp];
-    sip = zout[sp];
-    y3 = z[zb + 2 * n];
-    y3p = zout[zb + 2 * n];
-    es = eta[e1 + 2 * n + 1];
-  };
-  if (!kLateBox) load_y();
-  // group 2 of every child: (Q^{1/2} x^i, R^{1/2} u^i, tau/2, tau/2)
-  for (int c = fc; c < fc + n; ++c) {
-    const long long e2 = O.e2(c);
-    const long long tp = zb + 2LL * n + 1 + (c - fc);
-    S sc[2], ev[2];
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const int kk = on[s] ? lane + 64 * s : 0;
-      sc[s] = kk < nx ? P.sq[(size_t)c * nx + kk] : P.sr[(size_t)c * nu + (kk - nx)];
-      ev[s] = eta[e2 + kk];
-    }
-    const S tau = z[tp], taup = zout[tp];
-    const S ea = eta[e2 + K], ebb = eta[e2 + K + 1];
-    S wv[2], ov[2], lz[2];
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      wv[s] = on[s] ? ev[s] + al * sc[s] * (S(2) * zp[s] - zo[s]) : S(0);
-      lz[s] = sc[s] * (zo[s] - zp[s]);
-      ov[s] = 0;
-    }
-    const S wa = ea + al * S(0.5) * (S(2) * taup - tau);
-    const S wb = ebb + al * S(0.5) * (S(2) * taup - tau);
-    S oa, ob;
-    soc_prox<S, 64, 64>(wv, ov, K, wa, wb, oa, ob, al, lane);
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      if (on[s]) {
-        eout[e2 + lane + 64 * s] = ov[s];
-        const S re = ev[s] - ov[s];
-        st.row((double)re, (double)lz[s], (double)ia);
-        gc[s] += sc[s] * re;
-      }
-    }
-    if (lane == 0) {
-      const S rtau = tau - taup;
-      const S rea = ea - oa, reb = ebb - ob;
-      eout[e2 + K] = oa;
-      eout[e2 + K + 1] = ob;
-      st.row((double)rea, 0.5 * (double)rtau, (double)ia);
-      st.row((double)reb, 0.5 * (double)rtau, (double)ia);
-      st.col((double)rtau, 0.5 * ((double)rea + (double)reb), (double)ia);
-    }
-  }
-  // group 1: the boxes on (x^i, u^i) and the columns x^i, u^i
-  if (kLateBox) {
-#pragma unroll
-    for (int s = 0; s < 2; ++s) load_box(s);
-    load_y();
-  }
-#pragma unroll
-  for (int s = 0; s < 2; ++s) {
-    if (on[s]) {
-      const S w = eb[s] + al * (S(2) * zp[s] - zo[s]);
-      const S ep = w - al * clampv(w * ia, lo[s], hi[s]);
-      eout[e1x + lane + 64 * s] = ep;
-      const S re = eb[s] - ep;
-      const S rz = zo[s] - zp[s];
-      st.row((double)re, (double)rz, (double)ia);
-      st.col((double)rz, (double)(re + gc[s]), (double)ia);
-    }
-  }
-  // group 1: y in K* = R^{2n}_+ x R and the row s^i - b'y
-  double bw = lane < n ? (double)(pk * (S(2) * ypv - yv)) : 0.0;
-  double bry = lane < n ? (double)(pk * (yv - ypv)) : 0.0;
-  for (int k = lane + 64; k < n; k += 64) {  // more than 64 children
-    const S pq = P.p[fc + k];
-    const S y1 = z[zb + k], y1p = zout[zb + k];
-    bw += (double)(pq * (S(2) * y1p - y1));
-    bry += (double)(pq * (y1 - y1p));
-  }
-  const S bW = (S)team_sum<64>(bw) + (S(2) * y3p - y3);
-  const S bR = (S)team_sum<64>(bry) + (y3 - y3p);
-  const S ws = es + al * ((S(2) * sip - si) - bW);
-  const S es_new = ws < S(0) ? ws : S(0);
-  const S res_ = es - es_new;
-  auto yrow = [&](int k, S y, S yp, S e, S pq) {
-    const S w = e + al * (S(2) * yp - y);
-    const S ep = (k < 2 * n) ? (w < S(0) ? w : S(0)) : S(0);
-    eout[e1 + k] = ep;
-    const S re = e - ep;
-    const S ry = y - yp;
-    st.row((double)re, (double)ry, (double)ia);
-    const S bk = (k < n) ? pq : ((k == 2 * n) ? S(1) : S(0));
-    st.col((double)ry, (double)(re - bk * res_), (double)ia);
-  };
-  if (lane < ny) yrow(lane, yv, ypv, eyv, pk);
-  for (int k = lane + 64; k < ny; k += 64) yrow(k, z[zb + k], zout[zb + k], eta[e1 + k], k < n ? P.p[fc + k] : S(0));
-  if (lane == 0) {
-    eout[e1 + 2 * n + 1] = es_new;
-    const S rsi = si - sip;
-    st.row((double)res_, (double)(rsi - bR), (double)ia);
-    st.col((double)rsi, (double)res_, (double)ia);
-  }
-}
-
-// Leaf j: group 3 (box on x^j, (Q_N^{1/2} x^j, s/2, s/2) in the SOC) and
-// the columns x^j, s^j; one batch of loads as in flat_family.
-template <typename S>
-__device__ __forceinline__ void flat_leaf(const DevProb<S>& P, const Off<S>& O, const long long* __restrict__ spos,
-                                          const S* __restrict__ z, const S* __restrict__ eta,
-                                          const S* __restrict__ zout, S* __restrict__ eout, int j, int lane,
-                                          StatAcc& st) {
-  const int nx = P.nx;
-  const S al = P.alpha;
-  const S ia = S(1) / al;
-  const long long e3 = O.e3(j), xj = O.x(j);
-  const long long sp = spos[j];
-  const bool on = lane < nx;
-  const int kk = on ? lane : 0;
-  const S xc = zout[xj + kk], xin = z[xj + kk];
-  const S ebx = eta[e3 + kk], eq = eta[e3 + nx + kk];
-  const S lo = P.xlo[(size_t)j * nx + kk], hi = P.xhi[(size_t)j * nx + kk];
-  const S sqn = P.sqN[(size_t)j * nx + kk];
-  const S sv = z[sp], svp = zout[sp];
-  const S ea = eta[e3 + 2 * nx], ebb = eta[e3 + 2 * nx + 1];
-  const S w = ebx + al * (S(2) * xc - xin);
-  const S pb = w - al * clampv(w * ia, lo, hi);
-  const S rex = ebx - pb;
-  S wq[2] = {on ? eq + al * sqn * (S(2) * xc - xin) : S(0), S(0)}, oq[2] = {S(0), S(0)};
-  const S wsa = ea + al * S(0.5) * (S(2) * svp - sv);
-  const S wsb = ebb + al * S(0.5) * (S(2) * svp - sv);
-  S osa, osb;
-  soc_prox<S, 64, 64>(wq, oq, nx, wsa, wsb, osa, osb, al, lane);
-  if (on) {
-    eout[e3 + lane] = pb;
-    st.row((double)rex, (double)(xin - xc), (double)ia);
-    eout[e3 + nx + lane] = oq[0];
-    const S req = eq - oq[0];
-    st.row((double)req, (double)(sqn * (xin - xc)), (double)ia);
-    st.col((double)(xin - xc), (double)(rex + sqn * req), (double)ia);
-  }
-  if (lane == 0) {
-    const S rs = sv - svp;
-    eout[e3 + 2 * nx] = osa;
-    eout[e3 + 2 * nx + 1] = osb;
-    const S rea = ea - osa, reb = ebb - osb;
-    st.row((double)rea, 0.5 * (double)rs, (double)ia);
-    st.row((double)reb, 0.5 * (double)rs, (double)ia);
-    st.col((double)rs, 0.5 * ((double)rea + (double)reb), (double)ia);
-  }
-}
-
+// Flat post-pass: one wavefront per unit (flat_family, flat_leaf), a grid-stride
+// loop over units. Statistics: wavefront shuffles, then the block's four
+// wavefronts in order, one record per block.
 // Four wavefronts per SIMD: FP32 needs 122 VGPRs; FP64 (133 with the late
 // loads) is held to 128 at 12 bytes of scratch, measured faster than three.
 template <typename S>
@@ -374,19 +168,18 @@ k_post_flat(DevProb<S> P, const long long* __restrict__ spos,
   StatAcc st;
   const int stride = gridDim.x * 4;
   for (int u = blockIdx.x * 4 + wave; u < P.nn; u += stride) {
-    if (u < P.nl) flat_family<S>(P, O, spos, z, eta, zout, eout, u, lane, st);
-    else flat_leaf<S>(P, O, spos, z, eta, zout, eout, u, lane, st);
+    if (u < P.nl) {
+      const long long xi = O.x(u), ui = O.u(u);
+      flat_family<S, 64, 2, long long>(P, O, spos[u], z, eta, zout, eout, u, P.fc[u], P.nch[u], lane,
+                            [&](int kk) { return zout[kk < P.nx ? xi + kk : ui + (kk - P.nx)]; }, st);
+    } else {
+      const long long xj = O.x(u);
+      flat_leaf<S, 64, 1, long long>(P, O, spos[u], z, eta, zout, eout, u, lane, [&](int kk) { return zout[xj + kk]; }, st);
+    }
   }
   // wavefront, then the four wavefronts in order
-  double v[kStats] = {st.rz2, st.re2, st.cross, st.xip, st.xid};
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) {
-    v[0] += __shfl_xor(v[0], m, 64);
-    v[1] += __shfl_xor(v[1], m, 64);
-    v[2] += __shfl_xor(v[2], m, 64);
-    v[3] = fmax(v[3], __shfl_xor(v[3], m, 64));
-    v[4] = fmax(v[4], __shfl_xor(v[4], m, 64));
-  }
+  const double v[kStats] = {team_sum<64>(st.rz2), team_sum<64>(st.re2), team_sum<64>(st.cross), wave_max(st.xip),
+                            wave_max(st.xid)};
   __shared__ double red[4][kStats];
   if (lane == 0) {
 #pragma unroll
@@ -1551,177 +1344,6 @@ __global__ void __launch_bounds__(256) k_aa_dir(long long n, long long nv, const
     default: aa_dir_body<S, 4>(n, nv, r, dE, gamma, d, base, step); break;
   }
 }
-// Anderson step on the device (section 6.2, type-II; one thread, k <= 4):
-// the Gram row of the newest difference and the right-hand side <dR_j, r>
-// come from the push dot products; the oldest columns are dropped until the
-// Gram matrix of the kept ones has lambda_min / lambda_max >= 1e-12 (the
-// singular-value ratio 1e-6 of the residual differences; cyclic Jacobi until
-// the test is decided) and a Cholesky factor; gamma solves G gamma = rhs. gamma
-// is written for every column of the order (0 for dropped ones), and the
-// device ring takes the new order (the kept columns) and the direction's
-// columns.
-// Fixed-size (N <= 4) helpers, fully unrolled so that the matrices stay in
-// registers.
-template <int N>
-__device__ __forceinline__ bool dev_chol(double (&A)[16]) {
-#pragma unroll
-  for (int j = 0; j < N; ++j) {
-    double d = A[j * 4 + j];
-#pragma unroll
-    for (int k = 0; k < j; ++k) d -= A[j * 4 + k] * A[j * 4 + k];
-    if (!(d > 0.0) || !isfinite(d)) return false;
-    d = sqrt(d);
-    A[j * 4 + j] = d;
-#pragma unroll
-    for (int i = j + 1; i < N; ++i) {
-      double s = A[i * 4 + j];
-#pragma unroll
-      for (int k = 0; k < j; ++k) s -= A[i * 4 + k] * A[j * 4 + k];
-      A[i * 4 + j] = s / d;
-    }
-  }
-  return true;
-}
-
-// Rank test of a symmetric N x N matrix: lambda_min / lambda_max >= 1e-12
-// with lambda_max > 0. Cyclic Jacobi sweeps until the test is decided: with
-// off the sum of squares of the upper off-diagonal entries, every eigenvalue
-// lies within e = sqrt(2 off) of a diagonal entry (Weyl), so the extreme
-// eigenvalues are within e of the smallest and largest diagonal entries.
-template <int N>
-__device__ __forceinline__ bool dev_rank_ok(double (&A)[16]) {
-  constexpr double kTol = 1e-12;
-  for (int sweep = 0;; ++sweep) {
-    double off = 0, dmin = A[0], dmax = A[0];
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-      dmin = fmin(dmin, A[i * 4 + i]);
-      dmax = fmax(dmax, A[i * 4 + i]);
-#pragma unroll
-      for (int j = i + 1; j < N; ++j) off += A[i * 4 + j] * A[i * 4 + j];
-    }
-    const double e = sqrt(2.0 * off);
-    if (dmax - e > 0.0 && dmin - e >= kTol * (dmax + e)) return true;           // certainly passes
-    if (dmax + e <= 0.0 || (dmax - e > 0.0 && dmin + e < kTol * (dmax - e))) return false;  // certainly fails
-    if (sweep == 60 || off < 1e-300) return dmax > 0.0 && dmin >= kTol * dmax;  // the diagonal is the spectrum
-#pragma unroll
-    for (int p = 0; p < N; ++p)
-#pragma unroll
-      for (int q = p + 1; q < N; ++q) {
-        const double apq = A[p * 4 + q];
-        if (apq != 0.0) {
-          const double th = 0.5 * (A[q * 4 + q] - A[p * 4 + p]) / apq;
-          const double t = (th >= 0 ? 1.0 : -1.0) / (fabs(th) + sqrt(th * th + 1.0));
-          const double c = 1.0 / sqrt(t * t + 1.0), s = t * c;
-#pragma unroll
-          for (int k = 0; k < N; ++k) {
-            const double akp = A[k * 4 + p], akq = A[k * 4 + q];
-            A[k * 4 + p] = c * akp - s * akq;
-            A[k * 4 + q] = s * akp + c * akq;
-          }
-#pragma unroll
-          for (int k = 0; k < N; ++k) {
-            const double apk = A[p * 4 + k], aqk = A[q * 4 + k];
-            A[p * 4 + k] = c * apk - s * aqk;
-            A[q * 4 + k] = s * apk + c * aqk;
-          }
-        }
-      }
-  }
-}
-
-// Rank test and solve for the last N of the k active columns (rows/cols
-// `off..off+N` of Gk, right-hand side rk); true when kept.
-template <int N, int off>
-__device__ __forceinline__ bool dev_aa_try(const double (&Gk)[16], const double (&rk)[4], double (&g)[4]) {
-  double E[16], L[16];
-#pragma unroll
-  for (int i = 0; i < N; ++i)
-#pragma unroll
-    for (int j = 0; j < N; ++j) E[i * 4 + j] = L[i * 4 + j] = Gk[(off + i) * 4 + off + j];
-  if (!dev_rank_ok<N>(E) || !dev_chol<N>(L)) return false;
-  double y[4];
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    double s = rk[off + i];
-#pragma unroll
-    for (int j = 0; j < i; ++j) s -= L[i * 4 + j] * y[j];
-    y[i] = s / L[i * 4 + i];
-  }
-#pragma unroll
-  for (int i = N - 1; i >= 0; --i) {
-    double s = y[i];
-#pragma unroll
-    for (int j = i + 1; j < N; ++j) s -= L[j * 4 + i] * g[off + j];
-    g[off + i] = s / L[i * 4 + i];
-  }
-  return true;
-}
-
-// Tries the last K - DROP columns, then fewer; the number kept (0: none).
-template <int K, int DROP>
-__device__ __forceinline__ int aa_try_from(const double (&Gk)[16], const double (&rk)[4], double (&g)[4]) {
-  if constexpr (DROP >= K) {
-    return 0;
-  } else {
-    if (dev_aa_try<K - DROP, DROP>(Gk, rk, g)) return K - DROP;
-    return aa_try_from<K, DROP + 1>(Gk, rk, g);
-  }
-}
-
-// MO columns before the push (all indices fixed at compile time). Gold:
-// the Gram entries of the old columns (oldest first), read before the sums
-// were done; the new column's entries and the right-hand side <dR_j, r>
-// come from the dots. The new row is stored in G (by slot) for later pushes.
-template <int MO>
-__device__ __forceinline__ void aa_solve_dev(double* __restrict__ G, const double (&dots)[8],
-                                             const double (&Gold)[16], const AAPush& a,
-                                             double* __restrict__ gamma, AARingDev* __restrict__ ring) {
-  const int m = a.m, slot = a.slot;
-#pragma unroll
-  for (int j = 0; j < MO; ++j) {
-    G[a.order_old[j] * m + slot] = dots[j];
-    G[slot * m + a.order_old[j]] = dots[j];
-  }
-  G[slot * m + slot] = dots[MO];
-  constexpr int k = MO + 1;  // order_new = order_old + [slot]
-  // Gram matrix and right-hand side of the active columns, in registers
-  double Gk[16], rk[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    rk[i] = i < MO ? dots[MO + 1 + i] : (i == MO ? dots[2 * MO + 1] : 0.0);
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      Gk[i * 4 + j] = (i < MO && j < MO) ? Gold[i * 4 + j]
-                    : (i == MO && j < MO) ? dots[j]
-                    : (j == MO && i < MO) ? dots[i]
-                    : (i == MO && j == MO) ? dots[MO] : 0.0;
-  }
-  double g[4] = {0, 0, 0, 0};
-  // drop the oldest columns until the rest pass the rank test
-  const int kept = aa_try_from<k, 0>(Gk, rk, g);
-  if (kept == 0) g[0] = g[1] = g[2] = g[3] = 0.0;
-#pragma unroll
-  for (int j = 0; j < k; ++j) gamma[j] = g[j];
-  // the ring: the direction uses the k columns (dropped ones with gamma 0);
-  // the next push keeps the newest `kept`
-  int ord[4] = {0, 0, 0, 0};
-#pragma unroll
-  for (int j = 0; j < MO; ++j) ord[j] = a.order_old[j];
-  ord[MO] = slot;
-  ring->dk = k;
-#pragma unroll
-  for (int j = 0; j < k; ++j) ring->dslot[j] = ord[j];
-  ring->cnt = kept;
-#pragma unroll
-  for (int j = 0; j < k; ++j) {
-    int sel = 0;
-#pragma unroll
-    for (int q = 0; q < k; ++q) sel = (q == k - kept + j) ? ord[q] : sel;
-    if (j < kept) ring->order[j] = sel;
-  }
-}
-
 // Anderson push: r = v - Tv, dV = v - vprev, dR = r - rprev, with the
 // difference E = dV - dR stored in place of dV (the direction needs only E);
 // dots[j] = <dR_old_j, dR_new> (j < m_old), dots[m_old] = <dR_new, dR_new>,
@@ -1808,26 +1430,7 @@ __global__ void __launch_bounds__(256) k_aa_push(long long n, long long nv, cons
                                                  unsigned* __restrict__ counter, unsigned tag, double* __restrict__ G,
                                                  AARingDev* __restrict__ ring, double* __restrict__ gamma) {
   __shared__ double red[8][256];
-  // (fixed indices and selects only, so that nothing lands in scratch)
-  AAPush a{};
-  a.m = ring->m;
-  const int cnt = ring->cnt;
-  int o[kAAMax];
-#pragma unroll
-  for (int j = 0; j < kAAMax; ++j) o[j] = ring->order[j];
-  const bool full = cnt == a.m;
-  a.mo = full ? cnt - 1 : cnt;
-#pragma unroll
-  for (int j = 0; j < kAAMax; ++j) a.order_old[j] = full ? (j + 1 < kAAMax ? o[j + 1] : 0) : o[j];
-  int fr = kAAMax;  // lowest slot not in the order
-#pragma unroll
-  for (int s = kAAMax - 1; s >= 0; --s) {
-    bool used = false;
-#pragma unroll
-    for (int j = 0; j < kAAMax; ++j) used = used || (j < cnt && o[j] == s);
-    if (!used && s < a.m) fr = s;
-  }
-  a.slot = full ? o[0] : fr;
+  const AAPush a = aa_next_push(ring);
   VecPtrs<S> dR_old{};
 #pragma unroll
   for (int j = 0; j < kAAMax - 1; ++j) dR_old.p[j] = j < a.mo ? rb + a.order_old[j] * stride : nullptr;

@@ -372,7 +372,7 @@ struct BatchSettings {
   double eps_abs, eps_rel;
   int max_iters, method, m, max_ls;
   double c0, c1, c2, beta, sigma, lambda;
-  int write_out;  // 0: leave v_io untouched (timing runs of the autotuner)
+  int write_out;  // 0: leave v_io untouched
 };
 
 // One instance of a batched solve (device-resident descriptor).
@@ -380,16 +380,22 @@ template <typename S>
 struct BatchInst {
   DevProb<S> P;
   const int* stage_off;  // [N+2]
+  long long id;          // the instance's place in the call (results)
   const double* x0;      // [nx]
   S* vio;                // [n_v] warm start in, T(v^k) out
-  S* work;               // pool of vectors + sweep buffers
+  S* work;               // pool of vectors (16-byte aligned), then q/x, ubar and d
   long long nv;
 };
 
+// Largest tree of a batch (its exchange buffers' sizes).
+struct BatchShape {
+  int nn, nl, nx, nu, N;
+};
 template <typename S>
 hipError_t launch_solve_batched(const BatchInst<S>* insts_dev, int B, const BatchSettings& s, int team,
-                                int VM, double* infos_dev, int grid, hipStream_t st);
-size_t batched_pool_vectors();
+                                const BatchShape& sh, double* infos_dev, hipStream_t st);
+// elements of S of one instance's workspace
+size_t batched_work_elems(int nn, int nl, int nx, int nu, long long nv);
 
 // ---------------------------------------------------------------- adjoint (backward.hip)
 template <typename S>

@@ -84,3 +84,34 @@ def test_general_operators_at_dimension_edges(nx, nu, br, nc, ncN, dense, prec):
         ref = float(np.max(np.abs(rs[k])))
         check(f"edge_gen_{k}:{nx}:{nu}:{nc}:{prec}", abs(stats[k] - ref) / max(1.0, ref),
               1e-11 if prec == "fp64" else 2e-5)
+
+
+# teams of 8, 16, 32 and 64 lanes (two components a lane above 64), families
+# wider than a team, chains, a tree too large for the LDS form, N = 1; mixed
+# with a small tree so that the instances of a launch differ
+BLOCK = [(2, 1, [3, 3]), (6, 2, [11, 1]), (9, 7, [2, 2, 1, 1]), (20, 13, [2] * 4 + [1] * 2), (40, 30, [2, 1]),
+         (64, 64, [2]), (13, 7, [2] * 9), (3, 3, [70])]
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("nx,nu,br", BLOCK)
+def test_block_engine_matches_single_solves_at_edges(nx, nu, br, prec):
+    insts = [G.make_random_small(700 + nx + len(br), br, nx, nu), G.make_random_small(701, [1, 2], nx, nu),
+             G.make_random_small(702, [2], nx, nu)]
+    pr = SP.FP64 if prec == "fp64" else SP.FP32
+    probs = [SP.Problem.from_instance(i, precision=pr) for i in insts]
+    x0s = [dev(0.9 * i.x0 / max(1.0, np.max(np.abs(i.x0))), torch.float64) for i in insts]
+    for method, iters in (("cp", 10), ("spock", 4)):
+        s = SP.default_settings(eps_abs=1e-30, eps_rel=0.0, max_iters=iters, method=method)
+        vs = [torch.zeros(p.n_v, dtype=p.torch_dtype, device="cuda") for p in probs]
+        infos = SP.solve_batched(probs, x0s, vs, s)
+        for k, p in enumerate(probs):
+            ref = torch.zeros(p.n_v, dtype=p.torch_dtype, device="cuda")
+            one = p.solve(x0s[k], ref, s)
+            assert [infos[k][f] for f in ("iters", "t_evals", "n_k0", "n_k1", "n_k2")] == \
+                   [one[f] for f in ("iters", "t_evals", "n_k0", "n_k1", "n_k2")]
+            # a few hundred roundings per evaluation of T, grown over the budget
+            # of iterations (CP is nonexpansive; SPOCK divides by Gram pivots)
+            a, b = host(vs[k]), host(ref)
+            tol = {"cp": 1e-12, "spock": 1e-10}[method] if prec == "fp64" else {"cp": 2e-5, "spock": 2e-4}[method]
+            check(f"edge_block:{nx}:{nu}:{prec}:{method}:{k}", np.max(np.abs(a - b)) / max(1.0, np.max(np.abs(b))), tol)
