@@ -774,7 +774,8 @@ hipError_t launch_solve_batched(const BatchInst<S>* insts_dev, int B, const Batc
     case 8: return launch_team<S, 8, 1>(insts_dev, B, s, L, infos_dev, st);
     case 16: return launch_team<S, 16, 1>(insts_dev, B, s, L, infos_dev, st);
     case 32: return launch_team<S, 32, 1>(insts_dev, B, s, L, infos_dev, st);
-    default: return launch_team<S, 64, 2>(insts_dev, B, s, L, infos_dev, st);
+    default: return sh.nx + sh.nu <= 64 ? launch_team<S, 64, 1>(insts_dev, B, s, L, infos_dev, st)
+                                        : launch_team<S, 64, 2>(insts_dev, B, s, L, infos_dev, st);
   }
 }
 template hipError_t launch_solve_batched<double>(const BatchInst<double>*, int, const BatchSettings&, int,

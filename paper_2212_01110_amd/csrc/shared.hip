@@ -14,9 +14,10 @@
 // with the residual statistics, M) run the single-instance family steps on
 // each instance. Bp rounds B up to 16; the extra columns run on zeros.
 //
-// The host keeps each instance's state machine (Alg. 3: K0, line search with
-// K1/K2, KM) and its Anderson ring and solves the Gram systems in FP64 from
-// device dot products; the device does every vector operation.
+// Each instance's state machine (Alg. 3: K0, line search with K1/K2, KM), its
+// Anderson ring and Gram solve (FP64) live on the device: a round is a fixed
+// sequence of launches that the host queues without waiting for any of its
+// results; it only polls how many instances have ended, one round behind.
 #include "device_common.h"
 
 #include <algorithm>
@@ -87,18 +88,38 @@ __device__ __forceinline__ typename Mfma<S>::acc_t zero_acc() {
 }
 
 // ---------------------------------------------------------------- T on B instances
-// pre-pass of every (family, instance)
-template <typename S, int T>
+// pre-pass of every (unit, instance): a team of T lanes per family or leaf
+// (flat_pre_family; q = -xbar at a leaf). IX: 32-bit offsets while one
+// instance's iterate and the node arrays stay below 4 GiB.
+template <typename S, int T, int SL, typename IX>
 __global__ void __launch_bounds__(256) k_sh_pre(DevProb<S> P, const S* __restrict__ v, S* __restrict__ Tv,
                                                 S* __restrict__ xbar, S* __restrict__ ubar, S* __restrict__ q,
                                                 long long vs) {
   const int lane = threadIdx.x % T;
-  const int f = blockIdx.x * (blockDim.x / T) + threadIdx.x / T;
-  if (f >= P.nl) return;
+  const int i = blockIdx.x * (256 / T) + threadIdx.x / T;
+  if (i >= P.nn) return;  // whole teams only; no block barrier below
   const size_t b = blockIdx.y;
-  const long long wx = (long long)P.nn * P.nx, wu = (long long)P.nn * P.nu;
+  const int nx = P.nx, nu = P.nu;
+  const Off<S, IX> O(P);
   const S* z = v + b * vs;
-  fam_pre_team<S, T>(P, z, z + P.nz, Tv + b * vs, xbar + b * wx, ubar + b * wu, q + b * wx, f, lane);
+  const S* eta = z + P.nz;
+  const size_t wx = b * (size_t)P.nn * nx, wu = b * (size_t)P.nn * nu;
+  if (i >= P.nl) {
+    for (int o = lane; o < nx; o += T) {
+      const IX e3 = O.e3(i) + o;
+      const S Lt = at<S, IX>(eta, e3) + at<S, IX>(P.sqN, (IX)i * nx + o) * at<S, IX>(eta, e3 + nx);
+      q[wx + (size_t)i * nx + o] = P.alpha * Lt - at<S, IX>(z, O.x(i) + o);
+    }
+    return;
+  }
+  S bar[SL];
+  flat_pre_family<S, T, SL, IX>(P, O, z, eta, Tv + b * vs, i, P.fc[i], P.nch[i], lane, bar);
+#pragma unroll
+  for (int k = 0; k < SL; ++k) {
+    const int o = lane + T * k;
+    if (o < nx) xbar[wx + (size_t)i * nx + o] = bar[k];
+    else if (o < nx + nu) ubar[wu + (size_t)i * nu + (o - nx)] = bar[k];
+  }
 }
 
 // The sweeps of Alg. 2 for 16 instances per workgroup, workgroup barriers
@@ -109,17 +130,15 @@ __global__ void __launch_bounds__(256) k_sh_pre(DevProb<S> P, const S* __restric
 // phase): d^i = R~^{-1} ubar^i + sum_c Bt^c q^c, q^i = P1 ubar^i - xbar^i +
 // sum_c At^c q^c. Forward: u^i = K x^i + d^i, x^c = Abar^c x^i + B^c d^i.
 //
-// Phases (one launch each): kShWhole walks every stage, one workgroup per
-// 16-instance tile group. With a cut stage tc, the subtrees rooted at stage
-// tc are independent: kShBwdSub runs one workgroup per (tile group,
-// subtree) over the subtree's stages bottom-up, kShBwdTop the stages above
-// tc, kShFwdTop the root state and the stages above tc, kShFwdSub the
-// subtrees top-down; so more compute units share the wide stages.
-constexpr int kShWhole = 0, kShBwdSub = 1, kShBwdTop = 2, kShFwdTop = 3, kShFwdSub = 4;
-constexpr int kShMaxLevels = 128;  // subtree levels a workgroup keeps in LDS
+// The stages are cut into segments [ta, tb): the subtrees rooted at stage ta
+// are independent down to stage tb - 1, so a launch runs one workgroup per
+// (tile group, node of stage ta) over its part of the segment, bottom-up
+// (backward) or top-down (forward); the segments run in order, so that the
+// wide stages spread over the compute units.
+constexpr int kShMaxLevels = 128;  // stages of a segment a workgroup keeps in LDS
 
 struct ShSweepArgs {
-  int maxch, phase, tc, nsub;  // nsub: subtrees (nodes of stage tc) per tile group
+  int maxch, fwd, ta, tb, nsub;  // nsub: nodes of stage ta (subtrees per tile group)
 };
 
 template <typename S>
@@ -208,426 +227,532 @@ __global__ void __launch_bounds__(64 * kShWaves) k_sh_sweeps(DevProb<S> P, const
                                                               ShSweepArgs A) {
   __shared__ int lo[kShMaxLevels], hi[kShMaxLevels];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const bool sub = A.phase == kShBwdSub || A.phase == kShFwdSub;
-  const int g = sub ? blockIdx.x / A.nsub : blockIdx.x;  // tile group
+  const int g = blockIdx.x / A.nsub, r = blockIdx.x % A.nsub;  // tile group, subtree
   const size_t b0 = (size_t)g * kShCols;
   const int nx = P.nx, nu = P.nu;
   const long long wx = (long long)P.nn * nx, wu = (long long)P.nn * nu;
   const Off<S> O(P);
   S* q0 = q + b0 * wx;
   S* d0 = d + b0 * wu;
-  const S* xb0 = xbar + b0 * wx;
-  const S* ub0 = ubar + b0 * wu;
   S* z0 = Tv + b0 * vs;
-  if (sub) {
-    // node ranges of the subtree rooted at node stage_off[tc] + r, one per
-    // nonleaf stage tc .. N-1
-    const int r = blockIdx.x % A.nsub;
-    const int levels = P.N - A.tc;
-    if (threadIdx.x == 0) {
-      lo[0] = stage_off[A.tc] + r;
-      hi[0] = lo[0] + 1;
-      for (int l = 1; l < levels; ++l) {
-        lo[l] = P.fc[lo[l - 1]];
-        hi[l] = P.fc[hi[l - 1] - 1] + P.nch[hi[l - 1] - 1];
-      }
-    }
-    __syncthreads();
-    if (A.phase == kShBwdSub) {
-      for (int l = levels - 1; l >= 0; --l) {
-        sh_bwd_nodes<S>(P, lo[l], hi[l], q0, d0, xb0, ub0, wx, wu, lane, wave);
-        __syncthreads();
-      }
-    } else {
-      for (int l = 0; l < levels; ++l) {
-        sh_fwd_nodes<S>(P, lo[l], hi[l], z0, d0, vs, wu, A.maxch, lane, wave);
-        __syncthreads();
-      }
-    }
-    return;
-  }
-  const int tb = A.phase == kShWhole ? P.N : A.tc;  // stages [0, tb) here
-  if (A.phase == kShWhole || A.phase == kShBwdTop) {
-    for (int t = tb - 1; t >= 0; --t) {
-      sh_bwd_nodes<S>(P, stage_off[t], stage_off[t + 1], q0, d0, xb0, ub0, wx, wu, lane, wave);
-      __syncthreads();
+  // node ranges of the subtree rooted at node stage_off[ta] + r, per stage
+  const int levels = A.tb - A.ta;
+  if (threadIdx.x == 0) {
+    lo[0] = stage_off[A.ta] + r;
+    hi[0] = lo[0] + 1;
+    for (int l = 1; l < levels; ++l) {
+      lo[l] = P.fc[lo[l - 1]];
+      hi[l] = P.fc[hi[l - 1] - 1] + P.nch[hi[l - 1] - 1];
     }
   }
-  if (A.phase == kShWhole || A.phase == kShFwdTop) {
-    // root state of every instance
+  if (A.fwd && A.ta == 0) {  // root state of every instance
     for (int e = threadIdx.x; e < kShCols * nx; e += blockDim.x) {
       const int j = e / nx, o = e % nx;
       z0[(size_t)j * vs + O.x(0) + o] = (S)x0s[(b0 + j) * nx + o];
     }
-    __syncthreads();
-    for (int t = 0; t < tb; ++t) {
-      sh_fwd_nodes<S>(P, stage_off[t], stage_off[t + 1], z0, d0, vs, wu, A.maxch, lane, wave);
+  }
+  __syncthreads();
+  if (!A.fwd) {
+    for (int l = levels - 1; l >= 0; --l) {
+      sh_bwd_nodes<S>(P, lo[l], hi[l], q0, d0, xbar + b0 * wx, ubar + b0 * wu, wx, wu, lane, wave);
+      __syncthreads();
+    }
+  } else {
+    for (int l = 0; l < levels; ++l) {
+      sh_fwd_nodes<S>(P, lo[l], hi[l], z0, d0, vs, wu, A.maxch, lane, wave);
       __syncthreads();
     }
   }
 }
 
-// post-pass of every (family, instance): dual update and the instance's
-// residual statistics (block records at partials + b * gridDim.x * kStats)
-template <typename S, int T>
-__global__ void __launch_bounds__(256) k_sh_post(DevProb<S> P, const S* __restrict__ v, S* __restrict__ Tv,
-                                                 long long vs, int VM, double* __restrict__ partials) {
-  extern __shared__ unsigned char smem_raw[];
-  S* smem = reinterpret_cast<S*>(smem_raw);
+// post-pass of every (unit, instance): dual update and the instance's residual
+// statistics (block records at partials + b * gridDim.x * kStats)
+template <typename S, int T, int SL, typename IX>
+__global__ void __launch_bounds__(256) k_sh_post(DevProb<S> P, const long long* __restrict__ spos,
+                                                 const S* __restrict__ v, S* __restrict__ Tv, long long vs,
+                                                 double* __restrict__ partials) {
   const int lane = threadIdx.x % T;
-  const int team = threadIdx.x / T;
-  const int f = blockIdx.x * (blockDim.x / T) + team;
+  const int i = blockIdx.x * (256 / T) + threadIdx.x / T;
   const size_t b = blockIdx.y;
   const S* z = v + b * vs;
+  const S* eta = z + P.nz;
   S* zo = Tv + b * vs;
+  S* eo = zo + P.nz;
+  const Off<S, IX> O(P);
   StatAcc st;
-  if (f < P.nl) fam_post_team<S, T>(P, z, z + P.nz, zo, zo + P.nz, f, lane, smem + (size_t)team * 3 * VM, VM, st);
-  block_stats(st, partials + b * gridDim.x * kStats);
-}
-
-// Statistics of instance blockIdx.x from its nblk records (fixed order):
-// out[b][0..5] = xi_p, xi_d, omega^2, |r_z|^2, |r_eta|^2, <r_eta, L r_z>.
-__global__ void __launch_bounds__(256) k_sh_stats(const double* __restrict__ partials, int nblk, double alpha,
-                                                  double* __restrict__ out) {
-  __shared__ double red[kStats][256];
-  const double* p0 = partials + (size_t)blockIdx.x * nblk * kStats;
-  double a0 = 0, a1 = 0, a2 = 0, a3 = 0, a4 = 0;
-  for (int k = threadIdx.x; k < nblk; k += blockDim.x) {
-    const double* p = p0 + (size_t)k * kStats;
-    a0 += p[0];
-    a1 += p[1];
-    a2 += p[2];
-    a3 = fmax(a3, p[3]);
-    a4 = fmax(a4, p[4]);
+  if (i < P.nl) {
+    const IX xi = O.x(i), ui = O.u(i);
+    flat_family<S, T, SL, IX>(P, O, (IX)spos[i], z, eta, zo, eo, i, P.fc[i], P.nch[i], lane,
+                              [&](int k) { return at<S, IX>(zo, k < P.nx ? xi + k : ui + (k - P.nx)); }, st);
+  } else if (i < P.nn) {
+    const IX xj = O.x(i);
+    flat_leaf<S, T, SL, IX>(P, O, (IX)spos[i], z, eta, zo, eo, i, lane, [&](int k) { return at<S, IX>(zo, xj + k); },
+                            st);
   }
-  red[0][threadIdx.x] = a0;
-  red[1][threadIdx.x] = a1;
-  red[2][threadIdx.x] = a2;
-  red[3][threadIdx.x] = a3;
-  red[4][threadIdx.x] = a4;
-  __syncthreads();
-  for (int s = blockDim.x / 2; s >= 1; s >>= 1) {
-    if ((int)threadIdx.x < s) {
-      red[0][threadIdx.x] += red[0][threadIdx.x + s];
-      red[1][threadIdx.x] += red[1][threadIdx.x + s];
-      red[2][threadIdx.x] += red[2][threadIdx.x + s];
-      red[3][threadIdx.x] = fmax(red[3][threadIdx.x], red[3][threadIdx.x + s]);
-      red[4][threadIdx.x] = fmax(red[4][threadIdx.x], red[4][threadIdx.x + s]);
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    double* o = out + (size_t)blockIdx.x * 8;
-    o[0] = red[3][0];
-    o[1] = red[4][0];
-    o[2] = red[0][0] + red[1][0] - 2.0 * alpha * red[2][0];
-    o[3] = red[0][0];
-    o[4] = red[1][0];
-    o[5] = red[2][0];
-  }
-}
-
-// Fixed-order sum of K per-thread values over the workgroup (wavefront
-// butterflies, then the wavefront sums in order); the result in red[j][0].
-template <int K>
-__device__ __forceinline__ void sh_block_sums(double (&acc)[K], double (*red)[kShRed / 64]) {
-#pragma unroll
-  for (int j = 0; j < K; ++j)
-    for (int o = 32; o >= 1; o >>= 1) acc[j] += __shfl_xor(acc[j], o, 64);
-  const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const double w[kStats] = {team_sum<64>(st.rz2), team_sum<64>(st.re2), team_sum<64>(st.cross), wave_max(st.xip),
+                            wave_max(st.xid)};
+  __shared__ double red[4][kStats];
   if ((threadIdx.x & 63) == 0)
-    for (int j = 0; j < K; ++j) red[j][w] = acc[j];
+#pragma unroll
+    for (int k = 0; k < kStats; ++k) red[threadIdx.x >> 6][k] = w[k];
   __syncthreads();
-  if ((int)threadIdx.x < K) {
-    double s = 0;
-    for (int k = 0; k < nw; ++k) s += red[threadIdx.x][k];
-    red[threadIdx.x][0] = s;
+  if (threadIdx.x < kStats) {
+    const int k = threadIdx.x;
+    double a = red[0][k];
+    for (int j = 1; j < 4; ++j) a = (k < 3) ? a + red[j][k] : fmax(a, red[j][k]);
+    partials[(b * gridDim.x + blockIdx.x) * kStats + k] = a;
   }
-  __syncthreads();
 }
 
 // ---------------------------------------------------------------- vector steps
-// Buffers of the engine, each [Bp][vs]: the roles of the single-instance
-// solver (one copy per instance, no role swaps: accepted points are copied).
+// Buffers of the engine, each [Bp][vs], one copy per instance (accepted points
+// are copied, since instances decide differently in one round).
 template <typename S>
 struct ShVec {
   S* v;     // iterate
   S* tv;    // T(v)
-  S* vprev; // previous iterate
-  S* rprev; // previous residual
   S* rcur;  // residual v - T(v)
   S* dir;   // direction
   S* md;    // M dir
   S* vt;    // point of the next evaluation
   S* tvt;   // T(vt)
-  S* spare; // v + dir
   S* E;     // Anderson columns dV - dR, slot s at E + s * Bp * vs
   S* R;     // Anderson columns dR, slot s at R + s * Bp * vs
   long long vs, nv, slot;  // instance stride, vector length, slot stride
 };
 
-// vt = c0 v + c1 dir + c2 vt + c3 tvt + c4 rcur + c5 spare + c6 tv for the
-// instances with mask[b] (coefficients c[b][0..6], zero terms skipped)
+// State of one instance (device). Alg. 3 in phases: the phase says what the
+// evaluation of T that has just run was for.
+enum ShPhase : int { kShInit, kShK0, kShLS, kShK2, kShKM, kShCP, kShDone };
+enum ShNext : int { kShHold, kShDir, kShCombo, kShTv, kShFinish };
+struct ShState {
+  int phase, status, have_prev, k, ls, t_evals, n_k0, n_k1, n_k2, n_km, n_bt;
+  int commit;  // of this round: 0 nothing, 1 v = vt, 2 also the Anderson push
+  int prep;    // a residual and a direction follow the commit
+  int next;    // what the next evaluation's point is formed from (ShNext)
+  int line;    // the direction opens a line search: d is stored and M d formed
+  double xi0, xi, om2, tol, zeta, omega_safe, omega, tau;
+  double coef[5];  // kShCombo: of v, dir, vt, T(vt), r
+  double s0;       // s^0 of the returned point
+  AARingDev ring;
+  AAPush push;
+  double G[kAAMax * kAAMax], gamma[kAAMax];
+};
+struct ShSettings {
+  double eps_abs, eps_rel, c0, c1, c2, beta, sigma, lambda;
+  int max_iters, max_ls, m, cp;
+};
+// Buffers of the caller, one entry per instance
 template <typename S>
-__global__ void __launch_bounds__(256) k_sh_cand(ShVec<S> V, const double* __restrict__ coef,
-                                                 const int* __restrict__ mask) {
+struct ShIO {
+  const double* x0;
+  S* vio;
+};
+// What the host polls (pinned): rounds finished and instances ended
+struct ShMail {
+  unsigned long long round, done;
+};
+
+// Inputs of every instance in one launch: the warm start into vt, x0 into x0s,
+// the box test and the initial state (padding and rejected instances run on
+// zeros).
+template <typename S>
+__global__ void __launch_bounds__(256) k_sh_load(ShVec<S> V, const ShIO<S>* __restrict__ io, int B, int nx, int m,
+                                                 const double* __restrict__ box, double* __restrict__ x0s,
+                                                 ShState* __restrict__ state, unsigned* __restrict__ done) {
+  const int b = blockIdx.y;
+  bool out = false;
+  if (b < B && (int)threadIdx.x < nx) {
+    const double x = io[b].x0[threadIdx.x];
+    out = !(x >= box[threadIdx.x] && x <= box[nx + threadIdx.x]);
+    if (blockIdx.x == 0) x0s[(size_t)b * nx + threadIdx.x] = x;
+  } else if (blockIdx.x == 0 && (int)threadIdx.x < nx) {
+    x0s[(size_t)b * nx + threadIdx.x] = 0.0;
+  }
+  const bool rejected = __syncthreads_or(out);
+  const bool on = b < B && !rejected;
+  S* vt = V.vt + (size_t)b * V.vs;
+  for (long long e = blockIdx.x * 256LL + threadIdx.x; e < V.nv; e += gridDim.x * 256LL) vt[e] = on ? io[b].vio[e] : S(0);
+  if (blockIdx.x == 0 && threadIdx.x == 0 && b < B) {
+    ShState s{};
+    s.phase = on ? kShInit : kShDone;
+    s.status = on ? 0 : SPOCK_REJECTED;
+    s.tau = 1.0;
+    s.ring.m = m;
+    state[b] = s;
+    if (!on) atomicAdd(done, 1u);
+  }
+}
+
+// <vt - T(vt), M d> of the instances in a line search: block records in fixed
+// ranges (the decision adds them in order)
+template <typename S>
+__global__ void __launch_bounds__(256) k_sh_rdot(ShVec<S> V, const ShState* __restrict__ state, double* __restrict__ part) {
   const size_t b = blockIdx.y;
-  if (!mask[b]) return;
-  const double* c = coef + b * 8;
+  if (state[b].phase != kShLS) return;
   const size_t o = b * V.vs;
-  const S* src[7] = {V.v + o, V.dir + o, V.vt + o, V.tvt + o, V.rcur + o, V.spare + o, V.tv + o};
-  for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < V.nv; e += (long long)gridDim.x * blockDim.x) {
-    double acc = 0;
+  double acc = 0;
+  for (long long e = blockIdx.x * 256LL + threadIdx.x; e < V.nv; e += gridDim.x * 256LL)
+    acc += ((double)V.vt[o + e] - (double)V.tvt[o + e]) * (double)V.md[o + e];
+  acc = team_sum<64>(acc);
+  __shared__ double red[4];
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+  __syncthreads();
+  if (threadIdx.x == 0) part[b * gridDim.x + blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
+}
+
+// Per-instance sums of K values over n records (ld doubles apart), the last
+// two as maxima when MAX: threads stride over the records, then wavefronts in
+// order; results in every thread of the workgroup (256 threads).
+template <int K, bool MAX>
+__device__ __forceinline__ void sh_records(const double* __restrict__ rec, int n, int ld, double (&v)[K],
+                                           double (*red)[4]) {
+  constexpr int ks = MAX ? K - 2 : K;
 #pragma unroll
-    for (int j = 0; j < 7; ++j)
-      if (c[j] != 0.0) acc += c[j] * (double)src[j][e];
-    V.vt[o + e] = (S)acc;
-  }
-}
-
-// Accepting the evaluated point: mode 1 v = vt, tv = tvt; mode 2 also
-// vprev = v, rprev = rcur first (the ring of Alg. 3's accepted iterates).
-template <typename S>
-__global__ void __launch_bounds__(256) k_sh_commit(ShVec<S> V, const int* __restrict__ mode) {
-  const size_t b = blockIdx.y;
-  const int md = mode[b];
-  if (md == 0) return;
-  const size_t o = b * V.vs;
-  for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < V.nv; e += (long long)gridDim.x * blockDim.x) {
-    const size_t k = o + e;
-    if (md == 2) {
-      V.vprev[k] = V.v[k];
-      V.rprev[k] = V.rcur[k];
+  for (int j = 0; j < K; ++j) v[j] = 0;
+  for (int r = threadIdx.x; r < n; r += 256)
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+      const double x = rec[(size_t)r * ld + j];
+      v[j] = j < ks ? v[j] + x : fmax(v[j], x);
     }
-    V.v[k] = V.vt[k];
-    V.tv[k] = V.tvt[k];
+#pragma unroll
+  for (int j = 0; j < K; ++j) {
+    v[j] = j < ks ? team_sum<64>(v[j]) : wave_max(v[j]);
+    if ((threadIdx.x & 63) == 0) red[j][threadIdx.x >> 6] = v[j];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < K; ++j) {
+    double a = red[j][0];
+    for (int w = 1; w < 4; ++w) a = j < ks ? a + red[j][w] : fmax(a, red[j][w]);
+    v[j] = a;
+  }
+  __syncthreads();
+}
+
+// First half of an instance's decisions, from the statistics of the evaluation
+// that has just run: accept it (the commit and what follows) or form another
+// point (K2, a shorter step, KM).
+__global__ void __launch_bounds__(256) k_sh_judge(ShState* __restrict__ state, ShSettings s, const double* __restrict__ stats,
+                                                  int nstat, const double* __restrict__ rdots, int nrd, double alpha,
+                                                  unsigned* __restrict__ done) {
+  __shared__ double red[kStats][4];
+  const int b = blockIdx.x;
+  ShState& I = state[b];
+  const int phase = I.phase;
+  if (phase == kShDone) {
+    if (threadIdx.x == 0) {
+      I.commit = I.prep = 0;
+      I.next = kShHold;
+      I.line = 0;
+    }
+    return;
+  }
+  double v[kStats], rd[1] = {0};
+  sh_records<kStats, true>(stats + (size_t)b * nstat * kStats, nstat, kStats, v, red);
+  if (phase == kShLS) sh_records<1, false>(rdots + (size_t)b * nrd, nrd, 1, rd, red);
+  if (threadIdx.x != 0) return;
+  const double om2 = v[0] + v[1] - 2.0 * alpha * v[2], xi = fmax(v[3], v[4]);
+  const double om = sqrt(fmax(om2, 0.0));
+  const bool ok = isfinite(v[3]) && isfinite(v[4]) && isfinite(om2);
+  I.t_evals++;
+  I.commit = I.prep = 0;
+  I.next = kShHold;
+  I.line = 0;
+  auto accept = [&](int mode) {
+    I.commit = mode;
+    I.xi = xi;
+    I.om2 = om2;
+    if (!ok) {
+      I.phase = kShDone;  // T of the point reached is returned
+      I.status = SPOCK_NUMERICAL;
+      I.next = kShFinish;
+      atomicAdd(done, 1u);
+    } else {
+      I.prep = 1;
+      if (mode == 2) I.push = aa_next_push(&I.ring);
+    }
+  };
+  if (phase == kShInit) {
+    I.xi0 = xi;
+    I.tol = fmax(s.eps_abs, s.eps_rel * xi);
+    I.zeta = I.omega_safe = om;
+    accept(1);
+  } else if (phase == kShCP) {
+    I.k++;
+    accept(1);
+  } else if (phase != kShLS) {  // K0, K2, KM
+    I.k++;
+    accept(2);
+  } else {
+    bool backtrack = !ok;
+    if (ok) {
+      if (om == 0.0 || (I.omega <= I.omega_safe && om <= s.c1 * I.omega)) {  // K1
+        I.omega_safe = om + pow(s.c2, (double)I.k);
+        I.n_k1++;
+        I.k++;
+        accept(2);
+      } else {
+        const double rho = om * om - I.tau * rd[0];
+        if (rho >= s.sigma * om * I.omega) {  // K2: v - c (vt - T vt)
+          const double c = s.lambda * rho / (om * om);
+          I.next = kShCombo;
+          I.coef[0] = 1.0;
+          I.coef[1] = 0.0;
+          I.coef[2] = -c;
+          I.coef[3] = c;
+          I.coef[4] = 0.0;
+          I.n_k2++;
+          I.phase = kShK2;
+        } else {
+          backtrack = true;
+        }
+      }
+    }
+    if (backtrack) {
+      I.tau *= s.beta;
+      I.n_bt++;
+      const bool again = ++I.ls < s.max_ls;
+      I.next = kShCombo;
+      I.coef[0] = 1.0;
+      I.coef[1] = again ? I.tau : 0.0;
+      I.coef[2] = I.coef[3] = 0.0;
+      I.coef[4] = again ? 0.0 : -s.lambda;  // the plain KM step
+      if (!again) {
+        I.n_km++;
+        I.phase = kShKM;
+      }
+    }
   }
 }
 
-// Residual r = v - T(v) of the accepted point (mode >= 1); with mode 2 the
-// Anderson push: dR = r - rprev into slot ns, E = (v - vprev) - dR, and the
-// dot products dots[b][s] = <dR_s, dR>, dots[b][kAAMax + s] = <dR_s, r> for
-// s < m (the new slot's own column included). One workgroup per instance.
+// Accepting the evaluated point, in one pass: r = vt - T(vt); with commit 2 the
+// Anderson push against the iterate it replaces (dR = r - r_old, E = (vt - v)
+// - dR into the push's slot) and the block sums of <dR_j, dR>, <dR, dR>,
+// <dR_j, r>, <dR, r> (columns oldest first); then v = vt, T(v) = T(vt). Bound by
+// its traffic (4 + columns vectors read, 5 written); as a copy of four vectors
+// and a push of one workgroup per instance it took 42 + 537 us for 15 instances
+// of the 2047-node tree in FP64.
 template <typename S>
-__global__ void __launch_bounds__(kShRed) k_sh_push(ShVec<S> V, const int* __restrict__ mode, const int* __restrict__ ns,
-                                                    int m, double* __restrict__ dots) {
-  __shared__ double red[2 * kAAMax][kShRed / 64];
-  const size_t b = blockIdx.x;
-  const int md = mode[b];
-  if (md == 0) return;
+__global__ void __launch_bounds__(256) k_sh_commit(ShVec<S> V, const ShState* __restrict__ state, int cp,
+                                                   double* __restrict__ part) {
+  const size_t b = blockIdx.y;
+  const ShState& I = state[b];
+  const int mode = I.commit;
+  if (mode == 0) return;
   const size_t o = b * V.vs;
-  const int slot = ns[b];
+  const S* vt = V.vt + o;
+  const S* tvt = V.tvt + o;
+  S* v = V.v + o;
+  S* tv = V.tv + o;
+  S* rc = V.rcur + o;
+  const long long e0 = blockIdx.x * 256LL + threadIdx.x, de = gridDim.x * 256LL;
+  if (mode == 1 || cp) {
+    for (long long e = e0; e < V.nv; e += de) {
+      const S x = vt[e], t = tvt[e];
+      v[e] = x;
+      tv[e] = t;
+      if (!cp) rc[e] = (S)((double)x - (double)t);
+    }
+    return;
+  }
+  const AAPush a = I.push;
+  const S* Rj[kAAMax - 1];
+#pragma unroll
+  for (int j = 0; j < kAAMax - 1; ++j) Rj[j] = V.R + (size_t)(j < a.mo ? a.order_old[j] : 0) * V.slot + o;
+  S* En = V.E + (size_t)a.slot * V.slot + o;
+  S* Rn = V.R + (size_t)a.slot * V.slot + o;
   double acc[2 * kAAMax];
 #pragma unroll
   for (int j = 0; j < 2 * kAAMax; ++j) acc[j] = 0;
-  for (long long e = threadIdx.x; e < V.nv; e += blockDim.x) {
-    const size_t k = o + e;
-    const S vv = V.v[k];
-    const S r = vv - V.tv[k];
-    V.rcur[k] = r;
-    if (md == 2) {
-      const S dr = r - V.rprev[k];
-      V.R[(size_t)slot * V.slot + k] = dr;
-      V.E[(size_t)slot * V.slot + k] = (S)(((double)vv - (double)V.vprev[k]) - (double)dr);
+  for (long long e = e0; e < V.nv; e += de) {
+    const S x = vt[e], t = tvt[e], vo = v[e], ro = rc[e];
+    S col[kAAMax - 1];
 #pragma unroll
-      for (int s = 0; s < kAAMax; ++s)
-        if (s < m) {
-          const double ds = (s == slot) ? (double)dr : (double)V.R[(size_t)s * V.slot + k];
-          acc[s] += ds * (double)dr;
-          acc[kAAMax + s] += ds * (double)r;
-        }
+    for (int j = 0; j < kAAMax - 1; ++j) col[j] = j < a.mo ? Rj[j][e] : S(0);
+    const S r = x - t, dr = r - ro;
+    v[e] = x;
+    tv[e] = t;
+    rc[e] = r;
+    Rn[e] = dr;
+    En[e] = (S)(((double)x - (double)vo) - (double)dr);
+#pragma unroll
+    for (int j = 0; j < kAAMax - 1; ++j) {
+      acc[j] += (double)col[j] * (double)dr;
+      acc[kAAMax + j] += (double)col[j] * (double)r;
     }
+    acc[kAAMax - 1] += (double)dr * (double)dr;
+    acc[2 * kAAMax - 1] += (double)dr * (double)r;
   }
-  if (md != 2) return;  // uniform over the workgroup
-  sh_block_sums<2 * kAAMax>(acc, red);
-  if ((int)threadIdx.x < 2 * kAAMax) dots[b * 2 * kAAMax + threadIdx.x] = red[threadIdx.x][0];
-}
-
-// dir = -r - sum_s gamma[b][s] E_s, spare = v + dir (mask[b])
-template <typename S>
-__global__ void __launch_bounds__(256) k_sh_dir(ShVec<S> V, const double* __restrict__ gamma,
-                                                const int* __restrict__ mask) {
-  const size_t b = blockIdx.y;
-  if (!mask[b]) return;
-  const size_t o = b * V.vs;
-  const double* g = gamma + b * kAAMax;
-  for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < V.nv; e += (long long)gridDim.x * blockDim.x) {
-    const size_t k = o + e;
-    double acc = -(double)V.rcur[k];
+  __shared__ double red[4][2 * kAAMax];
 #pragma unroll
-    for (int s = 0; s < kAAMax; ++s)
-      if (g[s] != 0.0) acc -= g[s] * (double)V.E[(size_t)s * V.slot + k];
-    V.dir[k] = (S)acc;
-    V.spare[k] = (S)((double)V.v[k] + acc);
+  for (int j = 0; j < 2 * kAAMax; ++j) {
+    acc[j] = team_sum<64>(acc[j]);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][j] = acc[j];
+  }
+  __syncthreads();
+  if (threadIdx.x < 2 * kAAMax) {
+    const int j = threadIdx.x;
+    part[(b * gridDim.x + blockIdx.x) * (2 * kAAMax) + j] = ((red[0][j] + red[1][j]) + red[2][j]) + red[3][j];
   }
 }
 
-// md = M dir (mask[b]), one team of T lanes per family
-template <typename S, int T>
-__global__ void __launch_bounds__(256) k_sh_M(DevProb<S> P, ShVec<S> V, const int* __restrict__ mask) {
+// The Gram solve with MO older columns from the summed dot products
+template <int MO>
+__device__ __noinline__ void sh_gram(ShState& I, const double (&d)[2 * kAAMax]) {
+  double dots[8], Gold[16];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) dots[j] = 0;
+#pragma unroll
+  for (int j = 0; j < MO; ++j) {
+    dots[j] = d[j];
+    dots[MO + 1 + j] = d[kAAMax + j];
+  }
+  dots[MO] = d[kAAMax - 1];
+  dots[2 * MO + 1] = d[2 * kAAMax - 1];
+  const AAPush a = I.push;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) Gold[i * 4 + j] = (i < MO && j < MO) ? I.G[a.order_old[i] * a.m + a.order_old[j]] : 0.0;
+  aa_solve_dev<MO>(I.G, dots, Gold, a, I.gamma, &I.ring);
+}
+
+// Second half: the Gram solve, then the top of the next iteration of Alg. 3.
+__global__ void __launch_bounds__(256) k_sh_plan(ShState* __restrict__ state, ShSettings s, const double* __restrict__ part,
+                                                 int npart, unsigned* __restrict__ done) {
+  __shared__ double red[2 * kAAMax][4];
+  const int b = blockIdx.x;
+  ShState& I = state[b];
+  if (!I.prep) return;
+  const bool push = I.commit == 2 && !s.cp;
+  double d[2 * kAAMax];
+  if (push) sh_records<2 * kAAMax, false>(part + (size_t)b * npart * (2 * kAAMax), npart, 2 * kAAMax, d, red);
+  if (threadIdx.x != 0) return;
+  if (push) {
+    switch (I.push.mo) {
+      case 0: sh_gram<0>(I, d); break;
+      case 1: sh_gram<1>(I, d); break;
+      case 2: sh_gram<2>(I, d); break;
+      default: sh_gram<3>(I, d); break;
+    }
+  } else {
+    I.ring.dk = 0;
+  }
+  if (I.xi <= I.tol || I.k >= s.max_iters) {
+    I.status = I.xi <= I.tol ? SPOCK_CONVERGED : SPOCK_MAXITER;
+    I.phase = kShDone;
+    I.next = kShFinish;
+    atomicAdd(done, 1u);
+    return;
+  }
+  if (s.cp) {
+    I.phase = kShCP;
+    I.next = kShTv;
+    return;
+  }
+  I.omega = sqrt(fmax(I.om2, 0.0));
+  I.next = kShDir;
+  if (I.omega <= s.c0 * I.zeta) {  // K0: v + d
+    I.zeta = I.omega;
+    I.n_k0++;
+    I.phase = kShK0;
+    return;
+  }
+  I.line = 1;  // the line search from tau = 1
+  I.tau = 1.0;
+  I.ls = 0;
+  I.phase = kShLS;
+}
+
+// The point of the next evaluation: v + d with d = -r - sum_j gamma_j E_j (d
+// stored when a line search opens), a combination of v, d, vt, T(vt), r, or
+// T(v) (CP); or the returned point T(v) of an instance that ended. Block (0, 0)
+// publishes the round and how many instances have ended.
+template <typename S>
+__global__ void __launch_bounds__(256) k_sh_next(ShVec<S> V, ShState* __restrict__ state, int B, const ShIO<S>* __restrict__ io,
+                                                 const unsigned* __restrict__ done, ShMail* mail, unsigned long long round) {
   const size_t b = blockIdx.y;
-  if (!mask[b]) return;
+  if (blockIdx.x == 0 && b == 0 && threadIdx.x == 0) {
+    __hip_atomic_store(&mail->done, (unsigned long long)*done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&mail->round, round, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+  if ((int)b >= B) return;
+  const ShState& I = state[b];
+  const int next = I.next;
+  if (next == kShHold) return;
+  const size_t o = b * V.vs;
+  const S* v = V.v + o;
+  const S* tv = V.tv + o;
+  S* vt = V.vt + o;
+  const long long e0 = blockIdx.x * 256LL + threadIdx.x, de = gridDim.x * 256LL;
+  if (next == kShDir) {
+    const int dk = I.ring.dk, line = I.line;
+    double g[kAAMax];
+    const S* E[kAAMax];
+#pragma unroll
+    for (int j = 0; j < kAAMax; ++j) {
+      g[j] = j < dk ? I.gamma[j] : 0.0;
+      E[j] = V.E + (size_t)(j < dk ? I.ring.dslot[j] : 0) * V.slot + o;
+    }
+    const S* r = V.rcur + o;
+    S* dir = V.dir + o;
+    for (long long e = e0; e < V.nv; e += de) {
+      double acc = -(double)r[e];
+      S c[kAAMax];
+#pragma unroll
+      for (int j = 0; j < kAAMax; ++j) c[j] = j < dk ? E[j][e] : S(0);
+#pragma unroll
+      for (int j = 0; j < kAAMax; ++j) acc -= g[j] * (double)c[j];
+      if (line) {
+        const S q = (S)acc;
+        dir[e] = q;
+        acc = (double)q;
+      }
+      vt[e] = (S)((double)v[e] + acc);
+    }
+  } else if (next == kShCombo) {
+    const double c0 = I.coef[0], c1 = I.coef[1], c2 = I.coef[2], c3 = I.coef[3], c4 = I.coef[4];
+    const S* dir = V.dir + o;
+    const S* tvt = V.tvt + o;
+    const S* r = V.rcur + o;
+    for (long long e = e0; e < V.nv; e += de) {
+      double acc = c0 * (double)v[e];
+      if (c1 != 0.0) acc += c1 * (double)dir[e];
+      if (c2 != 0.0) acc += c2 * (double)vt[e];
+      if (c3 != 0.0) acc += c3 * (double)tvt[e];
+      if (c4 != 0.0) acc += c4 * (double)r[e];
+      vt[e] = (S)acc;
+    }
+  } else if (next == kShTv) {
+    for (long long e = e0; e < V.nv; e += de) vt[e] = tv[e];
+  } else {
+    S* out = io[b].vio;
+    for (long long e = e0; e < V.nv; e += de) out[e] = tv[e];
+    if (e0 == 0) state[b].s0 = (double)tv[0];
+  }
+}
+
+// md = M dir of the instances whose line search opens, one team of T lanes per family
+template <typename S, int T>
+__global__ void __launch_bounds__(256) k_sh_M(DevProb<S> P, ShVec<S> V, const ShState* __restrict__ state) {
+  const size_t b = blockIdx.y;
+  if (!state[b].line) return;
   const int lane = threadIdx.x % T;
   const int i = blockIdx.x * (blockDim.x / T) + threadIdx.x / T;
   if (i >= P.nl) return;
   fam_apply_M<S, T>(P, V.dir + b * V.vs, V.md + b * V.vs, i, lane);
 }
 
-// out[b] = <vt - tvt, md> (mask[b]), one workgroup per instance
-template <typename S>
-__global__ void __launch_bounds__(kShRed) k_sh_rdot(ShVec<S> V, const int* __restrict__ mask, double* __restrict__ out) {
-  __shared__ double red[1][kShRed / 64];
-  const size_t b = blockIdx.x;
-  if (!mask[b]) return;
-  const size_t o = b * V.vs;
-  double acc[1] = {0};
-  for (long long e = threadIdx.x; e < V.nv; e += blockDim.x)
-    acc[0] += ((double)V.vt[o + e] - (double)V.tvt[o + e]) * (double)V.md[o + e];
-  sh_block_sums<1>(acc, red);
-  if (threadIdx.x == 0) out[b] = red[0][0];
-}
-
 // ---------------------------------------------------------------- host engine
 namespace {
-
-enum ShPhase { kShInit, kShK0, kShLS, kShK2, kShKM, kShCP, kShDone };
-
-struct ShStats {
-  double xip = 0, xid = 0, om2 = 0;
-  double xi() const { return std::max(xip, xid); }
-  double omega() const { return std::sqrt(std::max(om2, 0.0)); }
-  bool ok() const { return std::isfinite(xip) && std::isfinite(xid) && std::isfinite(om2); }
-};
-
-// Anderson ring of one instance, the same rules as the single-instance
-// device ring: the new column takes the oldest slot when m columns are kept,
-// else the lowest free slot; the oldest columns are dropped until the Gram
-// matrix of the rest passes the rank test (lambda_min / lambda_max >= 1e-12,
-// cyclic Jacobi until decided) and has a Cholesky factor.
-struct ShRing {
-  int m = 1, cnt = 0, order[kAAMax] = {0, 0, 0, 0};
-  double G[kAAMax][kAAMax] = {};
-  int slot = 0, mo = 0, order_old[kAAMax] = {0, 0, 0, 0};
-
-  void begin_push() {
-    const bool full = cnt == m;
-    mo = full ? cnt - 1 : cnt;
-    for (int j = 0; j < kAAMax; ++j) order_old[j] = full ? (j + 1 < kAAMax ? order[j + 1] : 0) : order[j];
-    int fr = kAAMax;
-    for (int s = kAAMax - 1; s >= 0; --s) {
-      bool used = false;
-      for (int j = 0; j < cnt; ++j) used = used || order[j] == s;
-      if (!used && s < m) fr = s;
-    }
-    slot = full ? order[0] : fr;
-  }
-
-  static bool rank_ok(int n, double A[kAAMax][kAAMax]) {
-    const double kTol = 1e-12;
-    for (int sweep = 0;; ++sweep) {
-      double off = 0, dmin = A[0][0], dmax = A[0][0];
-      for (int i = 0; i < n; ++i) {
-        dmin = std::min(dmin, A[i][i]);
-        dmax = std::max(dmax, A[i][i]);
-        for (int j = i + 1; j < n; ++j) off += A[i][j] * A[i][j];
-      }
-      const double e = std::sqrt(2.0 * off);
-      if (dmax - e > 0.0 && dmin - e >= kTol * (dmax + e)) return true;
-      if (dmax + e <= 0.0 || (dmax - e > 0.0 && dmin + e < kTol * (dmax - e))) return false;
-      if (sweep == 60 || off < 1e-300) return dmax > 0.0 && dmin >= kTol * dmax;
-      for (int p = 0; p < n; ++p)
-        for (int q = p + 1; q < n; ++q) {
-          const double apq = A[p][q];
-          if (apq == 0.0) continue;
-          const double th = 0.5 * (A[q][q] - A[p][p]) / apq;
-          const double t = (th >= 0 ? 1.0 : -1.0) / (std::fabs(th) + std::sqrt(th * th + 1.0));
-          const double c = 1.0 / std::sqrt(t * t + 1.0), s = t * c;
-          for (int k = 0; k < n; ++k) {
-            const double akp = A[k][p], akq = A[k][q];
-            A[k][p] = c * akp - s * akq;
-            A[k][q] = s * akp + c * akq;
-          }
-          for (int k = 0; k < n; ++k) {
-            const double apk = A[p][k], aqk = A[q][k];
-            A[p][k] = c * apk - s * aqk;
-            A[q][k] = s * apk + c * aqk;
-          }
-        }
-    }
-  }
-
-  static bool chol(int n, double L[kAAMax][kAAMax]) {
-    for (int j = 0; j < n; ++j) {
-      double d = L[j][j];
-      for (int k = 0; k < j; ++k) d -= L[j][k] * L[j][k];
-      if (!(d > 0.0) || !std::isfinite(d)) return false;
-      d = std::sqrt(d);
-      L[j][j] = d;
-      for (int i = j + 1; i < n; ++i) {
-        double s = L[i][j];
-        for (int k = 0; k < j; ++k) s -= L[i][k] * L[j][k];
-        L[i][j] = s / d;
-      }
-    }
-    return true;
-  }
-
-  // dots as written by k_sh_push; gamma by slot (0 for unused or dropped)
-  void solve(const double* dots, double* gamma_by_slot) {
-    for (int j = 0; j < mo; ++j) {
-      G[order_old[j]][slot] = dots[order_old[j]];
-      G[slot][order_old[j]] = dots[order_old[j]];
-    }
-    G[slot][slot] = dots[slot];
-    const int k = mo + 1;
-    int ord[kAAMax];
-    for (int j = 0; j < mo; ++j) ord[j] = order_old[j];
-    ord[mo] = slot;
-    double rk[kAAMax];
-    for (int j = 0; j < k; ++j) rk[j] = dots[kAAMax + ord[j]];
-    double g[kAAMax] = {0, 0, 0, 0};
-    int kept = 0;
-    for (int drop = 0; drop < k && kept == 0; ++drop) {
-      const int n = k - drop;
-      double E[kAAMax][kAAMax], L[kAAMax][kAAMax];
-      for (int i = 0; i < n; ++i)
-        for (int j = 0; j < n; ++j) E[i][j] = L[i][j] = G[ord[drop + i]][ord[drop + j]];
-      if (!rank_ok(n, E) || !chol(n, L)) continue;
-      double y[kAAMax];
-      for (int i = 0; i < n; ++i) {
-        double s = rk[drop + i];
-        for (int j = 0; j < i; ++j) s -= L[i][j] * y[j];
-        y[i] = s / L[i][i];
-      }
-      for (int i = n - 1; i >= 0; --i) {
-        double s = y[i];
-        for (int j = i + 1; j < n; ++j) s -= L[j][i] * g[drop + j];
-        g[drop + i] = s / L[i][i];
-      }
-      kept = n;
-    }
-    for (int s = 0; s < kAAMax; ++s) gamma_by_slot[s] = 0.0;
-    for (int j = 0; j < k; ++j) gamma_by_slot[ord[j]] = g[j];
-    cnt = kept;
-    for (int j = 0; j < kept; ++j) order[j] = ord[k - kept + j];
-  }
-};
-
-struct ShInst {
-  int phase = kShDone;
-  bool active = false, have_prev = false;
-  double tol = 0, zeta = 0, omega_safe = 0, omega = 0, tau = 1;
-  int k = 0, ls = 0;
-  ShStats Sc;
-  ShRing ring;
-  spock_info info{};
-};
 
 // Device workspace of the engine (kept between calls, not thread safe).
 struct ShCache {
   void* mem = nullptr;
   size_t bytes = 0;
-  void* host = nullptr;  // pinned staging (parameters up, results down)
+  void* host = nullptr;  // pinned: the mail, then the tables up and the states down
   size_t host_bytes = 0;
 };
 ShCache& sh_cache() {
@@ -647,29 +772,137 @@ const DevProb<float>& sh_dev<float>(const Problem& P) { return P.dp32; }
     if ((x) != hipSuccess) return SPOCK_EHIP; \
   } while (0)
 
-template <typename S, int T>
-void sh_launch_post(const Problem& P, const DevProb<S>& D, const ShVec<S>& V, double* partials, int Bp,
-                    hipStream_t st) {
-  const int tpb = 256 / T;
-  const int VM = (std::max(P.nx, P.nu) + 3) & ~3;
-  const dim3 grid((P.tree->nl + tpb - 1) / tpb, Bp);
-  hipLaunchKernelGGL((k_sh_post<S, T>), grid, dim3(256), (size_t)tpb * 3 * VM * sizeof(S), st, D, V.vt, V.tvt, V.vs,
-                     VM, partials);
+// Lanes per unit of the flat passes: the fewest that hold a state and an input
+int sh_team(const Problem& P) {
+  int t = 8;
+  while (t < P.nx + P.nu && t < 64) t <<= 1;
+  return t;
+}
+// 32-bit offsets: one instance's iterate and the node arrays below 4 GiB
+template <typename S>
+bool sh_narrow(const Problem& P) {
+  const unsigned long long lim = (1ull << 32) / sizeof(S);
+  return (unsigned long long)(P.nz + P.neta) < lim &&
+         (unsigned long long)P.tree->nn * (8ull * P.nx + 8ull * P.nu) < lim;
+}
+int sh_post_blocks(const Problem& P) {
+  const int tpb = 256 / sh_team(P);
+  return (P.tree->nn + tpb - 1) / tpb;
 }
 
-template <typename S, int T>
-void sh_launch_pre(const Problem& P, const DevProb<S>& D, const ShVec<S>& V, S* xbar, S* ubar, S* q, int Bp,
-                   hipStream_t st) {
-  const int tpb = 256 / T;
-  const dim3 grid((P.tree->nl + tpb - 1) / tpb, Bp);
-  hipLaunchKernelGGL((k_sh_pre<S, T>), grid, dim3(256), 0, st, D, V.vt, V.tvt, xbar, ubar, q, V.vs);
+template <typename S>
+hipError_t sh_launch_pre(const Problem& P, const DevProb<S>& D, const S* in, S* out, S* xbar, S* ubar, S* q,
+                         long long vs, int Bp, hipStream_t st) {
+  const dim3 grid(sh_post_blocks(P), Bp);
+  auto go = [&](auto k) { hipLaunchKernelGGL(k, grid, dim3(256), 0, st, D, in, out, xbar, ubar, q, vs); };
+  const bool nar = sh_narrow<S>(P);
+  switch (sh_team(P)) {
+    case 8: nar ? go(k_sh_pre<S, 8, 1, unsigned>) : go(k_sh_pre<S, 8, 1, long long>); break;
+    case 16: nar ? go(k_sh_pre<S, 16, 1, unsigned>) : go(k_sh_pre<S, 16, 1, long long>); break;
+    case 32: nar ? go(k_sh_pre<S, 32, 1, unsigned>) : go(k_sh_pre<S, 32, 1, long long>); break;
+    default:
+      if (P.nx + P.nu <= 64) nar ? go(k_sh_pre<S, 64, 1, unsigned>) : go(k_sh_pre<S, 64, 1, long long>);
+      else nar ? go(k_sh_pre<S, 64, 2, unsigned>) : go(k_sh_pre<S, 64, 2, long long>);
+      break;
+  }
+  return hipGetLastError();
 }
 
-template <typename S, int T>
-void sh_launch_M(const Problem& P, const DevProb<S>& D, const ShVec<S>& V, const int* mask, int Bp, hipStream_t st) {
-  const int tpb = 256 / T;
-  const dim3 grid((P.tree->nl + tpb - 1) / tpb, Bp);
-  hipLaunchKernelGGL((k_sh_M<S, T>), grid, dim3(256), 0, st, D, V, mask);
+template <typename S>
+hipError_t sh_launch_post(const Problem& P, const DevProb<S>& D, const S* v, S* Tv, long long vs, double* partials,
+                          int Bp, hipStream_t st) {
+  const dim3 grid(sh_post_blocks(P), Bp);
+  auto go = [&](auto k) { hipLaunchKernelGGL(k, grid, dim3(256), 0, st, D, P.d_spos, v, Tv, vs, partials); };
+  const bool nar = sh_narrow<S>(P);
+  switch (sh_team(P)) {
+    case 8: nar ? go(k_sh_post<S, 8, 1, unsigned>) : go(k_sh_post<S, 8, 1, long long>); break;
+    case 16: nar ? go(k_sh_post<S, 16, 1, unsigned>) : go(k_sh_post<S, 16, 1, long long>); break;
+    case 32: nar ? go(k_sh_post<S, 32, 1, unsigned>) : go(k_sh_post<S, 32, 1, long long>); break;
+    default:
+      if (P.nx + P.nu <= 64) nar ? go(k_sh_post<S, 64, 1, unsigned>) : go(k_sh_post<S, 64, 1, long long>);
+      else nar ? go(k_sh_post<S, 64, 2, unsigned>) : go(k_sh_post<S, 64, 2, long long>);
+      break;
+  }
+  return hipGetLastError();
+}
+
+// Segments of stages of the sweeps: cut[k] .. cut[k + 1] - 1. A segment grows
+// while the items of its widest stage (nodes of one subtree times the 16-row
+// tiles of d and q) have a wavefront each, so chains
+// and narrow stages stay in one launch and a wide stage is spread over one
+// workgroup per subtree. 2047-node binary tree, n_x = n_u = 20, 15 instances,
+// FP64: both sweeps 155 us in 8 launches (four segments) against 680 us in the 4
+// launches of one cut at stage 3 (8 workgroups below it); the 95-node tree
+// keeps its cut at stage 3. SPOCK_SH_CUT sets one cut instead (0: one launch
+// over the whole tree).
+struct ShPlan {
+  std::vector<int> cut;
+  int maxch = 1;
+};
+ShPlan sh_plan(const Problem& P) {
+  const Tree& Tr = *P.tree;
+  ShPlan L;
+  for (int i = 0; i < Tr.nl; ++i) L.maxch = std::max(L.maxch, Tr.nch[i]);
+  L.cut.push_back(0);
+  if (const char* env = std::getenv("SPOCK_SH_CUT")) {
+    const int c = std::atoi(env);
+    if (c >= 1 && c < Tr.N) L.cut.push_back(c);
+  } else {
+    const int tiles = (P.nx + 15) / 16 + (P.nu + 15) / 16;
+    // node ranges of stage t under every node of the segment's first stage
+    std::vector<int> lo(1, 0), hi(1, 1);
+    for (int t = 1; t < Tr.N; ++t) {
+      int width = 0;
+      for (size_t r = 0; r < lo.size(); ++r) {
+        const int a = Tr.fc[lo[r]], b = Tr.fc[hi[r] - 1] + Tr.nch[hi[r] - 1];
+        lo[r] = a;
+        hi[r] = b;
+        width = std::max(width, b - a);
+      }
+      if (width > 1 && width * tiles > kShWaves) {  // stage t opens a segment
+        L.cut.push_back(t);
+        const int n = Tr.stage_off[t + 1] - Tr.stage_off[t];
+        lo.resize(n);
+        hi.resize(n);
+        for (int r = 0; r < n; ++r) {
+          lo[r] = Tr.stage_off[t] + r;
+          hi[r] = lo[r] + 1;
+        }
+      }
+    }
+  }
+  L.cut.push_back(Tr.N);
+  // the levels a workgroup keeps in LDS
+  for (size_t k = 0; k + 1 < L.cut.size(); ++k)
+    if (L.cut[k + 1] - L.cut[k] > kShMaxLevels) L.cut.insert(L.cut.begin() + k + 1, L.cut[k] + kShMaxLevels);
+  return L;
+}
+template <typename S>
+hipError_t sh_launch_sweeps(const Problem& P, const DevProb<S>& D, const ShPlan& L, S* Tv, const double* x0s, S* xbar,
+                            S* ubar, S* q, S* d, long long vs, int Bp, hipStream_t st) {
+  const Tree& Tr = *P.tree;
+  const int groups = Bp / kShCols, segs = (int)L.cut.size() - 1;
+  for (int j = 0; j < 2 * segs; ++j) {
+    const int fwd = j >= segs, k = fwd ? j - segs : segs - 1 - j;
+    const int ta = L.cut[k], nsub = Tr.stage_off[ta + 1] - Tr.stage_off[ta];
+    const ShSweepArgs A{L.maxch, fwd, ta, L.cut[k + 1], nsub};
+    hipLaunchKernelGGL(k_sh_sweeps<S>, dim3(groups * nsub), dim3(64 * kShWaves), 0, st, D, P.d_stage_off, Tv, x0s, xbar,
+                       ubar, q, d, vs, A);
+  }
+  return hipGetLastError();
+}
+
+template <typename S>
+hipError_t sh_launch_M(const Problem& P, const DevProb<S>& D, const ShVec<S>& V, const ShState* state, int B,
+                       hipStream_t st) {
+  const int T = std::max(P.nx, P.nu) <= 8 ? 8 : (std::max(P.nx, P.nu) <= 16 ? 16 : 32), tpb = 256 / T;
+  const dim3 grid((P.tree->nl + tpb - 1) / tpb, B);
+  switch (T) {
+    case 8: hipLaunchKernelGGL((k_sh_M<S, 8>), grid, dim3(256), 0, st, D, V, state); break;
+    case 16: hipLaunchKernelGGL((k_sh_M<S, 16>), grid, dim3(256), 0, st, D, V, state); break;
+    default: hipLaunchKernelGGL((k_sh_M<S, 32>), grid, dim3(256), 0, st, D, V, state); break;
+  }
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -679,12 +912,12 @@ int shared_solve(Problem& P, int B, const double* const* x0, const spock_setting
                  spock_info* infos, hipStream_t st) {
   const Tree& Tr = *P.tree;
   const DevProb<S>& D = sh_dev<S>(P);
-  const int nx = P.nx, nu = P.nu, T = P.team_pp;
+  const int nx = P.nx, nu = P.nu;
   const long long nv = P.nz + P.neta;
   const long long vs = (nv + 63) & ~63LL;
   const int Bp = (B + kShCols - 1) / kShCols * kShCols;
-  const int tpb = 256 / T;
-  const int nblk = (Tr.nl + tpb - 1) / tpb;
+  const int nblk = sh_post_blocks(P);
+  const int vblk = (int)std::min<long long>((nv + 511) / 512, 64);  // blocks of the vector passes per instance
   const size_t nvec = (size_t)Bp * vs;
   // device layout
   size_t off = 0;
@@ -693,19 +926,18 @@ int shared_solve(Problem& P, int B, const double* const* x0, const spock_setting
     off += (b + 255) & ~size_t(255);
     return o;
   };
-  const size_t o_vec = reserve(sizeof(S) * nvec * (10 + 2 * kAAMax));
+  const size_t o_vec = reserve(sizeof(S) * nvec * (7 + 2 * kAAMax));
   const size_t o_qx = reserve(sizeof(S) * (size_t)Bp * Tr.nn * nx * 2);
   const size_t o_du = reserve(sizeof(S) * (size_t)Bp * Tr.nn * nu * 2);
   const size_t o_x0 = reserve(sizeof(double) * (size_t)Bp * nx);
   const size_t o_part = reserve(sizeof(double) * (size_t)Bp * nblk * kStats);
-  const size_t o_res = reserve(sizeof(double) * (size_t)Bp * (8 + 1 + 2 * kAAMax));  // stats, rdot, dots
-  // parameters of the steps of a round, one staging slot per step (the host
-  // writes a slot only after the previous round's synchronisation, so no
-  // queued copy reads a slot the host is changing): coefficients [Bp][8],
-  // gamma [Bp][kAAMax], then int arrays mask, mode, slot [Bp]
-  const size_t par_bytes = ((sizeof(double) * (size_t)Bp * (8 + kAAMax) + sizeof(int) * (size_t)Bp * 3) + 255) & ~size_t(255);
-  enum { kParRdot, kParCommit, kParPush, kParDir, kParCand, kParSlots };
-  const size_t o_par = reserve(par_bytes * kParSlots);
+  const size_t o_dots = reserve(sizeof(double) * (size_t)B * vblk * (2 * kAAMax + 1));
+  const size_t o_state = reserve(sizeof(ShState) * (size_t)B);
+  // uploaded together: the callers' pointers, the root box, the count of ended instances
+  const size_t o_io = reserve(sizeof(ShIO<S>) * (size_t)B);
+  const size_t o_box = reserve(sizeof(double) * 2 * (size_t)nx);
+  const size_t o_done = reserve(sizeof(unsigned));
+  const size_t up_bytes = off - o_io;
   ShCache& C = sh_cache();
   if (C.bytes < off) {
     if (C.mem) (void)hipFree(C.mem);
@@ -714,374 +946,108 @@ int shared_solve(Problem& P, int B, const double* const* x0, const spock_setting
     if (hipMalloc(&C.mem, off) != hipSuccess) return SPOCK_ENOMEM;
     C.bytes = off;
   }
-  const size_t res_bytes = ((sizeof(double) * (size_t)Bp * (8 + 1 + 2 * kAAMax)) + 255) & ~size_t(255);
-  const size_t hbytes = res_bytes + par_bytes * kParSlots;
+  const size_t hbytes = 256 + std::max(up_bytes, sizeof(ShState) * (size_t)B);
   if (C.host_bytes < hbytes) {
     if (C.host) (void)hipHostFree(C.host);
     C.host = nullptr;
     C.host_bytes = 0;
-    if (hipHostMalloc(&C.host, hbytes, 0) != hipSuccess) return SPOCK_ENOMEM;
+    if (hipHostMalloc(&C.host, hbytes, hipHostMallocCoherent | hipHostMallocMapped) != hipSuccess) return SPOCK_ENOMEM;
     C.host_bytes = hbytes;
   }
+  ShMail* mail = static_cast<ShMail*>(C.host);
+  ShMail* mail_d = nullptr;
+  SH_TRY(hipHostGetDevicePointer(reinterpret_cast<void**>(&mail_d), mail, 0));
+  std::memset(static_cast<void*>(mail), 0, sizeof(ShMail));
+  char* up = static_cast<char*>(C.host) + 256;
   char* base = static_cast<char*>(C.mem);
-  // every vector starts at zero (padding instances stay at zero)
-  SH_TRY(hipMemsetAsync(base, 0, off, st));
   ShVec<S> V{};
   S* vb = reinterpret_cast<S*>(base + o_vec);
-  S** roles[10] = {&V.v, &V.tv, &V.vprev, &V.rprev, &V.rcur, &V.dir, &V.md, &V.vt, &V.tvt, &V.spare};
-  for (int r = 0; r < 10; ++r) *roles[r] = vb + (size_t)r * nvec;
-  V.E = vb + (size_t)10 * nvec;
+  S** roles[7] = {&V.v, &V.tv, &V.rcur, &V.dir, &V.md, &V.vt, &V.tvt};
+  for (int r = 0; r < 7; ++r) *roles[r] = vb + (size_t)r * nvec;
+  V.E = vb + (size_t)7 * nvec;
   V.R = V.E + (size_t)kAAMax * nvec;
   V.vs = vs;
   V.nv = nv;
   V.slot = (long long)nvec;
-  S* qx = reinterpret_cast<S*>(base + o_qx);
-  S* q = qx;
-  S* xbar = qx + (size_t)Bp * Tr.nn * nx;
-  S* du = reinterpret_cast<S*>(base + o_du);
-  S* d = du;
-  S* ubar = du + (size_t)Bp * Tr.nn * nu;
+  S* q = reinterpret_cast<S*>(base + o_qx);
+  S* xbar = q + (size_t)Bp * Tr.nn * nx;
+  S* d = reinterpret_cast<S*>(base + o_du);
+  S* ubar = d + (size_t)Bp * Tr.nn * nu;
   double* x0s = reinterpret_cast<double*>(base + o_x0);
   double* partials = reinterpret_cast<double*>(base + o_part);
-  double* res = reinterpret_cast<double*>(base + o_res);
-  double* stats_d = res;                        // [Bp][8]
-  double* rdot_d = res + (size_t)Bp * 8;        // [Bp]
-  double* dots_d = rdot_d + Bp;                 // [Bp][2 kAAMax]
-  char* par_d = base + o_par;
-  // host staging: results, then the parameter slots
-  double* hres = static_cast<double*>(C.host);
-  double* hstats = hres;
-  double* hrdot = hres + (size_t)Bp * 8;
-  double* hdots = hrdot + Bp;
-  char* par_h = static_cast<char*>(C.host) + res_bytes;
-  struct Par {
-    double* coef;
-    double* gamma;
-    int* mask;
-    int* mode;
-    int* slot;
-  };
-  auto par_at = [&](char* base_p, int k) {
-    char* p = base_p + (size_t)k * par_bytes;
-    Par r;
-    r.coef = reinterpret_cast<double*>(p);
-    r.gamma = r.coef + (size_t)Bp * 8;
-    r.mask = reinterpret_cast<int*>(r.gamma + (size_t)Bp * kAAMax);
-    r.mode = r.mask + Bp;
-    r.slot = r.mode + Bp;
-    return r;
-  };
-  auto clear = [&](int k) { std::memset(par_h + (size_t)k * par_bytes, 0, par_bytes); };
-  auto upload = [&](int k) -> int {
-    SH_TRY(hipMemcpyAsync(par_d + (size_t)k * par_bytes, par_h + (size_t)k * par_bytes, par_bytes,
-                          hipMemcpyHostToDevice, st));
-    return SPOCK_OK;
-  };
-  const dim3 vgrid((unsigned)std::min<long long>((nv + 255) / 256, 64), Bp);
-
-  // instances: x0 in the root box, warm start into vt
-  std::vector<ShInst> I(Bp);
-  std::vector<double> hx(nx);
-  for (int b = 0; b < B; ++b) {
-    ShInst& in = I[b];
-    in.info = spock_info{};
-    in.info.mapping = kTeamShared;
-    in.info.V_nested = std::nan("");
-    SH_TRY(hipMemcpyAsync(hx.data(), x0[b], sizeof(double) * nx, hipMemcpyDeviceToHost, st));
-    SH_TRY(hipStreamSynchronize(st));
-    bool inside = true;
-    for (int o = 0; o < nx; ++o) inside = inside && hx[o] >= P.xlo0[o] && hx[o] <= P.xhi0[o];
-    if (!inside) {
-      in.info.status = SPOCK_REJECTED;
-      continue;
-    }
-    SH_TRY(hipMemcpyAsync(x0s + (size_t)b * nx, x0[b], sizeof(double) * nx, hipMemcpyDeviceToDevice, st));
-    SH_TRY(hipMemcpyAsync(V.vt + (size_t)b * vs, vio[b], sizeof(S) * nv, hipMemcpyDeviceToDevice, st));
-    in.active = true;
-    in.phase = kShInit;
-    in.ring.m = s.m;
+  double* dots = reinterpret_cast<double*>(base + o_dots);
+  double* rdots = dots + (size_t)B * vblk * (2 * kAAMax);
+  ShState* state = reinterpret_cast<ShState*>(base + o_state);
+  const ShIO<S>* io = reinterpret_cast<const ShIO<S>*>(base + o_io);
+  const double* box = reinterpret_cast<const double*>(base + o_box);
+  unsigned* done = reinterpret_cast<unsigned*>(base + o_done);
+  // ---- inputs
+  {
+    std::memset(up, 0, up_bytes);
+    ShIO<S>* hio = reinterpret_cast<ShIO<S>*>(up);
+    for (int b = 0; b < B; ++b) hio[b] = ShIO<S>{x0[b], static_cast<S*>(vio[b])};
+    double* hbox = reinterpret_cast<double*>(up + (o_box - o_io));
+    std::copy(P.xlo0.begin(), P.xlo0.end(), hbox);
+    std::copy(P.xhi0.begin(), P.xhi0.end(), hbox + nx);
+    SH_TRY(hipMemcpyAsync(base + o_io, up, up_bytes, hipMemcpyHostToDevice, st));
   }
-  const bool cp = s.method == SPOCK_METHOD_CP;
-  auto finish = [&](int b, int status) -> int {
-    ShInst& in = I[b];
-    in.info.status = status;
-    in.info.iters = in.k;
-    in.info.xi = in.Sc.xi();
-    in.active = false;
-    in.phase = kShDone;
-    SH_TRY(hipMemcpyAsync(vio[b], V.tv + (size_t)b * vs, sizeof(S) * nv, hipMemcpyDeviceToDevice, st));
-    return SPOCK_OK;
-  };
-  auto any_active = [&]() {
-    for (int b = 0; b < B; ++b)
-      if (I[b].active) return true;
-    return false;
-  };
-  enum { cV = 0, cDIR = 1, cVT = 2, cTVT = 3, cRCUR = 4, cSPARE = 5, cTV = 6 };
-  auto set_cand = [&](int b, std::initializer_list<std::pair<int, double>> terms) {
-    const Par c = par_at(par_h, kParCand);
-    for (int j = 0; j < 8; ++j) c.coef[(size_t)b * 8 + j] = 0.0;
-    for (auto& t : terms) c.coef[(size_t)b * 8 + t.first] += t.second;
-    c.mask[b] = 1;
-  };
-  const Par hp_rdot = par_at(par_h, kParRdot), dp_rdot = par_at(par_d, kParRdot);
-  const Par hp_com = par_at(par_h, kParCommit), dp_com = par_at(par_d, kParCommit);
-  const Par hp_push = par_at(par_h, kParPush), dp_push = par_at(par_d, kParPush);
-  const Par hp_dir = par_at(par_h, kParDir), dp_dir = par_at(par_d, kParDir);
-  const Par dp_cand = par_at(par_d, kParCand);
-  const int sweep_grid = Bp / kShCols;
-  int maxch = 1;
-  for (int i = 0; i < Tr.nl; ++i) maxch = std::max(maxch, Tr.nch[i]);
-  // cut stage of the sweeps: the first stage with at least 8 nodes, if it
-  // has nonleaf stages below it (at most kShMaxLevels) and is not the root
-  // stage; SPOCK_SH_CUT overrides (0: one launch over the whole tree)
-  int sh_cut = 0;
-  for (int t = 1; t < Tr.N; ++t)
-    if (Tr.stage_off[t + 1] - Tr.stage_off[t] >= 8) {
-      sh_cut = t;
-      break;
-    }
-  if (const char* env = std::getenv("SPOCK_SH_CUT")) sh_cut = std::atoi(env);
-  if (sh_cut < 1 || sh_cut >= Tr.N || Tr.N - sh_cut > kShMaxLevels) sh_cut = 0;
-  std::vector<char> prep(Bp), head(Bp);
-  while (any_active()) {
-    // ---- one evaluation of T at vt for every instance
-    switch (T) {
-      case 8: sh_launch_pre<S, 8>(P, D, V, xbar, ubar, q, Bp, st); break;
-      case 16: sh_launch_pre<S, 16>(P, D, V, xbar, ubar, q, Bp, st); break;
-      case 32: sh_launch_pre<S, 32>(P, D, V, xbar, ubar, q, Bp, st); break;
-      default: sh_launch_pre<S, 64>(P, D, V, xbar, ubar, q, Bp, st); break;
-    }
-    if (sh_cut > 0) {
-      const int nsub = Tr.stage_off[sh_cut + 1] - Tr.stage_off[sh_cut];
-      for (int ph : {kShBwdSub, kShBwdTop, kShFwdTop, kShFwdSub}) {
-        const ShSweepArgs A{maxch, ph, sh_cut, nsub};
-        const bool subph = ph == kShBwdSub || ph == kShFwdSub;
-        hipLaunchKernelGGL(k_sh_sweeps<S>, dim3(subph ? sweep_grid * nsub : sweep_grid), dim3(64 * kShWaves), 0, st,
-                           D, P.d_stage_off, V.tvt, x0s, xbar, ubar, q, d, vs, A);
+  const dim3 vgrid(vblk, B);
+  hipLaunchKernelGGL(k_sh_load<S>, dim3(vblk, Bp), dim3(256), 0, st, V, io, B, nx, s.m, box, x0s, state, done);
+  SH_TRY(hipGetLastError());
+  const ShSettings S3{s.eps_abs, s.eps_rel, s.c0, s.c1, s.c2, s.beta, s.sigma, s.lambda, s.max_iters, s.max_ls, s.m,
+                      s.method == SPOCK_METHOD_CP ? 1 : 0};
+  const ShPlan plan = sh_plan(P);
+  // ---- rounds: one evaluation of T for every instance each; the host stays
+  // one round ahead of the count of ended instances
+  auto wait_round = [&](unsigned long long r) -> int {
+    for (unsigned n = 1;; ++n) {
+      if (__atomic_load_n(&mail->round, __ATOMIC_ACQUIRE) >= r) return SPOCK_OK;
+      if ((n & 4095u) == 0u) {
+        const hipError_t e = hipStreamQuery(st);
+        if (e == hipSuccess) return __atomic_load_n(&mail->round, __ATOMIC_ACQUIRE) >= r ? SPOCK_OK : SPOCK_EHIP;
+        if (e != hipErrorNotReady) return SPOCK_EHIP;
       }
-    } else {
-      const ShSweepArgs A{maxch, kShWhole, 0, 1};
-      hipLaunchKernelGGL(k_sh_sweeps<S>, dim3(sweep_grid), dim3(64 * kShWaves), 0, st, D, P.d_stage_off, V.tvt, x0s,
-                         xbar, ubar, q, d, vs, A);
     }
-    switch (T) {
-      case 8: sh_launch_post<S, 8>(P, D, V, partials, Bp, st); break;
-      case 16: sh_launch_post<S, 16>(P, D, V, partials, Bp, st); break;
-      case 32: sh_launch_post<S, 32>(P, D, V, partials, Bp, st); break;
-      default: sh_launch_post<S, 64>(P, D, V, partials, Bp, st); break;
-    }
-    hipLaunchKernelGGL(k_sh_stats, dim3(Bp), dim3(256), 0, st, partials, nblk, P.alpha, stats_d);
-    // <vt - T(vt), M d> of the instances in a line search
-    clear(kParRdot);
-    bool any_ls = false;
-    for (int b = 0; b < B; ++b)
-      if (I[b].active && I[b].phase == kShLS) any_ls = hp_rdot.mask[b] = 1;
-    if (any_ls) {
-      if (int rc = upload(kParRdot)) return rc;
-      hipLaunchKernelGGL(k_sh_rdot<S>, dim3(Bp), dim3(kShRed), 0, st, V, dp_rdot.mask, rdot_d);
-    }
+  };
+  for (unsigned long long r = 1;; ++r) {
+    SH_TRY(sh_launch_pre<S>(P, D, V.vt, V.tvt, xbar, ubar, q, vs, Bp, st));
+    SH_TRY(sh_launch_sweeps<S>(P, D, plan, V.tvt, x0s, xbar, ubar, q, d, vs, Bp, st));
+    SH_TRY(sh_launch_post<S>(P, D, V.vt, V.tvt, vs, partials, Bp, st));
+    if (!S3.cp) hipLaunchKernelGGL(k_sh_rdot<S>, vgrid, dim3(256), 0, st, V, state, rdots);
+    hipLaunchKernelGGL(k_sh_judge, dim3(B), dim3(256), 0, st, state, S3, partials, nblk, rdots, vblk, P.alpha, done);
+    hipLaunchKernelGGL(k_sh_commit<S>, vgrid, dim3(256), 0, st, V, state, S3.cp, dots);
+    hipLaunchKernelGGL(k_sh_plan, dim3(B), dim3(256), 0, st, state, S3, dots, vblk, done);
+    hipLaunchKernelGGL(k_sh_next<S>, vgrid, dim3(256), 0, st, V, state, B, io, done, mail_d, r);
+    if (!S3.cp) SH_TRY(sh_launch_M<S>(P, D, V, state, B, st));
     SH_TRY(hipGetLastError());
-    SH_TRY(hipMemcpyAsync(hres, res, sizeof(double) * (size_t)Bp * 9, hipMemcpyDeviceToHost, st));
-    SH_TRY(hipStreamSynchronize(st));
-    // ---- per-instance decisions (Alg. 3)
-    clear(kParCommit);
-    clear(kParPush);
-    clear(kParDir);
-    clear(kParCand);
-    std::fill(prep.begin(), prep.end(), 0);
-    std::fill(head.begin(), head.end(), 0);
-    for (int b = 0; b < B; ++b) {
-      ShInst& in = I[b];
-      if (!in.active) continue;
-      ShStats St;
-      St.xip = hstats[(size_t)b * 8 + 0];
-      St.xid = hstats[(size_t)b * 8 + 1];
-      St.om2 = hstats[(size_t)b * 8 + 2];
-      in.info.t_evals++;
-      switch (in.phase) {
-        case kShInit:
-          in.Sc = St;
-          in.info.xi0 = St.xi();
-          in.tol = std::max(s.eps_abs, s.eps_rel * in.info.xi0);
-          in.zeta = in.omega_safe = St.omega();
-          hp_com.mode[b] = 1;
-          if (!St.ok()) {
-            in.phase = kShDone;  // returned after the commit below
-            in.info.status = SPOCK_NUMERICAL;
-          } else if (cp) {
-            head[b] = 1;
-          } else {
-            prep[b] = 1;
-          }
-          break;
-        case kShCP:
-          hp_com.mode[b] = 1;
-          in.Sc = St;
-          ++in.k;
-          if (!St.ok()) {
-            in.phase = kShDone;
-            in.info.status = SPOCK_NUMERICAL;
-          } else {
-            head[b] = 1;
-          }
-          break;
-        case kShK0:
-        case kShK2:
-        case kShKM:
-          hp_com.mode[b] = 2;
-          in.have_prev = true;
-          in.Sc = St;
-          ++in.k;
-          if (!St.ok()) {
-            in.phase = kShDone;
-            in.info.status = SPOCK_NUMERICAL;
-          } else {
-            prep[b] = 1;
-          }
-          break;
-        case kShLS: {
-          bool backtrack = false;
-          if (!St.ok()) {
-            backtrack = true;
-          } else {
-            const double om_t = St.omega();
-            if (om_t == 0.0 || (in.omega <= in.omega_safe && om_t <= s.c1 * in.omega)) {  // K1
-              hp_com.mode[b] = 2;
-              in.have_prev = true;
-              in.Sc = St;
-              in.omega_safe = om_t + std::pow(s.c2, in.k);
-              in.info.n_k1++;
-              ++in.k;
-              prep[b] = 1;
-            } else {
-              const double rho = om_t * om_t - in.tau * hrdot[b];
-              if (rho >= s.sigma * om_t * in.omega) {  // K2: v - c (vt - T vt)
-                const double c = s.lambda * rho / (om_t * om_t);
-                set_cand(b, {{cV, 1.0}, {cVT, -c}, {cTVT, c}});
-                in.info.n_k2++;
-                in.phase = kShK2;
-              } else {
-                backtrack = true;
-              }
-            }
-          }
-          if (backtrack) {
-            in.tau *= s.beta;
-            in.info.n_backtracks++;
-            if (++in.ls < s.max_ls) {
-              set_cand(b, {{cV, 1.0}, {cDIR, in.tau}});
-            } else {  // plain KM step
-              set_cand(b, {{cV, 1.0}, {cRCUR, -s.lambda}});
-              in.info.n_km++;
-              in.phase = kShKM;
-            }
-          }
-          break;
-        }
-        default:
-          break;
-      }
+    if (r > 1) {
+      if (int rc = wait_round(r - 1)) return rc;
+      if (__atomic_load_n(&mail->done, __ATOMIC_RELAXED) >= (unsigned long long)B) break;
     }
-    // ---- the push parameters (host state only), then commit and push
-    // parameters in one upload (adjacent slots)
-    bool any_prep = false, any_push = false;
-    for (int b = 0; b < B; ++b) {
-      if (!prep[b]) continue;
-      ShInst& in = I[b];
-      any_prep = true;
-      hp_push.mode[b] = in.have_prev ? 2 : 1;
-      if (in.have_prev) {
-        in.ring.begin_push();
-        hp_push.slot[b] = in.ring.slot;
-        any_push = true;
-      }
-      hp_dir.mask[b] = 1;
-    }
-    static_assert(kParPush == kParCommit + 1, "adjacent staging slots");
-    SH_TRY(hipMemcpyAsync(par_d + (size_t)kParCommit * par_bytes, par_h + (size_t)kParCommit * par_bytes,
-                          2 * par_bytes, hipMemcpyHostToDevice, st));
-    // ---- accept the evaluated points (the K2 and KM candidates above read
-    // only rows of instances that commit nothing this round)
-    hipLaunchKernelGGL(k_sh_commit<S>, vgrid, dim3(256), 0, st, V, dp_com.mode);
-    for (int b = 0; b < B; ++b)  // ended numerically: T of the point reached
-      if (I[b].active && I[b].phase == kShDone)
-        if (int rc = finish(b, I[b].info.status)) return rc;
-    // ---- residual, Anderson push, Gram solve and direction
-    if (any_prep) {
-      hipLaunchKernelGGL(k_sh_push<S>, dim3(Bp), dim3(kShRed), 0, st, V, dp_push.mode, dp_push.slot, s.m, dots_d);
-      if (any_push) {
-        SH_TRY(hipMemcpyAsync(hdots, dots_d, sizeof(double) * (size_t)Bp * 2 * kAAMax, hipMemcpyDeviceToHost, st));
-        SH_TRY(hipStreamSynchronize(st));
-      }
-      for (int b = 0; b < B; ++b) {
-        if (!prep[b]) continue;
-        if (I[b].have_prev) I[b].ring.solve(hdots + (size_t)b * 2 * kAAMax, hp_dir.gamma + (size_t)b * kAAMax);
-        head[b] = 1;
-      }
-    }
-    // ---- top of the next iteration of Alg. 3
-    bool any_m = false;
-    for (int b = 0; b < B; ++b) {
-      ShInst& in = I[b];
-      if (!head[b] || !in.active) continue;
-      if (in.Sc.xi() <= in.tol) {
-        if (int rc = finish(b, SPOCK_CONVERGED)) return rc;
-        continue;
-      }
-      if (in.k >= s.max_iters) {
-        if (int rc = finish(b, SPOCK_MAXITER)) return rc;
-        continue;
-      }
-      if (cp) {
-        set_cand(b, {{cTV, 1.0}});
-        in.phase = kShCP;
-        continue;
-      }
-      in.omega = in.Sc.omega();
-      if (in.omega <= s.c0 * in.zeta) {  // K0: v + d
-        in.zeta = in.omega;
-        in.info.n_k0++;
-        set_cand(b, {{cSPARE, 1.0}});
-        in.phase = kShK0;
-        continue;
-      }
-      any_m = true;  // M d (marked in the slot array), then the line search from tau = 1
-      par_at(par_h, kParCand).slot[b] = 1;
-      in.tau = 1.0;
-      in.ls = 0;
-      set_cand(b, {{cV, 1.0}, {cDIR, 1.0}});
-      in.phase = kShLS;
-    }
-    // direction and candidate parameters in one upload (adjacent slots);
-    // the direction kernel writes dir and spare, which the copies of the
-    // instances that finished above do not read
-    static_assert(kParCand == kParDir + 1, "adjacent staging slots");
-    SH_TRY(hipMemcpyAsync(par_d + (size_t)kParDir * par_bytes, par_h + (size_t)kParDir * par_bytes, 2 * par_bytes,
-                          hipMemcpyHostToDevice, st));
-    if (any_prep) hipLaunchKernelGGL(k_sh_dir<S>, vgrid, dim3(256), 0, st, V, dp_dir.gamma, dp_dir.mask);
-    if (any_m) {
-      switch (T) {
-        case 8: sh_launch_M<S, 8>(P, D, V, dp_cand.slot, Bp, st); break;
-        case 16: sh_launch_M<S, 16>(P, D, V, dp_cand.slot, Bp, st); break;
-        case 32: sh_launch_M<S, 32>(P, D, V, dp_cand.slot, Bp, st); break;
-        default: sh_launch_M<S, 64>(P, D, V, dp_cand.slot, Bp, st); break;
-      }
-    }
-    hipLaunchKernelGGL(k_sh_cand<S>, vgrid, dim3(256), 0, st, V, dp_cand.coef, dp_cand.mask);
-    SH_TRY(hipGetLastError());
   }
-  // s^0 of each returned point
-  for (int b = 0; b < B; ++b) {
-    ShInst& in = I[b];
-    infos[b] = in.info;
-    if (in.info.status == SPOCK_REJECTED) continue;
-    S s0;
-    SH_TRY(hipMemcpyAsync(&s0, vio[b], sizeof(S), hipMemcpyDeviceToHost, st));
-    SH_TRY(hipStreamSynchronize(st));
-    infos[b].V_s0 = (double)s0;
-  }
+  ShState* hs = reinterpret_cast<ShState*>(up);
+  SH_TRY(hipMemcpyAsync(hs, state, sizeof(ShState) * (size_t)B, hipMemcpyDeviceToHost, st));
   SH_TRY(hipStreamSynchronize(st));
+  for (int b = 0; b < B; ++b) {
+    const ShState& I = hs[b];
+    spock_info n{};
+    n.status = I.status;
+    n.mapping = kTeamShared;
+    n.V_nested = std::numeric_limits<double>::quiet_NaN();
+    if (I.status != SPOCK_REJECTED) {
+      n.iters = I.k;
+      n.t_evals = I.t_evals;
+      n.n_k0 = I.n_k0;
+      n.n_k1 = I.n_k1;
+      n.n_k2 = I.n_k2;
+      n.n_km = I.n_km;
+      n.n_backtracks = I.n_bt;
+      n.xi0 = I.xi0;
+      n.xi = I.xi;
+      n.V_s0 = I.s0;
+    }
+    infos[b] = n;
+  }
   return SPOCK_OK;
 }
 
@@ -1218,7 +1184,7 @@ int shared_backward(Problem& P, int B, const void* const* vstar, const double* c
                     const spock_settings& s, spock_info* infos, hipStream_t st) {
   const Tree& Tr = *P.tree;
   const DevProb<S>& D = sh_dev<S>(P);
-  const int nx = P.nx, nu = P.nu, T = P.team_pp;
+  const int nx = P.nx, nu = P.nu;
   const long long nz = P.nz, ne = P.neta, nv = nz + ne;
   const long long vs = (nv + 63) & ~63LL;
   const int Bp = (B + kShCols - 1) / kShCols * kShCols;
@@ -1292,42 +1258,11 @@ int shared_backward(Problem& P, int B, const void* const* vstar, const double* c
                         gx0[b], gq ? gq[b] : nullptr, gqN ? gqN[b] : nullptr};
   SH_TRY(hipMemcpyAsync(tab_d, tab.data(), sizeof(AdjPtrs<S>) * B, hipMemcpyHostToDevice, st));
   SH_TRY(launch_adj_load<S>(P, gV, tab_d, vs, B, vec[kV], x0s, vec[kG], vec[kW], st));
-  // T of the instances without (with) the dual part: pre-pass, then the
-  // sweeps in the phases of the shared-tree form
-  int maxch = 1;
-  for (int i = 0; i < Tr.nl; ++i) maxch = std::max(maxch, Tr.nch[i]);
-  int sh_cut = 0;
-  for (int t = 1; t < Tr.N; ++t)
-    if (Tr.stage_off[t + 1] - Tr.stage_off[t] >= 8) {
-      sh_cut = t;
-      break;
-    }
-  if (const char* env = std::getenv("SPOCK_SH_CUT")) sh_cut = std::atoi(env);
-  if (sh_cut < 1 || sh_cut >= Tr.N || Tr.N - sh_cut > kShMaxLevels) sh_cut = 0;
-  const int sweep_grid = Bp / kShCols;
+  // prox_f of the instances: pre-pass, then the sweeps
+  const ShPlan plan = sh_plan(P);
   auto prox = [&](S* in, S* out, const double* xs0) -> int {
-    const int tpb = 256 / T;
-    const dim3 grid((Tr.nl + tpb - 1) / tpb, Bp);
-    switch (T) {
-      case 8: hipLaunchKernelGGL((k_sh_pre<S, 8>), grid, dim3(256), 0, st, D, in, out, xbar, ubar, q, vs); break;
-      case 16: hipLaunchKernelGGL((k_sh_pre<S, 16>), grid, dim3(256), 0, st, D, in, out, xbar, ubar, q, vs); break;
-      case 32: hipLaunchKernelGGL((k_sh_pre<S, 32>), grid, dim3(256), 0, st, D, in, out, xbar, ubar, q, vs); break;
-      default: hipLaunchKernelGGL((k_sh_pre<S, 64>), grid, dim3(256), 0, st, D, in, out, xbar, ubar, q, vs); break;
-    }
-    if (sh_cut > 0) {
-      const int nsub = Tr.stage_off[sh_cut + 1] - Tr.stage_off[sh_cut];
-      for (int ph : {kShBwdSub, kShBwdTop, kShFwdTop, kShFwdSub}) {
-        const ShSweepArgs A{maxch, ph, sh_cut, nsub};
-        const bool subph = ph == kShBwdSub || ph == kShFwdSub;
-        hipLaunchKernelGGL(k_sh_sweeps<S>, dim3(subph ? sweep_grid * nsub : sweep_grid), dim3(64 * kShWaves), 0, st,
-                           D, P.d_stage_off, out, xs0, xbar, ubar, q, d, vs, A);
-      }
-    } else {
-      const ShSweepArgs A{maxch, kShWhole, 0, 1};
-      hipLaunchKernelGGL(k_sh_sweeps<S>, dim3(sweep_grid), dim3(64 * kShWaves), 0, st, D, P.d_stage_off, out, xs0,
-                         xbar, ubar, q, d, vs, A);
-    }
-    SH_TRY(hipGetLastError());
+    SH_TRY(sh_launch_pre<S>(P, D, in, out, xbar, ubar, q, vs, Bp, st));
+    SH_TRY(sh_launch_sweeps<S>(P, D, plan, out, xs0, xbar, ubar, q, d, vs, Bp, st));
     return SPOCK_OK;
   };
   // pre-prox point of the dual update at v*: b* = eta* + alpha L (2 z+ - z*)

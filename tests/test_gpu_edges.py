@@ -115,3 +115,33 @@ def test_block_engine_matches_single_solves_at_edges(nx, nu, br, prec):
             a, b = host(vs[k]), host(ref)
             tol = {"cp": 1e-12, "spock": 1e-10}[method] if prec == "fp64" else {"cp": 2e-5, "spock": 2e-4}[method]
             check(f"edge_block:{nx}:{nu}:{prec}:{method}:{k}", np.max(np.abs(a - b)) / max(1.0, np.max(np.abs(b))), tol)
+
+
+# shared-tree form: a batch that pads to two tiles of 16, segments of stages of
+# every kind (wide, chains, one stage), teams of 8 to 64 lanes with one or two
+# components a lane, a rejected start among the instances
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("nx,nu,br,B", [(2, 1, [2] * 5, 17), (9, 5, [3, 1, 1, 2], 3), (17, 3, [2] * 6 + [1], 16),
+                                        (33, 17, [2, 2], 2), (64, 64, [1, 2], 5), (3, 2, [40, 1], 2)])
+def test_shared_form_matches_single_solves_at_edges(nx, nu, br, B, prec):
+    inst = G.make_random_small(800 + nx, br, nx, nu)
+    gp = SP.Problem.from_instance(inst, precision=SP.FP64 if prec == "fp64" else SP.FP32)
+    rng = np.random.default_rng([nx, B])
+    x0s = [dev(rng.uniform(-1.0, 1.0, nx), torch.float64) for _ in range(B)]
+    x0s[B // 2] = dev(np.full(nx, 6.0), torch.float64)  # outside the box
+    for method, iters in (("cp", 10), ("spock", 4)):
+        s = SP.default_settings(eps_abs=1e-30, eps_rel=0.0, max_iters=iters, method=method)
+        vs = [torch.full((gp.n_v,), 0.25, dtype=gp.torch_dtype, device="cuda") for _ in range(B)]
+        infos = SP.solve_batched([gp] * B, x0s, vs, s)
+        for k in range(B):
+            if k == B // 2:
+                assert infos[k]["status"] == "rejected" and bool((vs[k] == 0.25).all())
+                continue
+            ref = torch.full((gp.n_v,), 0.25, dtype=gp.torch_dtype, device="cuda")
+            one = gp.solve(x0s[k], ref, s)
+            assert [infos[k][f] for f in ("status", "iters", "t_evals", "n_k0", "n_k1", "n_k2", "n_km")] == \
+                   [one[f] for f in ("status", "iters", "t_evals", "n_k0", "n_k1", "n_k2", "n_km")]
+            a, b = host(vs[k]), host(ref)
+            # as for the block engine above
+            tol = {"cp": 1e-12, "spock": 1e-10}[method] if prec == "fp64" else {"cp": 2e-5, "spock": 2e-4}[method]
+            check(f"edge_shared:{nx}:{nu}:{prec}:{method}:{k}", np.max(np.abs(a - b)) / max(1.0, np.max(np.abs(b))), tol)
