@@ -18,23 +18,21 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
 }
 
-// The value of the partner lane of a butterfly step, without the LDS pipe:
-// steps 1 and 2 by quad permutes, 4 and 8 by the mirrors of 8 and 16 lanes
-// (a partner's value, since the smaller steps have made each group uniform),
-// 16 and 32 by the row and half swaps of the value with itself. A shuffle
-// through LDS costs about 120 cycles a step; these cost a few.
-template <int M>
+// The value of the partner lane of a butterfly step of 2^k lanes, the steps
+// taken from the widest down: 32 and 16 (and 4 in a team of 8) by shuffles, 8
+// to 1 by rotations of a 16-lane row. A rotation by M reaches a lane whose
+// value equals that of lane ^ M once the wider steps have made the row periodic
+// in 2 M. A shuffle through LDS costs about 120 cycles a step, a rotation a
+// few.
+template <int M, int T>
 __device__ __forceinline__ double lane_partner(double v) {
   unsigned w[2];
   __builtin_memcpy(w, &v, 8);
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
-    if constexpr (M <= 8) {
-      constexpr int ctrl = M == 1 ? 0xB1 : (M == 2 ? 0x4E : (M == 4 ? 0x141 : 0x140));
-      w[k] = (unsigned)__builtin_amdgcn_update_dpp((int)w[k], (int)w[k], ctrl, 0xF, 0xF, false);
-    } else {
-      w[k] = (unsigned)__shfl_xor((int)w[k], M, 64);
-    }
+    if constexpr (M <= 2) w[k] = (unsigned)__builtin_amdgcn_update_dpp((int)w[k], (int)w[k], M == 1 ? 0xB1 : 0x4E, 0xF, 0xF, false);
+    else if constexpr (M <= 8 && T >= 16) w[k] = (unsigned)__builtin_amdgcn_update_dpp((int)w[k], (int)w[k], 0x120 + M, 0xF, 0xF, false);
+    else w[k] = (unsigned)__shfl_xor((int)w[k], M, 64);
   }
   double o;
   __builtin_memcpy(&o, w, 8);
@@ -43,21 +41,21 @@ __device__ __forceinline__ double lane_partner(double v) {
 // Sum (maximum) over the team of T lanes, the same bits in every lane.
 template <int T>
 __device__ __forceinline__ double team_sum(double v) {
-  if constexpr (T >= 2) v += lane_partner<1>(v);
-  if constexpr (T >= 4) v += lane_partner<2>(v);
-  if constexpr (T >= 8) v += lane_partner<4>(v);
-  if constexpr (T >= 16) v += lane_partner<8>(v);
-  if constexpr (T >= 32) v += lane_partner<16>(v);
-  if constexpr (T >= 64) v += lane_partner<32>(v);
+  if constexpr (T >= 64) v += lane_partner<32, T>(v);
+  if constexpr (T >= 32) v += lane_partner<16, T>(v);
+  if constexpr (T >= 16) v += lane_partner<8, T>(v);
+  if constexpr (T >= 8) v += lane_partner<4, T>(v);
+  if constexpr (T >= 4) v += lane_partner<2, T>(v);
+  if constexpr (T >= 2) v += lane_partner<1, T>(v);
   return v;
 }
 __device__ __forceinline__ double wave_max(double v) {
-  v = fmax(v, lane_partner<1>(v));
-  v = fmax(v, lane_partner<2>(v));
-  v = fmax(v, lane_partner<4>(v));
-  v = fmax(v, lane_partner<8>(v));
-  v = fmax(v, lane_partner<16>(v));
-  return fmax(v, lane_partner<32>(v));
+  v = fmax(v, lane_partner<32, 64>(v));
+  v = fmax(v, lane_partner<16, 64>(v));
+  v = fmax(v, lane_partner<8, 64>(v));
+  v = fmax(v, lane_partner<4, 64>(v));
+  v = fmax(v, lane_partner<2, 64>(v));
+  return fmax(v, lane_partner<1, 64>(v));
 }
 
 template <typename S>
