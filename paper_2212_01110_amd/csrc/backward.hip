@@ -147,6 +147,266 @@ __global__ void __launch_bounds__(256) k_adj_load(long long nv, int nx, int nu, 
   }
 }
 
+// J_G d on a translated SOC block held in registers (soc_jg_wave's formulas):
+// vector part bv, dv in two components per lane (zero past the end), the
+// scalars ba, bb of b* and da, dt of d in every lane; results in place of dv,
+// da, dt.
+template <typename S>
+__device__ __forceinline__ void soc_jg_regs(const S (&bv)[2], S (&dv)[2], S ba, S bb, S& da, S& dt, S al) {
+  const S ia = S(1) / al;
+  double r2p = 0;
+#pragma unroll
+  for (int s = 0; s < 2; ++s) r2p += (double)(bv[s] * ia) * (double)(bv[s] * ia);
+  const S va = ba * ia - S(0.5);
+  const S t = bb * ia + S(0.5);
+  const S r = (S)sqrt(team_sum<64>(r2p) + (double)va * (double)va);
+  if (r <= t) {  // inside the cone: J_G = 0
+    dv[0] = dv[1] = da = dt = S(0);
+    return;
+  }
+  if (r <= -t) return;  // polar cone: J_G = I
+  const S ir = S(1) / r;
+  double xdp = 0;
+#pragma unroll
+  for (int s = 0; s < 2; ++s) xdp += (double)(bv[s] * ia * ir) * (double)dv[s];
+  const double xd = team_sum<64>(xdp) + (double)(va * ir) * (double)da;
+  const S tr = t * ir;
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    const S xh = bv[s] * ia * ir;
+    dv[s] -= S(0.5) * ((S(1) + tr) * dv[s] - tr * xh * (S)xd + xh * dt);
+  }
+  const S xh = va * ir;
+  const S ja = S(0.5) * ((S(1) + tr) * da - tr * xh * (S)xd + xh * dt);
+  const S jt = S(0.5) * ((S)xd + dt);
+  da -= ja;
+  dt -= jt;
+}
+
+// First half of an application of the transposed operator, up to the sweeps:
+//   lb = J_G(b*) w_eta,  tz = L* lb,  cz = w_z + 2 alpha tz,
+// then the pre-pass of J_f cz (zero dual part): xbar, ubar = cz on (x, u), q =
+// -cz_x at leaves, the S2 projection of the (y, tau, s) blocks into la, and
+// la's s^0 = cz's (the identity there). One wavefront per family and instance:
+// every row of lb and column of tz it needs is its own, but for s of a nonleaf
+// child, whose one row (the child's s-row) it computes again. One launch in
+// place of five (J_G, L*, the combination, the pre-pass, the s^0 copy), which
+// took 26 us per application on the 95-node tree in FP64. n <= 64 children.
+// Arrays of instance b: w at + b ws, the others at + b is.
+template <typename S>
+__global__ void __launch_bounds__(256) k_adj_front(DevProb<S> P, const long long* __restrict__ spos,
+                                                   const S* __restrict__ bs, const S* __restrict__ w, long long ws,
+                                                   S* __restrict__ lb, S* __restrict__ tz, S* __restrict__ cz,
+                                                   S* __restrict__ la, S* __restrict__ xbar, S* __restrict__ ubar,
+                                                   S* __restrict__ q, long long is) {
+  const size_t inst = blockIdx.y;
+  const int nx = P.nx, nu = P.nu, K = nx + nu;
+  bs += inst * is;
+  const S* wz = w + inst * ws;
+  const S* we = wz + P.nz;
+  lb += inst * is;
+  tz += inst * is;
+  cz += inst * is;
+  la += inst * is;
+  xbar += inst * (size_t)P.nn * nx;
+  q += inst * (size_t)P.nn * nx;
+  ubar += inst * (size_t)P.nn * nu;
+  const int lane = threadIdx.x & 63;
+  const Off<S> O(P);
+  const S al = P.alpha, ia = S(1) / al, al2 = S(2) * al;
+  const int i = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (i >= P.nl) return;
+  const int fc = P.fc[i], n = P.nch[i];
+  const long long e1 = O.e1(i), e1s = e1 + 2LL * n + 1, zb = O.z2(i);
+  const bool leaf = fc >= P.nl;
+  auto put = [&](long long e, S t) {  // one column: tz, cz; returns cz
+    const S c = wz[e] + al2 * t;
+    tz[e] = t;
+    cz[e] = c;
+    return c;
+  };
+  // ---- group 1: the s-row and the y rows (lane k: y1, y2 of child k)
+  const S res = bs[e1s] <= S(0) ? we[e1s] : S(0);
+  S y1 = 0, y2 = 0, th = 0, sh = 0;
+  if (lane < n) {
+    const S l1 = bs[e1 + lane] <= S(0) ? we[e1 + lane] : S(0);
+    const S l2 = bs[e1 + n + lane] <= S(0) ? we[e1 + n + lane] : S(0);
+    lb[e1 + lane] = l1;
+    lb[e1 + n + lane] = l2;
+    y1 = put(zb + lane, l1 - P.p[fc + lane] * res);
+    y2 = put(zb + n + lane, l2);
+    if (!leaf) {  // s of child `lane`: its s-row, owned (and stored) by that child's family
+      const long long ec = O.e1s(fc + lane);
+      sh = wz[zb + 3LL * n + 1 + lane] + al2 * (bs[ec] <= S(0) ? we[ec] : S(0));
+    }
+  }
+  const S y3 = wz[zb + 2 * n] + al2 * (S(0) - res);
+  if (lane == 0) {
+    lb[e1 + 2 * n] = S(0);  // the free entry
+    lb[e1s] = res;
+    put(zb + 2 * n, S(0) - res);
+    const S c = put(spos[i], res);
+    if (i == 0) la[0] = c;
+  }
+  // ---- the box rows (x, u) of group 1 and the columns x^i, u^i
+  bool on[2];
+  S acc[2];
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    const int k = lane + 64 * s;
+    on[s] = k < K;
+    acc[s] = 0;
+    if (!on[s]) continue;
+    const long long e = e1s + 1 + k;
+    const size_t bi = k < nx ? (size_t)i * nx + k : (size_t)i * nu + (k - nx);
+    const S v = bs[e] * ia;
+    const bool in = v > (k < nx ? P.xlo : P.ulo)[bi] && v < (k < nx ? P.xhi : P.uhi)[bi];
+    acc[s] = in ? S(0) : we[e];
+    lb[e] = acc[s];
+  }
+  // ---- group 2 of every child, group 3 of leaf children
+  for (int c = fc; c < fc + n; ++c) {
+    const long long e2 = O.e2(c);
+    S bv[2], dv[2], sc[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const int k = lane + 64 * s;
+      bv[s] = on[s] ? bs[e2 + k] : S(0);
+      dv[s] = on[s] ? we[e2 + k] : S(0);
+      sc[s] = !on[s] ? S(0) : (k < nx ? P.sq[(size_t)c * nx + k] : P.sr[(size_t)c * nu + (k - nx)]);
+    }
+    S da = we[e2 + K], dt = we[e2 + K + 1];
+    soc_jg_regs<S>(bv, dv, bs[e2 + K], bs[e2 + K + 1], da, dt, al);
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+      if (on[s]) {
+        lb[e2 + lane + 64 * s] = dv[s];
+        acc[s] += sc[s] * dv[s];
+      }
+    if (lane == 0) {
+      lb[e2 + K] = da;
+      lb[e2 + K + 1] = dt;
+    }
+    if (lane == c - fc) th = put(zb + 2LL * n + 1 + (c - fc), S(0.5) * (da + dt));
+    if (!leaf) continue;
+    const long long e3 = O.e3(c);
+    const bool ox = lane < nx;
+    S lx = 0, sq = 0;
+    S b3[2] = {S(0), S(0)}, d3[2] = {S(0), S(0)};
+    if (ox) {
+      const S v = bs[e3 + lane] * ia;
+      const size_t bi = (size_t)c * nx + lane;
+      lx = v > P.xlo[bi] && v < P.xhi[bi] ? S(0) : we[e3 + lane];
+      sq = P.sqN[bi];
+      b3[0] = bs[e3 + nx + lane];
+      d3[0] = we[e3 + nx + lane];
+    }
+    S ea = we[e3 + 2 * nx], eb = we[e3 + 2 * nx + 1];
+    soc_jg_regs<S>(b3, d3, bs[e3 + 2 * nx], bs[e3 + 2 * nx + 1], ea, eb, al);
+    if (ox) {
+      lb[e3 + lane] = lx;
+      lb[e3 + nx + lane] = d3[0];
+      q[(size_t)c * nx + lane] = -put(O.x(c) + lane, lx + sq * d3[0]);
+    }
+    if (lane == 0) {
+      lb[e3 + 2 * nx] = ea;
+      lb[e3 + 2 * nx + 1] = eb;
+    }
+    if (lane == c - fc) sh = put(zb + 3LL * n + 1 + (c - fc), S(0.5) * (ea + eb));
+  }
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    const int k = lane + 64 * s;
+    if (!on[s]) continue;
+    if (k < nx) xbar[(size_t)i * nx + k] = put(O.x(i) + k, acc[s]);
+    else ubar[(size_t)i * nu + (k - nx)] = put(O.u(i) + (k - nx), acc[s]);
+  }
+  // ---- S2 projection of the (y, tau, s) block (closed form, as the pre-pass)
+  const S a = P.a[i], cc = a * a + S(3);
+  const S g = a * y1 - y2 + y3 - th - sh;
+  const S corr = (S)team_sum<64>(lane < n ? (double)g : 0.0) / (cc + S(n));
+  const S pr = (g - corr) / cc;
+  const S Ws = (S)team_sum<64>(lane < n ? (double)pr : 0.0);
+  if (lane < n) {
+    la[zb + lane] = y1 - a * pr;
+    la[zb + n + lane] = y2 + pr;
+    la[zb + 2LL * n + 1 + lane] = th + pr;
+    la[zb + 3LL * n + 1 + lane] = sh + pr;
+  }
+  if (lane == 0) la[zb + 2 * n] = y3 - Ws;
+}
+
+// Second half: out = a v + s (J_T' w) + c g with J_T' w = (la - alpha tz, lb -
+// alpha L la): A(w) = J_T' w + g with (a, s, c) = (0, 1, 1), the next Krylov
+// vector v - J_T' v (the cotangent cancels) with (1, -1, 0). Wavefronts run
+// over the z entries first, then a family (or more) each for the rows of L la.
+// One launch in place of four (L, three combinations). Bound by the latency of
+// its loads.
+template <typename S>
+__global__ void __launch_bounds__(256) k_adj_back(DevProb<S> P, double a, const S* __restrict__ v, long long vs,
+                                                  double sg, const S* __restrict__ la, const S* __restrict__ tz,
+                                                  const S* __restrict__ lb, double cg, const S* __restrict__ g,
+                                                  S* __restrict__ out, long long os, long long is) {
+  const size_t inst = blockIdx.y;
+  v += inst * vs;
+  out += inst * os;
+  la += inst * is;
+  tz += inst * is;
+  lb += inst * is;
+  g += inst * is;
+  const int lane = threadIdx.x & 63;
+  const Off<S> O(P);
+  const int nx = P.nx, nu = P.nu, K = nx + nu;
+  const double al = (double)P.alpha;
+  auto put = [&](long long e, double j) {
+    double r = sg * j;
+    if (a != 0.0) r += a * (double)v[e];
+    if (cg != 0.0) r += cg * (double)g[e];
+    out[e] = (S)r;
+  };
+  for (long long e = blockIdx.x * 256LL + threadIdx.x; e < P.nz; e += gridDim.x * 256LL)
+    put(e, (double)la[e] - al * (double)tz[e]);
+  const long long nz = P.nz;
+  auto row = [&](long long e, S Ll) { put(nz + e, (double)lb[e] - al * (double)Ll); };
+  for (int i = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); i < P.nl; i += gridDim.x * 4) {
+    const int fc = P.fc[i], n = P.nch[i];
+    const long long zb = O.z2(i), e1 = O.e1(i), e1x = e1 + 2LL * n + 2;
+    double by = 0;
+    for (int k = lane; k < 2 * n + 1; k += 64) {
+      const S y = la[zb + k];
+      row(e1 + k, y);
+      if (k < n) by += (double)(P.p[fc + k] * y);
+    }
+    by = team_sum<64>(by) + (double)la[zb + 2 * n];
+    if (lane == 0) row(e1 + 2 * n + 1, la[O.s(i)] - (S)by);
+    S xu[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const int k = lane + 64 * s;
+      xu[s] = k < K ? la[k < nx ? O.x(i) + k : O.u(i) + (k - nx)] : S(0);
+      if (k < K) row(e1x + k, xu[s]);
+    }
+    for (int c = fc; c < fc + n; ++c) {
+      const long long e2 = O.e2(c);
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const int k = lane + 64 * s;
+        if (k < K) row(e2 + k, (k < nx ? P.sq[(size_t)c * nx + k] : P.sr[(size_t)c * nu + (k - nx)]) * xu[s]);
+      }
+      if (lane < 2) row(e2 + K + lane, S(0.5) * la[zb + 2LL * n + 1 + (c - fc)]);
+      if (c >= P.nl) {
+        const long long e3 = O.e3(c);
+        if (lane < nx) {
+          const S xc = la[O.x(c) + lane];
+          row(e3 + lane, xc);
+          row(e3 + nx + lane, P.sqN[(size_t)c * nx + lane] * xc);
+        }
+        if (lane < 2) row(e3 + 2 * nx + lane, S(0.5) * la[zb + 3LL * n + 1 + (c - fc)]);
+      }
+    }
+  }
+}
+
 // Transpose of the root-state map Phi of the S1 projection, one stage per
 // launch (stage N-1 .. 0) for every instance: mu^j = c_x^j at leaves, mu^i =
 // c_x^i + K^i' c_u^i + sum_c Abar^c' mu^c; mu^0 is the gradient with respect
@@ -289,6 +549,25 @@ hipError_t launch_adj_load(const Problem& P, double gV, const AdjPtrs<S>* tab, l
   return hipGetLastError();
 }
 template <typename S>
+hipError_t launch_adj_front(const Problem& P, const S* bs, const S* w, long long ws, S* lb, S* tz, S* cz, S* la,
+                            S* xbar, S* ubar, S* q, long long is, int B, hipStream_t st) {
+  const DevProb<S>& D = (sizeof(S) == 8) ? *reinterpret_cast<const DevProb<S>*>(&P.dp64)
+                                         : *reinterpret_cast<const DevProb<S>*>(&P.dp32);
+  hipLaunchKernelGGL(k_adj_front<S>, dim3((P.tree->nl + 3) / 4, B), dim3(256), 0, st, D, P.d_spos, bs, w, ws, lb, tz,
+                     cz, la, xbar, ubar, q, is);
+  return hipGetLastError();
+}
+template <typename S>
+hipError_t launch_adj_back(const Problem& P, double a, const S* v, long long vs, double sg, const S* la, const S* tz,
+                           const S* lb, double cg, const S* g, S* out, long long os, long long is, int B,
+                           hipStream_t st) {
+  const DevProb<S>& D = (sizeof(S) == 8) ? *reinterpret_cast<const DevProb<S>*>(&P.dp64)
+                                         : *reinterpret_cast<const DevProb<S>*>(&P.dp32);
+  hipLaunchKernelGGL(k_adj_back<S>, dim3(family_wave_blocks(P.tree->nl), B), dim3(256), 0, st, D, a, v, vs, sg, la, tz,
+                     lb, cg, g, out, os, is);
+  return hipGetLastError();
+}
+template <typename S>
 hipError_t launch_phiT(const Problem& P, const S* cz, long long is, S* mu, long long ms, int B,
                        const AdjPtrs<S>* tab, hipStream_t st) {
   const DevProb<S>& D = (sizeof(S) == 8) ? *reinterpret_cast<const DevProb<S>*>(&P.dp64)
@@ -318,6 +597,10 @@ hipError_t launch_maxdiff(long long n, const S* a, const S* b, double* partials,
 }
 
 #define SPK_BINST(S)                                                                                  \
+  template hipError_t launch_adj_front<S>(const Problem&, const S*, const S*, long long, S*, S*, S*, S*, S*, S*, S*, \
+                                          long long, int, hipStream_t);                               \
+  template hipError_t launch_adj_back<S>(const Problem&, double, const S*, long long, double, const S*, const S*,    \
+                                         const S*, double, const S*, S*, long long, long long, int, hipStream_t);    \
   template hipError_t launch_copy_elem<S>(S*, const S*, hipStream_t);                                 \
   template hipError_t launch_jg<S>(const Problem&, const S*, const S*, S*, hipStream_t);              \
   template hipError_t launch_jg_batch<S>(const Problem&, const S*, const S*, S*, long long, int, hipStream_t); \

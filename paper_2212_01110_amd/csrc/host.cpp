@@ -2031,7 +2031,6 @@ int backward_once(Problem& P, const S* vstar, const double* x0, double gV, const
   S* cz = W.pool[8];
   S* la = W.pool[9];
   S* tz = W.pool[10];
-  S* te = W.pool[11];
   // pre-prox point of the dual update at v*: b* = eta* + alpha L (2 z+ - z*)
   HIP_TRY(launch_T<S>(P, vstar, Tv, x0, W.q, W.d, W.xbar, W.ubar, W.partials, W.stats, st, W.eta_zero, true));
   HIP_TRY(launch_lincomb<S>(nz, dz, 2.0, Tv, -1.0, vstar, st));
@@ -2047,8 +2046,16 @@ int backward_once(Problem& P, const S* vstar, const double* x0, double gV, const
   HIP_TRY(launch_fill<S>(nv, zeros, 0.0, st));
   HIP_TRY(hipMemsetAsync(W.x0_zero, 0, sizeof(double) * kMaxDim, st));
   HIP_TRY(launch_fill<S>(ne, W.eta_zero, 0.0, st));
+  int maxch = 1;
+  for (int i = 0; i < T.nl; ++i) maxch = std::max(maxch, T.nch[i]);
+  const bool fused = maxch <= kAdjMaxCh;
   // one application of the transposed operator: writes lb, tz, cz, la
   auto partial = [&](const S* wv) -> int {
+    if (fused) {
+      HIP_TRY(launch_adj_front<S>(P, b, wv, 0, lb, tz, cz, la, W.xbar, W.ubar, W.q, 0, 1, st));
+      HIP_TRY(launch_sweeps<S>(P, la, W.x0_zero, W.q, W.d, W.xbar, W.ubar, st));
+      return SPOCK_OK;
+    }
     HIP_TRY(launch_jg<S>(P, b, wv + nz, lb, st));                  // lambda_b = J_G w_eta
     HIP_TRY(launch_Lt<S>(P, lb, tz, st));                          // L* lambda_b
     HIP_TRY(launch_lincomb<S>(nz, cz, 1.0, wv, 2.0 * al, tz, st)); // c = w_z + 2 alpha L* lambda_b
@@ -2066,9 +2073,7 @@ int backward_once(Problem& P, const S* vstar, const double* x0, double gV, const
   // dual part, and the cotangent
   auto apply_A = [&](const S* wv, S* out) -> int {
     if (int r = partial(wv)) return r;
-    HIP_TRY(launch_L<S>(P, la, te, st));
-    HIP_TRY(launch_lincomb3<S>(nz, out, 1.0, la, -al, tz, 1.0, g, st));
-    HIP_TRY(launch_lincomb3<S>(ne, out + nz, 1.0, lb, -al, te, 1.0, g + nz, st));
+    HIP_TRY(launch_adj_back<S>(P, 0.0, wv, 0, 1.0, la, tz, lb, 1.0, g, out, 0, 0, 1, st));
     return SPOCK_OK;
   };
   // The fixed point of the affine map solves (I - J_T') w = g: restarted
@@ -2222,11 +2227,11 @@ int backward_once(Problem& P, const S* vstar, const double* x0, double gV, const
     int j = 0;
     bool done = false;
     for (; j < kAdjRestart && k < s.max_iters; ++j) {
-      // V_{j+1} <- M V_j = V_j - A(V_j) + g, then two Gram-Schmidt passes
+      // V_{j+1} <- M V_j = V_j - J_T' V_j, then two Gram-Schmidt passes
       // and the normalisation, all on the device
-      if (int r = apply_A(V(j), Aw)) return r;
+      if (int r = partial(V(j))) return r;
       ++k;
-      HIP_TRY(launch_lincomb3<S>(nv, V(j + 1), 1.0, V(j), -1.0, Aw, 1.0, g, st));
+      HIP_TRY(launch_adj_back<S>(P, 1.0, V(j), 0, -1.0, la, tz, lb, 0.0, g, V(j + 1), 0, 0, 1, st));
       double* slot = hp_dev + (size_t)(j & 1) * 2 * (kAdjMax + 2);
       HIP_TRY(launch_basis_dots<S>(nv, j + 1, basis, nv, V(j + 1), false, dots_part, d1, st, slot));
       HIP_TRY(launch_basis_orth<S>(nv, j + 1, basis, nv, d1, false, V(j + 1), st));

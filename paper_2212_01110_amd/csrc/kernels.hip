@@ -718,12 +718,32 @@ int post_blocks(const Problem& P) {
 }
 
 template <typename S>
+hipError_t launch_sweeps(const Problem& P, S* zout, const double* x0, S* q, S* d, S* xbar, S* ubar, hipStream_t st,
+                         SweepMap map) {
+  const DevProb<S>& D = dev_of<S>(P);
+  const int team = map.team > 0 ? map.team : P.team;
+  const int cut = map.team > 0 ? map.cut : P.cut;
+  switch (team) {
+    case kTeamFlow: return launch_sweeps_flow<S>(P, D, zout, x0, xbar, ubar, q, d, st);
+    case 8: launch_sweeps_team<S, 8>(P, D, zout, x0, xbar, ubar, q, d, st); break;
+    case 16: launch_sweeps_team<S, 16>(P, D, zout, x0, xbar, ubar, q, d, st); break;
+    case 32: launch_sweeps_team<S, 32>(P, D, zout, x0, xbar, ubar, q, d, st); break;
+    case 64: launch_sweeps_team<S, 64>(P, D, zout, x0, xbar, ubar, q, d, st); break;
+    default: launch_sweeps_wg<S>(P, D, zout, x0, xbar, ubar, q, d, st, cut); break;
+  }
+  return hipGetLastError();
+}
+template hipError_t launch_sweeps<double>(const Problem&, double*, const double*, double*, double*, double*, double*,
+                                          hipStream_t, SweepMap);
+template hipError_t launch_sweeps<float>(const Problem&, float*, const double*, float*, float*, float*, float*,
+                                         hipStream_t, SweepMap);
+
+template <typename S>
 hipError_t launch_T(const Problem& P, const S* v, S* Tv, const double* x0, S* q, S* d, S* xbar,
                     S* ubar, double* partials, double* stats_dev, hipStream_t st,
                     const S* eta_zero, bool dual, Publish pub, SweepMap map) {
   const DevProb<S>& D = dev_of<S>(P);
   const int team = map.team > 0 ? map.team : P.team;
-  const int cut = map.team > 0 ? map.cut : P.cut;
   const S* z = v;
   const S* eta = dual ? v + P.nz : eta_zero;
   S* zout = Tv;
@@ -744,17 +764,9 @@ hipError_t launch_T(const Problem& P, const S* v, S* Tv, const double* x0, S* q,
     }
   }
   mark(1);
-  switch (team) {
-    case kTeamFlow: {
-      const hipError_t e = launch_sweeps_flow<S>(P, D, zout, x0, xbar, ubar, q, d, st);
-      if (e != hipSuccess) return e;
-      break;
-    }
-    case 8: launch_sweeps_team<S, 8>(P, D, zout, x0, xbar, ubar, q, d, st); break;
-    case 16: launch_sweeps_team<S, 16>(P, D, zout, x0, xbar, ubar, q, d, st); break;
-    case 32: launch_sweeps_team<S, 32>(P, D, zout, x0, xbar, ubar, q, d, st); break;
-    case 64: launch_sweeps_team<S, 64>(P, D, zout, x0, xbar, ubar, q, d, st); break;
-    default: launch_sweeps_wg<S>(P, D, zout, x0, xbar, ubar, q, d, st, cut); break;
+  {
+    const hipError_t e = launch_sweeps<S>(P, zout, x0, q, d, xbar, ubar, st, map);
+    if (e != hipSuccess) return e;
   }
   mark(2);
   if (dual) {

@@ -1122,7 +1122,8 @@ __global__ void __launch_bounds__(1024) k_bmaxdiff(long long n, const S* __restr
 // Krylov basis of instance b at basis + b * bs (vector j at + j * vs), its
 // vector x at x + b * xs. k_bdots: block (c, j, b) sums chunk c of <V_j, x>
 // (j < n; <x, x> for j = n) into part[(b * m + j) * cb + c], m = gridDim.y;
-// k_bdots_final (block b) adds the chunks in order into out[b * ldo + j].
+// k_bdots_final (block b) adds the chunks in order into out[b * ldo + j], and
+// into host (mapped pinned memory) too when given.
 template <typename S>
 __global__ void __launch_bounds__(256) k_bdots(long long nv, int n, const S* __restrict__ basis, long long bs,
                                                long long vs, const S* __restrict__ x, long long xs,
@@ -1145,12 +1146,13 @@ __global__ void __launch_bounds__(256) k_bdots(long long nv, int n, const S* __r
     part[((size_t)b * m + j) * gridDim.x + blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
 }
 __global__ void __launch_bounds__(256) k_bdots_final(const double* __restrict__ part, int cb, int m,
-                                                     double* __restrict__ out, int ldo) {
+                                                     double* __restrict__ out, int ldo, double* __restrict__ host) {
   const size_t b = blockIdx.x;
   for (int j = threadIdx.x; j < m; j += blockDim.x) {
     double acc = 0;
     for (int c = 0; c < cb; ++c) acc += part[((size_t)b * m + j) * cb + c];
     out[b * ldo + j] = acc;
+    if (host) host[b * ldo + j] = acc;
   }
 }
 // x_b += sgn sum_{j < n} c_b[j] V_j (c_b = c + b * ldc, device); with norm,
@@ -1195,9 +1197,9 @@ int shared_backward(Problem& P, int B, const void* const* vstar, const double* c
   const long long bs = (long long)(R + 1) * vs;  // basis stride between instances
   const int cb = std::max(1, std::min(64, (int)((nv + 8191) / 8192)));
   const int ldc = kMax + 2;
-  // ---- device memory: 14 batch vectors, the bases, sweep buffers, x0s,
+  // ---- device memory: 13 batch vectors, the bases, sweep buffers, x0s,
   // coefficients and partial sums
-  enum { kV, kTv, kDz, kLdz, kB, kG, kW, kAw, kLb, kCz, kLa, kTz, kTe, kIn, kNVec };
+  enum { kV, kTv, kDz, kLdz, kB, kG, kW, kAw, kLb, kCz, kLa, kTz, kIn, kNVec };
   const size_t nvec = (size_t)Bp * vs;
   size_t off = 0;
   auto reserve = [&](size_t bytes) {
@@ -1270,27 +1272,32 @@ int shared_backward(Problem& P, int B, const void* const* vstar, const double* c
   if (int r = lin3(nz, op(kDz), 2.0, op(kTv), -1.0, op(kV))) return r;
   SH_TRY(launch_L_batch<S>(P, vec[kDz], vec[kLdz], vs, Bp, st));
   if (int r = lin3(ne, op(kB), 1.0, op(kV, nz), al, op(kLdz))) return r;
-  // one application of the transposed operator to vec[kIn]: lb, tz, cz, la
-  auto partial = [&](int in) -> int {
-    SH_TRY(launch_jg_batch<S>(P, vec[kB], vec[in] + nz, vec[kLb], vs, Bp, st));  // lambda_b = J_G w_eta
-    SH_TRY(launch_Lt_batch<S>(P, vec[kLb], vec[kTz], vs, Bp, st));              // L* lambda_b
-    if (int r = lin3(nz, op(kCz), 1.0, op(in), 2.0 * al, op(kTz))) return r;    // w_z + 2 alpha L* lambda_b
-    if (int r = prox(vec[kCz], vec[kLa], x0zero)) return r;                      // J_f c (zero dual part)
-    if (int r = lin3(1, op(kLa), 1.0, op(kCz))) return r;                        // identity on s^0
+  // one application of the transposed operator to w (instances ws apart): lb, tz, cz, la
+  const bool fused = plan.maxch <= kAdjMaxCh;
+  auto partial = [&](const S* w, long long ws) -> int {
+    if (fused) {
+      SH_TRY(launch_adj_front<S>(P, vec[kB], w, ws, vec[kLb], vec[kTz], vec[kCz], vec[kLa], xbar, ubar, q, vs, Bp, st));
+      SH_TRY(sh_launch_sweeps<S>(P, D, plan, vec[kLa], x0zero, xbar, ubar, q, d, vs, Bp, st));
+      return SPOCK_OK;
+    }
+    if (w != vec[kIn])
+      SH_TRY(hipMemcpy2DAsync(vec[kIn], sizeof(S) * vs, w, sizeof(S) * ws, sizeof(S) * nv, Bp, hipMemcpyDeviceToDevice, st));
+    SH_TRY(launch_jg_batch<S>(P, vec[kB], vec[kIn] + nz, vec[kLb], vs, Bp, st));  // lambda_b = J_G w_eta
+    SH_TRY(launch_Lt_batch<S>(P, vec[kLb], vec[kTz], vs, Bp, st));                // L* lambda_b
+    if (int r = lin3(nz, op(kCz), 1.0, op(kIn), 2.0 * al, op(kTz))) return r;     // w_z + 2 alpha L* lambda_b
+    if (int r = prox(vec[kCz], vec[kLa], x0zero)) return r;                       // J_f c (zero dual part)
+    if (int r = lin3(1, op(kLa), 1.0, op(kCz))) return r;                         // identity on s^0
     return SPOCK_OK;
   };
-  // A(w) = J_T(v*)' w + g into vec[kAw]
-  auto apply_A = [&](int in) -> int {
-    if (int r = partial(in)) return r;
-    SH_TRY(launch_L_batch<S>(P, vec[kLa], vec[kTe], vs, Bp, st));
-    if (int r = lin3(nz, op(kAw), 1.0, op(kLa), -al, op(kTz), 1.0, op(kG))) return r;
-    if (int r = lin3(ne, op(kAw, nz), 1.0, op(kLb), -al, op(kTe), 1.0, op(kG, nz))) return r;
+  // out = a w + sg J_T(v*)' w + cg g after partial(w)
+  auto back = [&](double a, const S* w, long long ws, double sg, double cg, S* out, long long os) -> int {
+    SH_TRY(launch_adj_back<S>(P, a, w, ws, sg, vec[kLa], vec[kTz], vec[kLb], cg, vec[kG], out, os, vs, Bp, st));
     return SPOCK_OK;
   };
-  auto bdots = [&](int n, const S* x, long long xs, bool xx, double* out) -> int {
+  auto bdots = [&](int n, const S* x, long long xs, bool xx, double* out, double* hout = nullptr) -> int {
     const int m = n + (xx ? 1 : 0);
     hipLaunchKernelGGL(k_bdots<S>, dim3(cb, m, Bp), dim3(256), 0, st, nv, n, basis, bs, vs, x, xs, part);
-    hipLaunchKernelGGL(k_bdots_final, dim3(Bp), dim3(256), 0, st, part, cb, m, out, ldc);
+    hipLaunchKernelGGL(k_bdots_final, dim3(Bp), dim3(256), 0, st, part, cb, m, out, ldc, hout);
     SH_TRY(hipGetLastError());
     return SPOCK_OK;
   };
@@ -1305,7 +1312,29 @@ int shared_backward(Problem& P, int B, const void* const* vstar, const double* c
   const double tol = std::max(s.eps_abs, 1e-15);
   std::vector<int> kk(B, 0), state(B, 0);  // state: 0 running, 1 converged, 2 numerical, 3 max_iters
   std::vector<double> diff(B, 0.0);
-  std::vector<double> hmd((size_t)Bp * 2), hc1((size_t)Bp * ldc), hc2((size_t)Bp * ldc), hcm((size_t)Bp * ldc);
+  std::vector<double> hmd((size_t)Bp * 2), hc1((size_t)Bp * ldc), hcm((size_t)Bp * ldc);
+  // the Gram-Schmidt coefficients on the host: [2 slots][2 passes][Bp][ldc]
+  double* hp = nullptr;
+  if (hipHostMalloc(reinterpret_cast<void**>(&hp), sizeof(double) * 4 * (size_t)Bp * ldc,
+                    hipHostMallocCoherent | hipHostMallocMapped) != hipSuccess)
+    return SPOCK_ENOMEM;
+  hipEvent_t evs[2] = {nullptr, nullptr};
+  struct PipeGuard {
+    double* hp;
+    hipEvent_t* ev;
+    hipStream_t st;
+    ~PipeGuard() {
+      (void)hipStreamSynchronize(st);  // an early return: queued kernels write hp
+      for (int e = 0; e < 2; ++e)
+        if (ev[e]) (void)hipEventDestroy(ev[e]);
+      (void)hipHostFree(hp);
+    }
+  } pguard{hp, evs, st};
+  for (int e = 0; e < 2; ++e) SH_TRY(hipEventCreateWithFlags(&evs[e], hipEventDisableTiming));
+  double* hp_dev = nullptr;
+  SH_TRY(hipHostGetDevicePointer(reinterpret_cast<void**>(&hp_dev), hp, 0));
+  auto hslot = [&](int j, int pass) { return hp + ((size_t)(j & 1) * 2 + pass) * (size_t)Bp * ldc; };
+  auto hdev = [&](int j, int pass) { return hp_dev + ((size_t)(j & 1) * 2 + pass) * (size_t)Bp * ldc; };
   std::vector<double> Hm((size_t)B * (kMax + 1) * kMax), cs((size_t)B * kMax), sn((size_t)B * kMax),
       gvv((size_t)B * (kMax + 1));
   std::vector<int> jn(B), incyc(B);
@@ -1316,8 +1345,8 @@ int shared_backward(Problem& P, int B, const void* const* vstar, const double* c
   };
   while (running()) {
     // true residual of every instance at w
-    SH_TRY(hipMemcpyAsync(vec[kIn], vec[kW], sizeof(S) * nvec, hipMemcpyDeviceToDevice, st));
-    if (int r = apply_A(kIn)) return r;
+    if (int r = partial(vec[kW], vs)) return r;
+    if (int r = back(0.0, vec[kW], vs, 1.0, 1.0, vec[kAw], vs)) return r;
     hipLaunchKernelGGL(k_bmaxdiff<S>, dim3(Bp), dim3(1024), 0, st, nv, vec[kW], vec[kAw], vs, md);
     SH_TRY(hipGetLastError());
     SH_TRY(hipMemcpyAsync(hmd.data(), md, sizeof(double) * 2 * Bp, hipMemcpyDeviceToHost, st));
@@ -1350,19 +1379,13 @@ int shared_backward(Problem& P, int B, const void* const* vstar, const double* c
         if (incyc[b]) return true;
       return false;
     };
-    for (int j = 0; j < R && any_in(); ++j) {
-      SH_TRY(hipMemcpy2DAsync(vec[kIn], sizeof(S) * vs, V(j), sizeof(S) * bs, sizeof(S) * nv, Bp,
-                              hipMemcpyDeviceToDevice, st));
-      if (int r = apply_A(kIn)) return r;
-      // V_{j+1} = V_j - A(V_j) + g, two Gram-Schmidt passes, normalisation
-      if (int r = lin3(nv, BOp<S>{V(j + 1), bs, 0}, 1.0, op(kIn), -1.0, op(kAw), 1.0, op(kG))) return r;
-      if (int r = bdots(j + 1, V(j + 1), bs, false, c1)) return r;
-      if (int r = bcomb(j + 1, c1, -1.0, false, V(j + 1), bs)) return r;
-      if (int r = bdots(j + 1, V(j + 1), bs, true, c2)) return r;
-      if (int r = bcomb(j + 1, c2, -1.0, true, V(j + 1), bs)) return r;
-      SH_TRY(hipMemcpyAsync(hc1.data(), c1, sizeof(double) * Bp * ldc, hipMemcpyDeviceToHost, st));
-      SH_TRY(hipMemcpyAsync(hc2.data(), c2, sizeof(double) * Bp * ldc, hipMemcpyDeviceToHost, st));
-      SH_TRY(hipStreamSynchronize(st));
+    // Arnoldi steps are pipelined as in the one-instance form: the passes take
+    // their coefficients from device memory, the reductions also write them to
+    // mapped pinned memory, and the host reduces column j of every instance's
+    // Hessenberg matrix while step j + 1 runs (two slots, alternating). No step
+    // starts that every instance's cap on applications rules out.
+    auto column = [&](int j) -> int {
+      SH_TRY(hipEventSynchronize(evs[j & 1]));
       for (int b = 0; b < B; ++b) {
         if (!incyc[b]) continue;
         ++kk[b];
@@ -1371,8 +1394,8 @@ int shared_backward(Problem& P, int B, const void* const* vstar, const double* c
         double* csb = cs.data() + (size_t)b * kMax;
         double* snb = sn.data() + (size_t)b * kMax;
         double* gv = gvv.data() + (size_t)b * (kMax + 1);
-        const double* h1 = hc1.data() + (size_t)b * ldc;
-        const double* h2 = hc2.data() + (size_t)b * ldc;
+        const double* h1 = hslot(j, 0) + (size_t)b * ldc;
+        const double* h2 = hslot(j, 1) + (size_t)b * ldc;
         double hn = h2[j + 1];
         for (int i = 0; i <= j; ++i) {
           H(i, j) = h1[i] + h2[i];
@@ -1397,7 +1420,27 @@ int shared_backward(Problem& P, int B, const void* const* vstar, const double* c
         if (!std::isfinite(gv[j + 1]) || std::fabs(gv[j + 1]) <= 0.5 * thr || !(hn > 0.0) || kk[b] >= s.max_iters)
           incyc[b] = 0;
       }
+      return SPOCK_OK;
+    };
+    int steps = 0;  // Arnoldi steps of the cycle at most
+    for (int b = 0; b < B; ++b)
+      if (incyc[b]) steps = std::max(steps, std::min(R, s.max_iters - kk[b]));
+    int launched = 0;
+    for (int j = 0; j < steps && any_in(); ++j) {
+      if (int r = partial(V(j), bs)) return r;
+      // V_{j+1} = V_j - J_T' V_j, two Gram-Schmidt passes, normalisation
+      if (int r = back(1.0, V(j), bs, -1.0, 0.0, V(j + 1), bs)) return r;
+      if (int r = bdots(j + 1, V(j + 1), bs, false, c1, hdev(j, 0))) return r;
+      if (int r = bcomb(j + 1, c1, -1.0, false, V(j + 1), bs)) return r;
+      if (int r = bdots(j + 1, V(j + 1), bs, true, c2, hdev(j, 1))) return r;
+      if (int r = bcomb(j + 1, c2, -1.0, true, V(j + 1), bs)) return r;
+      SH_TRY(hipEventRecord(evs[j & 1], st));
+      launched = j + 1;
+      if (j > 0)
+        if (int r = column(j - 1)) return r;
     }
+    if (launched > 0)
+      if (int r = column(launched - 1)) return r;
     // w += V y per instance (H y = g, upper triangular; zero for the others)
     std::fill(hcm.begin(), hcm.end(), 0.0);
     int nmax = 0;
@@ -1418,8 +1461,7 @@ int shared_backward(Problem& P, int B, const void* const* vstar, const double* c
     SH_TRY(hipStreamSynchronize(st));  // hcm is reused
   }
   // gradients from the converged adjoints
-  SH_TRY(hipMemcpyAsync(vec[kIn], vec[kW], sizeof(S) * nvec, hipMemcpyDeviceToDevice, st));
-  if (int r = partial(kIn)) return r;
+  if (int r = partial(vec[kW], vs)) return r;
   SH_TRY(launch_phiT<S>(P, vec[kCz], vs, mu, (long long)Tr.nn * nx, B, tab_d, st));
   if (gq || gqN) SH_TRY(launch_grad_q<S>(P, vec[kV], vec[kLa], vec[kLb], vs, B, tab_d, st));
   for (int b = 0; b < B; ++b) {

@@ -219,6 +219,10 @@ template <typename S>
 hipError_t launch_T(const Problem& P, const S* v, S* Tv, const double* x0, S* q, S* d, S* xbar,
                     S* ubar, double* partials, double* stats_dev, hipStream_t st,
                     const S* eta_zero, bool dual, Publish pub = Publish{}, SweepMap map = SweepMap{});
+// the sweeps alone (prox_f's, after a pre-pass)
+template <typename S>
+hipError_t launch_sweeps(const Problem& P, S* zout, const double* x0, S* q, S* d, S* xbar, S* ubar, hipStream_t st,
+                         SweepMap map = SweepMap{});
 int post_blocks(const Problem& P);
 int flat_post_blocks(const Problem& P);
 int family_wave_blocks(int nl);
@@ -417,6 +421,18 @@ struct AdjPtrs {
 template <typename S>
 hipError_t launch_adj_load(const Problem& P, double gV, const AdjPtrs<S>* tab, long long is, int B, S* v, double* x0s,
                            S* g, S* w, hipStream_t st);
+// The transposed operator around the sweeps (w + b ws; the others + b is):
+// lb = J_G w_eta, tz = L* lb, cz = w_z + 2 alpha tz and the pre-pass of J_f cz
+// into la, xbar, ubar, q; after the sweeps out = a v + sg (la - alpha tz, lb -
+// alpha L la) + cg g. Families of at most kAdjMaxCh children.
+constexpr int kAdjMaxCh = 64;
+template <typename S>
+hipError_t launch_adj_front(const Problem& P, const S* bs, const S* w, long long ws, S* lb, S* tz, S* cz, S* la,
+                            S* xbar, S* ubar, S* q, long long is, int B, hipStream_t st);
+template <typename S>
+hipError_t launch_adj_back(const Problem& P, double a, const S* v, long long vs, double sg, const S* la, const S* tz,
+                           const S* lb, double cg, const S* g, S* out, long long os, long long is, int B,
+                           hipStream_t st);
 // mu: [nn][nx] per instance, ms apart; gx0 written from mu^0
 template <typename S>
 hipError_t launch_phiT(const Problem& P, const S* cz, long long is, S* mu, long long ms, int B,
