@@ -657,16 +657,16 @@ struct Work {
   unsigned* counters = nullptr;       // arrival counts of the push and the rdot [2][kRedCounters]
   unsigned long long* rec = nullptr;  // tagged records of their grid sums [kRedRecWords]
   AARingDev* ring = nullptr;          // Anderson ring (device)
-  unsigned tag = 0;                   // tag of their last launch (never 0 once launched)
-  unsigned next_tag() { return ++tag == 0u ? ++tag : tag; }
+  unsigned* tag = nullptr;            // the problem's tag of their last launch (never 0 once launched)
+  unsigned next_tag() { return ++*tag == 0u ? ++*tag : *tag; }
 };
 
 // Sizes and allocates the state of the dataflow form of the sweeps for
 // precision S: children per LDS chunk (largest count whose LDS stays within
 // the budget, at least one), resident workgroups from the occupancy of the
 // kernel at the register budget occ, and the flags (zeroed once; they are
-// epoch-tagged). The error word is cleared on every call (each API call
-// starts clean).
+// epoch-tagged). The error word starts at zero and is cleared by the call that
+// finds it set (flow_fallback, the autotuner).
 // Test knobs of the dataflow form, read on every sizing call:
 // SPOCK_FLOW_GRID caps the grid (fewer workgroups, each running more items,
 // so small trees also take the multi-item drain), SPOCK_FLOW_SPIN sets the
@@ -691,8 +691,7 @@ int ensure_flow(Problem& P, int occ = 0, int budget = 0) {
   if (const char* env = std::getenv("SPOCK_FLOW_OCC")) occ = std::max(4, std::min(7, std::atoi(env)));
   if (const char* env = std::getenv("SPOCK_FLOW_LDS")) budget = std::max(4096, std::atoi(env));
   if (F.mem && F.elem == (int)sizeof(S) && F.occ == occ && F.budget == budget) {
-    if (hipMemset(F.err, 0, sizeof(unsigned)) != hipSuccess) return SPOCK_EHIP;
-    flow_knobs(F);
+    flow_knobs(F);  // (the error word is zero: whoever reads it set clears it)
     return SPOCK_OK;
   }
   if (F.mem) (void)hipFree(F.mem);
@@ -794,6 +793,7 @@ int ensure_work(Problem& P, Work<S>& W) {
     if (hipMalloc(&P.work, bytes) != hipSuccess) return SPOCK_ENOMEM;
     P.work_bytes = bytes;
     if (hipMemset(P.work, 0, bytes) != hipSuccess) return SPOCK_EHIP;
+    P.red_tag = 0;
   }
   // base-relative offsets, in the same order as the size computation above
   size_t off = 0;
@@ -820,11 +820,10 @@ int ensure_work(Problem& P, Work<S>& W) {
   W.x0_zero = reinterpret_cast<double*>(take(sizeof(double) * kMaxDim));
   for (int k = 0; k < 10 + 2 * kMaxMem; ++k) W.pool[k] = reinterpret_cast<S*>(take(sizeof(S) * (size_t)nv));
   if (off > P.work_bytes) return SPOCK_ENOMEM;
-  // the layout depends on the precision: the counts and the tagged records
-  // (tag 0: never written) start cleared here
-  if (hipMemset(W.counters, 0, sizeof(unsigned) * 2 * kRedCounters) != hipSuccess) return SPOCK_EHIP;
-  if (hipMemset(W.rec, 0, sizeof(unsigned long long) * kRedRecWords) != hipSuccess) return SPOCK_EHIP;
-  W.tag = 0;
+  // the counts and the tagged records (tag 0: never written) start cleared with
+  // the block; the counts return to zero with every launch, and the tags go on
+  // from one call to the next
+  W.tag = &P.red_tag;
   if (!P.mbox) {
     void* hp = nullptr;
     if (hipHostMalloc(&hp, sizeof(Mailbox), hipHostMallocCoherent | hipHostMallocMapped) != hipSuccess)
@@ -990,6 +989,20 @@ int flow_fallback(Problem& P) {
   return SPOCK_OK;
 }
 
+// Polls the mailbox for the epoch; every 4096 polls the stream is asked
+// whether it drained (then the epoch must be there) or failed.
+int wait_mailbox(const Problem& P, unsigned long long epoch, hipStream_t st) {
+  for (unsigned n = 1;; ++n) {
+    if (__atomic_load_n(&P.mbox->flag, __ATOMIC_ACQUIRE) == epoch) return SPOCK_OK;
+    if ((n & 4095u) == 0u) {
+      const hipError_t e = hipStreamQuery(st);
+      if (e == hipSuccess)
+        return __atomic_load_n(&P.mbox->flag, __ATOMIC_ACQUIRE) == epoch ? SPOCK_OK : SPOCK_EHIP;
+      if (e != hipErrorNotReady) return SPOCK_EHIP;
+    }
+  }
+}
+
 struct Stats {
   double xip = 0, xid = 0, om2 = 0, rz2 = 0, re2 = 0, cross = 0;
   double xi() const { return std::max(xip, xid); }
@@ -1028,7 +1041,7 @@ struct Solver {
     return SPOCK_OK;
   }
   int wait(unsigned long long epoch, Stats& out, double* rdot = nullptr) {
-    const int rc = wait_mailbox(epoch);
+    const int rc = wait_mailbox(P, epoch, st);
     if (rc) return rc;
     for (int k = 0; k < 8; ++k) hbuf[k] = P.mbox->v[k];
     if (rdot) *rdot = hbuf[6];
@@ -1046,19 +1059,6 @@ struct Solver {
       if (gave_up) return kFlowGaveUp;
     }
     return SPOCK_OK;
-  }
-  // Polls the mailbox for the epoch; every 4096 polls the stream is asked
-  // whether it drained (then the epoch must be there) or failed.
-  int wait_mailbox(unsigned long long epoch) {
-    for (unsigned n = 1;; ++n) {
-      if (__atomic_load_n(&P.mbox->flag, __ATOMIC_ACQUIRE) == epoch) return SPOCK_OK;
-      if ((n & 4095u) == 0u) {
-        const hipError_t e = hipStreamQuery(st);
-        if (e == hipSuccess)
-          return __atomic_load_n(&P.mbox->flag, __ATOMIC_ACQUIRE) == epoch ? SPOCK_OK : SPOCK_EHIP;
-        if (e != hipErrorNotReady) return SPOCK_EHIP;
-      }
-    }
   }
   int fetch(double* dst, const double* src, int k) {
     HIP_TRY(hipMemcpyAsync(dst, src, k * sizeof(double), hipMemcpyDeviceToHost, st));
@@ -1622,21 +1622,24 @@ extern "C" int spock_prox_gstar(spock_problem* ph, const void* w, void* out, voi
 }
 
 namespace {
-// With the dataflow form, the operator entry points synchronise to read
-// the sweeps' error word; after a give-up they switch the problem to the
-// per-stage form and evaluate again.
+// With the dataflow form, the operator entry points wait for the sweeps' error
+// word; after a give-up they switch the problem to the per-stage form and
+// evaluate again. The word and the statistics come through the mailbox, not by
+// copies and stream synchronisations (two of each and three clears of the
+// workspace per call: 60 us around a T of the 20776-node tree).
 template <typename S>
 int prox_f_impl(Problem& P, const S* zin, const double* x0, S* zout, hipStream_t st) {
   for (int attempt = 0;; ++attempt) {
     Work<S> W;
     int rc = ensure_work<S>(P, W);
     if (rc) return rc;
-    HIP_TRY(launch_fill<S>(P.neta, W.eta_zero, 0.0, st));
     HIP_TRY(launch_T<S>(P, zin, zout, x0, W.q, W.d, W.xbar, W.ubar, W.partials, W.stats, st, W.eta_zero, false));
-    bool gave_up = false;
-    rc = flow_gave_up(P, st, gave_up);
+    if (P.team != kTeamFlow) return SPOCK_OK;
+    const Publish pub{P.mbox_dev, ++P.mbox_epoch};
+    HIP_TRY(launch_publish_word(P.flow.err, pub, st));
+    rc = wait_mailbox(P, pub.epoch, st);
     if (rc) return rc;
-    if (!gave_up) return SPOCK_OK;
+    if (P.mbox->v[0] == 0.0) return SPOCK_OK;
     if (attempt > 0) return SPOCK_EHIP;
     rc = flow_fallback(P);
     if (rc) return rc;
@@ -1647,19 +1650,26 @@ int T_impl(Problem& P, const S* v, const double* x0, S* Tv, double* stats, hipSt
   Work<S> W;
   int rc = ensure_work<S>(P, W);
   if (rc) return rc;
-  HIP_TRY(launch_T<S>(P, v, Tv, x0, W.q, W.d, W.xbar, W.ubar, W.partials, W.stats, st, W.eta_zero, true));
-  bool gave_up = false;
-  rc = flow_gave_up(P, st, gave_up);
+  const bool wait = stats || P.team == kTeamFlow;
+  const Publish pub = wait ? Publish{P.mbox_dev, ++P.mbox_epoch} : Publish{};
+  HIP_TRY(launch_T<S>(P, v, Tv, x0, W.q, W.d, W.xbar, W.ubar, W.partials, W.stats, st, W.eta_zero, true, pub));
+  if (!wait) return SPOCK_OK;
+  rc = wait_mailbox(P, pub.epoch, st);
   if (rc) return rc;
-  if (gave_up) {
-    rc = flow_fallback(P);
+  double r[6];
+  for (int k = 0; k < 6; ++k) r[k] = P.mbox->v[k];
+  if (!(std::isfinite(r[0]) && std::isfinite(r[1]) && std::isfinite(r[2]))) {
+    bool gave_up = false;
+    rc = flow_gave_up(P, st, gave_up);
     if (rc) return rc;
-    return T_impl<S>(P, v, x0, Tv, stats, st);
+    if (gave_up) {
+      rc = flow_fallback(P);
+      if (rc) return rc;
+      return T_impl<S>(P, v, x0, Tv, stats, st);
+    }
   }
-  if (stats) {
-    HIP_TRY(hipMemcpyAsync(stats, W.stats, 6 * sizeof(double), hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
-  }
+  if (stats)
+    for (int k = 0; k < 6; ++k) stats[k] = r[k];
   return SPOCK_OK;
 }
 }  // namespace
@@ -2045,7 +2055,6 @@ int backward_once(Problem& P, const S* vstar, const double* x0, double gV, const
   S* zeros = W.pool[12];
   HIP_TRY(launch_fill<S>(nv, zeros, 0.0, st));
   HIP_TRY(hipMemsetAsync(W.x0_zero, 0, sizeof(double) * kMaxDim, st));
-  HIP_TRY(launch_fill<S>(ne, W.eta_zero, 0.0, st));
   int maxch = 1;
   for (int i = 0; i < T.nl; ++i) maxch = std::max(maxch, T.nch[i]);
   const bool fused = maxch <= kAdjMaxCh;

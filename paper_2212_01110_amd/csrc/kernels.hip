@@ -621,6 +621,16 @@ __global__ void __launch_bounds__(256) k_reduce_stats(const double* __restrict__
   }
 }
 
+__global__ void k_publish_word(const unsigned* __restrict__ word, Publish pub) {
+  double r[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  r[0] = (double)__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  publish_stats(r, pub);
+}
+hipError_t launch_publish_word(const unsigned* word, Publish pub, hipStream_t st) {
+  hipLaunchKernelGGL(k_publish_word, dim3(1), dim3(1), 0, st, word, pub);
+  return hipGetLastError();
+}
+
 // ---------------------------------------------------------------- launch T
 template <typename S>
 static const DevProb<S>& dev_of(const Problem& P);

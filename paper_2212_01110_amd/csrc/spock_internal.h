@@ -204,6 +204,7 @@ struct Problem {
   Mailbox* mbox = nullptr;      // host view (hipHostMalloc, coherent)
   Mailbox* mbox_dev = nullptr;  // device view of the same memory
   unsigned long long mbox_epoch = 0;
+  unsigned red_tag = 0;  // tag of the last grid sum in the workspace's records
 };
 
 // ---------------------------------------------------------------- launchers
@@ -219,6 +220,8 @@ template <typename S>
 hipError_t launch_T(const Problem& P, const S* v, S* Tv, const double* x0, S* q, S* d, S* xbar,
                     S* ubar, double* partials, double* stats_dev, hipStream_t st,
                     const S* eta_zero, bool dual, Publish pub = Publish{}, SweepMap map = SweepMap{});
+// publishes *word (as v[0]) to the mailbox
+hipError_t launch_publish_word(const unsigned* word, Publish pub, hipStream_t st);
 // the sweeps alone (prox_f's, after a pre-pass)
 template <typename S>
 hipError_t launch_sweeps(const Problem& P, S* zout, const double* x0, S* q, S* d, S* xbar, S* ubar, hipStream_t st,
