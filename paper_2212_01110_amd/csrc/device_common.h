@@ -226,6 +226,38 @@ __device__ __forceinline__ void soc_prox(const S* wv, S* outv, int len, S wa, S 
   outb = wb - al * (S(-0.5) + pt);
 }
 
+// prox of g* on a translated SOC block (eq. S3-def, shift (0,..,0,1/2,-1/2))
+// by one wavefront: the vector part in two components per lane (w0 counts if
+// on0, w1 if on1), the two trailing scalars in every lane; out = w - alpha
+// (shift + proj_SOC(w / alpha - shift)).
+template <typename S>
+__device__ __forceinline__ void soc_prox_wave(S& w0, bool on0, S& w1, bool on1, S& wa, S& wb, S al) {
+  const S ia = S(1) / al;
+  const S t0 = w0 * ia, t1 = w1 * ia;
+  double part = 0;
+  if (on0) part += (double)t0 * (double)t0;
+  if (on1) part += (double)t1 * (double)t1;
+  const S va = wa * ia - S(0.5);
+  const S t = wb * ia + S(0.5);
+  const S nrm = (S)sqrt(team_sum<64>(part) + (double)va * (double)va);
+  S scale, pt;
+  if (nrm <= t) {
+    scale = S(1);
+    pt = t;
+  } else if (nrm <= -t) {
+    scale = S(0);
+    pt = S(0);
+  } else {
+    const S cc = S(0.5) * (nrm + t);
+    scale = cc / nrm;
+    pt = cc;
+  }
+  w0 = w0 - al * (scale * t0);
+  w1 = w1 - al * (scale * t1);
+  wa = wa - al * (S(0.5) + scale * va);
+  wb = wb - al * (S(-0.5) + pt);
+}
+
 // ---------------------------------------------------------------- family pieces
 // The functions below run on one team of T lanes (T <= 64, inside one
 // wavefront); lane o owns components o, o+T, ... of node vectors.

@@ -123,38 +123,6 @@ __device__ __forceinline__ S lt_s(const GOff<S>& O, const S* eta, int c) {
   return S(0.5) * (eta[e] + eta[e + 1]);
 }
 
-// prox of g* on a translated SOC block (eq. S3-def, shift (0,..,0,1/2,-1/2))
-// by one wavefront: the vector part in two components per lane (w0 counts if
-// on0, w1 if on1), the two trailing scalars in every lane; out = w - alpha
-// (shift + proj_SOC(w / alpha - shift)).
-template <typename S>
-__device__ __forceinline__ void soc_prox_wave(S& w0, bool on0, S& w1, bool on1, S& wa, S& wb, S al) {
-  const S ia = S(1) / al;
-  const S t0 = w0 * ia, t1 = w1 * ia;
-  double part = 0;
-  if (on0) part += (double)t0 * (double)t0;
-  if (on1) part += (double)t1 * (double)t1;
-  const S va = wa * ia - S(0.5);
-  const S t = wb * ia + S(0.5);
-  const S nrm = (S)sqrt(team_sum<64>(part) + (double)va * (double)va);
-  S scale, pt;
-  if (nrm <= t) {
-    scale = S(1);
-    pt = t;
-  } else if (nrm <= -t) {
-    scale = S(0);
-    pt = S(0);
-  } else {
-    const S cc = S(0.5) * (nrm + t);
-    scale = cc / nrm;
-    pt = cc;
-  }
-  w0 = w0 - al * (scale * t0);
-  w1 = w1 - al * (scale * t1);
-  wa = wa - al * (S(0.5) + scale * va);
-  wb = wb - al * (S(-0.5) + pt);
-}
-
 // prox of g* of one unit for the dual argument at w (rows as in eta), written
 // to out (which may be w): group 1 (K* on y, R_+ on the s-row, C^i on the
 // constraint rows) and group 2 of every child of a family, or group 3 of a

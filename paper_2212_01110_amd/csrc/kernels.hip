@@ -930,55 +930,62 @@ hipError_t launch_M(const Problem& P, const S* d, S* Md, hipStream_t st) {
 template hipError_t launch_M<double>(const Problem&, const double*, double*, hipStream_t);
 template hipError_t launch_M<float>(const Problem&, const float*, float*, hipStream_t);
 
-// prox of g* (test entry point): one thread per family, serial SOC norms.
+// prox of g*, one wavefront per unit: a family (group 1 of i, group 2 of each
+// child) or a leaf (group 3), lane o on component o of a state or input. Every
+// block is read before it is written (out may be w). Bound by the latency of
+// one batch of loads; one thread per family took 66 us on the 2047-node tree
+// (n_x = n_u = 20, FP32), which moves 1.3 MB.
 template <typename S>
-__device__ void soc_prox_serial(const S* w, S* out, int len, S al) {
-  // len counts the vector part; w[len], w[len+1] are the two scalars
-  const S ia = S(1) / al;
-  double n2 = 0;
-  for (int o = 0; o < len; ++o) n2 += (double)(w[o] * ia) * (double)(w[o] * ia);
-  const S va = w[len] * ia - S(0.5);
-  const S t = w[len + 1] * ia + S(0.5);
-  n2 += (double)va * (double)va;
-  const S nrm = (S)sqrt(n2);
-  S scale, pt;
-  if (nrm <= t) { scale = 1; pt = t; }
-  else if (nrm <= -t) { scale = 0; pt = 0; }
-  else { const S cc = S(0.5) * (nrm + t); scale = cc / nrm; pt = cc; }
-  for (int o = 0; o < len; ++o) out[o] = w[o] - al * scale * (w[o] * ia);
-  out[len] = w[len] - al * (S(0.5) + scale * va);
-  out[len + 1] = w[len + 1] - al * (S(-0.5) + pt);
-}
-
-template <typename S>
-__global__ void k_prox_gstar(DevProb<S> P, const S* __restrict__ w, S* __restrict__ out) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= P.nl) return;
+__global__ void __launch_bounds__(256) k_prox_gstar(DevProb<S> P, const S* w, S* out) {
+  const int lane = threadIdx.x & 63;
+  const int i = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (i >= P.nn) return;
   const Off<S> O(P);
-  const int nx = P.nx, nu = P.nu, fc = P.fc[i], n = P.nch[i];
+  const int nx = P.nx, nu = P.nu, K = nx + nu;
   const S al = P.alpha, ia = S(1) / al;
-  const long long e1 = O.e1(i);
-  for (int k = 0; k < 2 * n; ++k) out[e1 + k] = w[e1 + k] < S(0) ? w[e1 + k] : S(0);
-  out[e1 + 2 * n] = S(0);
-  out[e1 + 2 * n + 1] = w[e1 + 2 * n + 1] < S(0) ? w[e1 + 2 * n + 1] : S(0);
-  for (int o = 0; o < nx; ++o) {
-    const S v = w[O.e1x(i) + o];
-    out[O.e1x(i) + o] = v - al * clampv(v * ia, P.xlo[(size_t)i * nx + o], P.xhi[(size_t)i * nx + o]);
+  const bool onx = lane < nx, onu = lane < nu;
+  const size_t bx = (size_t)i * nx + (onx ? lane : 0);
+  if (i >= P.nl) {
+    const long long e3 = O.e3(i);
+    const S v = onx ? w[e3 + lane] : S(0);
+    S q = onx ? w[e3 + nx + lane] : S(0), none = S(0);
+    S wa = w[e3 + 2 * nx], wb = w[e3 + 2 * nx + 1];
+    soc_prox_wave(q, onx, none, false, wa, wb, al);
+    if (onx) {
+      out[e3 + lane] = v - al * clampv(v * ia, P.xlo[bx], P.xhi[bx]);
+      out[e3 + nx + lane] = q;
+    }
+    if (lane == 0) {
+      out[e3 + 2 * nx] = wa;
+      out[e3 + 2 * nx + 1] = wb;
+    }
+    return;
   }
-  for (int o = 0; o < nu; ++o) {
-    const S v = w[O.e1u(i) + o];
-    out[O.e1u(i) + o] = v - al * clampv(v * ia, P.ulo[(size_t)i * nu + o], P.uhi[(size_t)i * nu + o]);
+  const int fc = P.fc[i], n = P.nch[i];
+  const long long e1 = O.e1(i), e1x = e1 + 2LL * n + 2;
+  for (int k = lane; k < 2 * n + 2; k += 64) {  // y, then the s-row
+    const S v = w[e1 + k];
+    out[e1 + k] = k == 2 * n ? S(0) : (v < S(0) ? v : S(0));
   }
-  for (int k = 0; k < n; ++k) {
-    const int c = fc + k;
-    soc_prox_serial<S>(w + O.e2(c), out + O.e2(c), nx + nu, al);
-    if (c >= P.nl) {
-      const long long e3 = O.e3(c);
-      for (int o = 0; o < nx; ++o) {
-        const S v = w[e3 + o];
-        out[e3 + o] = v - al * clampv(v * ia, P.xlo[(size_t)c * nx + o], P.xhi[(size_t)c * nx + o]);
-      }
-      soc_prox_serial<S>(w + e3 + nx, out + e3 + nx, nx, al);
+  if (onx) {
+    const S v = w[e1x + lane];
+    out[e1x + lane] = v - al * clampv(v * ia, P.xlo[bx], P.xhi[bx]);
+  }
+  if (onu) {
+    const S v = w[e1x + nx + lane];
+    const size_t bu = (size_t)i * nu + lane;
+    out[e1x + nx + lane] = v - al * clampv(v * ia, P.ulo[bu], P.uhi[bu]);
+  }
+  for (int c = fc; c < fc + n; ++c) {
+    const long long e2 = O.e2(c);
+    S wx = onx ? w[e2 + lane] : S(0), wu = onu ? w[e2 + nx + lane] : S(0);
+    S wa = w[e2 + K], wb = w[e2 + K + 1];
+    soc_prox_wave(wx, onx, wu, onu, wa, wb, al);
+    if (onx) out[e2 + lane] = wx;
+    if (onu) out[e2 + nx + lane] = wu;
+    if (lane == 0) {
+      out[e2 + K] = wa;
+      out[e2 + K + 1] = wb;
     }
   }
 }
@@ -1014,8 +1021,7 @@ hipError_t launch_Lt(const Problem& P, const S* eta, S* z, hipStream_t st) {
 template <typename S>
 hipError_t launch_prox_gstar(const Problem& P, const S* w, S* out, hipStream_t st) {
   if (P.general) return launch_gen_prox_gstar<S>(P, w, out, st);
-  const int nl = P.tree->nl;
-  hipLaunchKernelGGL(k_prox_gstar<S>, dim3((nl + 127) / 128), dim3(128), 0, st, dev_of<S>(P), w, out);
+  hipLaunchKernelGGL(k_prox_gstar<S>, dim3((P.tree->nn + 3) / 4), dim3(256), 0, st, dev_of<S>(P), w, out);
   return hipGetLastError();
 }
 template hipError_t launch_L_batch<double>(const Problem&, const double*, double*, long long, int, hipStream_t);

@@ -145,3 +145,21 @@ def test_shared_form_matches_single_solves_at_edges(nx, nu, br, B, prec):
             # as for the block engine above
             tol = {"cp": 1e-12, "spock": 1e-10}[method] if prec == "fp64" else {"cp": 2e-5, "spock": 2e-4}[method]
             check(f"edge_shared:{nx}:{nu}:{prec}:{method}:{k}", np.max(np.abs(a - b)) / max(1.0, np.max(np.abs(b))), tol)
+
+
+# one wavefront per unit: dimensions of one lane, a partial and a full
+# wavefront, wide families, in place and out of place
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("nx,nu,br", [(1, 1, [2]), (64, 64, [1, 2]), (33, 5, [3, 1]), (4, 3, [70])])
+def test_prox_gstar_at_dimension_edges(nx, nu, br, prec):
+    inst = G.make_random_small(900 + nx, br, nx, nu)
+    op = O.Problem(inst)
+    gp = SP.Problem.from_instance(inst, precision=SP.FP64 if prec == "fp64" else SP.FP32, alpha=op.alpha)
+    w = dev(2.0 * np.random.default_rng([nx, 9]).standard_normal(gp.n_eta), gp.torch_dtype)
+    out = torch.zeros_like(w)
+    ref = O.prox_gstar(op.lay, inst, host(w), op.alpha)
+    gp.prox_gstar(w, out)
+    tol = 1e-12 if prec == "fp64" else 5e-6  # the per-operator bounds of the parity tests
+    check(f"edge_prox:{nx}:{nu}:{prec}", np.max(np.abs(host(out) - ref)) / max(1.0, np.max(np.abs(ref))), tol)
+    gp.prox_gstar(w, w)
+    assert torch.equal(w, out)
