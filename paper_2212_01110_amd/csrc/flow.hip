@@ -37,7 +37,7 @@
 // before the item's dependency wait: an item costs one HBM round trip, its
 // wait, and one phase of LDS mat-vecs, cut into wavefront-uniform units
 // (one output block and one input range per wavefront, lane = output).
-#include "device_common.h"
+#include "flow_common.h"
 
 #include <math.h>
 #include <algorithm>
@@ -45,10 +45,6 @@
 namespace spk {
 
 namespace {
-
-constexpr int kFW = 256;                   // threads per workgroup (4 wavefronts)
-
-typedef __attribute__((address_space(3))) void lds_void;
 
 // Word offsets of the dynamic LDS regions (32-bit words; every region is a
 // whole number of 64-word rows so that a wavefront copy may overrun it).
@@ -78,38 +74,6 @@ struct FlowLds {
   }
   __host__ __device__ int bytes() const { return words * 4; }
 };
-
-// Copies nwords 32-bit words from global memory into LDS (dst = word
-// offset, a multiple of 64). From a 16-byte aligned source, whole rows of
-// 256 words go as 16 bytes per lane (lane l fills words 4l..4l+3 of the
-// row); the rest (all of it from an unaligned source) goes in rows of 64
-// words, 4 bytes per lane, lanes past the end re-reading the last word (in
-// bounds) into the region's padding. Wavefront w issues rows w', w' + 4, ...
-// (w' = w rotated by `rot`, so that small copies spread over the
-// wavefronts).
-__device__ __forceinline__ void dma_words(const void* src, unsigned* lds, int dst, int nwords, int rot) {
-  const int lane = threadIdx.x & 63, w = ((threadIdx.x >> 6) + rot) & 3;
-  // uniform base + 32-bit lane byte offset (scalar-base addressing)
-  const char* s = static_cast<const char*>(src);
-  int done = 0;
-  if ((reinterpret_cast<uintptr_t>(src) & 15u) == 0) {
-    const int rows = nwords >> 8;
-    for (int r = w; r < rows; r += 4)
-      __builtin_amdgcn_global_load_lds(s + (unsigned)((r * 256 + lane * 4) * 4), (lds_void*)(lds + dst + r * 256), 16, 0,
-                                       0);
-    done = rows << 8;
-  }
-  const int rest = nwords - done;
-  for (int r = w; r * 64 < rest; r += 4) {
-    int e = r * 64 + lane;
-    e = e < rest ? e : rest - 1;
-    __builtin_amdgcn_global_load_lds(s + (unsigned)((done + e) * 4), (lds_void*)(lds + dst + done + r * 64), 4, 0, 0);
-  }
-}
-
-__device__ __forceinline__ void wait_vm() {
-  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-}
 
 // Partial mat-vec from LDS: M input-major (element (out o, in k) at
 // k * nout + o), v (nin) in LDS. Thread t < G * nout (g = t / nout,
@@ -179,58 +143,6 @@ __device__ __forceinline__ S fold_units(const S* red, int P, int o, int stride =
 // the ranges of the n_u-output block share one wavefront as lane groups of
 // n_u (same loop, per-lane base pointers). Half of n_x, rounded down to 4.
 __device__ __forceinline__ int half4(int n) { return (n / 2) & ~3; }
-
-__device__ __forceinline__ unsigned ld_flag(const unsigned* f) {
-  return __hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-
-
-
-// One wavefront polls the n tagged elements at src until all carry `tag`
-// (bounded), copying the values to dst (LDS).
-template <typename S>
-__device__ __forceinline__ void wait_tagged(const unsigned long long* src, int n, unsigned tag, S* dst,
-                                            unsigned* err, unsigned spin) {
-  const int lane = threadIdx.x & 63;
-  for (unsigned it = 0; it < spin; ++it) {
-    bool ok = true;
-    for (int e = lane; e < n; e += 64) {
-      S v;
-      ok = get_tagged<S>(src + (size_t)e * kTW<S>, tag, v) && ok;
-      dst[e] = v;
-    }
-    if (__all(ok)) return;
-    if ((it & 255u) == 255u && ld_flag(err) != 0u) return;
-    __builtin_amdgcn_s_sleep(1);
-  }
-  __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Same for two sources at once (one memory round trip per poll).
-template <typename S>
-__device__ __forceinline__ void wait_tagged2(const unsigned long long* srcA, int nA, S* dstA,
-                                             const unsigned long long* srcB, int nB, S* dstB, unsigned tag,
-                                             unsigned* err, unsigned spin) {
-  const int lane = threadIdx.x & 63;
-  for (unsigned it = 0; it < spin; ++it) {
-    bool ok = true;
-    for (int e = lane; e < nA; e += 64) {
-      S v;
-      ok = get_tagged<S>(srcA + (size_t)e * kTW<S>, tag, v) && ok;
-      dstA[e] = v;
-    }
-    for (int e = lane; e < nB; e += 64) {
-      S v;
-      ok = get_tagged<S>(srcB + (size_t)e * kTW<S>, tag, v) && ok;
-      dstB[e] = v;
-    }
-    if (__all(ok)) return;
-    if ((it & 255u) == 255u && ld_flag(err) != 0u) return;
-    __builtin_amdgcn_s_sleep(1);
-  }
-  __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 
 template <typename S>
 struct FlowArgs {
@@ -534,7 +446,7 @@ hipError_t launch_sweeps_flow(const Problem& P, const DevProb<S>& D, S* zout, co
   A.pt = F.pt;
   A.items = F.items;
   A.pbase = F.pbase;
-  A.err = F.err;
+  A.err = P.flow_err;
   A.spin = F.spin;
   if (++P.flow_epoch == 0u) P.flow_epoch = 1u;  // tag 0 is the cleared state
   A.tag = P.flow_epoch;

@@ -426,6 +426,10 @@ void set_mapping(Problem& P, int team, int cut) {
   if (P.cut > T.N) P.cut = T.N;
 }
 
+// The mapping that a call reports: both forms whose workgroups pass values on
+// are the dataflow mapping.
+int reported_team(const Problem& P) { return P.walk_on ? kTeamFlow : P.team; }
+
 // Default cut: the first stage with at least 256 nodes (enough subtrees to
 // fill the device), or none.
 int default_cut(const Tree& T) {
@@ -557,6 +561,7 @@ extern "C" int spock_problem_factor(const spock_tree* th, const spock_problem_da
     if (v == 8 || v == 16 || v == 32 || v == 64 || v == kTeamWG || v == kTeamFlow) {
       team = mapping_lds(P, v, elem) > 64 * 1024 ? kTeamWG : v;
       P.tuned = true;  // fixed by the caller's environment
+      P.walk_on = v == kTeamFlow && std::getenv("SPOCK_FLOW_WALK");
     }
   }
   int cut = default_cut(T);
@@ -587,6 +592,8 @@ extern "C" int spock_problem_destroy(spock_problem* p) {
   if (p->p.gmem) (void)hipFree(p->p.gmem);
   if (p->p.work) (void)hipFree(p->p.work);
   if (p->p.flow.mem) (void)hipFree(p->p.flow.mem);
+  if (p->p.walk.mem) (void)hipFree(p->p.walk.mem);
+  if (p->p.flow_err) (void)hipFree(p->p.flow_err);
   if (p->p.mbox) (void)hipHostFree(p->p.mbox);
   delete p;
   return SPOCK_OK;
@@ -605,8 +612,8 @@ extern "C" int spock_problem_sizes(const spock_problem* p, int64_t* nz, int64_t*
 extern "C" int spock_problem_mapping(const spock_problem* p, int32_t* mapping, int32_t* flow_grid,
                                      int32_t* flow_failed) {
   if (!p) return SPOCK_EINVAL;
-  if (mapping) *mapping = p->p.team;
-  if (flow_grid) *flow_grid = p->p.team == kTeamFlow ? p->p.flow.grid : 0;
+  if (mapping) *mapping = reported_team(p->p);
+  if (flow_grid) *flow_grid = p->p.walk_on ? p->p.walk.grid : p->p.team == kTeamFlow ? p->p.flow.grid : 0;
   if (flow_failed) *flow_failed = p->p.flow_failed ? 1 : 0;
   return SPOCK_OK;
 }
@@ -682,6 +689,68 @@ void flow_knobs(FlowState& F) {
   if (const char* env = std::getenv("SPOCK_FLOW_SPIN")) F.spin = (unsigned)std::strtoul(env, nullptr, 10);
 }
 
+// Resident workgroups and device state of a form whose launch takes lds bytes
+// per workgroup of a kernel built for waves wavefronts per SIMD.
+template <typename S>
+int place_flow(Problem& P, FlowState& F, const void* kernel, int waves, int lds, const std::vector<int>& items,
+               const std::vector<int>& pbase, int nslots) {
+  const Tree& T = *P.tree;
+  int dev = 0, ncu = 0, coop = 0, nb = 0, smax = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return SPOCK_EHIP;
+  if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return SPOCK_EHIP;
+  if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess) return SPOCK_EHIP;
+  if (hipDeviceGetAttribute(&smax, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) return SPOCK_EHIP;
+  const bool fits = lds <= smax;
+  if (fits && lds > 64 * 1024 &&
+      hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
+    return SPOCK_EHIP;
+  if (fits && hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kernel, 256, (size_t)lds) != hipSuccess)
+    return SPOCK_EHIP;
+  // Residency is what the waits rely on, so the count is also bounded by
+  // what the build guarantees: its wavefronts per SIMD (the register budget
+  // the kernel is compiled for; one wavefront of each workgroup per SIMD)
+  // and the LDS in blocks of 512 bytes out of 160 KiB per CU. The occupancy
+  // query alone granted grids that were not all resident (it reported the
+  // same register count for every budget and left the LDS rounding out).
+  if (fits && nb > 0) {
+    hipFuncAttributes fa{};
+    if (hipFuncGetAttributes(&fa, kernel) != hipSuccess) return SPOCK_EHIP;
+    const int by_lds = (160 * 1024) / std::max(512, ((lds + (int)fa.sharedSizeBytes + 511) / 512) * 512);
+    const int bound = std::min(waves, by_lds);
+    if (std::getenv("SPOCK_FLOW_DEBUG"))
+      std::fprintf(stderr, "[flow] occ %d nc %d lds %d: query %d per CU -> %d per CU\n", waves, F.nc, lds, nb,
+                   std::min(nb, bound));
+    nb = std::min(nb, bound);
+  }
+  if (!P.flow_err) {
+    if (hipMalloc(&P.flow_err, 256) != hipSuccess) return SPOCK_ENOMEM;
+    if (hipMemset(P.flow_err, 0, 256) != hipSuccess) return SPOCK_EHIP;
+  }
+  const size_t tw = sizeof(S) / 4;  // tagged words per element
+  const size_t nq = (size_t)T.nl * P.nx * tw, nd = (size_t)T.nl * P.nu * tw, nxw = (size_t)T.nn * P.nx * tw;
+  const size_t npw = (size_t)nslots * (P.nx + P.nu) * tw;
+  const size_t tagged = sizeof(unsigned long long) * (nq + nd + nxw + npw);
+  const size_t bytes = tagged + sizeof(int) * (items.size() + pbase.size());
+  if (hipMalloc(&F.mem, bytes) != hipSuccess) return SPOCK_ENOMEM;
+  if (hipMemset(F.mem, 0, bytes) != hipSuccess) return SPOCK_EHIP;
+  F.qt = static_cast<unsigned long long*>(F.mem);
+  F.dt = F.qt + nq;
+  F.xt = F.dt + nd;
+  F.pt = F.xt + nxw;
+  F.items = reinterpret_cast<int*>(static_cast<char*>(F.mem) + tagged);
+  F.pbase = F.items + items.size();
+  if (hipMemcpy(F.items, items.data(), sizeof(int) * items.size(), hipMemcpyHostToDevice) != hipSuccess ||
+      hipMemcpy(F.pbase, pbase.data(), sizeof(int) * pbase.size(), hipMemcpyHostToDevice) != hipSuccess)
+    return SPOCK_EHIP;
+  if (const char* env = std::getenv("SPOCK_FLOW_COOP")) F.coop = std::atoi(env) != 0;
+  F.lds = lds;
+  F.elem = (int)sizeof(S);
+  F.grid = (coop && fits) ? nb * ncu : 0;
+  F.resident = F.grid;
+  flow_knobs(F);
+  return SPOCK_OK;
+}
+
 template <typename S>
 int ensure_flow(Problem& P, int occ = 0, int budget = 0) {
   FlowState& F = P.flow;
@@ -700,66 +769,66 @@ int ensure_flow(Problem& P, int occ = 0, int budget = 0) {
   for (int i = 0; i < T.nl; ++i) maxch = std::max(maxch, T.nch[i]);
   int nc = std::min(maxch, 8);
   while (nc > 1 && flow_lds_bytes(P.nx, P.nu, nc, (int)sizeof(S)) > budget) --nc;
-  const int lds = flow_lds_bytes(P.nx, P.nu, nc, (int)sizeof(S));
-  int dev = 0, ncu = 0, coop = 0, nb = 0, smax = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return SPOCK_EHIP;
-  if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return SPOCK_EHIP;
-  if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess) return SPOCK_EHIP;
-  if (hipDeviceGetAttribute(&smax, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) return SPOCK_EHIP;
-  const bool fits = lds <= smax;
-  if (fits && lds > 64 * 1024 &&
-      hipFuncSetAttribute(flow_kernel<S>(occ), hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
-    return SPOCK_EHIP;
-  if (fits && hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, flow_kernel<S>(occ), 256, (size_t)lds) != hipSuccess)
-    return SPOCK_EHIP;
-  // Residency is what the waits rely on, so the count is also bounded by
-  // what the build guarantees: occ wavefronts per SIMD (the register budget
-  // the kernel is compiled for; one wavefront of each workgroup per SIMD)
-  // and the LDS in blocks of 512 bytes out of 160 KiB per CU. The occupancy
-  // query alone granted grids that were not all resident (it reported the
-  // same register count for every budget and left the LDS rounding out).
-  if (fits && nb > 0) {
-    hipFuncAttributes fa{};
-    if (hipFuncGetAttributes(&fa, flow_kernel<S>(occ)) != hipSuccess) return SPOCK_EHIP;
-    const int by_lds = (160 * 1024) / std::max(512, ((lds + (int)fa.sharedSizeBytes + 511) / 512) * 512);
-    const int bound = std::min(occ, by_lds);
-    if (std::getenv("SPOCK_FLOW_DEBUG"))
-      std::fprintf(stderr, "[flow] occ %d nc %d lds %d: query %d per CU -> %d per CU\n", occ, nc, lds, nb,
-                   std::min(nb, bound));
-    nb = std::min(nb, bound);
-  }
   // items: one per chunk of nc children; backward (reverse breadth-first),
   // then forward (breadth-first); partial slots for families of several chunks
   std::vector<int> items, pbase;
-  int nslots = 0, nbwd = 0;
-  if (build_flow_items(T, nc, kChunkCodes, items, pbase, nslots, nbwd) != SPOCK_OK) return SPOCK_EINVAL;
-  const size_t tw = sizeof(S) / 4;  // tagged words per element
-  const size_t nq = (size_t)T.nl * P.nx * tw, nd = (size_t)T.nl * P.nu * tw, nxw = (size_t)T.nn * P.nx * tw;
-  const size_t npw = (size_t)nslots * (P.nx + P.nu) * tw;
-  const size_t tagged = sizeof(unsigned long long) * (nq + nd + nxw + npw);
-  const size_t bytes = 256 + tagged + sizeof(int) * (items.size() + pbase.size());
-  if (hipMalloc(&F.mem, bytes) != hipSuccess) return SPOCK_ENOMEM;
-  if (hipMemset(F.mem, 0, bytes) != hipSuccess) return SPOCK_EHIP;
-  F.err = static_cast<unsigned*>(F.mem);
-  F.qt = reinterpret_cast<unsigned long long*>(static_cast<char*>(F.mem) + 256);
-  F.dt = F.qt + nq;
-  F.xt = F.dt + nd;
-  F.pt = F.xt + nxw;
-  F.items = reinterpret_cast<int*>(static_cast<char*>(F.mem) + 256 + tagged);
-  F.pbase = F.items + items.size();
-  F.nbwd = nbwd;
-  if (hipMemcpy(F.items, items.data(), sizeof(int) * items.size(), hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(F.pbase, pbase.data(), sizeof(int) * pbase.size(), hipMemcpyHostToDevice) != hipSuccess)
-    return SPOCK_EHIP;
+  int nslots = 0;
+  if (build_flow_items(T, nc, kChunkCodes, items, pbase, nslots, F.nbwd) != SPOCK_OK) return SPOCK_EINVAL;
+  F.nitems = (int)items.size();
   F.nc = nc;
   F.occ = occ;
   F.budget = budget;
-  if (const char* env = std::getenv("SPOCK_FLOW_COOP")) F.coop = std::atoi(env) != 0;
-  F.elem = (int)sizeof(S);
-  F.grid = (coop && fits) ? nb * ncu : 0;
-  F.resident = F.grid;
-  flow_knobs(F);
-  return SPOCK_OK;
+  return place_flow<S>(P, F, flow_kernel<S>(occ), occ, flow_lds_bytes(P.nx, P.nu, nc, (int)sizeof(S)), items, pbase,
+                       nslots);
+}
+
+// Items of the walk form: children per chunk nc for an LDS budget as above, and
+// the longest chains and path pieces that run KiB of LDS hold (0: none). Up to
+// one piece per compute unit (each recomputes the stages that it shares).
+template <typename S>
+int plan_walk(const Problem& P, int budget, int run, int& nc, WalkPlan& plan) {
+  const Tree& T = *P.tree;
+  int dev = 0, ncu = 0, smax = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return SPOCK_EHIP;
+  if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return SPOCK_EHIP;
+  if (hipDeviceGetAttribute(&smax, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) return SPOCK_EHIP;
+  nc = 1;
+  for (int i = 0; i < T.nl; ++i) nc = std::max(nc, std::min(T.nch[i], 8));
+  auto bytes = [&](int chain, int path) { return walk_lds_bytes(P.nx, P.nu, nc, (int)sizeof(S), chain, path); };
+  while (nc > 1 && bytes(1, 0) > budget) --nc;
+  int max_chain = 1, max_path = 0;
+  const int cap = std::min(run * 1024, smax);
+  while (max_chain < T.N && bytes(max_chain + 1, 0) <= cap) ++max_chain;
+  while (max_path < T.N && bytes(1, max_path + 1) <= cap) ++max_path;
+  return build_walk_plan(T, nc, kChunkCodes, max_chain, max_path, ncu, plan);
+}
+
+// The same for the walk form (SPOCK_FLOW_WALK fixes run).
+template <typename S>
+int ensure_walk(Problem& P, int budget = 0, int run = -1) {
+  FlowState& F = P.walk;
+  if (budget == 0) budget = F.mem ? F.budget : 32 * 1024;
+  if (run < 0) run = F.mem ? F.run : 0;
+  if (const char* env = std::getenv("SPOCK_FLOW_LDS")) budget = std::max(4096, std::atoi(env));
+  if (const char* env = std::getenv("SPOCK_FLOW_WALK")) run = std::max(0, std::min(160, std::atoi(env)));
+  if (F.mem && F.elem == (int)sizeof(S) && F.budget == budget && F.run == run) {
+    flow_knobs(F);
+    return SPOCK_OK;
+  }
+  if (F.mem) (void)hipFree(F.mem);
+  F = FlowState{};
+  WalkPlan plan;
+  const int rc = plan_walk<S>(P, budget, run, F.nc, plan);
+  if (rc) return rc;
+  F.nbwd = plan.nbwd;
+  F.nitems = plan.nitems;
+  F.rs = plan.rs;
+  F.budget = budget;
+  F.run = run;
+  int waves = 0;
+  const void* kernel = walk_kernel<S>(P.nx, P.nu, &waves);
+  const int lds = walk_lds_bytes(P.nx, P.nu, F.nc, (int)sizeof(S), plan.chain, plan.path);
+  return place_flow<S>(P, F, kernel, waves, lds, plan.items, plan.pbase, plan.nslots);
 }
 
 template <typename S>
@@ -838,6 +907,12 @@ int ensure_work(Problem& P, Work<S>& W) {
     P.mbox_dev = static_cast<Mailbox*>(dp);
     P.mbox_epoch = 0;
   }
+  if (P.flow_failed) P.walk_on = false;
+  if (P.walk_on) {
+    const int rc = ensure_walk<S>(P);
+    if (rc) return rc;
+    if (P.walk.grid <= 0) P.walk_on = false;
+  }
   if (P.team == kTeamFlow && P.flow_failed) set_mapping(P, kTeamWG, default_cut(*P.tree));
   if (P.team == kTeamFlow) {
     const int rc = ensure_flow<S>(P);
@@ -899,9 +974,9 @@ int autotune(Problem& P, hipStream_t st) {
       // a bounded wait that gave up (a grid that was not all resident):
       // the candidate is rejected, whatever its time
       unsigned err = 0;
-      HIP_TRY(hipMemcpy(&err, P.flow.err, sizeof(unsigned), hipMemcpyDeviceToHost));
+      HIP_TRY(hipMemcpy(&err, P.flow_err, sizeof(unsigned), hipMemcpyDeviceToHost));
       if (err != 0u) {
-        HIP_TRY(hipMemset(P.flow.err, 0, sizeof(unsigned)));
+        HIP_TRY(hipMemset(P.flow_err, 0, sizeof(unsigned)));
         continue;
       }
     }
@@ -956,6 +1031,46 @@ int autotune(Problem& P, hipStream_t st) {
       P.post_flat = ms < best_pp;
     }
   }
+  // The walk form against the mapping chosen so far. Its plan needs no timing:
+  // chunks in up to 64 KiB of LDS, chains and path pieces in up to 51 (three
+  // workgroups per CU) were within 3% of the fastest of 0, 51, 77 and 156 KiB
+  // everywhere (sweeps in us at 0 / 51 / 77 / 156: 223 nodes, n_x 20, FP64
+  // 28.8 / 21.3 / 21.6 / 21.6; 364 nodes, n_x 13, FP64 21.8 / 16.5 / 16.8 /
+  // 16.5; 2047 nodes, n_x 20, FP32 30.4 / 26.2 / 25.9 / 26.1; 4095 nodes, n_x
+  // 50, FP32 64.0 / 64.5 / 72.0 / 96.8). Not tried where the matrices' bytes
+  // alone take twice the time of the dependent stages (5 TB/s, 1.2 us): 20776
+  // nodes, n_x 50, n_u 20, FP32 run T in 250 us without it and 346 us with it;
+  // 4095 nodes, n_x = n_u = 50, FP32, below the line, have the sweeps in 101 us
+  // without it and 64 us with it.
+  const double mat_us = sizeof(S) * (double)T.nn * 2.0 * P.nx * (P.nx + P.nu) / 5e6;
+  if (!P.flow_failed && mat_us < 2.0 * 1.2 * 2 * T.N) {
+    float ms[2] = {0, 0};
+    for (int on = 0; on < 2; ++on) {
+      P.walk_on = on != 0;
+      if (on && (ensure_walk<S>(P, 64 * 1024, 51) != SPOCK_OK || P.walk.grid <= 0)) {
+        P.walk_on = false;
+        break;
+      }
+      for (int r = -1; r < 6; ++r) {
+        if (r == 0) HIP_TRY(hipEventRecord(e0, st));
+        HIP_TRY(launch_T<S>(P, W.pool[0], W.pool[1], W.x0_zero, W.q, W.d, W.xbar, W.ubar, W.partials, W.stats, st,
+                            W.eta_zero, true));
+      }
+      HIP_TRY(hipEventRecord(e1, st));
+      HIP_TRY(hipEventSynchronize(e1));
+      HIP_TRY(hipEventElapsedTime(&ms[on], e0, e1));
+    }
+    if (P.walk_on) {
+      unsigned err = 0;
+      HIP_TRY(hipMemcpy(&err, P.flow_err, sizeof(unsigned), hipMemcpyDeviceToHost));
+      if (err != 0u) HIP_TRY(hipMemset(P.flow_err, 0, sizeof(unsigned)));
+      P.walk_on = err == 0u && ms[1] < ms[0];
+    }
+    if (!P.walk_on && P.walk.mem) {
+      (void)hipFree(P.walk.mem);
+      P.walk = FlowState{};
+    }
+  }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   P.tuned = true;
@@ -972,10 +1087,10 @@ constexpr int kFlowGaveUp = 1000;
 // Reads the error word of the dataflow sweeps (synchronises the stream).
 int flow_gave_up(const Problem& P, hipStream_t st, bool& gave_up) {
   gave_up = false;
-  if (P.team != kTeamFlow || !P.flow.err) return SPOCK_OK;
+  if (!sweeps_wait(P) || !P.flow_err) return SPOCK_OK;
   unsigned err = 0;
   HIP_TRY(hipStreamSynchronize(st));
-  HIP_TRY(hipMemcpy(&err, P.flow.err, sizeof(unsigned), hipMemcpyDeviceToHost));
+  HIP_TRY(hipMemcpy(&err, P.flow_err, sizeof(unsigned), hipMemcpyDeviceToHost));
   gave_up = err != 0u;
   return SPOCK_OK;
 }
@@ -983,8 +1098,9 @@ int flow_gave_up(const Problem& P, hipStream_t st, bool& gave_up) {
 // After a give-up: clear the word and run the per-stage workgroup form from
 // now on (the problem never returns to the dataflow form).
 int flow_fallback(Problem& P) {
-  if (P.flow.err) HIP_TRY(hipMemset(P.flow.err, 0, sizeof(unsigned)));
+  if (P.flow_err) HIP_TRY(hipMemset(P.flow_err, 0, sizeof(unsigned)));
   P.flow_failed = true;
+  P.walk_on = false;
   set_mapping(P, kTeamWG, default_cut(*P.tree));
   return SPOCK_OK;
 }
@@ -1549,7 +1665,7 @@ extern "C" int spock_solve(spock_problem* ph, const double* x0_dev, const spock_
     const int rt = (P.precision == SPOCK_FP64) ? autotune<double>(P, st) : autotune<float>(P, st);
     if (rt) return rt;
   }
-  loc.mapping = P.team;
+  loc.mapping = reported_team(P);
   int rc = (P.precision == SPOCK_FP64)
                ? solve_impl<double>(P, x0_dev, *s, static_cast<double*>(v_io), loc, st)
                : solve_impl<float>(P, x0_dev, *s, static_cast<float*>(v_io), loc, st);
@@ -1560,7 +1676,7 @@ extern "C" int spock_solve(spock_problem* ph, const double* x0_dev, const spock_
     if (rc) return rc;
     loc = spock_info{};
     loc.V_nested = std::numeric_limits<double>::quiet_NaN();
-    loc.mapping = P.team;
+    loc.mapping = reported_team(P);
     loc.flow_fallback = 1;
     rc = (P.precision == SPOCK_FP64) ? solve_impl<double>(P, x0_dev, *s, static_cast<double*>(v_io), loc, st)
                                      : solve_impl<float>(P, x0_dev, *s, static_cast<float*>(v_io), loc, st);
@@ -1634,9 +1750,9 @@ int prox_f_impl(Problem& P, const S* zin, const double* x0, S* zout, hipStream_t
     int rc = ensure_work<S>(P, W);
     if (rc) return rc;
     HIP_TRY(launch_T<S>(P, zin, zout, x0, W.q, W.d, W.xbar, W.ubar, W.partials, W.stats, st, W.eta_zero, false));
-    if (P.team != kTeamFlow) return SPOCK_OK;
+    if (!sweeps_wait(P)) return SPOCK_OK;
     const Publish pub{P.mbox_dev, ++P.mbox_epoch};
-    HIP_TRY(launch_publish_word(P.flow.err, pub, st));
+    HIP_TRY(launch_publish_word(P.flow_err, pub, st));
     rc = wait_mailbox(P, pub.epoch, st);
     if (rc) return rc;
     if (P.mbox->v[0] == 0.0) return SPOCK_OK;
@@ -1650,9 +1766,14 @@ int T_impl(Problem& P, const S* v, const double* x0, S* Tv, double* stats, hipSt
   Work<S> W;
   int rc = ensure_work<S>(P, W);
   if (rc) return rc;
-  const bool wait = stats || P.team == kTeamFlow;
+  // In FP32 the statistics, FP64 sums over the FP32 residual, show the last
+  // bits of the sweeps: this call keeps the order of sums of the tuned mapping,
+  // without the walk form.
+  SweepMap map;
+  map.keep = sizeof(S) == 4;
+  const bool wait = stats || sweeps_wait(P, map);
   const Publish pub = wait ? Publish{P.mbox_dev, ++P.mbox_epoch} : Publish{};
-  HIP_TRY(launch_T<S>(P, v, Tv, x0, W.q, W.d, W.xbar, W.ubar, W.partials, W.stats, st, W.eta_zero, true, pub));
+  HIP_TRY(launch_T<S>(P, v, Tv, x0, W.q, W.d, W.xbar, W.ubar, W.partials, W.stats, st, W.eta_zero, true, pub, map));
   if (!wait) return SPOCK_OK;
   rc = wait_mailbox(P, pub.epoch, st);
   if (rc) return rc;
@@ -2297,7 +2418,7 @@ int backward_impl(Problem& P, const S* vstar, const double* x0, double gV, const
   rc = flow_fallback(P);
   if (rc) return rc;
   info.flow_fallback = 1;
-  info.mapping = P.team;
+  info.mapping = reported_team(P);
   rc = backward_once<S>(P, vstar, x0, gV, gu0, gx0, gq, gqN, s, info, st);
   return rc == kFlowGaveUp ? SPOCK_EHIP : rc;
 }
@@ -2342,7 +2463,7 @@ extern "C" int spock_backward(spock_problem* ph, const void* v_star, const doubl
     const int rt = (P.precision == SPOCK_FP64) ? autotune<double>(P, st) : autotune<float>(P, st);
     if (rt) return rt;
   }
-  loc.mapping = P.team;
+  loc.mapping = reported_team(P);
   const int rc = (P.precision == SPOCK_FP64)
                      ? backward_impl<double>(P, static_cast<const double*>(v_star), x0, gV, gu0, grad_x0,
                                              grad_q, grad_qN, *s, loc, st)

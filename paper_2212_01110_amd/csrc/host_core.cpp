@@ -583,6 +583,73 @@ int build_flow_items(const Tree& T, int nc, int chunk_codes, std::vector<int>& i
   return SPOCK_OK;
 }
 
+int build_walk_plan(const Tree& T, int nc, int chunk_codes, int max_chain, int max_path, int max_pieces, WalkPlan& F) {
+  F = WalkPlan{};
+  std::vector<int> codes;
+  int nb = 0;
+  const int rc = build_flow_items(T, nc, chunk_codes, codes, F.pbase, F.nslots, nb);
+  if (rc != SPOCK_OK) return rc;
+  max_chain = std::min(max_chain, 60);
+  max_path = std::min(max_path, 59);
+  std::vector<int> rec, at;  // records one after the other, and where each begins
+  auto begin = [&](int code, int links, int a, int b) {
+    at.push_back((int)rec.size());
+    rec.insert(rec.end(), {code, links, a, b});
+  };
+  std::vector<char> taken(T.nl, 0);  // families that a chain from below runs through
+  for (int k = 0; k < nb; ++k) {
+    const int i = codes[k] / chunk_codes, j = codes[k] % chunk_codes;
+    if (taken[i]) continue;
+    begin(codes[k], 1, T.fc[i], T.nch[i]);
+    int links = 1;
+    if ((j + 1) * nc >= T.nch[i])  // the family's last chunk goes on
+      for (int f = i; f > 0 && T.nch[T.anc[f]] == 1 && links < max_chain; ++links) {
+        f = T.anc[f];
+        rec.push_back(f);
+        taken[f] = 1;
+      }
+    rec[at.back() + 1] = links;
+    F.chain = std::max(F.chain, links);
+  }
+  F.nbwd = (int)at.size();
+  auto width = [&](int t) { return T.stage_off[t + 1] - T.stage_off[t]; };
+  size_t k = nb;  // next forward code
+  for (int t = 0; t < T.N;) {
+    int m = std::min(max_path, T.N - t);
+    while (m > 1 && width(t + m) > max_pieces) --m;
+    const bool pieces = m >= 2;
+    const int upto = pieces ? t + m : t + 1;
+    for (; k < codes.size() && codes[k] / chunk_codes < T.stage_off[upto]; ++k) {
+      const int i = codes[k] / chunk_codes;
+      if (!pieces) begin(codes[k], 0, T.fc[i], T.nch[i]);
+    }
+    if (pieces) {
+      std::vector<char> seen(T.nn, 0);
+      for (int c = T.stage_off[upto]; c < T.stage_off[upto + 1]; ++c) {
+        begin(0, m, m, 0);
+        rec.resize(rec.size() + m + 1);
+        int* r = &rec[at.back()];
+        for (int l = m, v = c; l >= 0; --l) {
+          r[4 + l] = v;
+          if (l > 0) v = T.anc[v];
+        }
+        while (r[2] > 0 && !seen[r[4 + r[2] - 1]]) --r[2];
+        for (int l = r[2]; l <= m; ++l) seen[r[4 + l]] = 1;
+        r[0] = r[4] * chunk_codes;
+      }
+      F.path = std::max(F.path, m);
+    }
+    t = upto;
+  }
+  F.nitems = (int)at.size();
+  at.push_back((int)rec.size());
+  for (int q = 0; q < F.nitems; ++q) F.rs = std::max(F.rs, at[q + 1] - at[q]);
+  F.items.assign((size_t)F.nitems * F.rs, 0);
+  for (int q = 0; q < F.nitems; ++q)
+    std::copy(rec.begin() + at[q], rec.begin() + at[q + 1], F.items.begin() + (size_t)q * F.rs);
+  return SPOCK_OK;
+}
+
 int build_post_blocks(const Tree& T, int cap, std::vector<int>& bfam) {
   bfam.clear();
   int count = 0;

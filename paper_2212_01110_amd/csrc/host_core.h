@@ -59,6 +59,27 @@ double nested_cost(const Tree& T, int nx, int nu, const double* q, const double*
 int build_flow_items(const Tree& T, int nc, int chunk_codes, std::vector<int>& items, std::vector<int>& pbase,
                      int& nslots, int& nbwd);
 
+// Work items of the walk form: these as records of rs ints (at most 64), runs
+// of stages joined:
+//   0  family * chunk_codes + chunk
+//   1  backward: links of the chain (1: the family alone); forward: links of
+//      the path piece, or 0 for a chunk of a family
+//   2  first child of the family; path piece: the first of its nodes that is
+//      its own to write
+//   3  children of the family (path piece: unused)
+//   4  chain: the families above, bottom up; path piece: its nodes from the top
+// A chain goes up from a family for as long as the parent has one child, with
+// at most max_chain links (the families above have no records of their own).
+// The forward sweep runs max_path stages at a time in path pieces, one per
+// node at the lower end, where these are at least two stages and at most
+// max_pieces nodes (fewer stages where that makes them fit), and the other
+// stages by chunks. chain and path are the longest ones there are.
+struct WalkPlan {
+  std::vector<int> items, pbase;
+  int rs = 4, nbwd = 0, nitems = 0, nslots = 0, chain = 1, path = 0;
+};
+int build_walk_plan(const Tree& T, int nc, int chunk_codes, int max_chain, int max_path, int max_pieces, WalkPlan& F);
+
 // Dense costs (spock_problem_data Qm, Rm, QNm): finite and symmetric, Q and
 // Q_N positive semidefinite, R positive definite (cyclic Jacobi
 // eigenvalues). Returns SPOCK_OK or SPOCK_EINVAL.

@@ -733,6 +733,7 @@ hipError_t launch_sweeps(const Problem& P, S* zout, const double* x0, S* q, S* d
   const DevProb<S>& D = dev_of<S>(P);
   const int team = map.team > 0 ? map.team : P.team;
   const int cut = map.team > 0 ? map.cut : P.cut;
+  if (map.team == 0 && P.walk_on && !map.keep) return launch_sweeps_walk<S>(P, D, zout, x0, xbar, ubar, q, st);
   switch (team) {
     case kTeamFlow: return launch_sweeps_flow<S>(P, D, zout, x0, xbar, ubar, q, d, st);
     case 8: launch_sweeps_team<S, 8>(P, D, zout, x0, xbar, ubar, q, d, st); break;
@@ -793,7 +794,7 @@ hipError_t launch_T(const Problem& P, const S* v, S* Tv, const double* x0, S* q,
     }
     mark(3);
     hipLaunchKernelGGL(k_reduce_stats, dim3(1), dim3(256), 0, st, partials, post_blocks(P),
-                       (double)D.alpha, stats_dev, team == kTeamFlow ? (const unsigned*)P.flow.err : nullptr,
+                       (double)D.alpha, stats_dev, sweeps_wait(P, map) ? (const unsigned*)P.flow_err : nullptr,
                        pub);
   }
   mark(4);

@@ -108,18 +108,20 @@ struct DevArrays {
 // Device state of the dataflow form of the sweeps: the tagged exchange
 // buffers (q, d of the backward step, x of the forward step; 64-bit words
 // holding the launch epoch and half of a value, zeroed once and never
-// cleared) and an error word raised by a bounded poll that gave up.
+// cleared). An error word of the problem (flow_err) is raised by a bounded
+// poll that gave up.
 constexpr int kChunkCodes = 64;  // item code = family * kChunkCodes + chunk (chunks per family < 64)
 struct FlowState {
   void* mem = nullptr;
-  unsigned* err = nullptr;          // [1]
   unsigned long long* qt = nullptr;  // [nl][nx][words per element]
   unsigned long long* dt = nullptr;  // [nl][nu][...]
   unsigned long long* xt = nullptr;  // [nn][nx][...]
   unsigned long long* pt = nullptr;  // [slots][nx + nu][...] partial sums of backward chunks
-  int* items = nullptr;              // family * kChunkCodes + chunk; backward, then forward
+  int* items = nullptr;              // family * kChunkCodes + chunk (walk form: records, WalkPlan); backward, then forward
   int* pbase = nullptr;              // [nl] first partial slot of a family with several chunks
-  int nbwd = 0;                      // backward items (as many forward items follow)
+  int nbwd = 0;                      // backward items (as many forward items follow in the dataflow form)
+  int nitems = 0, rs = 1;            // items in all, ints per item
+  int lds = 0;                       // bytes of LDS per workgroup
   int nc = 1;                        // children per LDS chunk
   int grid = 0;                      // workgroups launched (0: form unavailable)
   int resident = 0;                  // resident capacity the grid is bounded by
@@ -127,6 +129,7 @@ struct FlowState {
   int occ = 5;                       // register budget: 4 to 7 wavefronts per SIMD
   int elem = 0;                      // element size the state was sized for
   int budget = 32 * 1024;            // LDS budget the chunk size was chosen for
+  int run = 0;                       // walk form: LDS in KiB that chains and path pieces may take
   // cooperative launch (residency guaranteed by the runtime) or a plain
   // launch of the resident-sized grid (about 20 us less dispatch per T; a
   // grid that were not all resident ends with the error word set)
@@ -197,6 +200,11 @@ struct Problem {
   // runs the per-stage workgroup form for good
   bool flow_failed = false;
   FlowState flow;
+  // walk form of the sweeps (walk.hip): used in place of the tuned mapping
+  // where it measured faster
+  FlowState walk;
+  bool walk_on = false;
+  unsigned* flow_err = nullptr;  // error word of both forms
   mutable unsigned flow_epoch = 0;  // tag of the last dataflow launch (never 0 once launched)
   // when set, launch_T records prof[0..4] before the pre-pass, after it,
   // after the sweeps, after the post-pass and at the end (timing aid)
@@ -212,10 +220,16 @@ struct Problem {
 // T(v) (or prox_f of z when dual is false): parallel pre-pass, backward and
 // forward sweeps, parallel post-pass with the residual statistics.
 // Sweep mapping of one launch (team 0: the problem's own mapping and cut).
+// keep: the problem's own mapping without the walk form.
 struct SweepMap {
   int team = 0;
   int cut = 0;
+  bool keep = false;
 };
+// Whether a launch passes values between workgroups (and may raise flow_err).
+inline bool sweeps_wait(const Problem& P, const SweepMap& m = SweepMap{}) {
+  return m.team > 0 ? m.team == kTeamFlow : P.team == kTeamFlow || (P.walk_on && !m.keep);
+}
 template <typename S>
 hipError_t launch_T(const Problem& P, const S* v, S* Tv, const double* x0, S* q, S* d, S* xbar,
                     S* ubar, double* partials, double* stats_dev, hipStream_t st,
@@ -254,6 +268,13 @@ hipError_t launch_gen_M(const Problem& P, const S* d, S* Md, hipStream_t st);
 template <typename S>
 hipError_t launch_sweeps_flow(const Problem& P, const DevProb<S>& D, S* zout, const double* x0, const S* xbar,
                               const S* ubar, S* q, S* d, hipStream_t st);
+// Walk form (walk.hip).
+template <typename S>
+hipError_t launch_sweeps_walk(const Problem& P, const DevProb<S>& D, S* zout, const double* x0, const S* xbar,
+                              const S* ubar, const S* q, hipStream_t st);
+int walk_lds_bytes(int nx, int nu, int nc, int elem, int chain, int path);
+template <typename S>
+const void* walk_kernel(int nx, int nu, int* waves);
 int flow_lds_bytes(int nx, int nu, int nc, int elem);
 template <typename S>
 const void* flow_kernel(int occ);

@@ -163,3 +163,38 @@ def test_prox_gstar_at_dimension_edges(nx, nu, br, prec):
     check(f"edge_prox:{nx}:{nu}:{prec}", np.max(np.abs(host(out) - ref)) / max(1.0, np.max(np.abs(ref))), tol)
     gp.prox_gstar(w, w)
     assert torch.equal(w, out)
+
+
+# walk variant of the dataflow sweeps: chains (from a family of one, two and
+# several chunks), path pieces over all stages, over some with chunks below,
+# several pieces one after the other, dimensions on both sides of the lane
+# groups, and grids in which a workgroup runs items of every kind in turn
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("grid", ["1", "3", None])
+@pytest.mark.parametrize("walk", [160, 8])
+@pytest.mark.parametrize("nx,nu,br", [(3, 2, [2, 2, 2]), (9, 4, [2, 2, 1, 1, 3, 1, 1, 1]), (4, 3, [1, 1, 40, 1, 1]),
+                                      (22, 21, [2, 1, 1, 2]), (7, 33, [3, 1, 1]), (64, 64, [1, 1, 2]),
+                                      (5, 1, [2] * 9 + [1]), (2, 2, [1] * 30)])
+def test_walk_variant_of_the_sweeps(nx, nu, br, walk, grid, prec, monkeypatch):
+    monkeypatch.setenv("SPOCK_TEAM", "512")
+    monkeypatch.setenv("SPOCK_FLOW_WALK", str(walk))
+    if grid:
+        monkeypatch.setenv("SPOCK_FLOW_GRID", grid)
+    inst = G.make_random_small(1000 + nx, br, nx, nu)
+    op = O.Problem(inst)
+    gp = SP.Problem.from_instance(inst, precision=SP.FP64 if prec == "fp64" else SP.FP32, alpha=op.alpha)
+    rng = np.random.default_rng([nx, nu, walk])
+    tol = 1e-12 if prec == "fp64" else 5e-6  # the bounds of prox_f and T in the parity tests
+    for k in range(2):
+        v = dev(rng.standard_normal(gp.n_v), gp.torch_dtype)
+        x0 = dev(inst.x0, torch.float64)
+        zo = torch.zeros(op.lay.n_z, dtype=gp.torch_dtype, device="cuda")
+        gp.prox_f(v[:op.lay.n_z].contiguous(), x0, zo)
+        assert gp.mapping()["mapping"] == 512 and not gp.mapping()["flow_failed"]
+        ref = O.prox_f(op.lay, op.inst, op.fac, host(v)[:op.lay.n_z], op.alpha, op.inst.x0)
+        check(f"edge_walk:{nx}:{nu}:{walk}:{grid}:{prec}:{k}", np.max(np.abs(host(zo) - ref)) / max(1.0, np.max(np.abs(ref))), tol)
+        if prec == "fp64":
+            out = torch.zeros_like(v)
+            gp.T(v, x0, out)
+            ref = O.T_apply(op, host(v), inst.x0)
+            check(f"edge_walk_T:{nx}:{nu}:{walk}:{grid}:{k}", np.max(np.abs(host(out) - ref)) / max(1.0, np.max(np.abs(ref))), tol)
