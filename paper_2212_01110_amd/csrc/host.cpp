@@ -2228,7 +2228,7 @@ int backward_once(Problem& P, const S* vstar, const double* x0, double gV, const
   // Krylov vectors, the dot products of one Gram-Schmidt pass and their
   // per-chunk partial sums
   const size_t basis_bytes = (sizeof(S) * (size_t)(kAdjRestart + 1) * (size_t)nv + 255) & ~size_t(255);
-  const size_t dots_bytes = sizeof(double) * 2 * (kAdjMax + 2);  // the two passes' coefficients
+  const size_t dots_bytes = sizeof(double) * (kAdjMax + 2);
   void* kmem = nullptr;
   if (hipMalloc(&kmem, basis_bytes + dots_bytes + sizeof(double) * (size_t)(kAdjMax + 2) * kBasisChunks) !=
       hipSuccess)
@@ -2256,12 +2256,9 @@ int backward_once(Problem& P, const S* vstar, const double* x0, double gV, const
     HIP_TRY(launch_basis_mix<S>(nv, n, basis, nv, C, a, x, out, st));
     return SPOCK_OK;
   };
-  // Arnoldi steps are pipelined: the passes take their coefficients from
-  // device memory, the reduction kernels also write them to mapped pinned
-  // host memory, and the host reduces column j of the Hessenberg matrix
+  // Arnoldi steps are pipelined: the passes form their coefficients on the
+  // device and also write them to mapped pinned host memory, and the host reduces column j of the Hessenberg matrix
   // while step j + 1 runs (two slots, alternating).
-  double* d1 = dots_dev;
-  double* d2 = dots_dev + (kAdjMax + 2);
   double* hp = nullptr;
   if (hipHostMalloc(reinterpret_cast<void**>(&hp), sizeof(double) * 4 * (kAdjMax + 2),
                     hipHostMallocCoherent | hipHostMallocMapped) != hipSuccess)
@@ -2363,10 +2360,8 @@ int backward_once(Problem& P, const S* vstar, const double* x0, double gV, const
       ++k;
       HIP_TRY(launch_adj_back<S>(P, 1.0, V(j), 0, -1.0, la, tz, lb, 0.0, g, V(j + 1), 0, 0, 1, st));
       double* slot = hp_dev + (size_t)(j & 1) * 2 * (kAdjMax + 2);
-      HIP_TRY(launch_basis_dots<S>(nv, j + 1, basis, nv, V(j + 1), false, dots_part, d1, st, slot));
-      HIP_TRY(launch_basis_orth<S>(nv, j + 1, basis, nv, d1, false, V(j + 1), st));
-      HIP_TRY(launch_basis_dots<S>(nv, j + 1, basis, nv, V(j + 1), true, dots_part, d2, st, slot + (kAdjMax + 2)));
-      HIP_TRY(launch_basis_orth<S>(nv, j + 1, basis, nv, d2, true, V(j + 1), st));
+      HIP_TRY(launch_basis_orth<S>(nv, j + 1, basis, nv, false, dots_part, V(j + 1), slot, st));
+      HIP_TRY(launch_basis_orth<S>(nv, j + 1, basis, nv, true, dots_part, V(j + 1), slot + (kAdjMax + 2), st));
       HIP_TRY(hipEventRecord(evs[j & 1], st));
       if (j > 0) {
         const int r = column(j - 1);

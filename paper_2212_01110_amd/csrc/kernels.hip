@@ -1499,7 +1499,13 @@ hipError_t launch_aa_dir(long long n, const S* r, const S* eb, long long stride,
 // Krylov basis kernels of the adjoint GMRES. The basis vectors are
 // V_j = basis + j * stride. k_basis_dots: block (c, j) sums chunk c of
 // <V_j, x> (j < n; <x, x> for j = n when the grid has n + 1 rows) in FP64
-// into part[j * gridDim.x + c]; k_basis_final adds the chunks in order.
+// into part[j * gridDim.x + c]; the chunks are added in order by
+// k_basis_final, or by every workgroup of the Gram-Schmidt pass that follows
+// (k_basis_orth), which needs no launch in between. Bound by the latency of one
+// thread's loads, so chunks are short: 95 nodes (9 700 entries), FP64, 16
+// vectors, a dots launch took 6.9 us with chunks of 8192 entries and takes
+// 3.8 us with 1024; a step of the gradient's Krylov loop has two launches and
+// two gaps less (2.55 to 2.10 ms for 32 steps).
 template <typename S>
 __global__ void __launch_bounds__(256) k_basis_dots(long long nv, int n, const S* __restrict__ basis,
                                                     long long stride, const S* __restrict__ x,
@@ -1519,26 +1525,25 @@ __global__ void __launch_bounds__(256) k_basis_dots(long long nv, int n, const S
   if (threadIdx.x == 0) part[(size_t)j * gridDim.x + blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
 }
 __global__ void __launch_bounds__(256) k_basis_final(const double* __restrict__ part, int cb, int m,
-                                                     double* __restrict__ out, double* __restrict__ host_out) {
+                                                     double* __restrict__ out) {
   for (int j = threadIdx.x; j < m; j += blockDim.x) {
     double acc = 0;
     for (int c = 0; c < cb; ++c) acc += part[(size_t)j * cb + c];
     out[j] = acc;
-    if (host_out) host_out[j] = acc;  // mapped pinned memory, visible once the kernel completes
   }
 }
-// chunks per basis vector: about 8192 elements each, at most kBasisChunks
+// chunks per basis vector: about 1024 elements each, at most kBasisChunks
 static int basis_chunks(long long nv) {
-  const long long c = (nv + 8191) / 8192;
+  const long long c = (nv + 1023) / 1024;
   return (int)(c < 1 ? 1 : (c > kBasisChunks ? kBasisChunks : c));
 }
 template <typename S>
 hipError_t launch_basis_dots(long long nv, int n, const S* basis, long long stride, const S* x, bool xx,
-                             double* part, double* out_dev, hipStream_t st, double* host_out) {
+                             double* part, double* out_dev, hipStream_t st) {
   if (n < 0 || n + (xx ? 1 : 0) > kBasisMax + 1 || n + (xx ? 1 : 0) < 1) return hipErrorInvalidValue;
   const int cb = basis_chunks(nv), m = n + (xx ? 1 : 0);
   hipLaunchKernelGGL(k_basis_dots<S>, dim3(cb, m), dim3(256), 0, st, nv, n, basis, stride, x, part);
-  hipLaunchKernelGGL(k_basis_final, dim3(1), dim3(256), 0, st, part, cb, m, out_dev, host_out);
+  hipLaunchKernelGGL(k_basis_final, dim3(1), dim3(256), 0, st, part, cb, m, out_dev);
   return hipGetLastError();
 }
 // out = a x + sum_{j < n} C.c[j] V_j (out may be x: each element is read
@@ -1560,14 +1565,23 @@ hipError_t launch_basis_mix(long long nv, int n, const S* basis, long long strid
   return hipGetLastError();
 }
 
-// In-place Gram-Schmidt pass with device-resident coefficients: x -= sum_{j
-// < n} c[j] V_j; when norm, the result is also scaled by 1 / sqrt(c[n] -
-// sum_j c[j]^2) (c[n] = <x, x> before the pass; 0 when that is not
-// positive), so no coefficient has to travel to the host first.
+// In-place Gram-Schmidt pass from the partial dots of x (cb chunks each):
+// c[j] = <V_j, x>, x -= sum_{j < n} c[j] V_j; when norm, the result is also
+// scaled by 1 / sqrt(c[n] - sum_j c[j]^2) (c[n] = <x, x> before the pass; 0
+// when that is not positive). The c also go to host_out (mapped pinned memory,
+// visible once the kernel completes).
 template <typename S>
 __global__ void __launch_bounds__(256) k_basis_orth(long long nv, int n, const S* __restrict__ basis,
-                                                    long long stride, const double* __restrict__ c, int norm,
-                                                    S* x) {
+                                                    long long stride, const double* __restrict__ part, int cb, int norm,
+                                                    S* x, double* __restrict__ host_out) {
+  __shared__ double c[kBasisMax + 1];
+  for (int j = threadIdx.x; j < n + norm; j += 256) {
+    double acc = 0;
+    for (int k = 0; k < cb; ++k) acc += part[(size_t)j * cb + k];
+    c[j] = acc;
+    if (blockIdx.x == 0) host_out[j] = acc;
+  }
+  __syncthreads();
   double scale = 1.0;
   if (norm) {
     double h2 = c[n];
@@ -1576,16 +1590,19 @@ __global__ void __launch_bounds__(256) k_basis_orth(long long nv, int n, const S
   }
   SPK_GRID_LOOP(e, 0, nv) {
     double acc = (double)x[e];
+#pragma unroll 8
     for (int j = 0; j < n; ++j) acc -= c[j] * (double)basis[(size_t)j * (size_t)stride + e];
     x[e] = (S)(acc * scale);
   }
 }
 template <typename S>
-hipError_t launch_basis_orth(long long nv, int n, const S* basis, long long stride, const double* c_dev, bool norm,
-                             S* x, hipStream_t st) {
+hipError_t launch_basis_orth(long long nv, int n, const S* basis, long long stride, bool norm, double* part, S* x,
+                             double* host_out, hipStream_t st) {
   if (n < 0 || n > kBasisMax) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_basis_orth<S>, dim3(dots_blocks(nv)), dim3(256), 0, st, nv, n, basis, stride, c_dev,
-                     norm ? 1 : 0, x);
+  const int cb = basis_chunks(nv), m = n + (norm ? 1 : 0);
+  if (m > 0) hipLaunchKernelGGL(k_basis_dots<S>, dim3(cb, m), dim3(256), 0, st, nv, n, basis, stride, x, part);
+  hipLaunchKernelGGL(k_basis_orth<S>, dim3(dots_blocks(nv)), dim3(256), 0, st, nv, n, basis, stride, part, cb,
+                     norm ? 1 : 0, x, host_out);
   return hipGetLastError();
 }
 
@@ -1633,10 +1650,10 @@ hipError_t launch_colmix(long long n, const ColMix<S>& M, hipStream_t st) {
                                        const double*, S*, const S*, S*, hipStream_t);              \
   template hipError_t launch_colmix<S>(long long, const ColMix<S>&, hipStream_t);                  \
   template hipError_t launch_basis_dots<S>(long long, int, const S*, long long, const S*, bool, double*, \
-                                           double*, hipStream_t, double*);                              \
+                                           double*, hipStream_t);                              \
   template hipError_t launch_basis_mix<S>(long long, int, const S*, long long, const BasisCoef&, double,   \
                                           const S*, S*, hipStream_t);                                     \
-  template hipError_t launch_basis_orth<S>(long long, int, const S*, long long, const double*, bool, S*,  \
+  template hipError_t launch_basis_orth<S>(long long, int, const S*, long long, bool, double*, S*, double*, \
                                            hipStream_t);
 SPK_INST(double)
 SPK_INST(float)
