@@ -132,7 +132,7 @@ def measured_traffic():
     if not b or not h:
         return None
     sha = hashlib.sha256()
-    for f in ("flow.hip", "device_common.h", "spock_internal.h"):
+    for f in ("flow.hip", "flow_common.h", "device_common.h", "spock_internal.h"):
         sha.update(open(os.path.join(ROOT, "paper_2212_01110_amd", "csrc", f), "rb").read())
     return int(b.group(1)) if sha.hexdigest()[:16] == h.group(1) else None
 

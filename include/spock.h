@@ -295,9 +295,10 @@ int spock_apply_L(spock_problem* prob, const void* z_dev, void* eta_dev, void* s
 int spock_apply_Lt(spock_problem* prob, const void* eta_dev, void* z_dev, void* stream);
 /* zout_dev = prox_{alpha f}(zin_dev) (section 5.3): s^0 - alpha, projection on
  * S1 with root state x0_dev (Alg. 2), projection on S2. With the dataflow
- * mapping (512) this call and spock_T synchronise the stream to read the
- * sweeps' error word; if a bounded wait gave up they switch the problem to
- * the per-stage form and evaluate again. */
+ * mapping (512) this call and spock_T wait until the sweeps' error word has
+ * reached the host (their work on the stream is then complete); if a bounded
+ * wait gave up they switch the problem to the per-stage form and evaluate
+ * again. */
 int spock_prox_f(spock_problem* prob, const void* zin_dev, const double* x0_dev,
                  void* zout_dev, void* stream);
 /* out_dev = prox_{alpha g*}(w_dev) = w - alpha proj_S3(w / alpha) (section 5.4) */
@@ -305,7 +306,7 @@ int spock_prox_gstar(spock_problem* prob, const void* w_dev, void* out_dev, void
 /* Tv_dev = T(v_dev) (eq. chambolle-pock-operator). If stats_host is non-NULL it
  * receives {||xi_p||_inf, ||xi_d||_inf, omega^2, ||r_z||^2, ||r_eta||^2,
  * <r_eta, L r_z>} of r = v - T(v) (section 3, Alg. 3) and the call
- * synchronises. */
+ * waits for them (its work on the stream is then complete). */
 int spock_T(spock_problem* prob, const void* v_dev, const double* x0_dev, void* Tv_dev,
             double* stats_host, void* stream);
 

@@ -198,7 +198,7 @@ __global__ void __launch_bounds__(256) k_adj_front(DevProb<S> P, const long long
                                                    const S* __restrict__ bs, const S* __restrict__ w, long long ws,
                                                    S* __restrict__ lb, S* __restrict__ tz, S* __restrict__ cz,
                                                    S* __restrict__ la, S* __restrict__ xbar, S* __restrict__ ubar,
-                                                   S* __restrict__ q, long long is) {
+                                                   S* __restrict__ q, long long is, int tiles) {
   const size_t inst = blockIdx.y;
   const int nx = P.nx, nu = P.nu, K = nx + nu;
   bs += inst * is;
@@ -208,9 +208,11 @@ __global__ void __launch_bounds__(256) k_adj_front(DevProb<S> P, const long long
   tz += inst * is;
   cz += inst * is;
   la += inst * is;
-  xbar += inst * (size_t)P.nn * nx;
-  q += inst * (size_t)P.nn * nx;
-  ubar += inst * (size_t)P.nn * nu;
+  const size_t cs = tiles ? kTileCols : 1;  // from one entry to the next
+  const size_t bx = tiles ? tile_base(inst, (size_t)P.nn * nx) : inst * (size_t)P.nn * nx;
+  xbar += bx;
+  q += bx;
+  ubar += tiles ? tile_base(inst, (size_t)P.nn * nu) : inst * (size_t)P.nn * nu;
   const int lane = threadIdx.x & 63;
   const Off<S> O(P);
   const S al = P.alpha, ia = S(1) / al, al2 = S(2) * al;
@@ -306,7 +308,7 @@ __global__ void __launch_bounds__(256) k_adj_front(DevProb<S> P, const long long
     if (ox) {
       lb[e3 + lane] = lx;
       lb[e3 + nx + lane] = d3[0];
-      q[(size_t)c * nx + lane] = -put(O.x(c) + lane, lx + sq * d3[0]);
+      q[((size_t)c * nx + lane) * cs] = -put(O.x(c) + lane, lx + sq * d3[0]);
     }
     if (lane == 0) {
       lb[e3 + 2 * nx] = ea;
@@ -318,8 +320,8 @@ __global__ void __launch_bounds__(256) k_adj_front(DevProb<S> P, const long long
   for (int s = 0; s < 2; ++s) {
     const int k = lane + 64 * s;
     if (!on[s]) continue;
-    if (k < nx) xbar[(size_t)i * nx + k] = put(O.x(i) + k, acc[s]);
-    else ubar[(size_t)i * nu + (k - nx)] = put(O.u(i) + (k - nx), acc[s]);
+    if (k < nx) xbar[((size_t)i * nx + k) * cs] = put(O.x(i) + k, acc[s]);
+    else ubar[((size_t)i * nu + (k - nx)) * cs] = put(O.u(i) + (k - nx), acc[s]);
   }
   // ---- S2 projection of the (y, tau, s) block (closed form, as the pre-pass)
   const S a = P.a[i], cc = a * a + S(3);
@@ -550,11 +552,11 @@ hipError_t launch_adj_load(const Problem& P, double gV, const AdjPtrs<S>* tab, l
 }
 template <typename S>
 hipError_t launch_adj_front(const Problem& P, const S* bs, const S* w, long long ws, S* lb, S* tz, S* cz, S* la,
-                            S* xbar, S* ubar, S* q, long long is, int B, hipStream_t st) {
+                            S* xbar, S* ubar, S* q, long long is, int B, bool tiles, hipStream_t st) {
   const DevProb<S>& D = (sizeof(S) == 8) ? *reinterpret_cast<const DevProb<S>*>(&P.dp64)
                                          : *reinterpret_cast<const DevProb<S>*>(&P.dp32);
   hipLaunchKernelGGL(k_adj_front<S>, dim3((P.tree->nl + 3) / 4, B), dim3(256), 0, st, D, P.d_spos, bs, w, ws, lb, tz,
-                     cz, la, xbar, ubar, q, is);
+                     cz, la, xbar, ubar, q, is, tiles ? 1 : 0);
   return hipGetLastError();
 }
 template <typename S>
@@ -598,7 +600,7 @@ hipError_t launch_maxdiff(long long n, const S* a, const S* b, double* partials,
 
 #define SPK_BINST(S)                                                                                  \
   template hipError_t launch_adj_front<S>(const Problem&, const S*, const S*, long long, S*, S*, S*, S*, S*, S*, S*, \
-                                          long long, int, hipStream_t);                               \
+                                          long long, int, bool, hipStream_t);                         \
   template hipError_t launch_adj_back<S>(const Problem&, double, const S*, long long, double, const S*, const S*,    \
                                          const S*, double, const S*, S*, long long, long long, int, hipStream_t);    \
   template hipError_t launch_copy_elem<S>(S*, const S*, hipStream_t);                                 \

@@ -716,8 +716,7 @@ struct BlockSolver {
     }
     if (box_ok) {
       xi = Sc.xi();
-      if (s.write_out)
-        for (long long e = threadIdx.x; e < nv; e += kBT) vio[e] = Tv[e];
+      for (long long e = threadIdx.x; e < nv; e += kBT) vio[e] = Tv[e];
       if (threadIdx.x == 0) out[8] = (double)Tv[0];
     }
     if (threadIdx.x == 0) {

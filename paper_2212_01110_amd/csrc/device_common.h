@@ -1423,6 +1423,14 @@ __device__ __forceinline__ AAPush aa_next_push(const AARingDev* ring) {
   return a;
 }
 
+// Sweep buffers of a shared-tree batch hold kTileCols instances of an entry side
+// by side: entry e of instance b at tile_base(b, entries per instance) +
+// e * kTileCols.
+constexpr int kTileCols = 16;
+__device__ __forceinline__ size_t tile_base(size_t b, size_t per) {
+  return b / kTileCols * per * kTileCols + b % kTileCols;
+}
+
 // Tagged words: element e of a vector occupies kTW<S> 64-bit words, each
 // holding (epoch << 32) | one 32-bit half of the value.
 template <typename S>

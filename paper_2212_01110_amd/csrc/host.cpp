@@ -2006,7 +2006,7 @@ int batched_impl(int B, spock_problem* const* probs, const double* const* x0, co
   }
   HIP_TRY(hipMemcpyAsync(C.desc, h.data(), dbytes, hipMemcpyHostToDevice, stream));
   BatchSettings bs{st.eps_abs, st.eps_rel, st.max_iters, st.method, st.m, st.max_ls, st.c0, st.c1,
-                   st.c2, st.beta, st.sigma, st.lambda, 1};
+                   st.c2, st.beta, st.sigma, st.lambda};
   const auto* dev_desc = static_cast<const BatchInst<S>*>(C.desc);
   // Lanes per family: the fewest that hold a state and an input (two
   // components a lane above 64), so that the most families share a stage, or
@@ -2182,7 +2182,7 @@ int backward_once(Problem& P, const S* vstar, const double* x0, double gV, const
   // one application of the transposed operator: writes lb, tz, cz, la
   auto partial = [&](const S* wv) -> int {
     if (fused) {
-      HIP_TRY(launch_adj_front<S>(P, b, wv, 0, lb, tz, cz, la, W.xbar, W.ubar, W.q, 0, 1, st));
+      HIP_TRY(launch_adj_front<S>(P, b, wv, 0, lb, tz, cz, la, W.xbar, W.ubar, W.q, 0, 1, false, st));
       HIP_TRY(launch_sweeps<S>(P, la, W.x0_zero, W.q, W.d, W.xbar, W.ubar, st));
       return SPOCK_OK;
     }

@@ -9,10 +9,14 @@
 // matrix cores (MFMA 16x16x4, FP32 or FP64).
 //
 // Layout: vector buffers hold instance b at base + b * vs (the vector layout
-// of a single problem, vs >= n_v); the sweep buffers q, xbar [Bp][nn][nx] and
-// d, ubar [Bp][nn][nu] likewise, so the node-local passes (pre-pass, post-pass
-// with the residual statistics, M) run the single-instance family steps on
-// each instance. Bp rounds B up to 16; the extra columns run on zeros.
+// of a single problem, vs >= n_v), so the node-local passes (pre-pass,
+// post-pass with the residual statistics, M) run the single-instance family
+// steps on each instance. The sweep buffers q, xbar (then x) [Bp / 16][nn][nx]
+// [16] and d, ubar [Bp / 16][nn][nu][16] hold a tile's 16 instances of an entry
+// side by side: an MFMA operand is then 4 runs of 16 where instance-major rows
+// made it 16 cache lines, which the vector memory unit takes one by one
+// (both sweeps of 15 instances on 2047 nodes, FP64: 152 us against 140; 64 on 95
+// nodes, FP32: 66 against 58). Bp rounds B up to 16; the extra columns run on zeros.
 //
 // Each instance's state machine (Alg. 3: K0, line search with K1/K2, KM), its
 // Anderson ring and Gram solve (FP64) live on the device: a round is a fixed
@@ -21,7 +25,6 @@
 #include "device_common.h"
 
 #include <algorithm>
-#include <chrono>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -52,19 +55,18 @@ struct Mfma<double> {
 };
 
 constexpr int kShCols = 16;   // instances per MFMA tile
+static_assert(kShCols == kTileCols, "the pre-passes write tiles of this width");
 constexpr int kShWaves = 16;  // wavefronts per workgroup of the sweeps
-constexpr int kShRed = 1024;  // threads of the per-instance reductions
 
 // acc += A[m0 .. m0 + 16)[0 .. nin) X, A input-major (element (out o, in k)
-// at k nout + o), X column j (instance) at x + j * xs, element k at +k;
+// at k nout + o), entry k of X's column j (instance) at x[16 k + j];
 // nin <= 64. The operands of 8 steps (32 inputs) are loaded before their
 // MFMAs, so a chain waits for one round of loads per 32 inputs.
 template <typename S>
 __device__ __forceinline__ void tile_mma(typename Mfma<S>::acc_t& acc, const S* __restrict__ A, int nout, int nin,
-                                         int m0, const S* __restrict__ x, long long xs, int lane) {
+                                         int m0, const S* __restrict__ x, int lane) {
   const int r = lane & 15, kk = lane >> 4;
   const int m = m0 + r;
-  const S* xj = x + (size_t)r * xs;
   for (int k0 = 0; k0 < nin; k0 += 32) {
     S a[8], b[8];
 #pragma unroll
@@ -72,7 +74,7 @@ __device__ __forceinline__ void tile_mma(typename Mfma<S>::acc_t& acc, const S* 
       const int k = k0 + 4 * t + kk;
       const bool in = k < nin;
       a[t] = (in && m < nout) ? A[(size_t)k * nout + m] : S(0);
-      b[t] = in ? xj[k] : S(0);
+      b[t] = in ? x[kShCols * k + r] : S(0);
     }
 #pragma unroll
     for (int t = 0; t < 8; ++t)
@@ -103,12 +105,12 @@ __global__ void __launch_bounds__(256) k_sh_pre(DevProb<S> P, const S* __restric
   const Off<S, IX> O(P);
   const S* z = v + b * vs;
   const S* eta = z + P.nz;
-  const size_t wx = b * (size_t)P.nn * nx, wu = b * (size_t)P.nn * nu;
+  S* const qb = q + tile_base(b, (size_t)P.nn * nx);
   if (i >= P.nl) {
     for (int o = lane; o < nx; o += T) {
       const IX e3 = O.e3(i) + o;
       const S Lt = at<S, IX>(eta, e3) + at<S, IX>(P.sqN, (IX)i * nx + o) * at<S, IX>(eta, e3 + nx);
-      q[wx + (size_t)i * nx + o] = P.alpha * Lt - at<S, IX>(z, O.x(i) + o);
+      qb[((size_t)i * nx + o) * kShCols] = P.alpha * Lt - at<S, IX>(z, O.x(i) + o);
     }
     return;
   }
@@ -117,8 +119,8 @@ __global__ void __launch_bounds__(256) k_sh_pre(DevProb<S> P, const S* __restric
 #pragma unroll
   for (int k = 0; k < SL; ++k) {
     const int o = lane + T * k;
-    if (o < nx) xbar[wx + (size_t)i * nx + o] = bar[k];
-    else if (o < nx + nu) ubar[wu + (size_t)i * nu + (o - nx)] = bar[k];
+    if (o < nx) xbar[tile_base(b, (size_t)P.nn * nx) + ((size_t)i * nx + o) * kShCols] = bar[k];
+    else if (o < nx + nu) ubar[tile_base(b, (size_t)P.nn * nu) + ((size_t)i * nu + (o - nx)) * kShCols] = bar[k];
   }
 }
 
@@ -143,7 +145,7 @@ struct ShSweepArgs {
 
 template <typename S>
 __device__ __forceinline__ void sh_bwd_nodes(const DevProb<S>& P, int i0, int i1, S* q0, S* d0, const S* xb0,
-                                             const S* ub0, long long wx, long long wu, int lane, int wave) {
+                                             const S* ub0, int lane, int wave) {
   using acc_t = typename Mfma<S>::acc_t;
   const int col = lane & 15, kk = lane >> 4;
   const int nx = P.nx, nu = P.nu;
@@ -155,24 +157,24 @@ __device__ __forceinline__ void sh_bwd_nodes(const DevProb<S>& P, int i0, int i1
     acc_t acc = zero_acc<S>();
     if (sub < tu) {  // d^i, rows 16 sub ..
       const int m0 = 16 * sub;
-      tile_mma<S>(acc, P.Rinv + (size_t)i * nu * nu, nu, nu, m0, ub0 + (size_t)i * nu, wu, lane);
+      tile_mma<S>(acc, P.Rinv + (size_t)i * nu * nu, nu, nu, m0, ub0 + (size_t)i * nu * kShCols, lane);
       for (int k = 0; k < n; ++k)
-        tile_mma<S>(acc, P.BtR + (size_t)(fc + k) * nx * nu, nu, nx, m0, q0 + (size_t)(fc + k) * nx, wx, lane);
+        tile_mma<S>(acc, P.BtR + (size_t)(fc + k) * nx * nu, nu, nx, m0, q0 + (size_t)(fc + k) * nx * kShCols, lane);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int m = m0 + Mfma<S>::row(kk, r);
-        if (m < nu) d0[(size_t)col * wu + (size_t)i * nu + m] = acc[r];
+        if (m < nu) d0[((size_t)i * nu + m) * kShCols + col] = acc[r];
       }
     } else {  // q^i
       const int m0 = 16 * (sub - tu);
-      tile_mma<S>(acc, P.P1C + (size_t)i * nu * nx, nx, nu, m0, ub0 + (size_t)i * nu, wu, lane);
+      tile_mma<S>(acc, P.P1C + (size_t)i * nu * nx, nx, nu, m0, ub0 + (size_t)i * nu * kShCols, lane);
       for (int k = 0; k < n; ++k)
-        tile_mma<S>(acc, P.AtR + (size_t)(fc + k) * nx * nx, nx, nx, m0, q0 + (size_t)(fc + k) * nx, wx, lane);
+        tile_mma<S>(acc, P.AtR + (size_t)(fc + k) * nx * nx, nx, nx, m0, q0 + (size_t)(fc + k) * nx * kShCols, lane);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int m = m0 + Mfma<S>::row(kk, r);
         if (m < nx) {
-          const size_t e = (size_t)col * wx + (size_t)i * nx + m;
+          const size_t e = ((size_t)i * nx + m) * kShCols + col;
           q0[e] = acc[r] - xb0[e];
         }
       }
@@ -181,8 +183,8 @@ __device__ __forceinline__ void sh_bwd_nodes(const DevProb<S>& P, int i0, int i1
 }
 
 template <typename S>
-__device__ __forceinline__ void sh_fwd_nodes(const DevProb<S>& P, int i0, int i1, S* z0, const S* d0, long long vs,
-                                             long long wu, int maxch, int lane, int wave) {
+__device__ __forceinline__ void sh_fwd_nodes(const DevProb<S>& P, int i0, int i1, S* z0, S* xt0, const S* d0,
+                                             long long vs, int maxch, int lane, int wave) {
   using acc_t = typename Mfma<S>::acc_t;
   const int col = lane & 15, kk = lane >> 4;
   const int nx = P.nx, nu = P.nu;
@@ -193,27 +195,30 @@ __device__ __forceinline__ void sh_fwd_nodes(const DevProb<S>& P, int i0, int i1
   for (int it = wave; it < items; it += kShWaves) {
     const int i = i0 + it / per, sub = it % per;
     const int fc = P.fc[i], n = P.nch[i];
-    const S* xi = z0 + O.x(i);
-    const S* di = d0 + (size_t)i * nu;
+    const S* xi = xt0 + (size_t)i * nx * kShCols;
+    const S* di = d0 + (size_t)i * nu * kShCols;
     acc_t acc = zero_acc<S>();
     if (sub < tu) {  // u^i
       const int m0 = 16 * sub;
-      tile_mma<S>(acc, P.KC + (size_t)i * nx * nu, nu, nx, m0, xi, vs, lane);
+      tile_mma<S>(acc, P.KC + (size_t)i * nx * nu, nu, nx, m0, xi, lane);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int m = m0 + Mfma<S>::row(kk, r);
-        if (m < nu) z0[(size_t)col * vs + O.u(i) + m] = acc[r] + di[(size_t)col * wu + m];
+        if (m < nu) z0[(size_t)col * vs + O.u(i) + m] = acc[r] + di[m * kShCols + col];
       }
     } else {  // x^c of child k
       const int k = (sub - tu) / tx, m0 = 16 * ((sub - tu) % tx);
       if (k >= n) continue;
       const int c = fc + k;
-      tile_mma<S>(acc, P.AbC + (size_t)c * nx * nx, nx, nx, m0, xi, vs, lane);
-      tile_mma<S>(acc, P.BC + (size_t)c * nu * nx, nx, nu, m0, di, wu, lane);
+      tile_mma<S>(acc, P.AbC + (size_t)c * nx * nx, nx, nx, m0, xi, lane);
+      tile_mma<S>(acc, P.BC + (size_t)c * nu * nx, nx, nu, m0, di, lane);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int m = m0 + Mfma<S>::row(kk, r);
-        if (m < nx) z0[(size_t)col * vs + O.x(c) + m] = acc[r];
+        if (m < nx) {
+          z0[(size_t)col * vs + O.x(c) + m] = acc[r];
+          if (c < P.nl) xt0[((size_t)c * nx + m) * kShCols + col] = acc[r];
+        }
       }
     }
   }
@@ -230,10 +235,11 @@ __global__ void __launch_bounds__(64 * kShWaves) k_sh_sweeps(DevProb<S> P, const
   const int g = blockIdx.x / A.nsub, r = blockIdx.x % A.nsub;  // tile group, subtree
   const size_t b0 = (size_t)g * kShCols;
   const int nx = P.nx, nu = P.nu;
-  const long long wx = (long long)P.nn * nx, wu = (long long)P.nn * nu;
+  const size_t wx = (size_t)P.nn * nx, wu = (size_t)P.nn * nu;
   const Off<S> O(P);
   S* q0 = q + b0 * wx;
   S* d0 = d + b0 * wu;
+  S* xb0 = xbar + b0 * wx;  // xbar in the backward sweep, then x in the forward one
   S* z0 = Tv + b0 * vs;
   // node ranges of the subtree rooted at node stage_off[ta] + r, per stage
   const int levels = A.tb - A.ta;
@@ -248,18 +254,20 @@ __global__ void __launch_bounds__(64 * kShWaves) k_sh_sweeps(DevProb<S> P, const
   if (A.fwd && A.ta == 0) {  // root state of every instance
     for (int e = threadIdx.x; e < kShCols * nx; e += blockDim.x) {
       const int j = e / nx, o = e % nx;
-      z0[(size_t)j * vs + O.x(0) + o] = (S)x0s[(b0 + j) * nx + o];
+      const S x = (S)x0s[(b0 + j) * nx + o];
+      z0[(size_t)j * vs + O.x(0) + o] = x;
+      xb0[(size_t)o * kShCols + j] = x;
     }
   }
   __syncthreads();
   if (!A.fwd) {
     for (int l = levels - 1; l >= 0; --l) {
-      sh_bwd_nodes<S>(P, lo[l], hi[l], q0, d0, xbar + b0 * wx, ubar + b0 * wu, wx, wu, lane, wave);
+      sh_bwd_nodes<S>(P, lo[l], hi[l], q0, d0, xb0, ubar + b0 * wu, lane, wave);
       __syncthreads();
     }
   } else {
     for (int l = 0; l < levels; ++l) {
-      sh_fwd_nodes<S>(P, lo[l], hi[l], z0, d0, vs, wu, A.maxch, lane, wave);
+      sh_fwd_nodes<S>(P, lo[l], hi[l], z0, xb0, d0, vs, A.maxch, lane, wave);
       __syncthreads();
     }
   }
@@ -831,7 +839,7 @@ hipError_t sh_launch_post(const Problem& P, const DevProb<S>& D, const S* v, S* 
 // tiles of d and q) have a wavefront each, so chains
 // and narrow stages stay in one launch and a wide stage is spread over one
 // workgroup per subtree. 2047-node binary tree, n_x = n_u = 20, 15 instances,
-// FP64: both sweeps 155 us in 8 launches (four segments) against 680 us in the 4
+// FP64: both sweeps 140 us in 8 launches (four segments) against 680 us in the 4
 // launches of one cut at stage 3 (8 workgroups below it); the 95-node tree
 // keeps its cut at stage 3. SPOCK_SH_CUT sets one cut instead (0: one launch
 // over the whole tree).
@@ -1276,7 +1284,8 @@ int shared_backward(Problem& P, int B, const void* const* vstar, const double* c
   const bool fused = plan.maxch <= kAdjMaxCh;
   auto partial = [&](const S* w, long long ws) -> int {
     if (fused) {
-      SH_TRY(launch_adj_front<S>(P, vec[kB], w, ws, vec[kLb], vec[kTz], vec[kCz], vec[kLa], xbar, ubar, q, vs, Bp, st));
+      SH_TRY(launch_adj_front<S>(P, vec[kB], w, ws, vec[kLb], vec[kTz], vec[kCz], vec[kLa], xbar, ubar, q, vs, Bp,
+                                 true, st));
       SH_TRY(sh_launch_sweeps<S>(P, D, plan, vec[kLa], x0zero, xbar, ubar, q, d, vs, Bp, st));
       return SPOCK_OK;
     }

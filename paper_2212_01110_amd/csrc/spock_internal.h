@@ -400,7 +400,6 @@ struct BatchSettings {
   double eps_abs, eps_rel;
   int max_iters, method, m, max_ls;
   double c0, c1, c2, beta, sigma, lambda;
-  int write_out;  // 0: leave v_io untouched
 };
 
 // One instance of a batched solve (device-resident descriptor).
@@ -448,11 +447,12 @@ hipError_t launch_adj_load(const Problem& P, double gV, const AdjPtrs<S>* tab, l
 // The transposed operator around the sweeps (w + b ws; the others + b is):
 // lb = J_G w_eta, tz = L* lb, cz = w_z + 2 alpha tz and the pre-pass of J_f cz
 // into la, xbar, ubar, q; after the sweeps out = a v + sg (la - alpha tz, lb -
-// alpha L la) + cg g. Families of at most kAdjMaxCh children.
+// alpha L la) + cg g. Families of at most kAdjMaxCh children. tiles: xbar, ubar
+// and q are those of a shared-tree batch (tile_base), else one after the other.
 constexpr int kAdjMaxCh = 64;
 template <typename S>
 hipError_t launch_adj_front(const Problem& P, const S* bs, const S* w, long long ws, S* lb, S* tz, S* cz, S* la,
-                            S* xbar, S* ubar, S* q, long long is, int B, hipStream_t st);
+                            S* xbar, S* ubar, S* q, long long is, int B, bool tiles, hipStream_t st);
 template <typename S>
 hipError_t launch_adj_back(const Problem& P, double a, const S* v, long long vs, double sg, const S* la, const S* tz,
                            const S* lb, double cg, const S* g, S* out, long long os, long long is, int B,
