@@ -15,8 +15,9 @@ torch = pytest.importorskip("torch")
 
 
 # one lane per state component: one, a partial, a full wavefront; inputs
-# likewise; families of 1 to 5 children
-@pytest.mark.parametrize("nx,nu,br", [(1, 1, [5, 1]), (33, 7, [2, 3]), (64, 3, [1, 2])])
+# likewise; families of 1 to 5 children, and one wider than a wavefront (the
+# separate kernels in place of the fused ones)
+@pytest.mark.parametrize("nx,nu,br", [(1, 1, [5, 1]), (33, 7, [2, 3]), (64, 3, [1, 2]), (2, 1, [70])])
 def test_adjoint_gradients_at_dimension_edges(nx, nu, br):
     # V's gradients by the batched adjoint (three instances, one of them with
     # no u^0 cotangent given) against the envelope formula at the same v*
