@@ -191,14 +191,15 @@ __device__ __forceinline__ void soc_jg_regs(const S (&bv)[2], S (&dv)[2], S ba, 
 // every row of lb and column of tz it needs is its own, but for s of a nonleaf
 // child, whose one row (the child's s-row) it computes again. One launch in
 // place of five (J_G, L*, the combination, the pre-pass, the s^0 copy), which
-// took 26 us per application on the 95-node tree in FP64. n <= 64 children.
+// took 26 us per application on the 95-node tree in FP64. n <= 64 children. The
+// combination is formed in FP64 with the unrounded alpha and rounded once.
 // Arrays of instance b: w at + b ws, the others at + b is.
 template <typename S>
 __global__ void __launch_bounds__(256) k_adj_front(DevProb<S> P, const long long* __restrict__ spos,
                                                    const S* __restrict__ bs, const S* __restrict__ w, long long ws,
                                                    S* __restrict__ lb, S* __restrict__ tz, S* __restrict__ cz,
                                                    S* __restrict__ la, S* __restrict__ xbar, S* __restrict__ ubar,
-                                                   S* __restrict__ q, long long is, int tiles) {
+                                                   S* __restrict__ q, long long is, int tiles, double alpha2) {
   const size_t inst = blockIdx.y;
   const int nx = P.nx, nu = P.nu, K = nx + nu;
   bs += inst * is;
@@ -215,14 +216,15 @@ __global__ void __launch_bounds__(256) k_adj_front(DevProb<S> P, const long long
   ubar += tiles ? tile_base(inst, (size_t)P.nn * nu) : inst * (size_t)P.nn * nu;
   const int lane = threadIdx.x & 63;
   const Off<S> O(P);
-  const S al = P.alpha, ia = S(1) / al, al2 = S(2) * al;
+  const S al = P.alpha, ia = S(1) / al;
   const int i = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (i >= P.nl) return;
   const int fc = P.fc[i], n = P.nch[i];
   const long long e1 = O.e1(i), e1s = e1 + 2LL * n + 1, zb = O.z2(i);
   const bool leaf = fc >= P.nl;
+  auto comb = [&](long long e, S t) { return (S)((double)wz[e] + alpha2 * (double)t); };
   auto put = [&](long long e, S t) {  // one column: tz, cz; returns cz
-    const S c = wz[e] + al2 * t;
+    const S c = comb(e, t);
     tz[e] = t;
     cz[e] = c;
     return c;
@@ -239,10 +241,10 @@ __global__ void __launch_bounds__(256) k_adj_front(DevProb<S> P, const long long
     y2 = put(zb + n + lane, l2);
     if (!leaf) {  // s of child `lane`: its s-row, owned (and stored) by that child's family
       const long long ec = O.e1s(fc + lane);
-      sh = wz[zb + 3LL * n + 1 + lane] + al2 * (bs[ec] <= S(0) ? we[ec] : S(0));
+      sh = comb(zb + 3LL * n + 1 + lane, bs[ec] <= S(0) ? we[ec] : S(0));
     }
   }
-  const S y3 = wz[zb + 2 * n] + al2 * (S(0) - res);
+  const S y3 = comb(zb + 2 * n, S(0) - res);
   if (lane == 0) {
     lb[e1 + 2 * n] = S(0);  // the free entry
     lb[e1s] = res;
@@ -342,10 +344,10 @@ __global__ void __launch_bounds__(256) k_adj_front(DevProb<S> P, const long long
 // alpha L la): A(w) = J_T' w + g with (a, s, c) = (0, 1, 1), the next Krylov
 // vector v - J_T' v (the cotangent cancels) with (1, -1, 0). Wavefronts run
 // over the z entries first, then a family (or more) each for the rows of L la.
-// One launch in place of four (L, three combinations). Bound by the latency of
+// One launch in place of four (L, three combinations); al is the unrounded alpha. Bound by the latency of
 // its loads.
 template <typename S>
-__global__ void __launch_bounds__(256) k_adj_back(DevProb<S> P, double a, const S* __restrict__ v, long long vs,
+__global__ void __launch_bounds__(256) k_adj_back(DevProb<S> P, double al, double a, const S* __restrict__ v, long long vs,
                                                   double sg, const S* __restrict__ la, const S* __restrict__ tz,
                                                   const S* __restrict__ lb, double cg, const S* __restrict__ g,
                                                   S* __restrict__ out, long long os, long long is) {
@@ -359,7 +361,6 @@ __global__ void __launch_bounds__(256) k_adj_back(DevProb<S> P, double a, const 
   const int lane = threadIdx.x & 63;
   const Off<S> O(P);
   const int nx = P.nx, nu = P.nu, K = nx + nu;
-  const double al = (double)P.alpha;
   auto put = [&](long long e, double j) {
     double r = sg * j;
     if (a != 0.0) r += a * (double)v[e];
@@ -556,7 +557,7 @@ hipError_t launch_adj_front(const Problem& P, const S* bs, const S* w, long long
   const DevProb<S>& D = (sizeof(S) == 8) ? *reinterpret_cast<const DevProb<S>*>(&P.dp64)
                                          : *reinterpret_cast<const DevProb<S>*>(&P.dp32);
   hipLaunchKernelGGL(k_adj_front<S>, dim3((P.tree->nl + 3) / 4, B), dim3(256), 0, st, D, P.d_spos, bs, w, ws, lb, tz,
-                     cz, la, xbar, ubar, q, is, tiles ? 1 : 0);
+                     cz, la, xbar, ubar, q, is, tiles ? 1 : 0, 2.0 * P.alpha);
   return hipGetLastError();
 }
 template <typename S>
@@ -565,8 +566,8 @@ hipError_t launch_adj_back(const Problem& P, double a, const S* v, long long vs,
                            hipStream_t st) {
   const DevProb<S>& D = (sizeof(S) == 8) ? *reinterpret_cast<const DevProb<S>*>(&P.dp64)
                                          : *reinterpret_cast<const DevProb<S>*>(&P.dp32);
-  hipLaunchKernelGGL(k_adj_back<S>, dim3(family_wave_blocks(P.tree->nl), B), dim3(256), 0, st, D, a, v, vs, sg, la, tz,
-                     lb, cg, g, out, os, is);
+  hipLaunchKernelGGL(k_adj_back<S>, dim3(family_wave_blocks(P.tree->nl), B), dim3(256), 0, st, D, P.alpha, a, v, vs, sg,
+                     la, tz, lb, cg, g, out, os, is);
   return hipGetLastError();
 }
 template <typename S>
