@@ -473,8 +473,10 @@ struct BlockSolver {
     __syncthreads();
   }
 
-  // Anderson push with MO older columns (as k_aa_push): r, E = dV - dR and dR
-  // of the new column, its Gram row and the right-hand side, then the solve
+  // Anderson push with MO older columns: r, dV and dR of the new column, its
+  // Gram row and the right-hand side, then the solve. dV and dR stay apart: v
+  // and r change little from one iterate to the next, so both differences are
+  // mostly exact, and dV - dR, formed in FP64 with the direction, is too.
   template <int MO>
   __device__ void push(const S* v, const S* Tv, const S* vprev, const S* rprev, S* rcur, const AAPush& a, const AAPush* ap, double* G,
                        double* gamma, AARingDev* ring) const {
@@ -492,7 +494,7 @@ struct BlockSolver {
     map<4 + MO, 3>(in, out, [&](const S(&x)[4 + MO], S(&y)[3]) {
       const S r = x[0] - x[1], dr = r - x[3];
       y[0] = r;
-      y[1] = (S)(((double)x[0] - (double)x[2]) - (double)dr);
+      y[1] = x[0] - x[2];
       y[2] = dr;
 #pragma unroll
       for (int j = 0; j < MO; ++j) {
@@ -527,7 +529,7 @@ struct BlockSolver {
     S* vt = pool(7);
     S* Tvt = pool(8);
     S* spare = pool(9);
-    // Anderson columns of slot j: E at pool(10 + j), dR at pool(10 + kAAMax + j)
+    // Anderson columns of slot j: dV at pool(10 + j), dR at pool(10 + kAAMax + j)
     // x0 must lie in the root's state box
     bool box_ok = true;
     for (int o = 0; o < P.nx; ++o) box_ok = box_ok && x0[o] >= (double)P.xlo[o] && x0[o] <= (double)P.xhi[o];
@@ -641,9 +643,9 @@ struct BlockSolver {
       // residual r = v - T(v), the Anderson push and its Gram solve
       int dk = 0;
       double g[kAAMax] = {0, 0, 0, 0};
-      const S* E[kAAMax];
+      const S *dV[kAAMax], *dR[kAAMax];
 #pragma unroll
-      for (int j = 0; j < kAAMax; ++j) E[j] = rcur;
+      for (int j = 0; j < kAAMax; ++j) dV[j] = dR[j] = rcur;
       if (have_prev) {
         if (threadIdx.x == 0) next = aa_next_push(&ring);
         __syncthreads();
@@ -659,7 +661,8 @@ struct BlockSolver {
         for (int j = 0; j < kAAMax; ++j)
           if (j < dk) {
             g[j] = gamma[j];
-            E[j] = pool(10 + ring.dslot[j]);
+            dV[j] = pool(10 + ring.dslot[j]);
+            dR[j] = pool(10 + kAAMax + ring.dslot[j]);
           }
       } else {
         const S* in[2] = {v, Tv};
@@ -668,27 +671,31 @@ struct BlockSolver {
       }
       omega = Sc.omega();
       const bool k0 = omega <= s.c0 * zeta;
-      // d = -r - sum_j gamma_j E_j and the next point v + d (the K0 step, or
+      // d = -r - sum_j gamma_j (dV_j - dR_j) and the next point v + d (the K0 step, or
       // the first candidate of the line search, which keeps d as well)
       auto direction = [&](auto DK) {
         constexpr int D = decltype(DK)::value;
-        const S* in[2 + D];
+        constexpr int NI = 2 + 2 * D;
+        const S* in[NI];
         in[0] = rcur;
         in[1] = v;
 #pragma unroll
-        for (int j = 0; j < D; ++j) in[2 + j] = E[j];
-        auto one = [&](const S(&x)[2 + D]) {
+        for (int j = 0; j < D; ++j) {
+          in[2 + j] = dV[j];
+          in[2 + D + j] = dR[j];
+        }
+        auto one = [&](const S(&x)[NI]) {
           double acc = -(double)x[0];
 #pragma unroll
-          for (int j = 0; j < D; ++j) acc -= g[j] * (double)x[2 + j];
+          for (int j = 0; j < D; ++j) acc -= g[j] * ((double)x[2 + j] - (double)x[2 + D + j]);
           return (S)acc;
         };
         if (k0) {
           S* o1[1] = {spare};
-          map<2 + D, 1>(in, o1, [&](const S(&x)[2 + D], S(&y)[1]) { y[0] = (S)((double)x[1] + (double)one(x)); });
+          map<NI, 1>(in, o1, [&](const S(&x)[NI], S(&y)[1]) { y[0] = (S)((double)x[1] + (double)one(x)); });
         } else {
           S* o2[2] = {vt, dir};
-          map<2 + D, 2>(in, o2, [&](const S(&x)[2 + D], S(&y)[2]) {
+          map<NI, 2>(in, o2, [&](const S(&x)[NI], S(&y)[2]) {
             y[1] = one(x);
             y[0] = (S)((double)x[1] + (double)y[1]);
           });

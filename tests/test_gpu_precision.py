@@ -50,3 +50,34 @@ def test_adjoint_combinations_are_formed_in_fp64(tiles):
         assert back(gp.handle, a, p(v), gp.n_v, s, p(la), p(tz), p(lb), c, p(g), p(out), gp.n_v, gp.n_v, B, None) == 0
         hv, hl, hg = (_f32(t)[:, z].astype(np.float64) for t in (v, la, g))
         assert np.array_equal(_f32(out)[:, z], (a * hv + s * (hl - gp.alpha * ht) + c * hg).astype(np.float32))
+
+
+@pytest.mark.parametrize("nx,nu,br", [(5, 3, [2, 2, 1]), (20, 10, [2, 1, 2]), (40, 30, [2, 1])])
+def test_block_engine_direction_subtracts_its_columns_in_fp64(nx, nu, br):
+    # d = -r - gamma (dV - dR) from the FP32 columns dV and dR, subtracted in
+    # FP64. With c0 huge every step is K0 (v + d), so the second iterate follows
+    # in numpy from the engine's own T(v^0) and T(v^1); T of it must be, bit for
+    # bit, what the engine returns after two iterations. gamma's sums differ
+    # from numpy's in their order: 1e-16 relative, far below a rounding of d
+    inst = G.make_random_small(41, br, nx, nu, a=0.5)
+    gp = SP.Problem.from_instance(inst, precision=SP.FP32)
+    x0 = dev(0.9 * inst.x0 / max(1.0, np.max(np.abs(inst.x0))), torch.float64)
+
+    def engine(v, iters):
+        t = torch.as_tensor(v, device="cuda").clone()
+        s = SP.default_settings(eps_abs=1e-30, eps_rel=0.0, max_iters=iters, c0=1e30)
+        info, = SP.solve_batched([gp], [x0], [t], s)
+        assert info["iters"] == iters and info["t_evals"] == iters + 1
+        return _f32(t)
+
+    v0 = np.random.default_rng(nx).standard_normal(gp.n_v).astype(np.float32)
+    r0 = v0 - engine(v0, 0)
+    v1 = v0 - r0
+    T1 = engine(v1, 0)
+    assert np.array_equal(T1, engine(v0, 1))
+    r1 = v1 - T1
+    dV, dR = (v1 - v0).astype(np.float64), (r1 - r0).astype(np.float64)
+    gamma = (dR @ r1.astype(np.float64)) / (dR @ dR)
+    d1 = (-r1.astype(np.float64) - gamma * (dV - dR)).astype(np.float32)
+    v2 = (v1.astype(np.float64) + d1).astype(np.float32)
+    assert np.array_equal(engine(v2, 0), engine(v0, 2))
