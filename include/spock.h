@@ -167,11 +167,14 @@ int spock_problem_destroy(spock_problem* prob);
 /* sizes and step: n_z, n_eta, alpha and ||L|| (any pointer may be NULL) */
 int spock_problem_sizes(const spock_problem* prob, int64_t* n_z, int64_t* n_eta,
                         double* alpha, double* norm_L);
-/* The family-to-lane mapping the next evaluation of T will use (as
- * spock_info.mapping), the workgroups of the dataflow launch (0 for the
+/* The family-to-lane mapping the next spock_T will use (as
+ * spock_info.mapping), the workgroups of its dataflow launch (0 for the
  * other mappings) and whether the dataflow form has been given up for this
- * problem (1) after one of its bounded waits gave up. Any pointer may be
- * NULL. Errors: SPOCK_EINVAL. */
+ * problem (1) after one of its bounded waits gave up. On an FP32 problem,
+ * spock_T keeps the mapping chosen without the walk form of the sweeps (one
+ * launch, reported as 512), which spock_solve, spock_prox_f and
+ * spock_backward run where it measured faster: spock_info.mapping says what
+ * these ran. Any pointer may be NULL. Errors: SPOCK_EINVAL. */
 int spock_problem_mapping(const spock_problem* prob, int32_t* mapping, int32_t* flow_grid,
                           int32_t* flow_failed);
 
@@ -286,19 +289,21 @@ int spock_backward_batched(spock_problem* prob, int32_t B, const void* const* v_
                            void* stream);
 
 /* ---------------------------------------------------------------------------
- * Per-operator entry points (same kernels as the solver; used for operator
- * parity). All vectors are device arrays of the problem precision.
+ * Per-operator entry points (same kernels as the solver, but for the sweeps
+ * of an FP32 spock_T: see spock_problem_mapping; used for operator parity).
+ * All vectors are device arrays of the problem precision.
  * ------------------------------------------------------------------------- */
 /* eta_dev[n_eta] = L z_dev[n_z] (section 5.2, definition of L) */
 int spock_apply_L(spock_problem* prob, const void* z_dev, void* eta_dev, void* stream);
 /* z_dev[n_z] = L* eta_dev[n_eta], the adjoint of L */
 int spock_apply_Lt(spock_problem* prob, const void* eta_dev, void* z_dev, void* stream);
 /* zout_dev = prox_{alpha f}(zin_dev) (section 5.3): s^0 - alpha, projection on
- * S1 with root state x0_dev (Alg. 2), projection on S2. With the dataflow
- * mapping (512) this call and spock_T wait until the sweeps' error word has
- * reached the host (their work on the stream is then complete); if a bounded
- * wait gave up they switch the problem to the per-stage form and evaluate
- * again. */
+ * S1 with root state x0_dev (Alg. 2), projection on S2. When the solver's
+ * sweeps are one launch whose workgroups wait for each other
+ * (spock_info.mapping 512), this call waits until their error word has
+ * reached the host (its work on the stream is then complete); if a bounded
+ * wait gave up it switches the problem to the per-stage form and evaluates
+ * again. spock_T does the same when spock_problem_mapping gives 512. */
 int spock_prox_f(spock_problem* prob, const void* zin_dev, const double* x0_dev,
                  void* zout_dev, void* stream);
 /* out_dev = prox_{alpha g*}(w_dev) = w - alpha proj_S3(w / alpha) (section 5.4) */

@@ -280,7 +280,7 @@ class Problem:
                    getattr(inst, "Qm", None), getattr(inst, "Rm", None), getattr(inst, "QNm", None))
 
     def mapping(self) -> dict:
-        """Mapping the next evaluation of T uses, the dataflow grid, and
+        """Mapping the next call of T uses, its dataflow grid, and
         whether the dataflow form was given up for this problem."""
         m, g, f = ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int32()
         _check(lib().spock_problem_mapping(self.handle, ctypes.byref(m), ctypes.byref(g), ctypes.byref(f)),

@@ -428,7 +428,16 @@ void set_mapping(Problem& P, int team, int cut) {
 
 // The mapping that a call reports: both forms whose workgroups pass values on
 // are the dataflow mapping.
-int reported_team(const Problem& P) { return P.walk_on ? kTeamFlow : P.team; }
+int reported_team(const Problem& P, const SweepMap& m = SweepMap{}) { return sweeps_wait(P, m) ? kTeamFlow : P.team; }
+
+// The sweeps of spock_T. In FP32 the statistics, FP64 sums over the FP32
+// residual, show the last bits of the sweeps: the call keeps the order of sums
+// of the tuned mapping, without the walk form.
+SweepMap operator_T_map(const Problem& P) {
+  SweepMap m;
+  m.keep = P.precision == SPOCK_FP32;
+  return m;
+}
 
 // Default cut: the first stage with at least 256 nodes (enough subtrees to
 // fill the device), or none.
@@ -612,9 +621,11 @@ extern "C" int spock_problem_sizes(const spock_problem* p, int64_t* nz, int64_t*
 extern "C" int spock_problem_mapping(const spock_problem* p, int32_t* mapping, int32_t* flow_grid,
                                      int32_t* flow_failed) {
   if (!p) return SPOCK_EINVAL;
-  if (mapping) *mapping = reported_team(p->p);
-  if (flow_grid) *flow_grid = p->p.walk_on ? p->p.walk.grid : p->p.team == kTeamFlow ? p->p.flow.grid : 0;
-  if (flow_failed) *flow_failed = p->p.flow_failed ? 1 : 0;
+  const Problem& P = p->p;
+  const SweepMap m = operator_T_map(P);
+  if (mapping) *mapping = reported_team(P, m);
+  if (flow_grid) *flow_grid = !sweeps_wait(P, m) ? 0 : P.walk_on && !m.keep ? P.walk.grid : P.flow.grid;
+  if (flow_failed) *flow_failed = P.flow_failed ? 1 : 0;
   return SPOCK_OK;
 }
 
@@ -1766,11 +1777,7 @@ int T_impl(Problem& P, const S* v, const double* x0, S* Tv, double* stats, hipSt
   Work<S> W;
   int rc = ensure_work<S>(P, W);
   if (rc) return rc;
-  // In FP32 the statistics, FP64 sums over the FP32 residual, show the last
-  // bits of the sweeps: this call keeps the order of sums of the tuned mapping,
-  // without the walk form.
-  SweepMap map;
-  map.keep = sizeof(S) == 4;
+  const SweepMap map = operator_T_map(P);
   const bool wait = stats || sweeps_wait(P, map);
   const Publish pub = wait ? Publish{P.mbox_dev, ++P.mbox_epoch} : Publish{};
   HIP_TRY(launch_T<S>(P, v, Tv, x0, W.q, W.d, W.xbar, W.ubar, W.partials, W.stats, st, W.eta_zero, true, pub, map));
