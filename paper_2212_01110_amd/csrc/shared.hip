@@ -90,29 +90,16 @@ __device__ __forceinline__ typename Mfma<S>::acc_t zero_acc() {
 }
 
 // ---------------------------------------------------------------- T on B instances
-// How many of the n instances have ended, counted on the device (null: not
-// asked). The host learns it one round late, so a round may be queued that
-// nobody needs: its evaluation of T then ends at once (two instances on a chain
-// of 100 stages, n_x 4, FP32, 435 us a round: 2.72 ms for four iterations with
-// the unneeded evaluation). The count is read beside the first index loads.
-struct ShDone {
-  const unsigned* count;
-  unsigned n;
-  __device__ __forceinline__ bool all() const { return count && *count >= n; }
-};
-
 // pre-pass of every (unit, instance): a team of T lanes per family or leaf
 // (flat_pre_family; q = -xbar at a leaf). IX: 32-bit offsets while one
 // instance's iterate and the node arrays stay below 4 GiB.
 template <typename S, int T, int SL, typename IX>
 __global__ void __launch_bounds__(256) k_sh_pre(DevProb<S> P, const S* __restrict__ v, S* __restrict__ Tv,
                                                 S* __restrict__ xbar, S* __restrict__ ubar, S* __restrict__ q,
-                                                long long vs, ShDone done) {
+                                                long long vs) {
   const int lane = threadIdx.x % T;
   const int i = blockIdx.x * (256 / T) + threadIdx.x / T;
   if (i >= P.nn) return;  // whole teams only; no block barrier below
-  const int fc = P.fc[i], n = P.nch[i];
-  if (done.all()) return;
   const size_t b = blockIdx.y;
   const int nx = P.nx, nu = P.nu;
   const Off<S, IX> O(P);
@@ -128,7 +115,7 @@ __global__ void __launch_bounds__(256) k_sh_pre(DevProb<S> P, const S* __restric
     return;
   }
   S bar[SL];
-  flat_pre_family<S, T, SL, IX>(P, O, z, eta, Tv + b * vs, i, fc, n, lane, bar);
+  flat_pre_family<S, T, SL, IX>(P, O, z, eta, Tv + b * vs, i, P.fc[i], P.nch[i], lane, bar);
 #pragma unroll
   for (int k = 0; k < SL; ++k) {
     const int o = lane + T * k;
@@ -149,11 +136,22 @@ __global__ void __launch_bounds__(256) k_sh_pre(DevProb<S> P, const S* __restric
 // are independent down to stage tb - 1, so a launch runs one workgroup per
 // (tile group, node of stage ta) over its part of the segment, bottom-up
 // (backward) or top-down (forward); the segments run in order, so that the
-// wide stages spread over the compute units.
+// wide stages spread over the compute units. A tree of one segment runs both
+// sweeps in one launch.
+//
+// The host learns one round late that every instance has ended, so a round may
+// be queued that nobody needs: its sweeps end at once when *count (instances
+// that have ended) reaches all. One wavefront reads the count while another
+// finds the node ranges, so that the check adds nothing to a launch (read by
+// every wavefront it took 0.2 us of 14).
+struct ShDone {
+  const unsigned* count;
+  unsigned all;
+};
 constexpr int kShMaxLevels = 128;  // stages of a segment a workgroup keeps in LDS
 
 struct ShSweepArgs {
-  int maxch, fwd, ta, tb, nsub;  // nsub: nodes of stage ta (subtrees per tile group)
+  int maxch, ta, tb, nsub;  // nsub: nodes of stage ta (subtrees per tile group)
 };
 
 template <typename S>
@@ -237,13 +235,16 @@ __device__ __forceinline__ void sh_fwd_nodes(const DevProb<S>& P, int i0, int i1
   }
 }
 
-template <typename S>
+// DIR: 1 backward, 2 forward, 3 both (builds of their own: one that can do both,
+// told at run time, took 0.4 us a launch more)
+template <typename S, int DIR>
 __global__ void __launch_bounds__(64 * kShWaves) k_sh_sweeps(DevProb<S> P, const int* __restrict__ stage_off,
                                                               S* __restrict__ Tv, const double* __restrict__ x0s,
                                                               S* __restrict__ xbar, S* __restrict__ ubar,
                                                               S* __restrict__ q, S* __restrict__ d, long long vs,
                                                               ShSweepArgs A, ShDone done) {
   __shared__ int lo[kShMaxLevels], hi[kShMaxLevels];
+  __shared__ unsigned ended;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int g = blockIdx.x / A.nsub, r = blockIdx.x % A.nsub;  // tile group, subtree
   const size_t b0 = (size_t)g * kShCols;
@@ -256,7 +257,7 @@ __global__ void __launch_bounds__(64 * kShWaves) k_sh_sweeps(DevProb<S> P, const
   S* z0 = Tv + b0 * vs;
   // node ranges of the subtree rooted at node stage_off[ta] + r, per stage
   const int levels = A.tb - A.ta;
-  const bool idle = done.all();
+  if (threadIdx.x == 64) ended = *done.count;
   if (threadIdx.x == 0) {
     lo[0] = stage_off[A.ta] + r;
     hi[0] = lo[0] + 1;
@@ -265,22 +266,28 @@ __global__ void __launch_bounds__(64 * kShWaves) k_sh_sweeps(DevProb<S> P, const
       hi[l] = P.fc[hi[l - 1] - 1] + P.nch[hi[l - 1] - 1];
     }
   }
-  if (A.fwd && A.ta == 0) {  // root state of every instance
+  auto root = [&]() {  // root state of every instance, in xbar's place
     for (int e = threadIdx.x; e < kShCols * nx; e += blockDim.x) {
       const int j = e / nx, o = e % nx;
       const S x = (S)x0s[(b0 + j) * nx + o];
       z0[(size_t)j * vs + O.x(0) + o] = x;
       xb0[(size_t)o * kShCols + j] = x;
     }
-  }
+  };
+  if (DIR == 2 && A.ta == 0) root();
   __syncthreads();
-  if (idle) return;
-  if (!A.fwd) {
+  if (ended >= done.all) return;
+  if (DIR & 1) {
     for (int l = levels - 1; l >= 0; --l) {
       sh_bwd_nodes<S>(P, lo[l], hi[l], q0, d0, xb0, ubar + b0 * wu, lane, wave);
       __syncthreads();
     }
-  } else {
+  }
+  if (DIR == 3) {
+    root();
+    __syncthreads();
+  }
+  if (DIR & 2) {
     for (int l = 0; l < levels; ++l) {
       sh_fwd_nodes<S>(P, lo[l], hi[l], z0, xb0, d0, vs, A.maxch, lane, wave);
       __syncthreads();
@@ -293,7 +300,7 @@ __global__ void __launch_bounds__(64 * kShWaves) k_sh_sweeps(DevProb<S> P, const
 template <typename S, int T, int SL, typename IX>
 __global__ void __launch_bounds__(256) k_sh_post(DevProb<S> P, const long long* __restrict__ spos,
                                                  const S* __restrict__ v, S* __restrict__ Tv, long long vs,
-                                                 double* __restrict__ partials, ShDone done) {
+                                                 double* __restrict__ partials) {
   const int lane = threadIdx.x % T;
   const int i = blockIdx.x * (256 / T) + threadIdx.x / T;
   const size_t b = blockIdx.y;
@@ -302,17 +309,15 @@ __global__ void __launch_bounds__(256) k_sh_post(DevProb<S> P, const long long* 
   S* zo = Tv + b * vs;
   S* eo = zo + P.nz;
   const Off<S, IX> O(P);
-  const int u = i < P.nn ? i : 0, fc = P.fc[u], n = P.nch[u];
-  const IX sp = (IX)spos[u];
-  if (done.all()) return;
   StatAcc st;
   if (i < P.nl) {
     const IX xi = O.x(i), ui = O.u(i);
-    flat_family<S, T, SL, IX>(P, O, sp, z, eta, zo, eo, i, fc, n, lane,
+    flat_family<S, T, SL, IX>(P, O, (IX)spos[i], z, eta, zo, eo, i, P.fc[i], P.nch[i], lane,
                               [&](int k) { return at<S, IX>(zo, k < P.nx ? xi + k : ui + (k - P.nx)); }, st);
   } else if (i < P.nn) {
     const IX xj = O.x(i);
-    flat_leaf<S, T, SL, IX>(P, O, sp, z, eta, zo, eo, i, lane, [&](int k) { return at<S, IX>(zo, xj + k); }, st);
+    flat_leaf<S, T, SL, IX>(P, O, (IX)spos[i], z, eta, zo, eo, i, lane, [&](int k) { return at<S, IX>(zo, xj + k); },
+                            st);
   }
   const double w[kStats] = {team_sum<64>(st.rz2), team_sum<64>(st.re2), team_sum<64>(st.cross), wave_max(st.xip),
                             wave_max(st.xid)};
@@ -817,9 +822,9 @@ int sh_post_blocks(const Problem& P) {
 
 template <typename S>
 hipError_t sh_launch_pre(const Problem& P, const DevProb<S>& D, const S* in, S* out, S* xbar, S* ubar, S* q,
-                         long long vs, int Bp, hipStream_t st, ShDone done = ShDone{}) {
+                         long long vs, int Bp, hipStream_t st) {
   const dim3 grid(sh_post_blocks(P), Bp);
-  auto go = [&](auto k) { hipLaunchKernelGGL(k, grid, dim3(256), 0, st, D, in, out, xbar, ubar, q, vs, done); };
+  auto go = [&](auto k) { hipLaunchKernelGGL(k, grid, dim3(256), 0, st, D, in, out, xbar, ubar, q, vs); };
   const bool nar = sh_narrow<S>(P);
   switch (sh_team(P)) {
     case 8: nar ? go(k_sh_pre<S, 8, 1, unsigned>) : go(k_sh_pre<S, 8, 1, long long>); break;
@@ -835,9 +840,9 @@ hipError_t sh_launch_pre(const Problem& P, const DevProb<S>& D, const S* in, S* 
 
 template <typename S>
 hipError_t sh_launch_post(const Problem& P, const DevProb<S>& D, const S* v, S* Tv, long long vs, double* partials,
-                          int Bp, hipStream_t st, ShDone done) {
+                          int Bp, hipStream_t st) {
   const dim3 grid(sh_post_blocks(P), Bp);
-  auto go = [&](auto k) { hipLaunchKernelGGL(k, grid, dim3(256), 0, st, D, P.d_spos, v, Tv, vs, partials, done); };
+  auto go = [&](auto k) { hipLaunchKernelGGL(k, grid, dim3(256), 0, st, D, P.d_spos, v, Tv, vs, partials); };
   const bool nar = sh_narrow<S>(P);
   switch (sh_team(P)) {
     case 8: nar ? go(k_sh_post<S, 8, 1, unsigned>) : go(k_sh_post<S, 8, 1, long long>); break;
@@ -904,15 +909,20 @@ ShPlan sh_plan(const Problem& P) {
 }
 template <typename S>
 hipError_t sh_launch_sweeps(const Problem& P, const DevProb<S>& D, const ShPlan& L, S* Tv, const double* x0s, S* xbar,
-                            S* ubar, S* q, S* d, long long vs, int Bp, hipStream_t st, ShDone done = ShDone{}) {
+                            S* ubar, S* q, S* d, long long vs, int Bp, hipStream_t st, ShDone done) {
   const Tree& Tr = *P.tree;
   const int groups = Bp / kShCols, segs = (int)L.cut.size() - 1;
-  for (int j = 0; j < 2 * segs; ++j) {
-    const int fwd = j >= segs, k = fwd ? j - segs : segs - 1 - j;
+  auto launch = [&](auto kernel, int k) {
     const int ta = L.cut[k], nsub = Tr.stage_off[ta + 1] - Tr.stage_off[ta];
-    const ShSweepArgs A{L.maxch, fwd, ta, L.cut[k + 1], nsub};
-    hipLaunchKernelGGL(k_sh_sweeps<S>, dim3(groups * nsub), dim3(64 * kShWaves), 0, st, D, P.d_stage_off, Tv, x0s, xbar,
-                       ubar, q, d, vs, A, done);
+    const ShSweepArgs A{L.maxch, ta, L.cut[k + 1], nsub};
+    hipLaunchKernelGGL(kernel, dim3(groups * nsub), dim3(64 * kShWaves), 0, st, D, P.d_stage_off, Tv, x0s, xbar, ubar, q,
+                       d, vs, A, done);
+  };
+  if (segs == 1) {
+    launch(k_sh_sweeps<S, 3>, 0);
+  } else {
+    for (int k = segs - 1; k >= 0; --k) launch(k_sh_sweeps<S, 1>, k);
+    for (int k = 0; k < segs; ++k) launch(k_sh_sweeps<S, 2>, k);
   }
   return hipGetLastError();
 }
@@ -1036,9 +1046,9 @@ int shared_solve(Problem& P, int B, const double* const* x0, const spock_setting
     }
   };
   for (unsigned long long r = 1;; ++r) {
-    SH_TRY(sh_launch_pre<S>(P, D, V.vt, V.tvt, xbar, ubar, q, vs, Bp, st, ended));
+    SH_TRY(sh_launch_pre<S>(P, D, V.vt, V.tvt, xbar, ubar, q, vs, Bp, st));
     SH_TRY(sh_launch_sweeps<S>(P, D, plan, V.tvt, x0s, xbar, ubar, q, d, vs, Bp, st, ended));
-    SH_TRY(sh_launch_post<S>(P, D, V.vt, V.tvt, vs, partials, Bp, st, ended));
+    SH_TRY(sh_launch_post<S>(P, D, V.vt, V.tvt, vs, partials, Bp, st));
     if (!S3.cp) hipLaunchKernelGGL(k_sh_rdot<S>, vgrid, dim3(256), 0, st, V, state, rdots);
     hipLaunchKernelGGL(k_sh_judge, dim3(B), dim3(256), 0, st, state, S3, partials, nblk, rdots, vblk, P.alpha, done);
     hipLaunchKernelGGL(k_sh_commit<S>, vgrid, dim3(256), 0, st, V, state, S3.cp, dots);
@@ -1286,11 +1296,13 @@ int shared_backward(Problem& P, int B, const void* const* vstar, const double* c
                         gx0[b], gq ? gq[b] : nullptr, gqN ? gqN[b] : nullptr};
   SH_TRY(hipMemcpyAsync(tab_d, tab.data(), sizeof(AdjPtrs<S>) * B, hipMemcpyHostToDevice, st));
   SH_TRY(launch_adj_load<S>(P, gV, tab_d, vs, B, vec[kV], x0s, vec[kG], vec[kW], st));
+  // (every sweep runs: any word below the largest)
+  const ShDone never{reinterpret_cast<const unsigned*>(P.d_stage_off), ~0u};
   // prox_f of the instances: pre-pass, then the sweeps
   const ShPlan plan = sh_plan(P);
   auto prox = [&](S* in, S* out, const double* xs0) -> int {
     SH_TRY(sh_launch_pre<S>(P, D, in, out, xbar, ubar, q, vs, Bp, st));
-    SH_TRY(sh_launch_sweeps<S>(P, D, plan, out, xs0, xbar, ubar, q, d, vs, Bp, st));
+    SH_TRY(sh_launch_sweeps<S>(P, D, plan, out, xs0, xbar, ubar, q, d, vs, Bp, st, never));
     return SPOCK_OK;
   };
   // pre-prox point of the dual update at v*: b* = eta* + alpha L (2 z+ - z*)
@@ -1304,7 +1316,7 @@ int shared_backward(Problem& P, int B, const void* const* vstar, const double* c
     if (fused) {
       SH_TRY(launch_adj_front<S>(P, vec[kB], w, ws, vec[kLb], vec[kTz], vec[kCz], vec[kLa], xbar, ubar, q, vs, Bp,
                                  true, st));
-      SH_TRY(sh_launch_sweeps<S>(P, D, plan, vec[kLa], x0zero, xbar, ubar, q, d, vs, Bp, st));
+      SH_TRY(sh_launch_sweeps<S>(P, D, plan, vec[kLa], x0zero, xbar, ubar, q, d, vs, Bp, st, never));
       return SPOCK_OK;
     }
     if (w != vec[kIn])

@@ -39,3 +39,21 @@ def test_no_evaluation_after_the_last_instance_ended(prec):
     t0, t10 = seconds(0), seconds(10)
     evaluation = (t10 - t0) / 10
     assert t0 < 1.6 * evaluation, (t0, evaluation)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("nx,nu,br", [(4, 2, [1] * 9), (20, 10, [2, 2, 1]), (33, 17, [3]), (2, 1, [2, 1] * 2)])
+def test_one_launch_of_both_sweeps_gives_the_bits_of_two(nx, nu, br, prec, monkeypatch):
+    # a tree of one segment of stages runs both sweeps in one launch; cut in two
+    # segments, every sweep is a launch each: the same sums in the same order
+    inst = G.make_random_small(62 + nx, br, nx, nu)
+    gp = SP.Problem.from_instance(inst, precision=SP.FP64 if prec == "fp64" else SP.FP32)
+    x0s = [dev(s * inst.x0 / max(1.0, np.max(np.abs(inst.x0))), torch.float64) for s in np.linspace(-0.9, 0.9, 17)]
+    out = {}
+    for cut in ("0", "1"):
+        monkeypatch.setenv("SPOCK_SH_CUT", cut)
+        vs = [torch.full((gp.n_v,), 0.1, dtype=gp.torch_dtype, device="cuda") for _ in x0s]
+        s = SP.default_settings(eps_abs=1e-30, eps_rel=0.0, max_iters=5)
+        infos = SP.solve_batched([gp] * len(x0s), x0s, vs, s)
+        out[cut] = (torch.stack(vs), [i["t_evals"] for i in infos])
+    assert out["0"][1] == out["1"][1] and torch.equal(out["0"][0], out["1"][0])
