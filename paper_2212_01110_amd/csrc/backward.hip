@@ -222,7 +222,9 @@ __global__ void __launch_bounds__(256) k_adj_front(DevProb<S> P, const long long
   const int fc = P.fc[i], n = P.nch[i];
   const long long e1 = O.e1(i), e1s = e1 + 2LL * n + 1, zb = O.z2(i);
   const bool leaf = fc >= P.nl;
-  auto comb = [&](long long e, S t) { return (S)((double)wz[e] + alpha2 * (double)t); };
+  // (an FP64 problem's alpha is the unrounded one: no argument held for it)
+  const double al2 = sizeof(S) == 8 ? 2.0 * (double)al : alpha2;
+  auto comb = [&](long long e, S t) { return (S)((double)wz[e] + al2 * (double)t); };
   auto put = [&](long long e, S t) {  // one column: tz, cz; returns cz
     const S c = comb(e, t);
     tz[e] = t;

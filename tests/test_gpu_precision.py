@@ -7,7 +7,7 @@ import pytest
 
 import paper_2212_01110_amd as SP
 import spock_gen as G
-from tests.gpu_util import dev
+from tests.gpu_util import check, dev
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -81,3 +81,25 @@ def test_block_engine_direction_subtracts_its_columns_in_fp64(nx, nu, br):
     d1 = (-r1.astype(np.float64) - gamma * (dV - dR)).astype(np.float32)
     v2 = (v1.astype(np.float64) + d1).astype(np.float32)
     assert np.array_equal(engine(v2, 0), engine(v0, 2))
+
+
+@pytest.mark.parametrize("nx,nu,br", [(1, 1, [5, 1]), (33, 7, [2, 3]), (64, 3, [1, 2]), (2, 1, [70])])
+def test_fp32_adjoint_against_fp64_at_dimension_edges(nx, nu, br):
+    # the same point v*, cast to FP32, through the FP32 and the FP64 adjoint;
+    # adjoint tolerance and bound are those of the FP32 gradients of the 95-node
+    # workload (1e-7 and 1e-4)
+    inst = G.make_random_small(300 + nx, br, nx, nu, a=0.5, box=50.0)
+    g64 = SP.Problem.from_instance(inst, precision=SP.FP64)
+    g32 = SP.Problem.from_instance(inst, precision=SP.FP32, alpha=g64.alpha)
+    x0 = dev(inst.x0 / np.max(np.abs(inst.x0)), torch.float64)
+    v = torch.zeros(g64.n_v, dtype=torch.float64, device="cuda")
+    info = g64.solve(x0, v, SP.default_settings(eps_abs=1e-11, eps_rel=1e-11, max_iters=400000))
+    assert info["status"] == "converged", info
+    ref = g64.backward(v, x0)
+    s = SP.default_settings(eps_abs=1e-7, max_iters=400000)
+    one = g32.backward(v.float(), x0, settings=s)
+    two = SP.backward_batched(g32, [v.float()] * 2, [x0] * 2, settings=s)
+    for got in (one, *two):
+        assert got[3]["status"] == "converged", got[3]
+        for a, b in zip(got[:3], ref[:3]):
+            check(f"edge_fp32_adjoint:{nx}", float((a - b).abs().max() / max(1.0, float(b.abs().max()))), 1e-4)
