@@ -742,7 +742,11 @@ int place_flow(Problem& P, FlowState& F, const void* kernel, int waves, int lds,
   const size_t npw = (size_t)nslots * (P.nx + P.nu) * tw;
   const size_t tagged = sizeof(unsigned long long) * (nq + nd + nxw + npw);
   const size_t bytes = tagged + sizeof(int) * (items.size() + pbase.size());
-  if (hipMalloc(&F.mem, bytes) != hipSuccess) return SPOCK_ENOMEM;
+  if (hipMalloc(&F.mem, bytes) != hipSuccess) {
+    (void)hipGetLastError();  // the tuning goes on without this form: its launches must not report the error
+    F.mem = nullptr;
+    return SPOCK_ENOMEM;
+  }
   if (hipMemset(F.mem, 0, bytes) != hipSuccess) return SPOCK_EHIP;
   F.qt = static_cast<unsigned long long*>(F.mem);
   F.dt = F.qt + nq;
