@@ -667,9 +667,13 @@ def main():
     Tv = torch.empty_like(v)
     prof = gp.profile_T(v, x0, Tv, reps=args.t_reps)
     itemsize = 4 if prec == SP.FP32 else 8
-    kname = "k_T_flow (both Alg. 2 sweeps, one launch)" if info["mapping"] == 512 else \
-        "per-stage backward/forward sweep launches"
-    traffic = measured_traffic() if (args.config == 3 and prec == SP.FP32 and info["mapping"] == 512) else None
+    # the mapping of T itself, which the phase timing runs: one launch is k_T_flow in FP32, and in FP64 k_T_walk
+    # where that form measured faster (not on the 20 776-node tree, where it is not tried)
+    one_launch = gp.mapping()["mapping"] == 512
+    kname = "per-stage backward/forward sweep launches" if not one_launch else \
+        "k_T_flow (both Alg. 2 sweeps, one launch)" if prec == SP.FP32 or args.config == 3 else \
+        "k_T_flow or k_T_walk (both Alg. 2 sweeps, one launch)"
+    traffic = measured_traffic() if (args.config == 3 and prec == SP.FP32 and one_launch) else None
     roof = {"bound": "hbm", "peak": HBM_PEAK_GBS, "unit": "GB/s", "traffic": traffic, "kernel": kname}
     roof.update(roofline_of(prof, inst, itemsize))
     log(f"T phases (us): {prof}; sweeps {roof['achieved']} GB/s ({roof['frac']}), whole T {roof['T_whole_frac']}")

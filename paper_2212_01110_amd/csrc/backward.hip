@@ -520,7 +520,6 @@ __global__ void k_max_final(const double* __restrict__ partials, int nblk, doubl
   out[0] = m;
 }
 
-__global__ void k_copy_elem_d(double* dst, const double* src) { dst[0] = src[0]; }
 template <typename S>
 __global__ void k_copy_elem(S* dst, const S* src) { dst[0] = src[0]; }
 

@@ -1191,11 +1191,6 @@ struct Solver {
     }
     return SPOCK_OK;
   }
-  int fetch(double* dst, const double* src, int k) {
-    HIP_TRY(hipMemcpyAsync(dst, src, k * sizeof(double), hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
-    return SPOCK_OK;
-  }
 };
 
 // Anderson ring: slots of the active columns, oldest first (the Gram matrix

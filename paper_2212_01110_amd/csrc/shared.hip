@@ -356,7 +356,7 @@ struct ShVec {
 enum ShPhase : int { kShInit, kShK0, kShLS, kShK2, kShKM, kShCP, kShDone };
 enum ShNext : int { kShHold, kShDir, kShCombo, kShTv, kShFinish };
 struct ShState {
-  int phase, status, have_prev, k, ls, t_evals, n_k0, n_k1, n_k2, n_km, n_bt;
+  int phase, status, k, ls, t_evals, n_k0, n_k1, n_k2, n_km, n_bt;
   int commit;  // of this round: 0 nothing, 1 v = vt, 2 also the Anderson push
   int prep;    // a residual and a direction follow the commit
   int next;    // what the next evaluation's point is formed from (ShNext)
