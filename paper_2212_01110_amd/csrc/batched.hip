@@ -27,11 +27,14 @@
 // stages, about 0.26 ms per iteration of a 511-node tree (n_x 10, n_u 5, FP32);
 // 1024 threads at 128 registers give four wavefronts per SIMD to cover it. For
 // many, the vector passes' traffic too (31 GB/s per CU in the push, 8 TB/s in
-// all). Six FP32 SPOCK iterations of 512 trees (5 to 511 nodes): 10.8 -> 1.93
-// ms; eight FP64 iterations of 60 trees (n_x 13, n_u 7): 11.5 -> 2.58 ms,
-// against 256 threads with a team per family, two mat-vec phases a stage and
-// flat accesses. Of that, largest trees first: 2.63 -> 2.0 ms; accesses known
-// to be global with 32-bit offsets: 3.8 -> 2.63 ms.
+// all). 128 registers do not hold the iteration's state in either precision:
+// FP32 (16 lanes, form in LDS) spills 148 vector and 477 scalar registers (592
+// bytes of scratch a lane), FP64 (32 lanes) 180 and 382 (704 bytes). Six FP32
+// SPOCK iterations of 512 trees (5 to 511 nodes): 10.8 -> 1.93 ms; eight FP64
+// iterations of 60 trees (n_x 13, n_u 7): 11.4 -> 2.70 ms, against 256 threads
+// with a team per family, two mat-vec phases a stage and flat accesses. Of
+// that, largest trees first: 2.63 -> 2.0 ms; accesses known to be global with
+// 32-bit offsets: 3.8 -> 2.63 ms.
 #include "device_common.h"
 
 #include <algorithm>
@@ -473,10 +476,13 @@ struct BlockSolver {
     __syncthreads();
   }
 
-  // Anderson push with MO older columns: r, dV and dR of the new column, its
-  // Gram row and the right-hand side, then the solve. dV and dR stay apart: v
-  // and r change little from one iterate to the next, so both differences are
-  // mostly exact, and dV - dR, formed in FP64 with the direction, is too.
+  // In FP32 the columns dV and dR stay apart and the direction subtracts them
+  // in FP64: v and r change little from one iterate to the next, so both are
+  // mostly exact, and so is dV - dR, which FP32 would round (1 to 2% of an
+  // iteration). In FP64 the column E = dV - dR has the same bits either way.
+  static constexpr bool kApart = sizeof(S) == 4;
+  // Anderson push with MO older columns: r, dV (or E) and dR of the new column,
+  // its Gram row and the right-hand side, then the solve
   template <int MO>
   __device__ void push(const S* v, const S* Tv, const S* vprev, const S* rprev, S* rcur, const AAPush& a, const AAPush* ap, double* G,
                        double* gamma, AARingDev* ring) const {
@@ -494,7 +500,7 @@ struct BlockSolver {
     map<4 + MO, 3>(in, out, [&](const S(&x)[4 + MO], S(&y)[3]) {
       const S r = x[0] - x[1], dr = r - x[3];
       y[0] = r;
-      y[1] = x[0] - x[2];
+      y[1] = kApart ? x[0] - x[2] : (x[0] - x[2]) - dr;
       y[2] = dr;
 #pragma unroll
       for (int j = 0; j < MO; ++j) {
@@ -529,7 +535,7 @@ struct BlockSolver {
     S* vt = pool(7);
     S* Tvt = pool(8);
     S* spare = pool(9);
-    // Anderson columns of slot j: dV at pool(10 + j), dR at pool(10 + kAAMax + j)
+    // Anderson columns of slot j: dV (or E) at pool(10 + j), dR at pool(10 + kAAMax + j)
     // x0 must lie in the root's state box
     bool box_ok = true;
     for (int o = 0; o < P.nx; ++o) box_ok = box_ok && x0[o] >= (double)P.xlo[o] && x0[o] <= (double)P.xhi[o];
@@ -662,7 +668,7 @@ struct BlockSolver {
           if (j < dk) {
             g[j] = gamma[j];
             dV[j] = pool(10 + ring.dslot[j]);
-            dR[j] = pool(10 + kAAMax + ring.dslot[j]);
+            if (kApart) dR[j] = pool(10 + kAAMax + ring.dslot[j]);
           }
       } else {
         const S* in[2] = {v, Tv};
@@ -675,19 +681,19 @@ struct BlockSolver {
       // the first candidate of the line search, which keeps d as well)
       auto direction = [&](auto DK) {
         constexpr int D = decltype(DK)::value;
-        constexpr int NI = 2 + 2 * D;
+        constexpr int NI = 2 + (kApart ? 2 * D : D);
         const S* in[NI];
         in[0] = rcur;
         in[1] = v;
 #pragma unroll
         for (int j = 0; j < D; ++j) {
           in[2 + j] = dV[j];
-          in[2 + D + j] = dR[j];
+          if (kApart) in[NI - D + j] = dR[j];
         }
         auto one = [&](const S(&x)[NI]) {
           double acc = -(double)x[0];
 #pragma unroll
-          for (int j = 0; j < D; ++j) acc -= g[j] * ((double)x[2 + j] - (double)x[2 + D + j]);
+          for (int j = 0; j < D; ++j) acc -= g[j] * ((double)x[2 + j] - (kApart ? (double)x[NI - D + j] : 0.0));
           return (S)acc;
         };
         if (k0) {
