@@ -346,8 +346,8 @@ __global__ void __launch_bounds__(256) k_adj_front(DevProb<S> P, const long long
 // alpha L la): A(w) = J_T' w + g with (a, s, c) = (0, 1, 1), the next Krylov
 // vector v - J_T' v (the cotangent cancels) with (1, -1, 0). Wavefronts run
 // over the z entries first, then a family (or more) each for the rows of L la.
-// One launch in place of four (L, three combinations); al is the unrounded alpha. Bound by the latency of
-// its loads.
+// One launch in place of four (L, three combinations); al is the unrounded
+// alpha. Bound by the latency of its loads.
 template <typename S>
 __global__ void __launch_bounds__(256) k_adj_back(DevProb<S> P, double al, double a, const S* __restrict__ v, long long vs,
                                                   double sg, const S* __restrict__ la, const S* __restrict__ tz,
@@ -419,8 +419,8 @@ __global__ void __launch_bounds__(256) k_adj_back(DevProb<S> P, double al, doubl
 // component o (nx <= 64): the rows of K and Abar are read coalesced and the
 // sums run in the order of the formula. Bound by the latency of a stage's
 // chain; one thread per node walked nx (nu + n nx) dependent loads (85 us per
-// stage on the 95-node tree in FP64, once per instance: 43 of the 60 ms of a
-// 64-instance adjoint of 32 applications, now 10.5 ms in all).
+// stage on the 95-node tree in FP64, once per instance: 43 of the 60 ms that a
+// 64-instance adjoint of 32 applications took; it takes 7.6 ms in all now).
 template <typename S>
 __global__ void __launch_bounds__(256) k_phiT(DevProb<S> P, const S* __restrict__ cz, long long is,
                                               S* __restrict__ mu, long long ms, int first, int count,

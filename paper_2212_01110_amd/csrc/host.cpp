@@ -1056,7 +1056,11 @@ int autotune(Problem& P, hipStream_t st) {
   // alone take twice the time of the dependent stages (5 TB/s, 1.2 us): 20776
   // nodes, n_x 50, n_u 20, FP32 run T in 250 us without it and 346 us with it;
   // 4095 nodes, n_x = n_u = 50, FP32, below the line, have the sweeps in 101 us
-  // without it and 64 us with it.
+  // without it and 64 us with it. The line only saves tuning time, since the
+  // forms are timed below it: where the walk form stops winning depends on the
+  // dimensions (FP64 sweeps, dataflow over walk time at this quotient: n_x 50,
+  // n_u 20 1.10 at 0.36, 0.92 at 0.64, 0.87 at 1.9; n_x 20, n_u 10 1.37 at 0.19, 1.08
+  // at 0.55; n_x = n_u = 50 1.23 at 0.5, 1.13 at 1.6, 1.07 at 4.6).
   const double mat_us = sizeof(S) * (double)T.nn * 2.0 * P.nx * (P.nx + P.nu) / 5e6;
   if (!P.flow_failed && mat_us < 2.0 * 1.2 * 2 * T.N) {
     float ms[2] = {0, 0};
@@ -2015,10 +2019,10 @@ int batched_impl(int B, spock_problem* const* probs, const double* const* x0, co
                    st.c2, st.beta, st.sigma, st.lambda};
   const auto* dev_desc = static_cast<const BatchInst<S>*>(C.desc);
   // Lanes per family: the fewest that hold a state and an input (two
-  // components a lane above 64), so that the most families share a stage, or
+  // components a lane above 64), so that the most families share a pass, or
   // more when SPOCK_BATCH_TEAM asks for them (512 trees of n_x 10, n_u 5 in
-  // FP32, six iterations of the earlier 256-thread form: 10.1 ms at 16 lanes,
-  // 16.0 at 32, 26.3 at 64).
+  // FP32, six iterations: 2.0 ms at 16 lanes, 2.3 at 32, 2.9 at 64; 60 trees of
+  // n_x 13, n_u 7 in FP64, eight iterations: 2.8 ms at 32 lanes, 4.0 at 64).
   const int tmin = next_pow2_team(nx + nu);
   int team = tmin;
   if (const char* env = std::getenv("SPOCK_BATCH_TEAM")) {

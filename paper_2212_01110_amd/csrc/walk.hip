@@ -36,8 +36,8 @@ namespace spk {
 
 namespace {
 
-// Word offsets of the dynamic LDS regions (32-bit words; every region is a
-// whole number of 64-word rows so that a wavefront copy may overrun it).
+// Word offsets of the dynamic LDS regions (32-bit words; every region starts at
+// a multiple of 64 words, so that the copies' 16-byte units land aligned).
 struct WalkLds {
   int esz;     // words per element
   int sA, sB;  // per-child strides of the At / Abar and Bt / B regions
@@ -687,7 +687,13 @@ const void* walk_pick(int* waves) {
 }  // namespace
 
 // The build for the dimensions (rows per wavefront: a quarter of the larger,
-// over the sizes built) and the wavefronts per SIMD it is compiled for.
+// over the sizes built) and the wavefronts per SIMD it is compiled for. A size
+// costs about what the largest of its build costs, since the rows past the end
+// are multiplied too; six builds keep that within a fifth up to n_x 52, and the
+// dataflow form is slower at every size (sweeps of 223 nodes in FP64, us, walk /
+// dataflow: n_x 8 19.7 / 41, 9 21.7 / 42, 12 21.3 / 43, 13 24.4 / 44, 20 23.5 /
+// 45, 21 28.4 / 46, 32 30 / 47, 33 35.5 / 50, 44 36 to 42 / 49 to 55, 52 41 / 52 to
+// 57, 53 46 to 50 / 53 to 58, 64 43 / 54 to 60).
 template <typename S>
 const void* walk_kernel(int nx, int nu, int* waves) {
   const int n = std::max(nx, nu);
