@@ -291,7 +291,10 @@ int spock_backward_batched(spock_problem* prob, int32_t B, const void* const* v_
 /* ---------------------------------------------------------------------------
  * Per-operator entry points (same kernels as the solver, but for the sweeps
  * of an FP32 spock_T: see spock_problem_mapping; used for operator parity).
- * All vectors are device arrays of the problem precision.
+ * All vectors are device arrays of the problem precision. Calls on one
+ * problem share its workspace: after a call that returned without waiting, one
+ * on another blocking stream runs after it; order streams made without
+ * blocking yourself.
  * ------------------------------------------------------------------------- */
 /* eta_dev[n_eta] = L z_dev[n_z] (section 5.2, definition of L) */
 int spock_apply_L(spock_problem* prob, const void* z_dev, void* eta_dev, void* stream);

@@ -846,9 +846,21 @@ int ensure_walk(Problem& P, int budget = 0, int run = -1) {
   return place_flow<S>(P, F, kernel, waves, lds, plan.items, plan.pbase, plan.nslots);
 }
 
+// The workspace for a call on stream st. A call that returns without waiting
+// leaves its work in flight; one on another stream is ordered after it as the
+// legacy stream orders blocking streams (and not at all against streams made
+// without blocking, whose order is the caller's). Under capture the order is the
+// caller's too.
 template <typename S>
-int ensure_work(Problem& P, Work<S>& W) {
+int ensure_work(Problem& P, Work<S>& W, hipStream_t st) {
   const Tree& T = *P.tree;
+  if (P.queued && P.queued_on != st) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    HIP_TRY(hipStreamIsCapturing(st, &cap));
+    if (cap == hipStreamCaptureStatusNone) HIP_TRY(hipStreamSynchronize(nullptr));
+  }
+  P.queued = true;
+  P.queued_on = st;
   const long long nv = P.nz + P.neta;
   const int nblk = dots_blocks(nv);
   size_t bytes = 0;
@@ -945,7 +957,7 @@ template <typename S>
 int autotune(Problem& P, hipStream_t st) {
   if (P.tuned) return SPOCK_OK;
   Work<S> W;
-  int rc = ensure_work<S>(P, W);
+  int rc = ensure_work<S>(P, W, st);
   if (rc) return rc;
   const long long nv = P.nz + P.neta;
   HIP_TRY(launch_fill<S>(nv, W.pool[0], 0.0, st));
@@ -1463,7 +1475,7 @@ template <typename S>
 int solve_impl(Problem& P, const double* x0, const spock_settings& s, S* vio, spock_info& info,
                hipStream_t st) {
   Solver<S> SV(P, st, x0);
-  int rc = ensure_work<S>(P, SV.W);
+  int rc = ensure_work<S>(P, SV.W, st);
   if (rc) return rc;
   Work<S>& W = SV.W;
   const long long nv = SV.nv;
@@ -1496,6 +1508,7 @@ int solve_impl(Problem& P, const double* x0, const spock_settings& s, S* vio, sp
   auto finish = [&](int status) -> int {
     HIP_TRY(hipMemcpyAsync(vio, Tv, sizeof(S) * nv, hipMemcpyDeviceToDevice, st));
     HIP_TRY(hipStreamSynchronize(st));
+    P.queued = false;
     info.status = status;
     info.iters = k;
     info.t_evals = SV.t_evals;
@@ -1761,7 +1774,7 @@ template <typename S>
 int prox_f_impl(Problem& P, const S* zin, const double* x0, S* zout, hipStream_t st) {
   for (int attempt = 0;; ++attempt) {
     Work<S> W;
-    int rc = ensure_work<S>(P, W);
+    int rc = ensure_work<S>(P, W, st);
     if (rc) return rc;
     HIP_TRY(launch_T<S>(P, zin, zout, x0, W.q, W.d, W.xbar, W.ubar, W.partials, W.stats, st, W.eta_zero, false));
     if (!sweeps_wait(P)) return SPOCK_OK;
@@ -1769,6 +1782,7 @@ int prox_f_impl(Problem& P, const S* zin, const double* x0, S* zout, hipStream_t
     HIP_TRY(launch_publish_word(P.flow_err, pub, st));
     rc = wait_mailbox(P, pub.epoch, st);
     if (rc) return rc;
+    P.queued = false;
     if (P.mbox->v[0] == 0.0) return SPOCK_OK;
     if (attempt > 0) return SPOCK_EHIP;
     rc = flow_fallback(P);
@@ -1778,7 +1792,7 @@ int prox_f_impl(Problem& P, const S* zin, const double* x0, S* zout, hipStream_t
 template <typename S>
 int T_impl(Problem& P, const S* v, const double* x0, S* Tv, double* stats, hipStream_t st) {
   Work<S> W;
-  int rc = ensure_work<S>(P, W);
+  int rc = ensure_work<S>(P, W, st);
   if (rc) return rc;
   const SweepMap map = operator_T_map(P);
   const bool wait = stats || sweeps_wait(P, map);
@@ -1787,6 +1801,7 @@ int T_impl(Problem& P, const S* v, const double* x0, S* Tv, double* stats, hipSt
   if (!wait) return SPOCK_OK;
   rc = wait_mailbox(P, pub.epoch, st);
   if (rc) return rc;
+  P.queued = false;
   double r[6];
   for (int k = 0; k < 6; ++k) r[k] = P.mbox->v[k];
   if (!(std::isfinite(r[0]) && std::isfinite(r[1]) && std::isfinite(r[2]))) {
@@ -2156,7 +2171,7 @@ int backward_once(Problem& P, const S* vstar, const double* x0, double gV, const
                   double* gx0, double* gq, double* gqN, const spock_settings& s, spock_info& info,
                   hipStream_t st) {
   Work<S> W;
-  int rc = ensure_work<S>(P, W);
+  int rc = ensure_work<S>(P, W, st);
   if (rc) return rc;
   const Tree& T = *P.tree;
   const long long nz = P.nz, ne = P.neta, nv = nz + ne;
@@ -2409,6 +2424,7 @@ int backward_once(Problem& P, const S* vstar, const double* x0, double gV, const
   HIP_TRY(launch_phiT<S>(P, cz, 0, W.q, 0, 1, tab_d + 1, st));
   if (gq || gqN) HIP_TRY(launch_grad_q<S>(P, vstar, la, lb, 0, 1, tab_d + 1, st));
   HIP_TRY(hipStreamSynchronize(st));
+  P.queued = false;
   return SPOCK_OK;
 }
 

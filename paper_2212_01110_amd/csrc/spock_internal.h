@@ -213,6 +213,10 @@ struct Problem {
   Mailbox* mbox_dev = nullptr;  // device view of the same memory
   unsigned long long mbox_epoch = 0;
   unsigned red_tag = 0;  // tag of the last grid sum in the workspace's records
+  // the stream that work on the workspace was last queued on, while the host
+  // has not waited for it
+  bool queued = false;
+  hipStream_t queued_on = nullptr;
 };
 
 // ---------------------------------------------------------------- launchers
